@@ -34,6 +34,11 @@
  * the host and never allocate, and a conv call with re-laid-out weights enqueues
  * nothing but its kernels, so it may be captured into a HIP graph.
  *
+ * Precision: fp32 in, fp32 out, sums in fp32.  Kernels bound by matrix arithmetic multiply on the bf16 matrix cores with
+ * every fp32 factor split into three bf16 parts (all 24 bits); the products are at least as accurate as fp32
+ * multiply-adds for normal numbers, keep an absolute accuracy of 2^-134 for factors below 2^-110, and turn an infinite
+ * factor into NaN.
+ *
  * Errors: every function returns a tdc_status (0 = success, negative =
  * failure).  Nothing aborts, throws or prints.
  */
@@ -123,6 +128,8 @@ enum {
  *   tile_h, tile_w : output tile of one workgroup            (FUSED, CHAIN)
  *   waves          : wavefronts (of 64 lanes) per workgroup  (SPLIT: per stage; FUSED, CHAIN: waves[0];
  *                    MERGED: [0] for stage 1, [1] for the merged convolution, likewise mb and pb)
+ *   DENSE          : either mb[1], pb[1], waves[1] (the latency kernel), or a tile: tile_h = 64 or 128 output channels
+ *                    by tile_w = 64 pixels, waves[1] = 4 or 8 (two groups of 4 that split the contraction)
  *   mb, pb         : 16-channel and 16-pixel blocks per wavefront register tile, per stage
  *                    (CHAIN uses mb[0] and pb[0]; its stage-2 tile is all of R2 by construction) */
 typedef struct tdc_tuning {

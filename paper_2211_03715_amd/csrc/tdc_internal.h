@@ -56,6 +56,10 @@ hipError_t tdc_launch_pack_core(const TdcDims &d, hipStream_t s, const float *co
 // U_in as usual; Wm[R1][N][K][K] = core x_2 U_out into `wm`, then re-laid out into `wm_p` [NB3][K*K*NB1]
 hipError_t tdc_launch_pack_merged(const TdcDims &d, hipStream_t s, const float *U_in, const float *core,
                                   const float *U_out, float *uin_p, float *wm, float *wm_p);
+// The same re-layout with every weight split into three bf16 parts (tdc_bf3.h): [m-block][step][part][lane][8], a step being
+// two k-groups, component j = what the fp32 layout has as component j%4 of k-group 2*step + j/4 (zero past the last one).
+inline size_t tdc_packed3_bytes(int m_blocks, int k_groups) { return (size_t)m_blocks * ((k_groups + 1) / 2) * 3072; }
+hipError_t tdc_launch_pack3_core(const TdcDims &d, hipStream_t s, const float *core, void *core_p3);
 size_t tdc_packed_floats_uin(const TdcDims &d);
 size_t tdc_packed_floats_core(const TdcDims &d);
 size_t tdc_packed_floats_uout(const TdcDims &d);
@@ -73,6 +77,12 @@ hipError_t tdc_launch_split(const TdcDims &d, const tdc_tuning &t, hipStream_t s
 // the dense K x K layer through the stage-2 kernel; `d` has R1 = C, R2 = N
 hipError_t tdc_launch_dense(const TdcDims &d, const tdc_tuning &t, hipStream_t s, const float *x,
                             const float *w_p, float *y, const TdcEpi &epi);
+
+// the same layer in tm x tp tiles of (channels x pixels) on the bf16 matrix cores (tdc_tile.hip), the contraction dealt to
+// `ks` groups of wavefronts; w3: tdc_launch_pack3_core's layout
+bool tdc_tile_supported(int tm, int tp, int ks);
+bool tdc_tile_applies(const TdcDims &d);
+hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipStream_t s, const float *x, const void *w3, float *y, const TdcEpi &epi);
 
 // stage 1, then stages 2 and 3 as one implicit GEMM with the merged kernel
 hipError_t tdc_launch_merged(const TdcDims &d, const tdc_tuning &t, hipStream_t s, const float *x,

@@ -1,6 +1,7 @@
 // Weight re-layout kernels: caller layouts -> the frag-major packed layout of tdc_internal.h.
 // The paper (section 5.2) converts its core weights to a coalescing-friendly layout once,
 // offline; this is the same step for this library's MFMA operand order.
+#include "tdc_bf3.h"
 #include "tdc_internal.h"
 
 size_t tdc_packed_floats_uin(const TdcDims &d) { return (size_t)d.NB1 * d.KG1 * 256; }
@@ -42,6 +43,26 @@ __global__ void pack_core_kernel(TdcDims d, const float *__restrict__ core, floa
     const int d1 = 16 * (kg % d.NB1) + k16;
     const int r = tap / d.K, s = tap % d.K;
     out[e] = (d1 < d.R1 && m < d.R2) ? core[(((size_t)d1 * d.R2 + m) * d.K + r) * d.K + s] : 0.f;
+}
+
+// One thread per pair of components of the three-part layout: e = ((mb*S + step)*64 + lane)*4 + pair.
+__global__ void pack3_core_kernel(TdcDims d, const float *__restrict__ core, unsigned *__restrict__ out, size_t total)
+{
+    const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= total) return;
+    const int KG = d.K * d.K * d.NB1, S = (KG + 1) / 2;
+    const int pair = (int)(e & 3), lane = (int)((e >> 2) & 63);
+    const size_t blk = e >> 8;
+    const int step = (int)(blk % S), mb = (int)(blk / S);
+    const int kg = 2 * step + (pair >> 1), m = 16 * mb + (lane & 15);
+    const int tap = kg / d.NB1, r = tap / d.K, s = tap % d.K;
+    const int d1 = 16 * (kg % d.NB1) + 4 * (lane >> 4) + 2 * (pair & 1);
+    float v[2];
+    for (int i = 0; i < 2; ++i)
+        v[i] = (kg < KG && d1 + i < d.R1 && m < d.R2) ? core[(((size_t)(d1 + i) * d.R2 + m) * d.K + r) * d.K + s] : 0.f;
+    unsigned p[3];
+    tdc_split2(v[0], v[1], p[0], p[1], p[2]);
+    for (int i = 0; i < 3; ++i) out[(blk * 3 + i) * 256 + lane * 4 + pair] = p[i];
 }
 
 __global__ void pack_uout_kernel(TdcDims d, const float *__restrict__ U_out, float *__restrict__ out, size_t total)
@@ -102,5 +123,13 @@ hipError_t tdc_launch_pack_core(const TdcDims &d, hipStream_t s, const float *co
     const int T = 256;
     const size_t n2 = tdc_packed_floats_core(d);
     hipLaunchKernelGGL(pack_core_kernel, dim3((unsigned)((n2 + T - 1) / T)), dim3(T), 0, s, d, core, core_p, n2);
+    return hipGetLastError();
+}
+
+hipError_t tdc_launch_pack3_core(const TdcDims &d, hipStream_t s, const float *core, void *core_p3)
+{
+    const int T = 256;
+    const size_t n = tdc_packed3_bytes(d.NB2, d.K * d.K * d.NB1) / 12;
+    hipLaunchKernelGGL(pack3_core_kernel, dim3((unsigned)((n + T - 1) / T)), dim3(T), 0, s, d, core, (unsigned *)core_p3, n);
     return hipGetLastError();
 }

@@ -465,6 +465,52 @@ StageChoice best_stage(const TdcDeviceInfo &dev, int batch, int n_mblocks, int n
     return best;
 }
 
+// The dense layer in tiles on the bf16 matrix cores (tdc_tile.hip).  Either a workgroup's own chain of steps bounds the
+// launch -- few workgroups, each alone on its compute unit -- or the work of all of them, S steps of every tile dealt to the
+// compute units plus what a tile costs however short its contraction (first loads, epilogue).  Microseconds, from the 30
+// dense layers of the batch-32 ResNet-50-shaped network and a dozen 3x3 layers (14 % off at worst where the tile kernel
+// is chosen): an own step takes 0.50 us in a 64-channel tile and 0.68 in a 128-channel one (two groups of wavefronts: a
+// pair of steps in 0.77 and 1.1), a step among others 0.40 and 0.64, in NCHW a K x K layer's 4-byte loads make it 0.48 and 0.76.
+enum { T_LAUNCH, T_OWN_64, T_OWN_64X2, T_OWN_128, T_OWN_128X2, T_LOAD_64, T_LOAD_128, T_TILE_64, T_TILE_128, T_TERMS };
+const char *const kTileTermNames[T_TERMS] = {"launch", "own_64", "own_64x2", "own_128", "own_128x2", "load_64", "load_128", "tile_64", "tile_128"};
+const double kTileCoef[T_TERMS] = {3.5, 0.50, 0.77, 0.68, 1.1, 0.40, 0.64, 1.1, 3.2};
+
+void tile_terms(double (&f)[T_TERMS], const TdcDims &d, const TdcDeviceInfo &dev, int tm, int ks)
+{
+    const double S = (d.K * d.K * d.NB1 + 1) / 2, tiles = (double)cdiv(d.NB2 * 16, tm) * cdiv(d.B * d.Ho * d.Wo, 64);
+    const double per_cu = tiles / dev.cus, gather = !d.nhwc && d.K > 1 ? 1.2 : 1.0;
+    const int own = tm == 64 ? (ks == 2 ? T_OWN_64X2 : T_OWN_64) : ks == 2 ? T_OWN_128X2 : T_OWN_128;
+    const int load = tm == 64 ? T_LOAD_64 : T_LOAD_128, tile = tm == 64 ? T_TILE_64 : T_TILE_128;
+    for (double &v : f) v = 0.0;
+    f[T_LAUNCH] = 1.0;
+    const double chain = gather * std::ceil(S / ks), work = gather * S * per_cu;
+    if (kTileCoef[own] * chain + kTileCoef[tile] > kTileCoef[load] * work + kTileCoef[tile] * per_cu) {
+        f[own] = chain;
+        f[tile] = 1.0;
+    } else {
+        f[load] = work;
+        f[tile] = per_cu;
+    }
+}
+
+struct TileChoice {
+    double us = 1e300;
+    int tm = 0, ks = 0;
+};
+TileChoice best_tile(const TdcDims &d, const TdcDeviceInfo &dev)
+{
+    TileChoice best;
+    if (!tdc_tile_applies(d)) return best;
+    for (int tm : {64, 128})
+        for (int ks : {1, 2}) {
+            double f[T_TERMS];
+            tile_terms(f, d, dev, tm, ks);
+            const double us = dot(kTileCoef, f, T_TERMS);
+            if (us < best.us) best = {us, tm, ks};
+        }
+    return best;
+}
+
 }  // namespace
 
 // The terms of the estimate for a fully specified tuning (see tdc_model_terms in tdc.h).
@@ -511,6 +557,11 @@ int tdc_select_terms(const TdcDims &d, const TdcDeviceInfo &dev, const tdc_tunin
             stage_terms(f, dev, d.B, n_mblocks, n_pblocks, kgroups, t.mb[st], t.pb[st], t.waves[st], conv_stride);
             for (int i = 0; i < G_TERMS; ++i) sum[i] += f[i];
         };
+        if (t.variant == TDC_VARIANT_DENSE && t.tile_h) {
+            double ft[T_TERMS];
+            tile_terms(ft, d, dev, t.tile_h, t.waves[1] / 4);
+            return emit(ft, kTileTermNames, T_TERMS, "dense_tile");
+        }
         if (t.variant == TDC_VARIANT_DENSE) {
             double fd[D_TERMS];
             dense_terms(fd, dev, d.B, d.NB2, pb_out, KG2, t.mb[1], t.pb[1], t.waves[1], d.stride, d.nhwc != 0);
@@ -556,8 +607,34 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
     if (forced.variant == TDC_VARIANT_NAIVE) return TDC_OK;
     if (forced.variant == TDC_VARIANT_DENSE) {
         // the stage-2 kernel on the layer's own channels: `d` has R1 = C and R2 = N
+        const auto tiled = [&](int tm, int ks, double us) {
+            t->tile_h = tm; t->tile_w = 64;
+            for (int i = 0; i < 3; ++i) {
+                t->mb[i] = t->pb[i] = 1; t->waves[i] = 4 * ks;
+            }
+            if (model_us) *model_us = us;
+            return TDC_OK;
+        };
+        if (forced.tile_h) {
+            if (forced.tile_w && forced.tile_w != 64) return TDC_ERR_BAD_TUNING;
+            const int tm = forced.tile_h, ks = forced.waves[1] ? forced.waves[1] / 4 : 1;
+            if (!tdc_tile_supported(tm, 64, ks) || (forced.waves[1] && forced.waves[1] != 4 * ks)) return TDC_ERR_BAD_TUNING;
+            double f[T_TERMS];
+            tile_terms(f, d, dev, tm, ks);
+            return tiled(tm, ks, dot(kTileCoef, f, T_TERMS));
+        }
         const StageChoice c = best_stage(dev, d.B, d.NB2, cdiv(d.Ho * d.Wo, 16), d.K * d.K * d.NB1, forced.mb[1],
                                          forced.pb[1], forced.waves[1], d.stride, true, d.nhwc != 0);
+        // Tiles against the latency kernel, by estimate.  With less than 1.5 tiles of 64 x 64 per compute unit they have to win by
+        // 5 %: batch 1 stays with the latency kernel (64 -> 256 at 56x56: 4.8 against 5.0 us, 1024 -> 256 at 14x14: 5.6 against
+        // 14.8 us).  With more, the other table, fitted on batch 1, is too low by 15-45 % (it knows neither memory bandwidth nor
+        // the shortcut's bytes) and they win up to 1.2 times it: 64 -> 256 at 56x56, batch 32: 59.6 -> 50.3 us in NHWC, 93.9 ->
+        // 50.1 in NCHW; batch 2: 7.4 -> 6.7 and 8.7 -> 7.2 us.  16 -> 32 stays (7.4 against 10.6 us): half of every tile would be padding.
+        if (!forced.mb[1] && !forced.pb[1] && !forced.waves[1]) {
+            const TileChoice tc = best_tile(d, dev);
+            const double tiles = (double)cdiv(d.NB2 * 16, 64) * cdiv(d.B * d.Ho * d.Wo, 64);
+            if (tc.us < (tiles < 1.5 * dev.cus ? 0.95 : 1.2) * c.us) return tiled(tc.tm, tc.ks, tc.us);
+        }
         if (c.us >= 1e299) return TDC_ERR_BAD_TUNING;
         t->tile_h = t->tile_w = 0;
         for (int i = 0; i < 3; ++i) {

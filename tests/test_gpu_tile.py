@@ -1,0 +1,97 @@
+"""GPU parity of the dense layer in tiles on the bf16 matrix cores (every factor in three parts), at the sizes where its
+tiling can go wrong: contractions that are not whole steps (two 16-wide k-groups), channel counts and pixel counts that leave
+part of a tile empty, images much smaller than a tile, taps outside the image, both activation layouts, both tile heights,
+the contraction dealt to one and to two groups of wavefronts."""
+import numpy as np
+import pytest
+
+from parity_util import assert_parity
+from paper_2211_03715_amd import binding as B
+from paper_2211_03715_amd.workloads import Layer, make_dense_inputs
+
+pytestmark = pytest.mark.gpu
+
+LAYERS = [
+    Layer(1, 16, 64, 8, 8, 1, 1, 1, 1, 0),         # one k-group: half a step, one exact tile
+    Layer(1, 32, 128, 8, 8, 1, 1, 1, 1, 0),        # one step
+    Layer(70, 48, 68, 1, 1, 1, 1, 1, 1, 0),        # single-pixel images, 1.5 steps, pixels and channels just past a tile
+    Layer(9, 100, 60, 3, 5, 1, 1, 1, 1, 0),        # several images per tile, C no multiple of 16, N below a tile
+    Layer(2, 64, 132, 13, 9, 1, 1, 1, 2, 0),       # strided 1x1 (a projection shortcut)
+    Layer(3, 20, 24, 19, 23, 1, 1, 3, 1, 1),       # K x K, 4.5 steps of which none holds one tap alone
+    Layer(2, 36, 72, 16, 12, 1, 1, 3, 2, 1),
+    Layer(1, 12, 8, 7, 40, 1, 1, 5, 1, 2),
+    Layer(2, 8, 16, 9, 8, 1, 1, 7, 3, 6),          # taps far outside, stride 3
+]
+
+
+def _oracle(orc, layer, inputs, bias=None, residual=None):
+    want, _ = orc.conv_dense_with(orc.Shape(**layer.asdict()), inputs["x"], inputs["W"].astype(np.float64))
+    if bias is not None:
+        want = np.maximum(want + bias.astype(np.float64)[None, :, None, None] + residual, 0.0)
+    return want
+
+
+def _run(layer, inputs, tm, waves, nhwc, bias=None, residual=None, offset=0):
+    import torch
+    from paper_2211_03715_amd.layer import DenseConv2d
+    dev = torch.device("cuda:0")
+    put = lambda a: torch.from_numpy(np.ascontiguousarray(a.transpose(0, 2, 3, 1) if nhwc else a)).to(dev)
+    conv = DenseConv2d(layer, 0, B.make_tuning(tile_h=tm, tile_w=64, waves=(waves,) * 3), B.LAYOUT_NHWC if nhwc else B.LAYOUT_NCHW)
+    try:
+        W = torch.from_numpy(inputs["W"]).to(dev)
+        conv.pack(W)
+        shape = conv.out_shape()
+        whole = torch.full((offset + int(np.prod(shape)),), float("nan"), device=dev)
+        y = whole[offset:].view(shape)                      # offset 1: only 4-byte aligned
+        conv(put(inputs["x"]), y, bias=None if bias is None else torch.from_numpy(bias).to(dev),
+             residual=None if residual is None else put(residual), relu=bias is not None)
+        torch.cuda.synchronize()
+        got = y.cpu().numpy()
+        return got.transpose(0, 3, 1, 2) if nhwc else got
+    finally:
+        conv.close()
+
+
+@pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
+@pytest.mark.parametrize("layer", LAYERS, ids=lambda l: l.name())
+def test_tiles(orc, layer, nhwc):
+    if nhwc and (layer.C % 4 or layer.N % 4):
+        pytest.skip("NHWC needs channel counts that are multiples of 4")
+    inputs = make_dense_inputs(layer, 77)
+    want = _oracle(orc, layer, inputs)
+    for tm in (64, 128):
+        for waves in (4, 8):
+            print("[case] tiles", layer.name(), "nhwc" if nhwc else "nchw", tm, waves, flush=True)
+            got = _run(layer, inputs, tm, waves, nhwc)
+            assert_parity(got, want, "%s tile %d waves %d" % (layer.name(), tm, waves))
+            # fp32 sums of at most 800 terms here: an fp32 chain shows about 6e-7 (sqrt(800) roundings of 2^-25 relative to the
+            # root of the sum), the split products about the same; two parts instead of three would show 5e-6
+            rel = np.linalg.norm(got - want) / np.linalg.norm(want)
+            assert rel <= 1.2e-6, rel
+
+
+@pytest.mark.parametrize("nhwc,offset", ((False, 0), (False, 1), (True, 0)), ids=("nchw", "nchw_4_byte_aligned_y", "nhwc"))
+def test_tiles_with_epilogue(orc, nhwc, offset):
+    """Bias, shortcut and ReLU in the store; P = 12 (16-byte stores in NCHW) and P = 15 (quads that cross an image)."""
+    for layer in (Layer(7, 40, 72, 3, 4, 1, 1, 1, 1, 0), Layer(7, 40, 72, 3, 5, 1, 1, 1, 1, 0)):
+        print("[case] tiles epilogue", layer.name(), nhwc, offset, flush=True)
+        inputs = make_dense_inputs(layer, 78)
+        rng = np.random.default_rng(5)
+        bias = rng.standard_normal(layer.N, dtype=np.float32)
+        residual = rng.standard_normal((layer.batch, layer.N, layer.Ho, layer.Wo), dtype=np.float32)
+        got = _run(layer, inputs, 64, 4, nhwc, bias, residual, offset)
+        assert_parity(got, _oracle(orc, layer, inputs, bias, residual), layer.name())
+
+
+def test_the_selector_takes_tiles_for_large_launches_only():
+    """A batch of 32 goes to the tiles, the same layer at batch 1 does not, and a chosen tile is accepted when forced."""
+    for lay in (B.LAYOUT_NCHW, B.LAYOUT_NHWC):
+        dense = B.make_tuning(variant=B.VARIANT_DENSE)
+        assert B.tdc_select_tuning(B.make_shape(1, 1024, 256, 14, 14, 1, 1, 1, 1, 0, lay), tuning=dense).as_dict()["tile_h"] == 0
+        shape = B.make_shape(32, 1024, 256, 14, 14, 1, 1, 1, 1, 0, lay)
+        t = B.tdc_select_tuning(shape, tuning=B.make_tuning(variant=B.VARIANT_DENSE))
+        assert t.as_dict()["tile_h"] in (64, 128) and t.as_dict()["tile_w"] == 64
+        B.tdc_plan_destroy(B.tdc_plan_create(shape, 0, t))
+    for bad in (dict(tile_h=96, tile_w=64), dict(tile_h=64, tile_w=128), dict(tile_h=64, tile_w=64, waves=(3, 3, 3))):
+        with pytest.raises(B.TdcError):
+            B.tdc_plan_create(B.make_shape(1, 64, 64, 8, 8, 1, 1, 1, 1, 0), 0, B.make_tuning(variant=B.VARIANT_DENSE, **bad))
