@@ -106,6 +106,12 @@ TdcDims make_dims(const tdc_shape &s)
     return d;
 }
 
+TdcFusedGeom chain_geometry(const TdcDims &d, const tdc_tuning &t, int lds_limit)
+{
+    return tdc_is_chain3(t) ? tdc_chain3_geometry(d, t.tile_h, t.tile_w)
+                            : tdc_chain_geometry(d, t.tile_h, t.tile_w, t.waves[0], t.pb[0], lds_limit);
+}
+
 int check_tuning(const tdc_plan &p, const TdcDeviceInfo &dev)
 {
     const tdc_tuning &t = p.tuning;
@@ -119,6 +125,12 @@ int check_tuning(const tdc_plan &p, const TdcDeviceInfo &dev)
     const int nb[3] = {dense ? p.dims.NB2 : p.dims.NB1, merged ? p.dims.NB3 : p.dims.NB2, dense ? p.dims.NB2 : p.dims.NB3};
     if (t.variant == TDC_VARIANT_DENSE && t.tile_h) {
         return tdc_tile_supported(t.tile_h, t.tile_w, t.waves[1] / 4) && tdc_tile_applies(p.dims) ? TDC_OK : TDC_ERR_BAD_TUNING;
+    }
+    if (tdc_is_chain3(t)) {
+        if (t.tile_h < 1 || t.tile_w < 1 || t.tile_h * t.tile_w > 4096 || t.waves[0] != 4) return TDC_ERR_BAD_TUNING;
+        if (!tdc_chain3_supported(p.dims, t.mb[0], t.pb[0]) || (long)p.geom.lds_bytes > dev.lds_per_wg) return TDC_ERR_BAD_TUNING;
+        if ((long long)p.geom.tiles_x * p.geom.tiles_y * p.dims.B > 0x7fffffffLL) return TDC_ERR_BAD_TUNING;
+        return TDC_OK;
     }
     for (int i = 0; i < 3; ++i)
         if (t.mb[i] < 1 || nb[i] % t.mb[i]) return TDC_ERR_BAD_TUNING;   // whole register tiles only
@@ -177,7 +189,11 @@ void describe(tdc_plan &p)
 {
     const tdc_tuning &t = p.tuning;
     const char *names[] = {"auto", "naive", "split", "fused"};
-    if (t.variant == TDC_VARIANT_CHAIN)
+    if (tdc_is_chain3(t))
+        snprintf(p.desc, sizeof(p.desc), "chain bf3 tile=%dx%d in=%dx%d waves=%d units(mb1,pb)=(%d,%d) grid=%dx%d lds=%zuB model=%.1fus",
+                 t.tile_h, t.tile_w, p.geom.QH, p.geom.QW, t.waves[0], t.mb[0], t.pb[0], p.geom.tiles_x * p.geom.tiles_y, p.dims.B,
+                 p.geom.lds_bytes, p.model_us);
+    else if (t.variant == TDC_VARIANT_CHAIN)
         snprintf(p.desc, sizeof(p.desc),
                  "chain tile=%dx%d in=%dx%d waves=%d units(mb1,pb)=(%d,%d) grid=%dx%d lds=%zuB%s model=%.1fus",
                  t.tile_h, t.tile_w, p.geom.QH, p.geom.QW, t.waves[0], t.mb[0], t.pb[0],
@@ -304,7 +320,7 @@ int tdc_plan_create_tuned(tdc_plan **out, const tdc_shape *shape, int device, co
     if (rc == TDC_OK && p->tuning.variant == TDC_VARIANT_FUSED)
         p->geom = tdc_fused_geometry(p->dims, p->tuning.tile_h, p->tuning.tile_w, dev.lds_per_wg);
     if (rc == TDC_OK && p->tuning.variant == TDC_VARIANT_CHAIN)
-        p->geom = tdc_chain_geometry(p->dims, p->tuning.tile_h, p->tuning.tile_w, p->tuning.waves[0], p->tuning.pb[0], dev.lds_per_wg);
+        p->geom = chain_geometry(p->dims, p->tuning, dev.lds_per_wg);
     if (rc == TDC_OK && p->tuning.variant == TDC_VARIANT_FUSED_MERGED)
         p->geom = tdc_fm_geometry(p->dims, p->tuning.tile_h, p->tuning.tile_w, p->tuning.waves[0], p->tuning.mb[1]);
     if (rc == TDC_OK) rc = check_tuning(*p, dev);
@@ -356,10 +372,14 @@ int tdc_plan_create_tuned(tdc_plan **out, const tdc_shape *shape, int device, co
         p->ws_bytes += (n_z1 + n_z2) * sizeof(float);
     }
     if (!dense && !merged && p->tuning.variant != TDC_VARIANT_NAIVE) {
-        ok = ok && hipMalloc((void **)&p->uin_p, n_w1 * sizeof(float)) == hipSuccess;
-        ok = ok && hipMalloc((void **)&p->core_p, n_w2 * sizeof(float)) == hipSuccess;
-        ok = ok && hipMalloc((void **)&p->uout_p, n_w3 * sizeof(float)) == hipSuccess;
-        p->ws_bytes += (n_w1 + n_w2 + n_w3) * sizeof(float);
+        const bool parts = tdc_is_chain3(p->tuning);
+        const size_t b1 = parts ? tdc_packed3_bytes(d.NB1, d.KG1) : n_w1 * sizeof(float);
+        const size_t b2 = parts ? tdc_packed3_bytes(d.NB2, d.K * d.K * d.NB1) : n_w2 * sizeof(float);
+        const size_t b3 = parts ? tdc_packed3_bytes(d.NB3, d.NB2) : n_w3 * sizeof(float);
+        ok = ok && hipMalloc((void **)&p->uin_p, b1) == hipSuccess;
+        ok = ok && hipMalloc((void **)&p->core_p, b2) == hipSuccess;
+        ok = ok && hipMalloc((void **)&p->uout_p, b3) == hipSuccess;
+        p->ws_bytes += b1 + b2 + b3;
     }
     if (!ok) {
         (void)hipGetLastError();
@@ -372,6 +392,8 @@ int tdc_plan_create_tuned(tdc_plan **out, const tdc_shape *shape, int device, co
         hipError_t e = hipSuccess;
         if (p->tuning.variant == TDC_VARIANT_FUSED)
             e = tdc_launch_fused(d, p->tuning, p->geom, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, none, true);
+        else if (tdc_is_chain3(p->tuning))
+            e = tdc_launch_chain3(d, p->tuning, p->geom, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, none, true);
         else if (p->tuning.variant == TDC_VARIANT_CHAIN)
             e = tdc_launch_chain(d, p->tuning, p->geom, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, none, true);
         else if (p->tuning.variant == TDC_VARIANT_FUSED_MERGED)
@@ -408,7 +430,7 @@ int tdc_select_tuning(const tdc_shape *shape, int compute_units, int lds_bytes, 
     if (rc == TDC_OK && tmp.tuning.variant == TDC_VARIANT_FUSED)
         tmp.geom = tdc_fused_geometry(tmp.dims, tmp.tuning.tile_h, tmp.tuning.tile_w, dev.lds_per_wg);
     if (rc == TDC_OK && tmp.tuning.variant == TDC_VARIANT_CHAIN)
-        tmp.geom = tdc_chain_geometry(tmp.dims, tmp.tuning.tile_h, tmp.tuning.tile_w, tmp.tuning.waves[0], tmp.tuning.pb[0], dev.lds_per_wg);
+        tmp.geom = chain_geometry(tmp.dims, tmp.tuning, dev.lds_per_wg);
     if (rc == TDC_OK && tmp.tuning.variant == TDC_VARIANT_FUSED_MERGED)
         tmp.geom = tdc_fm_geometry(tmp.dims, tmp.tuning.tile_h, tmp.tuning.tile_w, tmp.tuning.waves[0], tmp.tuning.mb[1]);
     if (rc == TDC_OK) rc = check_tuning(tmp, dev);
@@ -437,7 +459,7 @@ int tdc_model_terms(const tdc_shape *shape, const tdc_tuning *tuning, int comput
     if (tuning->variant == TDC_VARIANT_FUSED)
         tmp.geom = tdc_fused_geometry(tmp.dims, tuning->tile_h, tuning->tile_w, lds_bytes);
     if (tuning->variant == TDC_VARIANT_CHAIN)
-        tmp.geom = tdc_chain_geometry(tmp.dims, tuning->tile_h, tuning->tile_w, tuning->waves[0], tuning->pb[0], lds_bytes);
+        tmp.geom = chain_geometry(tmp.dims, *tuning, lds_bytes);
     if (tuning->variant == TDC_VARIANT_FUSED_MERGED)
         tmp.geom = tdc_fm_geometry(tmp.dims, tuning->tile_h, tuning->tile_w, tuning->waves[0], tuning->mb[1]);
     rc = check_tuning(tmp, dev);
@@ -464,6 +486,15 @@ int tdc_plan_destroy(tdc_plan *p)
     return rc;
 }
 
+static hipError_t pack_tucker(const tdc_plan &p, hipStream_t s, const float *U_in, const float *core, const float *U_out)
+{
+    const int v = p.tuning.variant;
+    if (v == TDC_VARIANT_MERGED || v == TDC_VARIANT_FUSED_MERGED || v == TDC_VARIANT_MERGED_XCD)
+        return tdc_launch_pack_merged(p.dims, s, U_in, core, U_out, p.uin_p, p.wm, p.core_p);
+    if (tdc_is_chain3(p.tuning)) return tdc_launch_pack3(p.dims, s, U_in, core, U_out, p.uin_p, p.core_p, p.uout_p);
+    return tdc_launch_pack(p.dims, s, U_in, core, U_out, p.uin_p, p.core_p, p.uout_p);
+}
+
 int tdc_plan_pack_weights(tdc_plan *p, void *hip_stream, const float *U_in, const float *core, const float *U_out)
 {
     if (!p || !U_in || !core || !U_out) return TDC_ERR_NULL;
@@ -475,12 +506,7 @@ int tdc_plan_pack_weights(tdc_plan *p, void *hip_stream, const float *U_in, cons
     }
     DeviceGuard guard(p->device);
     if (!guard.ok) return TDC_ERR_HIP;
-    const bool merged_weights = p->tuning.variant == TDC_VARIANT_MERGED || p->tuning.variant == TDC_VARIANT_FUSED_MERGED ||
-                                p->tuning.variant == TDC_VARIANT_MERGED_XCD;
-    const hipError_t e = merged_weights
-                             ? tdc_launch_pack_merged(p->dims, (hipStream_t)hip_stream, U_in, core, U_out, p->uin_p, p->wm, p->core_p)
-                             : tdc_launch_pack(p->dims, (hipStream_t)hip_stream, U_in, core, U_out, p->uin_p, p->core_p, p->uout_p);
-    if (e != hipSuccess) return TDC_ERR_HIP;
+    if (pack_tucker(*p, (hipStream_t)hip_stream, U_in, core, U_out) != hipSuccess) return TDC_ERR_HIP;
     p->packed_from[0] = U_in; p->packed_from[1] = core; p->packed_from[2] = U_out;
     return TDC_OK;
 }
@@ -513,11 +539,7 @@ int tdc_conv_tucker2_ex(tdc_plan *p, void *hip_stream, const float *x, const flo
     const bool packed = p->packed_from[0] == U_in && p->packed_from[1] == core && p->packed_from[2] == U_out;
     if (!packed) {   // no stored copy for these pointers: re-lay out on the stream, remember nothing
         p->packed_from[0] = p->packed_from[1] = p->packed_from[2] = nullptr;
-        e = (p->tuning.variant == TDC_VARIANT_MERGED || p->tuning.variant == TDC_VARIANT_FUSED_MERGED ||
-             p->tuning.variant == TDC_VARIANT_MERGED_XCD)
-                ? tdc_launch_pack_merged(d, s, U_in, core, U_out, p->uin_p, p->wm, p->core_p)
-                : tdc_launch_pack(d, s, U_in, core, U_out, p->uin_p, p->core_p, p->uout_p);
-        if (e != hipSuccess) return TDC_ERR_HIP;
+        if (pack_tucker(*p, s, U_in, core, U_out) != hipSuccess) return TDC_ERR_HIP;
     }
     if (p->tuning.variant == TDC_VARIANT_FUSED_MERGED)
         e = tdc_launch_fm(d, p->tuning, p->geom, s, x, p->uin_p, p->core_p, y, epi);
@@ -527,6 +549,8 @@ int tdc_conv_tucker2_ex(tdc_plan *p, void *hip_stream, const float *x, const flo
         e = tdc_launch_merged_xcd(d, p->tuning, s, x, p->uin_p, p->core_p, p->z1, p->arrive, p->status, p->wait_limit, y, epi);
     else if (p->tuning.variant == TDC_VARIANT_SPLIT)
         e = tdc_launch_split(d, p->tuning, s, x, p->uin_p, p->core_p, p->uout_p, p->z1, p->z2, y, epi);
+    else if (tdc_is_chain3(p->tuning))
+        e = tdc_launch_chain3(d, p->tuning, p->geom, s, x, p->uin_p, p->core_p, p->uout_p, y, epi);
     else if (p->tuning.variant == TDC_VARIANT_CHAIN)
         e = tdc_launch_chain(d, p->tuning, p->geom, s, x, p->uin_p, p->core_p, p->uout_p, y, epi);
     else

@@ -31,10 +31,14 @@ typedef unsigned tdc_u4 __attribute__((ext_vector_type(4)));
 // two fp32 -> their three bf16 parts, packed in pairs (11 VALU instructions)
 __device__ __forceinline__ void tdc_split2(float a, float b, unsigned &p1, unsigned &p2, unsigned &p3)
 {
-    // as an instruction, not a conversion: the compiler would convert the low value a second time rather than shift the pair
+    // Opaque after the conversion: the compiler would else convert the low value a second time rather than shift the pair.
+    // The conversion itself must not be written as asm: it may read a matrix-core result, and the compiler inserts the wait
+    // states that needs only in front of instructions it knows.
     const auto pack = [](float u, float v) {
-        unsigned r;
-        asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(u), "v"(v));
+        typedef float f2 __attribute__((ext_vector_type(2)));
+        typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+        unsigned r = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){u, v}, bf2));
+        asm("" : "+v"(r));
         return r;
     };
     p1 = pack(a, b);

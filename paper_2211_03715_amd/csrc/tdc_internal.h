@@ -60,6 +60,8 @@ hipError_t tdc_launch_pack_merged(const TdcDims &d, hipStream_t s, const float *
 // two k-groups, component j = what the fp32 layout has as component j%4 of k-group 2*step + j/4 (zero past the last one).
 inline size_t tdc_packed3_bytes(int m_blocks, int k_groups) { return (size_t)m_blocks * ((k_groups + 1) / 2) * 3072; }
 hipError_t tdc_launch_pack3_core(const TdcDims &d, hipStream_t s, const float *core, void *core_p3);
+hipError_t tdc_launch_pack3(const TdcDims &d, hipStream_t s, const float *U_in, const float *core, const float *U_out,
+                            void *uin_p3, void *core_p3, void *uout_p3);
 size_t tdc_packed_floats_uin(const TdcDims &d);
 size_t tdc_packed_floats_core(const TdcDims &d);
 size_t tdc_packed_floats_uout(const TdcDims &d);
@@ -123,6 +125,16 @@ TdcFusedGeom tdc_chain_geometry(const TdcDims &d, int tile_h, int tile_w, int nw
 hipError_t tdc_launch_chain(const TdcDims &d, const tdc_tuning &t, const TdcFusedGeom &g, hipStream_t s,
                             const float *x, const float *uin_p, const float *core_p,
                             const float *uout_p, float *y, const TdcEpi &epi, bool prepare_only = false);
+
+// ---- the same on the bf16 matrix cores (tdc_chain3.hip, kernel in tdc_chain3_kernel.h): weights in tdc_launch_pack3's layout,
+// workgroups of four wavefronts.  A CHAIN tuning asks for it with mb[1] == TDC_CHAIN3_PARTS; pb[0] is 2 or 4.
+constexpr int TDC_CHAIN3_PARTS = 3;
+inline bool tdc_is_chain3(const tdc_tuning &t) { return t.variant == TDC_VARIANT_CHAIN && t.mb[1] == TDC_CHAIN3_PARTS; }
+bool tdc_chain3_supported(const TdcDims &d, int mb1, int pb);
+TdcFusedGeom tdc_chain3_geometry(const TdcDims &d, int tile_h, int tile_w);
+hipError_t tdc_launch_chain3(const TdcDims &d, const tdc_tuning &t, const TdcFusedGeom &g, hipStream_t s, const float *x,
+                             const void *uin_p3, const void *core_p3, const void *uout_p3, float *y, const TdcEpi &epi,
+                             bool prepare_only = false);
 
 // ---- one-launch kernel: stage 1 into LDS, then the merged stage-2/3 convolution (tdc_fm.hip).
 // Tuning fields: tile_h, tile_w, waves[0], mb[0] = stage-1 register tile, mb[1] = output-channel

@@ -45,24 +45,39 @@ __global__ void pack_core_kernel(TdcDims d, const float *__restrict__ core, floa
     out[e] = (d1 < d.R1 && m < d.R2) ? core[(((size_t)d1 * d.R2 + m) * d.K + r) * d.K + s] : 0.f;
 }
 
-// One thread per pair of components of the three-part layout: e = ((mb*S + step)*64 + lane)*4 + pair.
+// One thread per pair of components of the three-part layout: e = ((mb*S + step)*64 + lane)*4 + pair.  weight(kg, k, m) is
+// the value of k-group kg's contraction index k (0..15) and output channel m, zero past the end of either.
+template <class Weight>
+__device__ __forceinline__ void pack3(size_t e, int KG, unsigned *__restrict__ out, Weight weight)
+{
+    const int S = (KG + 1) / 2;
+    const int pair = (int)(e & 3), lane = (int)((e >> 2) & 63);
+    const size_t blk = e >> 8;
+    const int step = (int)(blk % S), mb = (int)(blk / S);
+    const int kg = 2 * step + (pair >> 1), m = 16 * mb + (lane & 15), k = 4 * (lane >> 4) + 2 * (pair & 1);
+    unsigned p[3];
+    tdc_split2(kg < KG ? weight(kg, k, m) : 0.f, kg < KG ? weight(kg, k + 1, m) : 0.f, p[0], p[1], p[2]);
+    for (int i = 0; i < 3; ++i) out[(blk * 3 + i) * 256 + lane * 4 + pair] = p[i];
+}
+
 __global__ void pack3_core_kernel(TdcDims d, const float *__restrict__ core, unsigned *__restrict__ out, size_t total)
 {
     const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= total) return;
-    const int KG = d.K * d.K * d.NB1, S = (KG + 1) / 2;
-    const int pair = (int)(e & 3), lane = (int)((e >> 2) & 63);
-    const size_t blk = e >> 8;
-    const int step = (int)(blk % S), mb = (int)(blk / S);
-    const int kg = 2 * step + (pair >> 1), m = 16 * mb + (lane & 15);
-    const int tap = kg / d.NB1, r = tap / d.K, s = tap % d.K;
-    const int d1 = 16 * (kg % d.NB1) + 4 * (lane >> 4) + 2 * (pair & 1);
-    float v[2];
-    for (int i = 0; i < 2; ++i)
-        v[i] = (kg < KG && d1 + i < d.R1 && m < d.R2) ? core[(((size_t)(d1 + i) * d.R2 + m) * d.K + r) * d.K + s] : 0.f;
-    unsigned p[3];
-    tdc_split2(v[0], v[1], p[0], p[1], p[2]);
-    for (int i = 0; i < 3; ++i) out[(blk * 3 + i) * 256 + lane * 4 + pair] = p[i];
+    pack3(e, d.K * d.K * d.NB1, out, [&](int kg, int k, int m) {
+        const int tap = kg / d.NB1, r = tap / d.K, s = tap % d.K, d1 = 16 * (kg % d.NB1) + k;
+        return d1 < d.R1 && m < d.R2 ? core[(((size_t)d1 * d.R2 + m) * d.K + r) * d.K + s] : 0.f;
+    });
+}
+
+// U_in [C][R1] and U_out [R2][N]: w[k][m], `rows` x `cols`
+__global__ void pack3_matrix_kernel(int rows, int cols, const float *__restrict__ w, unsigned *__restrict__ out, size_t total)
+{
+    const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= total) return;
+    pack3(e, (rows + 15) / 16, out, [&](int kg, int k, int m) {
+        return 16 * kg + k < rows && m < cols ? w[(size_t)(16 * kg + k) * cols + m] : 0.f;
+    });
 }
 
 __global__ void pack_uout_kernel(TdcDims d, const float *__restrict__ U_out, float *__restrict__ out, size_t total)
@@ -132,4 +147,14 @@ hipError_t tdc_launch_pack3_core(const TdcDims &d, hipStream_t s, const float *c
     const size_t n = tdc_packed3_bytes(d.NB2, d.K * d.K * d.NB1) / 12;
     hipLaunchKernelGGL(pack3_core_kernel, dim3((unsigned)((n + T - 1) / T)), dim3(T), 0, s, d, core, (unsigned *)core_p3, n);
     return hipGetLastError();
+}
+
+hipError_t tdc_launch_pack3(const TdcDims &d, hipStream_t s, const float *U_in, const float *core, const float *U_out,
+                            void *uin_p3, void *core_p3, void *uout_p3)
+{
+    const int T = 256;
+    const size_t n1 = tdc_packed3_bytes(d.NB1, d.KG1) / 12, n3 = tdc_packed3_bytes(d.NB3, d.NB2) / 12;
+    hipLaunchKernelGGL(pack3_matrix_kernel, dim3((unsigned)((n1 + T - 1) / T)), dim3(T), 0, s, d.C, d.R1, U_in, (unsigned *)uin_p3, n1);
+    hipLaunchKernelGGL(pack3_matrix_kernel, dim3((unsigned)((n3 + T - 1) / T)), dim3(T), 0, s, d.R2, d.N, U_out, (unsigned *)uout_p3, n3);
+    return tdc_launch_pack3_core(d, s, core, core_p3);
 }

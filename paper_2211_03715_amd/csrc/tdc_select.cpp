@@ -298,6 +298,69 @@ FusedChoice best_chain(const TdcDims &d, const TdcDeviceInfo &dev, const tdc_tun
     return best;
 }
 
+// CHAIN on the bf16 matrix cores (tdc_chain3.hip): a workgroup of four wavefronts is a chain of phases, in cycles of its SIMD
+// (96 per fp32 product block: six MFMAs of 16 cycles): stage 1 in rounds of four units, then one group of two pixel blocks
+// per wavefront.  Sweeps of ten layers (tiles of 32 to 800 pixels, groups of two and four blocks) were won by tiles that give
+// every wavefront exactly one group of two -- 128 pixels at most -- or lay within 4 % of such a tile, so only those are
+// compared.  Two or three workgroups that share a compute unit overlap half of their chains.
+struct Chain3Choice {
+    double us = 1e300;
+    int th = 0, tw = 0, mb1 = 0, pb = 0;
+};
+
+// terms: constant; thousands of cycles of stage 1, of stages 2 and 3, and chains, each times what sharing a compute unit adds
+enum { X_LAUNCH, X_S1, X_S23, X_PHASES, X_TERMS };
+const char *const kChain3TermNames[X_TERMS] = {"launch", "s1_kcycles", "s23_kcycles", "phases"};
+const double kChain3Coef[X_TERMS] = {3.0, 0.5, 0.5, 3.0};
+
+void chain3_terms(double (&f)[X_TERMS], const TdcDims &d, const TdcDeviceInfo &dev, const TdcFusedGeom &g, bool runs, int mb1, int pb)
+{
+    const int S1 = (d.KG1 + 1) / 2, S2 = (d.K * d.K * d.NB1 + 1) / 2, S3 = (d.NB2 + 1) / 2;
+    const int pb1 = runs ? 4 : 2, rpr = runs ? tdc_runs_per_row(d.W, d.Wo, g.TW, d.K, d.stride, d.pad) : 0;
+    const int u1 = (runs ? cdiv(g.QH * rpr, 16) : cdiv(g.QB, 2)) * cdiv(d.NB1, mb1), u2 = cdiv(g.PBk, pb);
+    // a step of stage 1: its products, the splitting of x, and what of the loads is not hidden
+    const double c1 = S1 * (mb1 * pb1 * 96.0 + pb1 * 180.0 + 250.0);
+    const double c23 = S2 * (d.NB2 * pb * 96.0 + 60.0) + d.NB3 * (S3 * pb * 96.0 + 60.0);
+    const double per_cu = std::max(1.0, (double)g.tiles_x * g.tiles_y * d.B / dev.cus);
+    const int fit = std::max(1, std::min((int)(dev.lds_per_wg / std::max<size_t>(g.lds_bytes, 1)), 3));
+    const int r = std::min(fit, (int)std::ceil(per_cu));
+    const double chains = (1.0 + 0.5 * (r - 1)) * std::max(1.0, per_cu / r);
+    f[X_LAUNCH] = 1.0;
+    f[X_S1] = chains * cdiv(u1, 4) * c1 * 1e-3;
+    f[X_S23] = chains * cdiv(u2, 4) * c23 * 1e-3;
+    f[X_PHASES] = chains;
+}
+
+double chain3_us(const TdcDims &d, const TdcDeviceInfo &dev, const TdcFusedGeom &g, bool runs, int mb1, int pb)
+{
+    double f[X_TERMS];
+    chain3_terms(f, d, dev, g, runs, mb1, pb);
+    return dot(kChain3Coef, f, X_TERMS);
+}
+
+Chain3Choice best_chain3(const TdcDims &d, const TdcDeviceInfo &dev, const tdc_tuning &forced)
+{
+    const bool runs = tdc_runs_apply(d, dev.cus);
+    Chain3Choice best;
+    const int th_lo = forced.tile_h ? forced.tile_h : 1, th_hi = forced.tile_h ? forced.tile_h : std::min(d.Ho, 32);
+    const int tw_lo = forced.tile_w ? forced.tile_w : std::min(d.Wo, 4), tw_hi = forced.tile_w ? forced.tile_w : std::min(d.Wo, 64);
+    for (int th = th_lo; th <= th_hi; ++th)
+        for (int tw = tw_lo; tw <= tw_hi; ++tw) {
+            if (!forced.tile_w && !d.nhwc && d.Wo % 4 == 0 && tw % 4) continue;   // whole 16-byte quads where the image allows them
+            if ((!forced.tile_h || !forced.tile_w) && th * tw > 128) continue;
+            const TdcFusedGeom g = tdc_chain3_geometry(d, th, tw);
+            if ((long)g.lds_bytes > dev.lds_per_wg) continue;
+            for (int mb1 = 1; mb1 <= 3; ++mb1)
+                for (int pb : {2, 4}) {
+                    if ((forced.mb[0] && mb1 != forced.mb[0]) || pb != (forced.pb[0] ? forced.pb[0] : 2)) continue;
+                    if (!tdc_chain3_supported(d, mb1, pb)) continue;
+                    const double us = chain3_us(d, dev, g, runs, mb1, pb);
+                    if (us < best.us) best = {us, th, tw, mb1, pb};
+                }
+        }
+    return best;
+}
+
 // FUSED_MERGED: stage 1 as in FUSED (dealt over nw wavefronts), then every wavefront runs its
 // slice of the merged convolution out of registers and LDS.  Fitted to ~6600 tunings of 27 batch-1
 // layer shapes in both activation layouts (median relative error 8%; the picked tuning on average
@@ -535,6 +598,11 @@ int tdc_select_terms(const TdcDims &d, const TdcDeviceInfo &dev, const tdc_tunin
         fused_terms(f, throughput, d, dev, g, runs, t.waves[0], t.mb[0], t.mb[1], t.mb[2], t.pb[0]);
         return emit(f, kFusedTermNames, F_TERMS, throughput ? "fused_throughput" : "fused_latency");
     }
+    if (tdc_is_chain3(t)) {
+        double f[X_TERMS];
+        chain3_terms(f, d, dev, tdc_chain3_geometry(d, t.tile_h, t.tile_w), runs, t.mb[0], t.pb[0]);
+        return emit(f, kChain3TermNames, X_TERMS, "chain");
+    }
     if (t.variant == TDC_VARIANT_CHAIN) {
         const TdcFusedGeom g = tdc_chain_geometry(d, t.tile_h, t.tile_w, t.waves[0], t.pb[0], dev.lds_per_wg);
         double f[C_TERMS];
@@ -678,6 +746,19 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
         }
         return TDC_OK;
     }
+    const auto chain3 = [&](const Chain3Choice &c) {
+        t->variant = TDC_VARIANT_CHAIN;
+        t->tile_h = c.th; t->tile_w = c.tw;
+        t->waves[0] = t->waves[1] = t->waves[2] = 4;
+        t->mb[0] = c.mb1; t->mb[1] = TDC_CHAIN3_PARTS; t->mb[2] = 1;
+        t->pb[0] = t->pb[1] = t->pb[2] = c.pb;
+        if (model_us) *model_us = c.us;
+        return TDC_OK;
+    };
+    if (tdc_is_chain3(forced) && (!forced.waves[0] || forced.waves[0] == 4)) {
+        const Chain3Choice c = best_chain3(d, dev, forced);
+        if (c.us < 1e299) return chain3(c);
+    }
     if (forced.variant == TDC_VARIANT_CHAIN) {
         const FusedChoice c = best_chain(d, dev, forced);
         if (c.us >= 1e299) return TDC_ERR_BAD_TUNING;
@@ -689,6 +770,16 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
         return TDC_OK;
     }
 
+    // The throughput regime proper: from 64 output pixels per compute unit CHAIN on the bf16 matrix cores is the fastest form
+    // timed (fp32 CHAIN or FUSED -> bf16 parts, 98 pixels: 46.8 -> 33.5, 38.2 -> 34.9, 26.8 -> 23.8 us; 196: 37.5 -> 27.5;
+    // 784: 103.3 -> 66.6).  At 24 pixels a workgroup has its compute unit to itself, nothing overlaps its phases, and the
+    // kernels that cut a tile along channels as well win (22.4 against 27.5, 19.0 against 22.7 us).
+    if (forced.variant == TDC_VARIANT_AUTO && (long)d.B * d.Ho * d.Wo >= 64L * dev.cus) {
+        tdc_tuning free_choice = forced;
+        free_choice.mb[0] = free_choice.pb[0] = free_choice.tile_h = free_choice.tile_w = 0;
+        const Chain3Choice c = best_chain3(d, dev, free_choice);
+        if (c.us < 1e299) return chain3(c);
+    }
     FusedChoice f;
     if (forced.variant == TDC_VARIANT_AUTO || forced.variant == TDC_VARIANT_FUSED) f = best_fused(d, dev, forced);
     // output pixels alone give every CU a 16-pixel block: the throughput regime

@@ -1,0 +1,85 @@
+"""GPU parity of CHAIN on the bf16 matrix cores (mb[1] = 3: every factor in three parts) at the sizes where it can go wrong:
+odd numbers of k-groups in each contraction, channel counts and ranks that fill no block, tiles that leave part of a pixel
+group or of the image empty, taps outside the image, the three ways x is read (NHWC, NCHW four bytes at a time, NCHW in aligned
+runs of four pixels), every unit size."""
+import numpy as np
+import pytest
+
+from parity_util import assert_parity
+from paper_2211_03715_amd import binding as B
+from paper_2211_03715_amd.workloads import Layer, make_inputs
+
+pytestmark = pytest.mark.gpu
+
+# (layer, tiles): the last three have 16 output pixels per compute unit and W % 4 == 0, so NCHW reads them in runs
+CASES = [
+    (Layer(2, 24, 40, 20, 18, 16, 24, 3, 1, 1), ((20, 18), (3, 5))),     # one z1 block: 9 k-groups, C = 1.5 groups of 16
+    (Layer(3, 100, 148, 37, 28, 24, 40, 5, 1, 2), ((4, 8), (5, 7))),     # three z2 blocks, 5x5
+    (Layer(2, 64, 64, 12, 16, 64, 80, 3, 2, 1), ((6, 8), (2, 4))),       # five z2 blocks, stride 2
+    (Layer(1, 36, 36, 9, 7, 36, 52, 3, 1, 1), ((9, 7),)),                # three z1 blocks, four z2 blocks
+    (Layer(1, 4, 4, 1, 1, 1, 1, 1, 1, 0), ((1, 1),)),                    # a single pixel
+    (Layer(1, 12, 12, 15, 17, 6, 5, 7, 4, 6), ((2, 3), (6, 7))),         # 7x7, stride 4, taps far outside
+    (Layer(40, 64, 96, 28, 28, 20, 33, 3, 2, 1), ((7, 14), (14, 12))),   # runs, stride 2
+    (Layer(40, 20, 24, 12, 12, 16, 16, 3, 1, 1), ((12, 12), (5, 8))),    # runs, tiles past the last row and column
+    (Layer(5, 8, 36, 32, 36, 50, 60, 1, 1, 0), ((4, 32), (8, 8))),       # runs, 1x1, C below one group
+]
+
+
+def _run(layer, inputs, tuning, nhwc, bias=None, residual=None, offset=0):
+    import torch
+    from paper_2211_03715_amd.layer import TuckerConv2d
+    dev = torch.device("cuda:0")
+    put = lambda a: torch.from_numpy(np.ascontiguousarray(a.transpose(0, 2, 3, 1) if nhwc else a)).to(dev)
+    conv = TuckerConv2d(layer, 0, tuning, layout=B.LAYOUT_NHWC if nhwc else B.LAYOUT_NCHW)
+    try:
+        assert "bf3" in conv.describe(), conv.describe()
+        w = [torch.from_numpy(inputs[k]).to(dev) for k in ("U_in", "core", "U_out")]
+        conv.pack(*w)
+        shape = conv.out_shape()
+        whole = torch.full((offset + int(np.prod(shape)),), float("nan"), device=dev)
+        y = whole[offset:].view(shape)                      # offset 1: only 4-byte aligned
+        conv(put(inputs["x"]), y, bias=None if bias is None else torch.from_numpy(bias).to(dev),
+             residual=None if residual is None else put(residual), relu=bias is not None)
+        torch.cuda.synchronize()
+        got = y.cpu().numpy()
+        return got.transpose(0, 3, 1, 2) if nhwc else got
+    finally:
+        conv.close()
+
+
+def _units(layer):
+    nb1, nb2 = (layer.R1 + 15) // 16, (layer.R2 + 15) // 16
+    return [(mb1, pb) for mb1 in (1, 2, 3) if mb1 <= nb1 for pb in ((2, 4) if nb2 <= 3 else (2,))]
+
+
+@pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
+@pytest.mark.parametrize("layer,tiles", CASES, ids=lambda v: v.name() if isinstance(v, Layer) else "")
+def test_chain3(orc, layer, tiles, nhwc):
+    inputs = make_inputs(layer, 91)
+    want, _ = orc.conv_factored(orc.Shape(**layer.asdict()), **inputs)
+    rng = np.random.default_rng(6)
+    bias = rng.standard_normal(layer.N, dtype=np.float32)
+    residual = rng.standard_normal(want.shape, dtype=np.float32)
+    with_epi = np.maximum(want + bias.astype(np.float64)[None, :, None, None] + residual, 0.0)
+    for th, tw in tiles:
+        for mb1, pb in _units(layer):
+            t = B.make_tuning(variant=B.VARIANT_CHAIN, tile_h=th, tile_w=tw, waves=(4, 4, 4), mb=(mb1, 3, 1), pb=(pb,) * 3)
+            print("[case] chain3", layer.name(), "nhwc" if nhwc else "nchw", th, tw, mb1, pb, flush=True)
+            got = _run(layer, inputs, t, nhwc)
+            assert_parity(got, want, "%s tile %dx%d units %d,%d" % (layer.name(), th, tw, mb1, pb))
+            # three chained sums of at most 600 terms: fp32 multiply-adds show up to 1e-6, the split products no more; two
+            # parts instead of three would show 5e-6 in each
+            assert np.linalg.norm(got - want) <= 1.5e-6 * max(np.linalg.norm(want), 1e-30)
+        got = _run(layer, inputs, t, nhwc, bias, residual, 0 if nhwc else 1)
+        assert_parity(got, with_epi, "%s tile %dx%d epilogue" % (layer.name(), th, tw))
+
+
+def test_the_selector_takes_it_from_64_pixels_per_compute_unit():
+    for lay in (B.LAYOUT_NCHW, B.LAYOUT_NHWC):
+        t = B.tdc_select_tuning(B.make_shape(256, 128, 128, 28, 28, 32, 32, layout=lay))
+        assert t.variant == B.VARIANT_CHAIN and t.mb[1] == 3 and t.tile_h * t.tile_w <= 128
+        B.tdc_plan_destroy(B.tdc_plan_create(B.make_shape(256, 128, 128, 28, 28, 32, 32, layout=lay), 0, t))
+        assert B.tdc_select_tuning(B.make_shape(32, 256, 256, 14, 14, 64, 64, layout=lay)).mb[1] != 3
+    # six z2 blocks: no such instance, the fp32 kernel takes the tuning
+    t = B.make_tuning(variant=B.VARIANT_CHAIN, mb=(0, 3, 0))
+    assert B.tdc_select_tuning(B.make_shape(64, 96, 96, 28, 28, 96, 96), tuning=t).mb[1] == 1
