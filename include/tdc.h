@@ -36,8 +36,9 @@
  *
  * Precision: fp32 in, fp32 out, sums in fp32.  Kernels bound by matrix arithmetic multiply on the bf16 matrix cores with
  * every fp32 factor split into three bf16 parts (all 24 bits); the products are at least as accurate as fp32
- * multiply-adds for normal numbers, keep an absolute accuracy of 2^-134 for factors below 2^-110, and turn an infinite
- * factor into NaN.
+ * multiply-adds for normal numbers and keep an absolute accuracy of 2^-134 for factors below 2^-110.  The dense layer gives
+ * infinite factors' outputs as fp32 arithmetic does; in a Tucker layer, where an infinity reaches every channel of z1 with
+ * either sign, they come out as NaN.
  *
  * Errors: every function returns a tdc_status (0 = success, negative =
  * failure).  Nothing aborts, throws or prints.

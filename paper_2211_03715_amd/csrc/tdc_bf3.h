@@ -12,7 +12,7 @@
 // v_mfma_f32_16x16x4_f32 gives 1.1e-7 / 3.1e-7 / 7.1e-7 / 1.3e-6; all nine products give the same figures as six.
 // Time per 16 x 16 x 32 block: 6 x 16 cycles against 8 x 32.
 // Values below 2^-110 keep an absolute accuracy of 2^-134 instead of a relative one (bf16 has no smaller subnormals);
-// an infinite value comes out as NaN (inf - inf in the split).
+// an infinite value comes out as NaN (inf - inf in the split): a kernel whose fp32 form gave infinities looks for that.
 //
 // Operand layout of v_mfma_f32_16x16x32_bf16 (D 16x16 += A 16x32 * B 32x16): lane l holds A[m = l%16][k(l/16, j)] and
 // B[k(l/16, j)][p = l%16], j = 0..7, for any assignment k(g, j) that A and B share; D as in tdc_mfma.h.  Here a step is a pair of

@@ -46,6 +46,31 @@ __device__ __forceinline__ int tile_logical_block(int bid, int n)
     return xcd * per + min(xcd, rem) + slot;
 }
 
+// One output by fp32 multiply-adds, for the outputs the split products cannot give.
+template <int ACT, bool CONV>
+__device__ __forceinline__ void tile_plain_output(const TileArgs &a, int m, int p)
+{
+    const int b = tdc_div(p, a.div_P), pix = p - b * a.P;
+    const int oh = CONV ? tdc_div(pix, a.div_Wo) : 0, h0 = oh * a.stride - a.pad, w0 = (pix - oh * a.Wo) * a.stride - a.pad;
+    const float *x = a.act + (size_t)b * a.C * a.HW;
+    const unsigned short *w = reinterpret_cast<const unsigned short *>(a.w3) + (size_t)(m >> 4) * a.S * 1536;
+    const auto part = [](unsigned short v) { return __builtin_bit_cast(float, (unsigned)v << 16); };
+    float sum = 0.f;
+    for (int kg = 0; kg < a.KG; ++kg) {
+        const int tap = CONV ? tdc_div(kg, a.div_NBk) : 0, c0 = 16 * (kg - tap * a.NBk);
+        const int r = tap / a.K, h = h0 + r, wx = w0 + tap - r * a.K;
+        if (CONV && (h < 0 || h >= a.H || wx < 0 || wx >= a.W)) continue;
+        const int q = CONV ? h * a.W + wx : pix;
+        for (int k = 0; k < 16 && c0 + k < a.C; ++k) {
+            const unsigned short *f = w + (size_t)(kg >> 1) * 1536 + ((m & 15) + 16 * (k >> 2)) * 8 + (kg & 1) * 4 + (k & 3);
+            const float w1 = part(f[0]), ww = fabsf(w1) == INFINITY ? w1 : w1 + (part(f[512]) + part(f[1024]));
+            sum = fmaf(ww, ACT == TDC_ACT_NHWC ? x[(size_t)q * a.C + c0 + k] : x[(size_t)(c0 + k) * a.HW + q], sum);
+        }
+    }
+    const size_t idx = ACT == TDC_ACT_NHWC ? (size_t)p * a.M + m : ((size_t)b * a.M + m) * a.P + pix;
+    a.out[idx] = tdc_apply_epilogue(a.epi, sum, m, idx);
+}
+
 template <int ACT, bool CONV, int WM, int MB, int PB, int KS>
 __global__ __launch_bounds__(256 * KS, 3) void tdc_tile_kernel(TileArgs a)
 {
@@ -254,6 +279,23 @@ __global__ __launch_bounds__(256 * KS, 3) void tdc_tile_kernel(TileArgs a)
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int pb = 0; pb < PB; ++pb) acc[mb][pb] += red[((wave * MB + mb) * PB + pb) * 64 + lane];
+    }
+
+    // An infinite factor has no three parts (inf - inf in the split) and turns its sums into NaN where fp32 arithmetic has an
+    // infinity.  A lane that holds a NaN computes its outputs once more, in fp32, from x and the weights put together again.
+    float all = 0.f;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) all += (acc[mb][pb][0] + acc[mb][pb][1]) + (acc[mb][pb][2] + acc[mb][pb][3]);
+    if (all != all) {
+        for (int e = 0; e < MB * PB * 4; ++e) {
+            const int i = e & 3, pb = (e >> 2) % PB, mb = (e >> 2) / PB;
+            const int p = p_base + 16 * pb + (SWAP ? 4 * g + i : l16), m = 16 * (mb0 + mb) + (SWAP ? l16 : 4 * g + i);
+            if (p >= a.Ptot || m >= a.M) continue;
+            tile_plain_output<ACT, CONV>(a, m, p);
+        }
+        return;
     }
 
     const auto emit = [&](int mb, int pb, tdc_f4 v) {

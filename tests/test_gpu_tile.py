@@ -95,3 +95,20 @@ def test_the_selector_takes_tiles_for_large_launches_only():
     for bad in (dict(tile_h=96, tile_w=64), dict(tile_h=64, tile_w=128), dict(tile_h=64, tile_w=64, waves=(3, 3, 3))):
         with pytest.raises(B.TdcError):
             B.tdc_plan_create(B.make_shape(1, 64, 64, 8, 8, 1, 1, 1, 1, 0), 0, B.make_tuning(variant=B.VARIANT_DENSE, **bad))
+
+
+@pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
+@pytest.mark.parametrize("layer", (Layer(2, 40, 72, 13, 9, 1, 1, 3, 1, 1), Layer(2, 40, 72, 8, 8, 1, 1, 1, 1, 0)), ids=lambda l: l.name())
+def test_infinite_inputs_give_what_fp32_arithmetic_gives(orc, layer, nhwc):
+    """An infinite value has no three parts; the outputs it reaches are infinities of the right sign all the same, and those it
+    does not reach keep their accuracy."""
+    inputs = make_dense_inputs(layer, 79)
+    inputs["x"][0, 3, 4, 5] = np.inf
+    with np.errstate(invalid="ignore"):
+        want = _oracle(orc, layer, inputs)
+    for tm, waves in ((64, 4), (128, 8)):
+        print("[case] tiles, infinite input", layer.name(), "nhwc" if nhwc else "nchw", tm, waves, flush=True)
+        got = _run(layer, inputs, tm, waves, nhwc)
+        finite = np.isfinite(want)
+        assert (~finite).any() and np.array_equal(got[~finite], want[~finite].astype(np.float32))
+        assert_parity(got[finite], want[finite], layer.name())
