@@ -701,7 +701,12 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
         if (!forced.mb[1] && !forced.pb[1] && !forced.waves[1]) {
             const TileChoice tc = best_tile(d, dev);
             const double tiles = (double)cdiv(d.NB2 * 16, 64) * cdiv(d.B * d.Ho * d.Wo, 64);
-            if (tc.us < (tiles < 1.5 * dev.cus ? 0.95 : 1.2) * c.us) return tiled(tc.tm, tc.ks, tc.us);
+            const double fill = (double)d.N / (64 * cdiv(d.N, 64));     // the part of the tiles' channels that exists
+            // From 8 tiles per compute unit on the launch is bound by memory bandwidth, which the tiles use better than either
+            // estimate says: they were faster up to 1.8 times the other estimate (NHWC, batch 32, 56x56: 64 -> 256 51.6 -> 41.2
+            // us, 48 -> 192 36.7 -> 29.7; batch 64: 32 -> 128 37.6 -> 30.0), not at 1.96 times (24 -> 96: 23.3 -> 28.9).
+            const double margin = tiles < 1.5 * dev.cus ? 0.95 : tiles < 8.0 * dev.cus ? 1.2 : std::max(1.2, 1.85 * fill);
+            if (tc.us < margin * c.us) return tiled(tc.tm, tc.ks, tc.us);
         }
         if (c.us >= 1e299) return TDC_ERR_BAD_TUNING;
         t->tile_h = t->tile_w = 0;
