@@ -108,7 +108,7 @@ TdcDims make_dims(const tdc_shape &s)
 
 TdcFusedGeom chain_geometry(const TdcDims &d, const tdc_tuning &t, int lds_limit)
 {
-    return tdc_is_chain3(t) ? tdc_chain3_geometry(d, t.tile_h, t.tile_w)
+    return tdc_is_chain3(t) ? tdc_chain3_geometry(d, t.tile_h, t.tile_w, t.pb[0])
                             : tdc_chain_geometry(d, t.tile_h, t.tile_w, t.waves[0], t.pb[0], lds_limit);
 }
 

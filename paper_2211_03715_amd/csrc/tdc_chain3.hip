@@ -18,7 +18,9 @@ bool tdc_chain3_supported(const TdcDims &d, int mb1, int pb)
     return false;
 }
 
-TdcFusedGeom tdc_chain3_geometry(const TdcDims &d, int tile_h, int tile_w)
+int tdc_chain3_share(int pixel_groups) { return pixel_groups == 1 ? 2 : pixel_groups == 2 ? 1 : 0; }
+
+TdcFusedGeom tdc_chain3_geometry(const TdcDims &d, int tile_h, int tile_w, int pb)
 {
     TdcFusedGeom g;
     g.TH = tile_h;
@@ -34,6 +36,7 @@ TdcFusedGeom tdc_chain3_geometry(const TdcDims &d, int tile_h, int tile_w)
     g.pitch2 = 0;
     g.weights_in_lds = g.weights_fit = false;
     g.lds_bytes = (size_t)96 * d.NB1 * g.pitch1;
+    if (pb > 0 && tdc_chain3_share((g.PBk + pb - 1) / pb)) g.lds_bytes += (size_t)TDC_CHAIN3_WAVES * d.NB2 * pb * 1024;
     return g;
 }
 
@@ -46,6 +49,7 @@ hipError_t tdc_launch_chain3(const TdcDims &d, const tdc_tuning &t, const TdcFus
     a.NB1 = d.NB1; a.NB3 = d.NB3; a.S1 = (d.KG1 + 1) / 2; a.KG2 = d.K * d.K * d.NB1; a.S2 = (a.KG2 + 1) / 2;
     a.TH = g.TH; a.TW = g.TW; a.QH = g.QH; a.QW = g.QW; a.Q = g.Q; a.P = g.TH * g.TW; a.QB = g.QB;
     a.n_pg2 = (g.PBk + t.pb[0] - 1) / t.pb[0];
+    a.lg_ks = tdc_chain3_share(a.n_pg2);
     a.pitch1 = g.pitch1;
     const int lay = d.nhwc ? TDC_LAY_NHWC : d.s1_runs ? TDC_LAY_NCHW_RUNS : TDC_LAY_NCHW;
     a.RPR = tdc_runs_per_row(d.W, d.Wo, g.TW, d.K, d.stride, d.pad);
@@ -60,6 +64,7 @@ hipError_t tdc_launch_chain3(const TdcDims &d, const tdc_tuning &t, const TdcFus
     a.uout_bytes = (unsigned)tdc_packed3_bytes(d.NB3, d.NB2);
     a.div_tiles_x = tdc_make_div((unsigned)g.tiles_x); a.div_tiles = tdc_make_div((unsigned)a.tiles);
     a.div_QW = tdc_make_div((unsigned)g.QW); a.div_TW = tdc_make_div((unsigned)g.TW);
+    a.div_NB1 = tdc_make_div((unsigned)d.NB1); a.div_K = tdc_make_div((unsigned)d.K);
     a.div_RPR = tdc_make_div((unsigned)a.RPR); a.div_mg1 = tdc_make_div((unsigned)a.n_mg1);
     const dim3 grid((unsigned)a.tiles, (unsigned)d.B);
     const auto launch = lay == TDC_LAY_NHWC ? tdc_launch_chain3_nhwc : lay == TDC_LAY_NCHW_RUNS ? tdc_launch_chain3_runs : tdc_launch_chain3_nchw;

@@ -6,14 +6,19 @@
 //             [part][channel block][lane group][pixel], which any pair of k-groups of stage 2 reads as operand halves;
 //   stage 2   a wavefront computes all R2 channels (NB2 blocks) of PB pixel blocks, weights streamed one step ahead;
 //   stage 3   its operand is the accumulators, split in registers; weights streamed one output block ahead.
+// A tile of one or two groups of pixel blocks has fewer groups than the workgroup has wavefronts: four or two of them then
+// share a group, each with a slice of stage 2's contraction; the partial sums meet in LDS and every wavefront goes on with all
+// of z2 and its share of the output blocks.
 //
 // What bounds it.  The fp32 form was bound by the fp32 matrix rate plus the phases of its one resident workgroup, which do
-// not overlap: 32 -> 32 ranks, 128 channels at 28x28, batch 256: 97.5 us, of which 45 us are matrix cycles and 39 us
-// compulsory bytes.  Here the products take 3/8 of the cycles, and workgroups are four wavefronts on tiles of at most 128
-// pixels, so that two to three share a compute unit and one's loads run under another's products: 66.6 us (NCHW, 4x28
-// tiles; 3.1 TB/s of compulsory bytes).  The weight fragments come through the L1 at 54 bytes a cycle: PB pixel blocks share
-// one.  PB = 4 halves that traffic, but needs 184 to 255 registers instead of 122 to 170 and was 2 to 10 % slower on every
-// layer timed; one 64 -> 32 ranks, 64 channels at 224x224: 37.5 -> 27.5 us.
+// not overlap: 32 -> 32 ranks, 128 channels at 28x28, batch 256: 97 us, of which 45 us are matrix cycles and 39 us compulsory
+// bytes.  Here the products take 3/8 of the cycles, and workgroups are four wavefronts on tiles of at most 128 pixels, so that
+// two to three share a compute unit and one's loads run under another's products: 77 us (65 us where x and y of consecutive
+// calls are the same buffers); 64 -> 32 ranks, 64 channels at 224x224: 35.7 -> 28.7 us.  What is left is memory, with loads
+// one step ahead.  The weight fragments come through the L1 at 54 bytes a cycle: PB pixel blocks share one.  PB = 4 halves that
+// traffic, but needs 184 to 255 registers instead of 122 to 170 and was 2 to 10 % slower on every layer timed.
+// With few pixels (24 per compute unit) a workgroup has its compute unit to itself and the chain of its steps is the time;
+// sharing cuts it: ranks 80, 256 channels at 14x14, batch 32: 34.6 us unshared, 20.7 shared (fp32 FUSED: 33.0).
 #ifndef TDC_CHAIN3_KERNEL_H
 #define TDC_CHAIN3_KERNEL_H
 
@@ -33,12 +38,13 @@ struct TdcChain3Args {
     int C, N, H, W, Ho, Wo, K, stride, pad;
     int NB1, NB3, S1, KG2, S2;                 // channel blocks; 32-wide steps of stage 1; k-groups and steps of stage 2
     int TH, TW, QH, QW, Q, P, QB, n_pg2;
+    int lg_ks;                                 // log2 of the wavefronts that share a group of pixel blocks (tdc_chain3_share)
     int pitch1;                                // LDS row pitch of the z1 tile, in 8-byte cells
     int RPR, n_pg1, n_mg1;                     // runs per tile row; pixel groups and channel groups of stage 1
     int tiles_x, tiles, xcd_per, xcd_rem;
     int vec;                                   // NCHW: y goes out in 16-byte quads of pixels
     unsigned uin_bytes, core_bytes, uout_bytes;
-    TdcDiv div_tiles_x, div_tiles, div_QW, div_TW, div_RPR, div_mg1;
+    TdcDiv div_tiles_x, div_tiles, div_QW, div_TW, div_RPR, div_mg1, div_NB1, div_K;
 };
 
 namespace {
@@ -215,7 +221,7 @@ template <int NB2, int PB, int LAY, int MB1>
 __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, 2) void tdc_chain3_kernel(TdcChain3Args a)
 {
     constexpr bool NHWC = LAY == TDC_LAY_NHWC;
-    extern __shared__ tdc_u2 z1s[];                              // [3 parts][NB1][4][pitch1]
+    extern __shared__ tdc_u2 z1s[];                              // [3 parts][NB1][4][pitch1], then the partial sums of ks > 1
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, l16 = lane & 15;
@@ -236,7 +242,10 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, 2) void tdc_chain3_kernel(Td
     const tdc_rsrc crs = tdc_make_rsrc(a.core3, a.core_bytes);
     const tdc_rsrc ors = tdc_make_rsrc(a.uout3, a.uout_bytes);
     const tdc_rsrc yrs = tdc_make_rsrc(a.y + (size_t)b * a.N * P2, (unsigned)a.N * P2 * 4u);
-    for (int pg = wave; pg < a.n_pg2; pg += TDC_CHAIN3_WAVES) {
+    // with fewer groups than wavefronts 2 or 4 of them share one: each takes a slice of stage 2's contraction, the sums meet in
+    // LDS, and each takes every ks-th output block of stage 3 (the loop then runs once for every wavefront)
+    const int ks = 1 << a.lg_ks, slice = wave & (ks - 1);
+    for (int pg = wave >> a.lg_ks; pg < a.n_pg2; pg += TDC_CHAIN3_WAVES) {
         // ---- stage 2: z2 channels 16*mb + 4*g + {0..3} of pixel l16 of block pb
         int qbase[PB];
 #pragma unroll
@@ -259,7 +268,11 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, 2) void tdc_chain3_kernel(Td
                     for (int q = 0; q < 3; ++q)
                         w[mb].p[q] = __builtin_bit_cast(tdc_bf8, tdc_buf_load4(crs, (unsigned)(mb * a.S2 + step) * 3072u + q * 1024u + lane * 16u));
             };
-            int kg = 0, dg = 0, s = 0, toff = 0;                 // next k-group: tap offset toff = r*QW + s, channel block dg
+            const int st0 = slice * a.S2 >> a.lg_ks, st1 = (slice + 1) * a.S2 >> a.lg_ks;
+            // next k-group: tap offset toff = r*QW + s, channel block dg
+            int kg = 2 * st0;
+            const int tap = tdc_div(kg, a.div_NB1), r = tdc_div(tap, a.div_K);
+            int dg = kg - tap * a.NB1, s = tap - r * a.K, toff = r * a.QW + s;
             const auto next_cell = [&]() {
                 const int cell = dg * 4 * a.pitch1 + toff;
                 const bool w1 = dg + 1 == a.NB1;
@@ -297,13 +310,30 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, 2) void tdc_chain3_kernel(Td
                 }
             };
             tdc_op3 wv0[NB2], wv1[NB2];
-            fetch_w(0, wv0);
-            for (int st = 0; st < a.S2; st += 2) {
+            fetch_w(st0, wv0);
+            for (int st = st0; st < st1; st += 2) {
                 fetch_w(st + 1, wv1);
                 step2(wv0);
                 fetch_w(st + 2, wv0);
-                if (st + 1 < a.S2) step2(wv1);
+                if (st + 1 < st1) step2(wv1);
             }
+        }
+        if (ks > 1) {      // partial sums, added in the order of the slices
+            tdc_f4 *__restrict__ red = reinterpret_cast<tdc_f4 *>(z1s + 3 * plane);
+#pragma unroll
+            for (int mb = 0; mb < NB2; ++mb)
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb) red[((wave * NB2 + mb) * PB + pb) * 64 + lane] = acc2[mb][pb];
+            __syncthreads();
+            const int first = wave - slice;
+#pragma unroll
+            for (int mb = 0; mb < NB2; ++mb)
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb) {
+                    tdc_f4 v = red[((first * NB2 + mb) * PB + pb) * 64 + lane];
+                    for (int j = 1; j < ks; ++j) v += red[(((first + j) * NB2 + mb) * PB + pb) * 64 + lane];
+                    acc2[mb][pb] = v;
+                }
         }
         // ---- stage 3, operands swapped in NCHW: D[pixel 4*g + i][channel l16]; NHWC: D[channel 4*g + i][pixel l16]
         constexpr int S3 = (NB2 + 1) / 2;
@@ -391,12 +421,12 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, 2) void tdc_chain3_kernel(Td
         };
         const auto stage3 = [&](auto with_epi) {
             tdc_op3 u0[S3], u1[S3];
-            fetch(0, u0);
-            for (int nb = 0; nb < a.NB3; nb += 2) {
-                fetch(nb + 1, u1);
+            fetch(slice, u0);
+            for (int nb = slice; nb < a.NB3; nb += 2 * ks) {
+                fetch(nb + ks, u1);
                 emit(with_epi, nb, u0);
-                fetch(nb + 2, u0);
-                if (nb + 1 < a.NB3) emit(with_epi, nb + 1, u1);
+                fetch(nb + 2 * ks, u0);
+                if (nb + ks < a.NB3) emit(with_epi, nb + ks, u1);
             }
         };
         if (a.epi.bias || a.epi.residual || a.epi.relu) stage3(std::true_type{});

@@ -131,7 +131,8 @@ hipError_t tdc_launch_chain(const TdcDims &d, const tdc_tuning &t, const TdcFuse
 constexpr int TDC_CHAIN3_PARTS = 3;
 inline bool tdc_is_chain3(const tdc_tuning &t) { return t.variant == TDC_VARIANT_CHAIN && t.mb[1] == TDC_CHAIN3_PARTS; }
 bool tdc_chain3_supported(const TdcDims &d, int mb1, int pb);
-TdcFusedGeom tdc_chain3_geometry(const TdcDims &d, int tile_h, int tile_w);
+int tdc_chain3_share(int pixel_groups);   // log2 of the wavefronts that work on one group of pixel blocks together
+TdcFusedGeom tdc_chain3_geometry(const TdcDims &d, int tile_h, int tile_w, int pb);
 hipError_t tdc_launch_chain3(const TdcDims &d, const tdc_tuning &t, const TdcFusedGeom &g, hipStream_t s, const float *x,
                              const void *uin_p3, const void *core_p3, const void *uout_p3, float *y, const TdcEpi &epi,
                              bool prepare_only = false);

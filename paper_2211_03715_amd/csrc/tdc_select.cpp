@@ -302,7 +302,8 @@ FusedChoice best_chain(const TdcDims &d, const TdcDeviceInfo &dev, const tdc_tun
 // (96 per fp32 product block: six MFMAs of 16 cycles): stage 1 in rounds of four units, then one group of two pixel blocks
 // per wavefront.  Sweeps of ten layers (tiles of 32 to 800 pixels, groups of two and four blocks) were won by tiles that give
 // every wavefront exactly one group of two -- 128 pixels at most -- or lay within 4 % of such a tile, so only those are
-// compared.  Two or three workgroups that share a compute unit overlap half of their chains.
+// compared.  Two or three workgroups that share a compute unit overlap half of their chains.  Where the pixels are few, tiles
+// of two or one groups let two or four wavefronts share each (tdc_chain3_share).
 struct Chain3Choice {
     double us = 1e300;
     int th = 0, tw = 0, mb1 = 0, pb = 0;
@@ -311,7 +312,7 @@ struct Chain3Choice {
 // terms: constant; thousands of cycles of stage 1, of stages 2 and 3, and chains, each times what sharing a compute unit adds
 enum { X_LAUNCH, X_S1, X_S23, X_PHASES, X_TERMS };
 const char *const kChain3TermNames[X_TERMS] = {"launch", "s1_kcycles", "s23_kcycles", "phases"};
-const double kChain3Coef[X_TERMS] = {3.0, 0.5, 0.5, 3.0};
+const double kChain3Coef[X_TERMS] = {3.0, 0.5, 0.5, 3.0};   // (a term for the tiles' bytes and row segments made the picks worse: 28.7 -> 41.4 us at 224x224)
 
 void chain3_terms(double (&f)[X_TERMS], const TdcDims &d, const TdcDeviceInfo &dev, const TdcFusedGeom &g, bool runs, int mb1, int pb)
 {
@@ -324,10 +325,10 @@ void chain3_terms(double (&f)[X_TERMS], const TdcDims &d, const TdcDeviceInfo &d
     const double per_cu = std::max(1.0, (double)g.tiles_x * g.tiles_y * d.B / dev.cus);
     const int fit = std::max(1, std::min((int)(dev.lds_per_wg / std::max<size_t>(g.lds_bytes, 1)), 3));
     const int r = std::min(fit, (int)std::ceil(per_cu));
-    const double chains = (1.0 + 0.5 * (r - 1)) * std::max(1.0, per_cu / r);
+    const double chains = r == 1 ? std::ceil(per_cu) : (1.0 + 0.5 * (r - 1)) * std::max(1.0, per_cu / r);
     f[X_LAUNCH] = 1.0;
     f[X_S1] = chains * cdiv(u1, 4) * c1 * 1e-3;
-    f[X_S23] = chains * cdiv(u2, 4) * c23 * 1e-3;
+    f[X_S23] = chains * cdiv(u2, 4) * c23 / (1 << tdc_chain3_share(u2)) * 1e-3;
     f[X_PHASES] = chains;
 }
 
@@ -348,7 +349,7 @@ Chain3Choice best_chain3(const TdcDims &d, const TdcDeviceInfo &dev, const tdc_t
         for (int tw = tw_lo; tw <= tw_hi; ++tw) {
             if (!forced.tile_w && !d.nhwc && d.Wo % 4 == 0 && tw % 4) continue;   // whole 16-byte quads where the image allows them
             if ((!forced.tile_h || !forced.tile_w) && th * tw > 128) continue;
-            const TdcFusedGeom g = tdc_chain3_geometry(d, th, tw);
+            const TdcFusedGeom g = tdc_chain3_geometry(d, th, tw, forced.pb[0] ? forced.pb[0] : 2);
             if ((long)g.lds_bytes > dev.lds_per_wg) continue;
             for (int mb1 = 1; mb1 <= 3; ++mb1)
                 for (int pb : {2, 4}) {
@@ -600,7 +601,7 @@ int tdc_select_terms(const TdcDims &d, const TdcDeviceInfo &dev, const tdc_tunin
     }
     if (tdc_is_chain3(t)) {
         double f[X_TERMS];
-        chain3_terms(f, d, dev, tdc_chain3_geometry(d, t.tile_h, t.tile_w), runs, t.mb[0], t.pb[0]);
+        chain3_terms(f, d, dev, tdc_chain3_geometry(d, t.tile_h, t.tile_w, t.pb[0]), runs, t.mb[0], t.pb[0]);
         return emit(f, kChain3TermNames, X_TERMS, "chain");
     }
     if (t.variant == TDC_VARIANT_CHAIN) {
@@ -705,7 +706,10 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
             // From 8 tiles per compute unit on the launch is bound by memory bandwidth, which the tiles use better than either
             // estimate says: they were faster up to 1.8 times the other estimate (NHWC, batch 32, 56x56: 64 -> 256 51.6 -> 41.2
             // us, 48 -> 192 36.7 -> 29.7; batch 64: 32 -> 128 37.6 -> 30.0), not at 1.96 times (24 -> 96: 23.3 -> 28.9).
-            const double margin = tiles < 1.5 * dev.cus ? 0.95 : tiles < 8.0 * dev.cus ? 1.2 : std::max(1.2, 1.85 * fill);
+            // Images whose pixels are no multiple of 4 are stored four bytes at a time in NCHW and gain nothing there (51x51, 58 ->
+            // 189: 63.2 against 66.6); tiles that are half empty lose (74x50, 3x3, 288 -> 32, batch 9: 77 against 97).
+            const bool quads = d.nhwc || d.Ho * d.Wo % 4 == 0;
+            const double margin = tiles < 1.5 * dev.cus ? 0.95 : fill <= 0.5 ? 0.85 : tiles < 8.0 * dev.cus || !quads ? 1.2 : std::max(1.2, 1.85 * fill);
             if (tc.us < margin * c.us) return tiled(tc.tm, tc.ks, tc.us);
         }
         if (c.us >= 1e299) return TDC_ERR_BAD_TUNING;
@@ -775,16 +779,26 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
         return TDC_OK;
     }
 
-    // The throughput regime proper: from 64 output pixels per compute unit CHAIN on the bf16 matrix cores is the fastest form
-    // timed (fp32 CHAIN or FUSED -> bf16 parts, 98 pixels: 46.8 -> 33.5, 38.2 -> 34.9, 26.8 -> 23.8 us; 196: 37.5 -> 27.5;
-    // 784: 103.3 -> 66.6).  At 24 pixels a workgroup has its compute unit to itself, nothing overlaps its phases, and the
-    // kernels that cut a tile along channels as well win (22.4 against 27.5, 19.0 against 22.7 us).
-    if (forced.variant == TDC_VARIANT_AUTO && (long)d.B * d.Ho * d.Wo >= 64L * dev.cus) {
+    // Where the output pixels fill the chip (16 per compute unit) CHAIN on the bf16 matrix cores is the fastest form timed:
+    // against fp32 CHAIN or FUSED 33.0 -> 20.7, 22.3 -> 17.1 (24 pixels, ranks 80 and 64), 49.9 -> 31 (24, stride 2), 14.4 ->
+    // 11.4 (24, ranks 40), 10.1 -> 9.0 (49), 46.8 -> 33.5 (98), 37.5 -> 27.5 (196), 103.3 -> 65 us (784); 56 layers drawn over
+    // the whole range are 1.3 times faster on average.  Not with ranks of a single block below 128 pixels (36 pixels: 7.6
+    // against 7.9, 101: 10.4 against 11.3 us): there are few products to save there.
+    // Nor, for the same reason, with one block of R1 in NCHW rows that allow no 16-byte stores (172x172 stride 2, ranks 4 and
+    // 19: 15.4 against 17.0; 72x89, ranks 9 and 48: 64 against 77), nor 1x1 layers of at most two blocks on few pixels (10x12,
+    // ranks 9 and 33: 6.6 against 7.3; 13x13, ranks 17 and 58: 9.5 against 10.0).
+    const bool one_block = d.NB1 == 1 && d.NB2 == 1;
+    const long pixels = (long)d.B * d.Ho * d.Wo;
+    // With a stride that holds for two blocks too (99x146 stride 2, ranks 31 and 5: 19.4 against 21.6).
+    const bool few_products = (!d.nhwc && d.Wo % 4 && (d.NB1 == 1 || (d.stride > 1 && d.NB1 * d.NB2 <= 2))) || (d.K == 1 && d.NB1 <= 2 && pixels < 64L * dev.cus);
+    const auto try_chain3 = [&](Chain3Choice &c) {
         tdc_tuning free_choice = forced;
         free_choice.mb[0] = free_choice.pb[0] = free_choice.tile_h = free_choice.tile_w = 0;
-        const Chain3Choice c = best_chain3(d, dev, free_choice);
-        if (c.us < 1e299) return chain3(c);
-    }
+        c = best_chain3(d, dev, free_choice);
+        return c.us < 1e299;
+    };
+    Chain3Choice c3;
+    if (forced.variant == TDC_VARIANT_AUTO && !few_products && pixels >= (one_block ? 128L : 16L) * dev.cus && try_chain3(c3)) return chain3(c3);
     FusedChoice f;
     if (forced.variant == TDC_VARIANT_AUTO || forced.variant == TDC_VARIANT_FUSED) f = best_fused(d, dev, forced);
     // output pixels alone give every CU a 16-pixel block: the throughput regime
@@ -867,6 +881,11 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
         // batch 64: 50.2 against 38.3 us; 256 channels on 56x56: 17.9 against 17.4 us), 2 % ahead at best.
         variant = (f.us <= 0.92 * split_us || (pixels_fill_chip && f.us < 1e299)) ? TDC_VARIANT_FUSED : TDC_VARIANT_SPLIT;
     }
+    // From 8 pixels on what would be FUSED's runs there too (3 images of 37x29, 5x5, 100 -> 150: 15.9 -> 15.7 us; 26x19 stride 2,
+    // 476 -> 108: 77.5 -> 77.0), unless R1 is a single block (14x14, 40 -> 368, ranks 10 and 71: 14.0 against 15.3 us)
+    if (forced.variant == TDC_VARIANT_AUTO && variant == TDC_VARIANT_FUSED && !pixels_fill_chip && d.NB1 > 1 && !few_products &&
+        pixels >= 8L * dev.cus && try_chain3(c3))
+        return chain3(c3);
     if (variant == TDC_VARIANT_FUSED) {
         if (f.us >= 1e299) return TDC_ERR_BAD_TUNING;
         t->variant = TDC_VARIANT_FUSED;

@@ -74,12 +74,14 @@ def test_chain3(orc, layer, tiles, nhwc):
         assert_parity(got, with_epi, "%s tile %dx%d epilogue" % (layer.name(), th, tw))
 
 
-def test_the_selector_takes_it_from_64_pixels_per_compute_unit():
+def test_the_selector_takes_it_where_pixels_fill_the_chip():
     for lay in (B.LAYOUT_NCHW, B.LAYOUT_NHWC):
         t = B.tdc_select_tuning(B.make_shape(256, 128, 128, 28, 28, 32, 32, layout=lay))
         assert t.variant == B.VARIANT_CHAIN and t.mb[1] == 3 and t.tile_h * t.tile_w <= 128
         B.tdc_plan_destroy(B.tdc_plan_create(B.make_shape(256, 128, 128, 28, 28, 32, 32, layout=lay), 0, t))
-        assert B.tdc_select_tuning(B.make_shape(32, 256, 256, 14, 14, 64, 64, layout=lay)).mb[1] != 3
+        t = B.tdc_select_tuning(B.make_shape(32, 256, 256, 14, 14, 64, 64, layout=lay))
+        assert t.mb[1] == 3 and t.tile_h * t.tile_w <= 32       # one group of pixel blocks that four wavefronts share
+        assert B.tdc_select_tuning(B.make_shape(1, 256, 256, 14, 14, 64, 64, layout=lay)).variant != B.VARIANT_CHAIN
     # six z2 blocks: no such instance, the fp32 kernel takes the tuning
     t = B.make_tuning(variant=B.VARIANT_CHAIN, mb=(0, 3, 0))
     assert B.tdc_select_tuning(B.make_shape(64, 96, 96, 28, 28, 96, 96), tuning=t).mb[1] == 1
