@@ -709,7 +709,7 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
             // Images whose pixels are no multiple of 4 are stored four bytes at a time in NCHW and gain nothing there (51x51, 58 ->
             // 189: 63.2 against 66.6); tiles that are half empty lose (74x50, 3x3, 288 -> 32, batch 9: 77 against 97).
             const bool quads = d.nhwc || d.Ho * d.Wo % 4 == 0;
-            const double margin = tiles < 1.5 * dev.cus ? 0.95 : fill <= 0.5 ? 0.85 : tiles < 8.0 * dev.cus || !quads ? 1.2 : std::max(1.2, 1.85 * fill);
+            const double margin = tiles < 1.5 * dev.cus ? 0.95 : fill <= 0.5 ? 0.85 : tiles < 8.0 * dev.cus ? 1.2 : !quads ? 1.0 : std::max(1.2, 1.85 * fill);
             if (tc.us < margin * c.us) return tiled(tc.tm, tc.ks, tc.us);
         }
         if (c.us >= 1e299) return TDC_ERR_BAD_TUNING;
