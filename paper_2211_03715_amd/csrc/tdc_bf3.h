@@ -11,8 +11,11 @@
 // normal inputs (one 16 x 16 block): relative error 3.7e-8 / 2.3e-7 / 5.7e-7 / 1.1e-6 at n = 32 / 256 / 1152 / 4608, where
 // v_mfma_f32_16x16x4_f32 gives 1.1e-7 / 3.1e-7 / 7.1e-7 / 1.3e-6; all nine products give the same figures as six.
 // Time per 16 x 16 x 32 block: 6 x 16 cycles against 8 x 32.
-// Values below 2^-110 keep an absolute accuracy of 2^-134 instead of a relative one (bf16 has no smaller subnormals);
-// an infinite value comes out as NaN (inf - inf in the split): a kernel whose fp32 form gave infinities looks for that.
+// Values below 2^-110 keep an absolute accuracy of 2^-134 instead of a relative one (bf16 has no smaller subnormals).
+// Infinities have no three parts, nor have finite values the conversion rounds to infinity (above 3.39e38): split, they give
+// NaN (inf - inf).  Where parts are stored such a value, like every one from 2^126 on, is kept raw: its fp32 bits in the
+// second and third part, behind a first part that is a NaN (TDC_RAW).  Either way every sum it reaches is NaN; a kernel that
+// ends up with a NaN or a magnitude from 2^126 on computes those sums once more with fp32 multiply-adds on the joined parts.
 //
 // Operand layout of v_mfma_f32_16x16x32_bf16 (D 16x16 += A 16x32 * B 32x16): lane l holds A[m = l%16][k(l/16, j)] and
 // B[k(l/16, j)][p = l%16], j = 0..7, for any assignment k(g, j) that A and B share; D as in tdc_mfma.h.  Here a step is a pair of
@@ -27,6 +30,11 @@
 typedef __bf16 tdc_bf8 __attribute__((ext_vector_type(8)));
 typedef unsigned tdc_u2 __attribute__((ext_vector_type(2)));
 typedef unsigned tdc_u4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ tdc_u2 tdc_buf_load2(tdc_rsrc r, unsigned byte_off)
+{
+    return __builtin_bit_cast(tdc_u2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)byte_off, 0, 0));
+}
 
 // two fp32 -> their three bf16 parts, packed in pairs (11 VALU instructions)
 __device__ __forceinline__ void tdc_split2(float a, float b, unsigned &p1, unsigned &p2, unsigned &p3)
@@ -47,12 +55,93 @@ __device__ __forceinline__ void tdc_split2(float a, float b, unsigned &p1, unsig
     p3 = pack(ra - __builtin_bit_cast(float, p2 << 16), rb - __builtin_bit_cast(float, p2 & 0xffff0000u));
 }
 
+// Largest magnitude, NaN if one is (v_maximum3_f32: two values an instruction).
+constexpr float TDC_BIG = 0x1p126f;
+__device__ __forceinline__ float tdc_largest(float m, tdc_f4 v)
+{
+    m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, fabsf(v[0])), fabsf(v[1]));
+    return __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, fabsf(v[2])), fabsf(v[3]));
+}
+__device__ __forceinline__ bool tdc_any_lane(bool b) { return __builtin_amdgcn_ballot_w64(b) != 0; }
+
+// first part of a value whose fp32 bits are the other two
+constexpr unsigned TDC_RAW = 0x7fffu;
+
+// tdc_split2 for values that are stored: those without three parts are kept raw (a NaN is a NaN in every part)
+__device__ __forceinline__ void tdc_split2_raw(float a, float b, unsigned &p1, unsigned &p2, unsigned &p3)
+{
+    tdc_split2(a, b, p1, p2, p3);
+    const unsigned ua = __builtin_bit_cast(unsigned, a), ub = __builtin_bit_cast(unsigned, b);
+    if (!(fabsf(a) < TDC_BIG)) {
+        p1 = (p1 & 0xffff0000u) | (a != a ? 0x7fc0u : TDC_RAW);
+        p2 = (p2 & 0xffff0000u) | ua >> 16;
+        p3 = (p3 & 0xffff0000u) | (ua & 0xffffu);
+    }
+    if (!(fabsf(b) < TDC_BIG)) {
+        p1 = (p1 & 0xffffu) | (b != b ? 0x7fc0u : TDC_RAW) << 16;
+        p2 = (p2 & 0xffffu) | (ub & 0xffff0000u);
+        p3 = (p3 & 0xffffu) | ub << 16;
+    }
+}
+
+// the fp32 value of stored parts
+__device__ __forceinline__ float tdc_join(unsigned p1, unsigned p2, unsigned p3)
+{
+    const auto part = [](unsigned v) { return __builtin_bit_cast(float, v << 16); };
+    return p1 == TDC_RAW ? __builtin_bit_cast(float, p2 << 16 | p3) : part(p1) + (part(p2) + part(p3));
+}
+__device__ __forceinline__ tdc_f4 tdc_join4(const tdc_u2 (&p)[3])
+{
+    tdc_f4 v;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const unsigned u[3] = {p[0][j >> 1], p[1][j >> 1], p[2][j >> 1]};
+        v[j] = j & 1 ? tdc_join(u[0] >> 16, u[1] >> 16, u[2] >> 16) : tdc_join(u[0] & 0xffffu, u[1] & 0xffffu, u[2] & 0xffffu);
+    }
+    return v;
+}
+
+// k-group kg's share of a lane's weights of 16-channel block `block`, from the three-part layout (tdc_internal.h)
+__device__ __forceinline__ tdc_f4 tdc_join_weights(tdc_rsrc r, int block, int steps, int kg, int lane)
+{
+    tdc_u2 p[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) p[q] = tdc_buf_load2(r, (unsigned)(block * steps + (kg >> 1)) * 3072u + q * 1024u + lane * 16u + 8u * (kg & 1));
+    return tdc_join4(p);
+}
+
+// Whether the NaNs among some sums can only come from NaNs among their factors: there is one, and the other factors are too
+// small for products or sums of three stages to overflow.
+struct TdcFactors {
+    float largest = 0.f;       // magnitude of the largest that is not NaN
+    bool nan = false;
+    __device__ __forceinline__ void see(tdc_f4 v)
+    {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            nan |= v[j] != v[j];
+            largest = fmaxf(largest, fabsf(v[j]));
+        }
+    }
+    __device__ __forceinline__ bool explain_nan() const { return tdc_any_lane(nan) && !tdc_any_lane(largest >= 0x1p30f); }
+};
+
 // four fp32 (one lane's share of a 16-wide k-group) -> three 8-byte operand halves
 __device__ __forceinline__ void tdc_split4(tdc_f4 v, tdc_u2 &p1, tdc_u2 &p2, tdc_u2 &p3)
 {
     unsigned a1, a2, a3, b1, b2, b3;
     tdc_split2(v[0], v[1], a1, a2, a3);
     tdc_split2(v[2], v[3], b1, b2, b3);
+    p1 = (tdc_u2){a1, b1};
+    p2 = (tdc_u2){a2, b2};
+    p3 = (tdc_u2){a3, b3};
+}
+
+__device__ __forceinline__ void tdc_split4_raw(tdc_f4 v, tdc_u2 &p1, tdc_u2 &p2, tdc_u2 &p3)
+{
+    unsigned a1, a2, a3, b1, b2, b3;
+    tdc_split2_raw(v[0], v[1], a1, a2, a3);
+    tdc_split2_raw(v[2], v[3], b1, b2, b3);
     p1 = (tdc_u2){a1, b1};
     p2 = (tdc_u2){a2, b2};
     p3 = (tdc_u2){a3, b3};

@@ -56,7 +56,7 @@ __device__ __forceinline__ void pack3(size_t e, int KG, unsigned *__restrict__ o
     const int step = (int)(blk % S), mb = (int)(blk / S);
     const int kg = 2 * step + (pair >> 1), m = 16 * mb + (lane & 15), k = 4 * (lane >> 4) + 2 * (pair & 1);
     unsigned p[3];
-    tdc_split2(kg < KG ? weight(kg, k, m) : 0.f, kg < KG ? weight(kg, k + 1, m) : 0.f, p[0], p[1], p[2]);
+    tdc_split2_raw(kg < KG ? weight(kg, k, m) : 0.f, kg < KG ? weight(kg, k + 1, m) : 0.f, p[0], p[1], p[2]);
     for (int i = 0; i < 3; ++i) out[(blk * 3 + i) * 256 + lane * 4 + pair] = p[i];
 }
 

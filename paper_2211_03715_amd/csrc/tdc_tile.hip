@@ -54,7 +54,6 @@ __device__ __forceinline__ void tile_plain_output(const TileArgs &a, int m, int 
     const int oh = CONV ? tdc_div(pix, a.div_Wo) : 0, h0 = oh * a.stride - a.pad, w0 = (pix - oh * a.Wo) * a.stride - a.pad;
     const float *x = a.act + (size_t)b * a.C * a.HW;
     const unsigned short *w = reinterpret_cast<const unsigned short *>(a.w3) + (size_t)(m >> 4) * a.S * 1536;
-    const auto part = [](unsigned short v) { return __builtin_bit_cast(float, (unsigned)v << 16); };
     float sum = 0.f;
     for (int kg = 0; kg < a.KG; ++kg) {
         const int tap = CONV ? tdc_div(kg, a.div_NBk) : 0, c0 = 16 * (kg - tap * a.NBk);
@@ -63,8 +62,7 @@ __device__ __forceinline__ void tile_plain_output(const TileArgs &a, int m, int 
         const int q = CONV ? h * a.W + wx : pix;
         for (int k = 0; k < 16 && c0 + k < a.C; ++k) {
             const unsigned short *f = w + (size_t)(kg >> 1) * 1536 + ((m & 15) + 16 * (k >> 2)) * 8 + (kg & 1) * 4 + (k & 3);
-            const float w1 = part(f[0]), ww = fabsf(w1) == INFINITY ? w1 : w1 + (part(f[512]) + part(f[1024]));
-            sum = fmaf(ww, ACT == TDC_ACT_NHWC ? x[(size_t)q * a.C + c0 + k] : x[(size_t)(c0 + k) * a.HW + q], sum);
+            sum = fmaf(tdc_join(f[0], f[512], f[1024]), ACT == TDC_ACT_NHWC ? x[(size_t)q * a.C + c0 + k] : x[(size_t)(c0 + k) * a.HW + q], sum);
         }
     }
     const size_t idx = ACT == TDC_ACT_NHWC ? (size_t)p * a.M + m : ((size_t)b * a.M + m) * a.P + pix;

@@ -112,3 +112,28 @@ def test_infinite_inputs_give_what_fp32_arithmetic_gives(orc, layer, nhwc):
         finite = np.isfinite(want)
         assert (~finite).any() and np.array_equal(got[~finite], want[~finite].astype(np.float32))
         assert_parity(got[finite], want[finite], layer.name())
+
+
+@pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
+@pytest.mark.parametrize("layer", (Layer(2, 24, 72, 13, 9, 1, 1, 3, 1, 1), Layer(2, 72, 72, 8, 8, 1, 1, 1, 1, 0)), ids=lambda l: l.name())
+@pytest.mark.parametrize("value", (np.finfo(np.float32).max, 3.4e38, np.inf), ids=("largest", "just_above_bf16", "infinite"))
+def test_weights_without_three_parts_give_what_fp32_arithmetic_gives(orc, value, layer, nhwc):
+    """The largest finite weights round to infinity in bf16.  9 and 3 steps: the second of two groups of wavefronts multiplies a
+    step past the end.  With the epilogue, whose ReLU would make a NaN a 0."""
+    inputs = make_dense_inputs(layer, 80)
+    inputs["W"][5, 7, layer.K // 2, layer.K // 2] = value
+    inputs["x"] = np.abs(inputs["x"]) * np.float32(1e-12)
+    rng = np.random.default_rng(6)
+    bias = rng.standard_normal(layer.N, dtype=np.float32)
+    residual = rng.standard_normal((layer.batch, layer.N, layer.Ho, layer.Wo), dtype=np.float32)
+    want = _oracle(orc, layer, inputs, bias, residual)
+    for tm, waves in ((64, 4), (128, 8)):
+        print("[case] tiles, weight", value, layer.name(), "nhwc" if nhwc else "nchw", tm, waves, flush=True)
+        got = _run(layer, inputs, tm, waves, nhwc, bias, residual)
+        reached = np.zeros(want.shape, bool)
+        reached[:, 7] = True
+        if np.isinf(value):
+            assert np.array_equal(got[reached], want[reached].astype(np.float32))
+        else:
+            assert_parity(got[reached], want[reached], layer.name())
+        assert_parity(got[~reached], want[~reached], layer.name())
