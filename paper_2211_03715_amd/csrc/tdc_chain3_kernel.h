@@ -60,6 +60,7 @@ struct Chain3Stage1 {
     int lane, g, l16, wave, h0, w0, wa, n_units;
     int fu, fs, fmg;                                   // fetch cursor: unit, step, channel group of the unit
     unsigned xoff[RUNS ? 1 : PB];
+    float largest = 0.f;                               // magnitude of this lane's largest z1 value, NaN if there is one
 
     __device__ __forceinline__ Chain3Stage1(const TdcChain3Args &args, int lane_, int wave_, int b, int h0_, int w0_) : a(args)
     {
@@ -161,6 +162,8 @@ struct Chain3Stage1 {
                 for (int mb = 0; mb < MB1; ++mb) acc[mb][pb] = tdc_mfma_bf(w[mb].p[TDC_BF3_A[i]], b.p[TDC_BF3_B[i]], acc[mb][pb]);
         }
     }
+    // RAW: for sums some of which have no three parts
+    template <bool RAW>
     __device__ __forceinline__ void store(tdc_u2 *__restrict__ z1s, int unit, const tdc_f4 (&acc)[MB1][PB]) const
     {
         const int pg = tdc_div(unit, a.div_mg1), mg = unit - pg * a.n_mg1;
@@ -174,7 +177,8 @@ struct Chain3Stage1 {
             for (int mb = 0; mb < MB1; ++mb) {
                 const int blk = mg * MB1 + mb;
                 tdc_u2 p[3];
-                tdc_split4(acc[mb][pb], p[0], p[1], p[2]);
+                if (RAW) tdc_split4_raw(acc[mb][pb], p[0], p[1], p[2]);
+                else tdc_split4(acc[mb][pb], p[0], p[1], p[2]);
                 if (ok && blk < a.NB1) {
 #pragma unroll
                     for (int q = 0; q < 3; ++q) z1s[((q * a.NB1 + blk) * 4 + g) * a.pitch1 + pix] = p[q];
@@ -198,7 +202,11 @@ struct Chain3Stage1 {
         };
         const auto done = [&]() {
             if (++step < a.S1) return;
-            store(z1s, unit, acc);
+#pragma unroll
+            for (int mb = 0; mb < MB1; ++mb)
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb) largest = tdc_largest(largest, acc[mb][pb]);
+            store<false>(z1s, unit, acc);
             unit += TDC_CHAIN3_WAVES;
             step = 0;
             clear();
@@ -215,7 +223,240 @@ struct Chain3Stage1 {
             }
         }
     }
+    // The wavefront's units once more in fp32, one load at a time (see tdc_bf3.h); those whose NaNs are x's or the weights' stay.
+    __device__ __forceinline__ void redo(tdc_u2 *__restrict__ z1s)
+    {
+        tdc_f4 x[NR];
+        tdc_op3 w[MB1];
+        const auto join = [&](int mb, int h) {
+            tdc_u2 p[3];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                const tdc_u4 u = __builtin_bit_cast(tdc_u4, w[mb].p[q]);
+                p[q] = h ? (tdc_u2){u[2], u[3]} : (tdc_u2){u[0], u[1]};
+            }
+            return tdc_join4(p);
+        };
+        for (int unit = wave; unit < n_units; unit += TDC_CHAIN3_WAVES) {
+            TdcFactors seen;
+            fu = unit;
+            place();
+            for (int i = 0; i < a.S1; ++i) {
+                fetch(x, w);
+#pragma unroll
+                for (int j = 0; j < NR; ++j) seen.see(x[j]);
+#pragma unroll
+                for (int mb = 0; mb < MB1; ++mb) {
+                    seen.see(join(mb, 0));
+                    seen.see(join(mb, 1));
+                }
+            }
+            if (seen.explain_nan()) continue;
+            tdc_f4 acc[MB1][PB];
+#pragma unroll
+            for (int mb = 0; mb < MB1; ++mb)
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb) acc[mb][pb] = tdc_f4_zero();
+            fu = unit;
+            place();
+            for (int i = 0; i < a.S1; ++i) {
+                fetch(x, w);
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int mb = 0; mb < MB1; ++mb) {
+                        const tdc_f4 wh = join(mb, h);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+#pragma unroll
+                            for (int pb = 0; pb < PB; ++pb)
+                                acc[mb][pb] = tdc_mfma(wh[j], RUNS ? x[(4 * h + j) % NR][pb] : x[(2 * pb + h) % NR][j], acc[mb][pb]);
+                    }
+            }
+            store<true>(z1s, unit, acc);
+        }
+    }
 };
+
+// The image and the tile of this workgroup: one contiguous range of (image, tile) pairs per XCD, so that halos are shared
+// within its L2.
+struct Chain3Tile {
+    int b, i0, j0;
+    __device__ __forceinline__ Chain3Tile(const TdcChain3Args &a)
+    {
+        const int lin = blockIdx.y * a.tiles + blockIdx.x, xcd = lin & 7, slot = lin >> 3;
+        const int lb = xcd * a.xcd_per + min(xcd, a.xcd_rem) + slot;
+        b = tdc_div(lb, a.div_tiles);
+        const int tile = lb - b * a.tiles, ty = tdc_div(tile, a.div_tiles_x), tx = tile - ty * a.tiles_x;
+        i0 = ty * a.TH;
+        j0 = tx * a.TW;
+    }
+};
+
+// z1 cells of the (0, 0) tap of pixel l16 of each block of a group
+template <int PB>
+__device__ __forceinline__ void chain3_z1_base(const TdcChain3Args &a, int group, int lane, int (&qbase)[PB])
+{
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) {
+        const int p = 16 * (group * PB + pb) + (lane & 15);
+        const int ph = tdc_div(p, a.div_TW), pw = p - ph * a.TW;
+        qbase[pb] = (lane >> 4) * a.pitch1 + (p < a.P ? ph * a.stride * a.QW + pw * a.stride : 0);
+    }
+}
+
+// The outputs of a group of pixel blocks.
+template <int PB, bool NHWC>
+struct Chain3Out {
+    const TdcChain3Args &a;
+    int g, l16, b, P2;
+    tdc_rsrc yrs;
+    unsigned yq[PB][4];      // NCHW: byte offset of pixel 4*g + i of block pb in one channel plane, or TDC_OOB
+    int ypix[PB];            // NHWC: index of pixel l16 of block pb in the output image, or -1
+
+    __device__ __forceinline__ Chain3Out(const TdcChain3Args &args, const Chain3Tile &at, int group, int lane) : a(args)
+    {
+        g = lane >> 4; l16 = lane & 15; b = at.b;
+        P2 = a.Ho * a.Wo;
+        yrs = tdc_make_rsrc(a.y + (size_t)b * a.N * P2, (unsigned)a.N * P2 * 4u);
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int p = 16 * (group * PB + pb) + 4 * g + i;
+                const int ph = tdc_div(p, a.div_TW), pw = p - ph * a.TW;
+                const int oi = at.i0 + ph, oj = at.j0 + pw;
+                yq[pb][i] = (p < a.P && oi < a.Ho && oj < a.Wo) ? (unsigned)(oi * a.Wo + oj) * 4u : TDC_OOB;
+            }
+            const int p = 16 * (group * PB + pb) + l16;
+            const int ph = tdc_div(p, a.div_TW), pw = p - ph * a.TW;
+            const int oi = at.i0 + ph, oj = at.j0 + pw;
+            ypix[pb] = (p < a.P && oi < a.Ho && oj < a.Wo) ? oi * a.Wo + oj : -1;
+        }
+    }
+    // sums of output block nb, through the epilogue
+    template <bool EPI>
+    __device__ __forceinline__ void put(int nb, tdc_f4 (&acc3)[PB]) const
+    {
+        if (NHWC) {
+            const int n = 16 * nb + 4 * g;
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb)
+                if (ypix[pb] >= 0 && n < a.N) {
+                    const size_t cell = ((size_t)b * P2 + ypix[pb]) * a.N + n;
+                    if constexpr (EPI) tdc_store_nhwc<true>(a.y, a.epi, acc3[pb], n, cell);
+                    else tdc_store4_stream(reinterpret_cast<tdc_f4 *>(a.y + cell), acc3[pb]);
+                }
+            return;
+        }
+        // channels past N lie beyond the descriptor: the hardware drops those stores
+        const unsigned row = (unsigned)(16 * nb + l16) * P2 * 4u;
+        if constexpr (EPI) {
+            const int n = 16 * nb + l16;
+            const float bias = (a.epi.bias && n < a.N) ? a.epi.bias[n] : 0.f;
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float v = acc3[pb][i] + bias;
+                    if (a.epi.residual && n < a.N && !(yq[pb][i] & TDC_OOB))
+                        v += a.epi.residual[(size_t)b * a.N * P2 + (size_t)n * P2 + (yq[pb][i] >> 2)];
+                    acc3[pb][i] = a.epi.relu ? fmaxf(v, 0.f) : v;
+                }
+        }
+        typedef unsigned u4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) {
+            if (a.vec) {
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, acc3[pb]), yrs, (int)((row + yq[pb][0]) | (yq[pb][0] & TDC_OOB)), 0, 0);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float v = acc3[pb][i];   // a copy: __builtin_bit_cast of a vector element reads element 0
+                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), yrs, (int)((row + yq[pb][i]) | (yq[pb][i] & TDC_OOB)), 0, 0);
+                }
+            }
+        }
+    }
+};
+
+// Stages 2 and 3 of a group once more in fp32, one load at a time (see tdc_bf3.h), unless its NaNs are z1's or the weights'.
+template <int NB2, int PB, int LAY>
+__device__ __forceinline__ void chain3_redo(const TdcChain3Args &a, const tdc_u2 *__restrict__ z1s, int group, int lane, int slice)
+{
+    constexpr bool NHWC = LAY == TDC_LAY_NHWC;
+    constexpr int S3 = (NB2 + 1) / 2;
+    const tdc_rsrc crs = tdc_make_rsrc(a.core3, a.core_bytes), ors = tdc_make_rsrc(a.uout3, a.uout_bytes);
+    int qbase[PB];
+    chain3_z1_base<PB>(a, group, lane, qbase);
+    const auto cell_of = [&](int kg) {
+        const int tap = tdc_div(kg, a.div_NB1), r = tdc_div(tap, a.div_K);
+        return (kg - tap * a.NB1) * 4 * a.pitch1 + r * a.QW + tap - r * a.K;
+    };
+    const auto z1_at = [&](int cell, int pb) {
+        tdc_u2 u[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) u[q] = z1s[q * a.NB1 * 4 * a.pitch1 + cell + qbase[pb]];
+        return tdc_join4(u);
+    };
+    TdcFactors seen;
+    for (int kg = 0; kg < a.KG2; ++kg) {
+        const int cell = cell_of(kg);
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) seen.see(z1_at(cell, pb));
+#pragma unroll
+        for (int mb = 0; mb < NB2; ++mb) seen.see(tdc_join_weights(crs, mb, a.S2, kg, lane));
+    }
+    for (int nb = 0; nb < a.NB3; ++nb)
+#pragma unroll
+        for (int kg = 0; kg < NB2; ++kg) seen.see(tdc_join_weights(ors, nb, S3, kg, lane));
+    if (seen.explain_nan()) return;
+
+    tdc_f4 z2[NB2][PB];
+#pragma unroll
+    for (int mb = 0; mb < NB2; ++mb)
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) z2[mb][pb] = tdc_f4_zero();
+    for (int kg = 0; kg < a.KG2; ++kg) {
+        const int cell = cell_of(kg);
+        tdc_f4 z[PB];
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) z[pb] = z1_at(cell, pb);
+#pragma unroll
+        for (int mb = 0; mb < NB2; ++mb) {
+            const tdc_f4 w = tdc_join_weights(crs, mb, a.S2, kg, lane);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb) z2[mb][pb] = tdc_mfma(w[j], z[pb][j], z2[mb][pb]);
+        }
+    }
+    __threadfence();         // the outputs stored before are in place, these follow them
+    const Chain3Out<PB, NHWC> out(a, Chain3Tile(a), group, lane);
+    for (int nb = slice; nb < a.NB3; nb += 1 << a.lg_ks) {
+        tdc_f4 acc3[PB];
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) acc3[pb] = tdc_f4_zero();
+#pragma unroll
+        for (int kg = 0; kg < NB2; ++kg) {
+            const tdc_f4 w = tdc_join_weights(ors, nb, S3, kg, lane);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb)
+                    acc3[pb] = NHWC ? tdc_mfma(w[j], z2[kg][pb][j], acc3[pb]) : tdc_mfma(z2[kg][pb][j], w[j], acc3[pb]);
+        }
+        out.template put<true>(nb, acc3);
+    }
+}
+
+// The kernel's arguments, read anew where this is called: what is hardly ever run keeps no registers of what always is.
+__device__ __forceinline__ const TdcChain3Args &chain3_args_again()
+{
+    const __attribute__((address_space(4))) TdcChain3Args *p = (const __attribute__((address_space(4))) TdcChain3Args *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const TdcChain3Args *)p;
+}
 
 template <int NB2, int PB, int LAY, int MB1>
 __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, 2) void tdc_chain3_kernel(TdcChain3Args a)
@@ -224,36 +465,29 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, 2) void tdc_chain3_kernel(Td
     extern __shared__ tdc_u2 z1s[];                              // [3 parts][NB1][4][pitch1], then the partial sums of ks > 1
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int g = lane >> 4, l16 = lane & 15;
-    // one contiguous range of (image, tile) pairs per XCD, so that halos are shared within its L2
-    const int lin = blockIdx.y * a.tiles + blockIdx.x, xcd = lin & 7, slot = lin >> 3;
-    const int lb = xcd * a.xcd_per + min(xcd, a.xcd_rem) + slot;
-    const int b = tdc_div(lb, a.div_tiles), tile = lb - b * a.tiles;
-    const int ty = tdc_div(tile, a.div_tiles_x), tx = tile - ty * a.tiles_x;
-    const int i0 = ty * a.TH, j0 = tx * a.TW;
+    const auto stage1 = [&](const TdcChain3Args &args) {
+        const Chain3Tile t(args);
+        return Chain3Stage1<LAY, MB1>(args, lane, wave, t.b, t.i0 * args.stride - args.pad, t.j0 * args.stride - args.pad);
+    };
     {
-        Chain3Stage1<LAY, MB1> s1(a, lane, wave, b, i0 * a.stride - a.pad, j0 * a.stride - a.pad);
+        Chain3Stage1<LAY, MB1> s1 = stage1(a);
         s1.run(z1s);
+        // a value without three parts among x, the weights or z1 itself
+        if (__builtin_expect(tdc_any_lane(!(s1.largest < TDC_BIG)), 0)) stage1(chain3_args_again()).redo(z1s);
     }
+    const Chain3Tile at(a);
     __syncthreads();
 
-    const int P2 = a.Ho * a.Wo;
     const int plane = a.NB1 * 4 * a.pitch1;                      // cells of one part
     const tdc_rsrc crs = tdc_make_rsrc(a.core3, a.core_bytes);
     const tdc_rsrc ors = tdc_make_rsrc(a.uout3, a.uout_bytes);
-    const tdc_rsrc yrs = tdc_make_rsrc(a.y + (size_t)b * a.N * P2, (unsigned)a.N * P2 * 4u);
     // with fewer groups than wavefronts 2 or 4 of them share one: each takes a slice of stage 2's contraction, the sums meet in
     // LDS, and each takes every ks-th output block of stage 3 (the loop then runs once for every wavefront)
     const int ks = 1 << a.lg_ks, slice = wave & (ks - 1);
     for (int pg = wave >> a.lg_ks; pg < a.n_pg2; pg += TDC_CHAIN3_WAVES) {
         // ---- stage 2: z2 channels 16*mb + 4*g + {0..3} of pixel l16 of block pb
         int qbase[PB];
-#pragma unroll
-        for (int pb = 0; pb < PB; ++pb) {
-            const int p = 16 * (pg * PB + pb) + l16;
-            const int ph = tdc_div(p, a.div_TW), pw = p - ph * a.TW;
-            qbase[pb] = g * a.pitch1 + (p < a.P ? ph * a.stride * a.QW + pw * a.stride : 0);
-        }
+        chain3_z1_base<PB>(a, pg, lane, qbase);
         tdc_f4 acc2[NB2][PB];
 #pragma unroll
         for (int mb = 0; mb < NB2; ++mb)
@@ -337,27 +571,18 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, 2) void tdc_chain3_kernel(Td
         }
         // ---- stage 3, operands swapped in NCHW: D[pixel 4*g + i][channel l16]; NHWC: D[channel 4*g + i][pixel l16]
         constexpr int S3 = (NB2 + 1) / 2;
+        float largest = 0.f;                                     // magnitude of the largest of z2 and y, NaN if there is one
+#pragma unroll
+        for (int mb = 0; mb < NB2; ++mb)
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb) largest = tdc_largest(largest, acc2[mb][pb]);
+        asm("" : "+v"(largest));                                 // now: not behind the outputs, with all of acc2 kept until then
         tdc_op3 zb[S3][PB];
 #pragma unroll
         for (int st = 0; st < S3; ++st)
 #pragma unroll
             for (int pb = 0; pb < PB; ++pb) zb[st][pb] = tdc_split_op(acc2[2 * st][pb], 2 * st + 1 < NB2 ? acc2[(2 * st + 1) % NB2][pb] : tdc_f4_zero());
-        unsigned yq[PB][4];      // NCHW: byte offset of pixel 4*g + i of block pb in one channel plane, or TDC_OOB
-        int ypix[PB];            // NHWC: index of pixel l16 of block pb in the output image, or -1
-#pragma unroll
-        for (int pb = 0; pb < PB; ++pb) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int p = 16 * (pg * PB + pb) + 4 * g + i;
-                const int ph = tdc_div(p, a.div_TW), pw = p - ph * a.TW;
-                const int oi = i0 + ph, oj = j0 + pw;
-                yq[pb][i] = (p < a.P && oi < a.Ho && oj < a.Wo) ? (unsigned)(oi * a.Wo + oj) * 4u : TDC_OOB;
-            }
-            const int p = 16 * (pg * PB + pb) + l16;
-            const int ph = tdc_div(p, a.div_TW), pw = p - ph * a.TW;
-            const int oi = i0 + ph, oj = j0 + pw;
-            ypix[pb] = (p < a.P && oi < a.Ho && oj < a.Wo) ? oi * a.Wo + oj : -1;
-        }
+        const Chain3Out<PB, NHWC> out(a, at, pg, lane);
         const auto fetch = [&](int nb, tdc_op3(&u)[S3]) {
 #pragma unroll
             for (int st = 0; st < S3; ++st)
@@ -367,7 +592,6 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, 2) void tdc_chain3_kernel(Td
         };
         // two instances of the loop, as in tdc_chain_kernel.h: without epilogue loads nothing ever waits for the stores
         const auto emit = [&](auto with_epi, int nb, const tdc_op3(&u)[S3]) {
-            constexpr bool EPI = decltype(with_epi)::value;
             tdc_f4 acc3[PB];
 #pragma unroll
             for (int pb = 0; pb < PB; ++pb) acc3[pb] = tdc_f4_zero();
@@ -379,45 +603,9 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, 2) void tdc_chain3_kernel(Td
                     for (int pb = 0; pb < PB; ++pb)
                         acc3[pb] = NHWC ? tdc_mfma_bf(u[st].p[TDC_BF3_A[i]], zb[st][pb].p[TDC_BF3_B[i]], acc3[pb])
                                         : tdc_mfma_bf(zb[st][pb].p[TDC_BF3_B[i]], u[st].p[TDC_BF3_A[i]], acc3[pb]);
-            if (NHWC) {
-                const int n = 16 * nb + 4 * g;
 #pragma unroll
-                for (int pb = 0; pb < PB; ++pb)
-                    if (ypix[pb] >= 0 && n < a.N) {
-                        const size_t cell = ((size_t)b * P2 + ypix[pb]) * a.N + n;
-                        if constexpr (EPI) tdc_store_nhwc<true>(a.y, a.epi, acc3[pb], n, cell);
-                        else tdc_store4_stream(reinterpret_cast<tdc_f4 *>(a.y + cell), acc3[pb]);
-                    }
-                return;
-            }
-            // channels past N lie beyond the descriptor: the hardware drops those stores
-            const unsigned row = (unsigned)(16 * nb + l16) * P2 * 4u;
-            if constexpr (EPI) {
-                const int n = 16 * nb + l16;
-                const float bias = (a.epi.bias && n < a.N) ? a.epi.bias[n] : 0.f;
-#pragma unroll
-                for (int pb = 0; pb < PB; ++pb)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        float v = acc3[pb][i] + bias;
-                        if (a.epi.residual && n < a.N && !(yq[pb][i] & TDC_OOB))
-                            v += a.epi.residual[(size_t)b * a.N * P2 + (size_t)n * P2 + (yq[pb][i] >> 2)];
-                        acc3[pb][i] = a.epi.relu ? fmaxf(v, 0.f) : v;
-                    }
-            }
-            typedef unsigned u4 __attribute__((ext_vector_type(4)));
-#pragma unroll
-            for (int pb = 0; pb < PB; ++pb) {
-                if (a.vec) {
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, acc3[pb]), yrs, (int)((row + yq[pb][0]) | (yq[pb][0] & TDC_OOB)), 0, 0);
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float v = acc3[pb][i];   // a copy: __builtin_bit_cast of a vector element reads element 0
-                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), yrs, (int)((row + yq[pb][i]) | (yq[pb][i] & TDC_OOB)), 0, 0);
-                    }
-                }
-            }
+            for (int pb = 0; pb < PB; ++pb) largest = tdc_largest(largest, acc3[pb]);
+            out.template put<decltype(with_epi)::value>(nb, acc3);
         };
         const auto stage3 = [&](auto with_epi) {
             tdc_op3 u0[S3], u1[S3];
@@ -431,6 +619,12 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, 2) void tdc_chain3_kernel(Td
         };
         if (a.epi.bias || a.epi.residual || a.epi.relu) stage3(std::true_type{});
         else stage3(std::false_type{});
+        // a NaN, or z2 too large for three parts: only then can an output be wrong
+        if (__builtin_expect(tdc_any_lane(!(largest < TDC_BIG)), 0)) {
+            int group = pg;
+            asm volatile("" : "+s"(group));                      // its addresses are computed there, not kept from above
+            chain3_redo<NB2, PB, LAY>(chain3_args_again(), z1s, group, lane, slice);
+        }
     }
 }
 

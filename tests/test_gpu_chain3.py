@@ -25,14 +25,14 @@ CASES = [
 ]
 
 
-def _run(layer, inputs, tuning, nhwc, bias=None, residual=None, offset=0):
+def _run(layer, inputs, tuning, nhwc, bias=None, residual=None, offset=0, bf3=True):
     import torch
     from paper_2211_03715_amd.layer import TuckerConv2d
     dev = torch.device("cuda:0")
     put = lambda a: torch.from_numpy(np.ascontiguousarray(a.transpose(0, 2, 3, 1) if nhwc else a)).to(dev)
     conv = TuckerConv2d(layer, 0, tuning, layout=B.LAYOUT_NHWC if nhwc else B.LAYOUT_NCHW)
     try:
-        assert "bf3" in conv.describe(), conv.describe()
+        assert ("bf3" in conv.describe()) == bf3, conv.describe()
         w = [torch.from_numpy(inputs[k]).to(dev) for k in ("U_in", "core", "U_out")]
         conv.pack(*w)
         shape = conv.out_shape()
@@ -72,6 +72,104 @@ def test_chain3(orc, layer, tiles, nhwc):
             assert np.linalg.norm(got - want) <= 1.5e-6 * max(np.linalg.norm(want), 1e-30)
         got = _run(layer, inputs, t, nhwc, bias, residual, 0 if nhwc else 1)
         assert_parity(got, with_epi, "%s tile %dx%d epilogue" % (layer.name(), th, tw))
+
+
+FLT_MAX = float(np.finfo(np.float32).max)
+
+
+def _one_sign(a):
+    return np.abs(a) + np.float32(1e-3)
+
+
+# What reaches a sum that three bf16 parts cannot carry.  Gains below 1 keep the finite cases finite.
+def _masked_x(i):                    # a mask value of the type's lowest
+    i["x"][0, 3, 2:5, 3:9] = -FLT_MAX
+    i["x"][-1, 1, 0, 0] = FLT_MAX
+
+
+def _infinite_x(i):
+    i["x"][0, 3, 4, 5], i["x"][-1, 2, 0, 0] = np.inf, -np.inf
+    for k in ("U_in", "core", "U_out"):
+        i[k][...] = _one_sign(i[k])
+
+
+def _large_U_in(i):
+    i["U_in"][2, 1] = FLT_MAX
+    i["x"][...] *= np.float32(1e-20)
+
+
+def _large_core(i):
+    i["core"][3, 2, 0, 0] = -FLT_MAX
+    i["x"][...] *= np.float32(1e-20)
+
+
+def _large_U_out(i):
+    i["U_out"][1, 4] = FLT_MAX
+    i["x"][...] *= np.float32(1e-20)
+
+
+def _infinite_core(i):
+    i["x"][...], i["U_in"][...], i["U_out"][...] = _one_sign(i["x"]), _one_sign(i["U_in"]), _one_sign(i["U_out"])
+    i["core"][2, 1, i["core"].shape[2] // 2, i["core"].shape[3] // 2] = np.inf
+
+
+def _infinite_U_out(i):
+    i["x"][...], i["U_in"][...], i["core"][...] = _one_sign(i["x"]), _one_sign(i["U_in"]), _one_sign(i["core"])
+    i["U_out"][1, 2] = -np.inf
+
+
+def _overflowing_z1(i):
+    i["x"][0, :, 3, 3] = 1e30
+    for k in ("U_in", "core", "U_out"):
+        i[k][...] = _one_sign(i[k])
+    i["U_in"][...] *= np.float32(1e12)
+
+
+def _overflowing_y(i):
+    for k in ("x", "U_in", "core", "U_out"):
+        i[k][...] = _one_sign(i[k])
+    i["x"][...] *= np.float32(1e18)
+    i["U_out"][:, 2] *= np.float32(-1e30)
+
+
+def _nan_x(i):
+    i["x"][0, 3, 4, 5] = np.nan
+
+
+def _nan_beside_infinity(i):
+    _infinite_x(i)
+    i["x"][0, 1, 1, 1] = np.nan
+
+
+EXTREMES = (_masked_x, _infinite_x, _large_U_in, _large_core, _large_U_out, _infinite_core, _infinite_U_out, _overflowing_z1,
+            _overflowing_y, _nan_x, _nan_beside_infinity)
+
+
+@pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
+@pytest.mark.parametrize("layer,tiles", ((Layer(2, 32, 48, 12, 12, 32, 16, 3, 1, 1), ((12, 12), (4, 4))),
+                                         (Layer(40, 20, 24, 12, 12, 16, 33, 3, 2, 1), ((6, 6), (5, 4))),
+                                         (Layer(40, 20, 24, 12, 12, 40, 80, 1, 1, 0), ((12, 12), (5, 8)))),
+                         ids=lambda v: v.name() if isinstance(v, Layer) else "")
+@pytest.mark.parametrize("extreme", EXTREMES, ids=lambda f: f.__name__[1:])
+def test_values_without_three_parts_give_what_fp32_arithmetic_gives(orc, extreme, layer, tiles, nhwc):
+    inputs = {k: v.copy() for k, v in make_inputs(layer, 92).items()}
+    extreme(inputs)
+    with np.errstate(invalid="ignore", over="ignore"):
+        want = orc.conv_factored(orc.Shape(**layer.asdict()), **inputs)[0].astype(np.float32).astype(np.float64)
+    for th, tw in tiles:
+        fp32 = _run(layer, inputs, B.make_tuning(variant=B.VARIANT_CHAIN, tile_h=th, tile_w=tw, waves=(4, 4, 4), mb=(1, 1, 1), pb=(1,) * 3), nhwc, bf3=False)
+        t = B.make_tuning(variant=B.VARIANT_CHAIN, tile_h=th, tile_w=tw, waves=(4, 4, 4), mb=(1, 3, 1), pb=(2,) * 3)
+        print("[case] chain3", extreme.__name__, layer.name(), "nhwc" if nhwc else "nchw", th, tw, flush=True)
+        got = _run(layer, inputs, t, nhwc)
+        # NaN, infinities and their signs exactly as the fp32 kernel has them; the rest as accurate as always, the outputs an
+        # extreme value reaches and the others each against their own size
+        assert np.array_equal(np.isnan(got), np.isnan(fp32)) and np.array_equal(np.where(np.isinf(got), got, 0), np.where(np.isinf(fp32), fp32, 0))
+        finite = np.isfinite(got) & np.isfinite(want)
+        assert extreme not in (_masked_x, _large_U_in, _large_core, _large_U_out) or np.isfinite(got).all()
+        reached = np.abs(want) > (1e25 if extreme is _masked_x else 1e5)
+        for part in (finite & reached, finite & ~reached):
+            w, g = want[part], got.astype(np.float64)[part]
+            assert part.sum() == 0 or np.linalg.norm(g - w) <= 1.5e-6 * max(np.linalg.norm(w), 1e-30)
 
 
 def test_the_selector_takes_it_where_pixels_fill_the_chip():
