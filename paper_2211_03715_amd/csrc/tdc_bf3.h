@@ -109,6 +109,10 @@ __device__ __forceinline__ tdc_f4 tdc_join_weights(tdc_rsrc r, int block, int st
     for (int q = 0; q < 3; ++q) p[q] = tdc_buf_load2(r, (unsigned)(block * steps + (kg >> 1)) * 3072u + q * 1024u + lane * 16u + 8u * (kg & 1));
     return tdc_join4(p);
 }
+__device__ __forceinline__ tdc_u2 tdc_first_parts(tdc_rsrc r, int block, int steps, int kg, int lane)
+{
+    return tdc_buf_load2(r, (unsigned)(block * steps + (kg >> 1)) * 3072u + lane * 16u + 8u * (kg & 1));
+}
 
 // Whether the NaNs among some sums can only come from NaNs among their factors: there is one, and the other factors are too
 // small for products or sums of three stages to overflow.
@@ -123,8 +127,30 @@ struct TdcFactors {
             largest = fmaxf(largest, fabsf(v[j]));
         }
     }
+    // four stored values by their first parts
+    __device__ __forceinline__ void see(tdc_u2 p1)
+    {
+        tdc_f4 v;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const unsigned u = p1[j >> 1] >> 16 * (j & 1) & 0xffffu;
+            v[j] = __builtin_bit_cast(float, u == TDC_RAW ? 0x7f800000u : u << 16);
+        }
+        see(v);
+    }
     __device__ __forceinline__ bool explain_nan() const { return tdc_any_lane(nan) && !tdc_any_lane(largest >= 0x1p30f); }
 };
+
+// The kernel's arguments (its one parameter), read anew where this is called: what is hardly ever run keeps no registers of what
+// always is.
+template <class Args>
+__device__ __forceinline__ const Args &tdc_args_again()
+{
+    typedef const __attribute__((address_space(4))) Args *Ptr;
+    Ptr p = (Ptr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const Args *)p;
+}
 
 // four fp32 (one lane's share of a 16-wide k-group) -> three 8-byte operand halves
 __device__ __forceinline__ void tdc_split4(tdc_f4 v, tdc_u2 &p1, tdc_u2 &p2, tdc_u2 &p3)

@@ -247,8 +247,9 @@ struct Chain3Stage1 {
                 for (int j = 0; j < NR; ++j) seen.see(x[j]);
 #pragma unroll
                 for (int mb = 0; mb < MB1; ++mb) {
-                    seen.see(join(mb, 0));
-                    seen.see(join(mb, 1));
+                    const tdc_u4 u = __builtin_bit_cast(tdc_u4, w[mb].p[0]);
+                    seen.see((tdc_u2){u[0], u[1]});
+                    seen.see((tdc_u2){u[2], u[3]});
                 }
             }
             if (seen.explain_nan()) continue;
@@ -403,13 +404,13 @@ __device__ __forceinline__ void chain3_redo(const TdcChain3Args &a, const tdc_u2
     for (int kg = 0; kg < a.KG2; ++kg) {
         const int cell = cell_of(kg);
 #pragma unroll
-        for (int pb = 0; pb < PB; ++pb) seen.see(z1_at(cell, pb));
+        for (int pb = 0; pb < PB; ++pb) seen.see(z1s[cell + qbase[pb]]);
 #pragma unroll
-        for (int mb = 0; mb < NB2; ++mb) seen.see(tdc_join_weights(crs, mb, a.S2, kg, lane));
+        for (int mb = 0; mb < NB2; ++mb) seen.see(tdc_first_parts(crs, mb, a.S2, kg, lane));
     }
     for (int nb = 0; nb < a.NB3; ++nb)
 #pragma unroll
-        for (int kg = 0; kg < NB2; ++kg) seen.see(tdc_join_weights(ors, nb, S3, kg, lane));
+        for (int kg = 0; kg < NB2; ++kg) seen.see(tdc_first_parts(ors, nb, S3, kg, lane));
     if (seen.explain_nan()) return;
 
     tdc_f4 z2[NB2][PB];
@@ -450,14 +451,6 @@ __device__ __forceinline__ void chain3_redo(const TdcChain3Args &a, const tdc_u2
     }
 }
 
-// The kernel's arguments, read anew where this is called: what is hardly ever run keeps no registers of what always is.
-__device__ __forceinline__ const TdcChain3Args &chain3_args_again()
-{
-    const __attribute__((address_space(4))) TdcChain3Args *p = (const __attribute__((address_space(4))) TdcChain3Args *)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(p));
-    return *(const TdcChain3Args *)p;
-}
-
 template <int NB2, int PB, int LAY, int MB1>
 __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, 2) void tdc_chain3_kernel(TdcChain3Args a)
 {
@@ -473,7 +466,7 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, 2) void tdc_chain3_kernel(Td
         Chain3Stage1<LAY, MB1> s1 = stage1(a);
         s1.run(z1s);
         // a value without three parts among x, the weights or z1 itself
-        if (__builtin_expect(tdc_any_lane(!(s1.largest < TDC_BIG)), 0)) stage1(chain3_args_again()).redo(z1s);
+        if (__builtin_expect(tdc_any_lane(!(s1.largest < TDC_BIG)), 0)) stage1(tdc_args_again<TdcChain3Args>()).redo(z1s);
     }
     const Chain3Tile at(a);
     __syncthreads();
@@ -623,7 +616,7 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, 2) void tdc_chain3_kernel(Td
         if (__builtin_expect(tdc_any_lane(!(largest < TDC_BIG)), 0)) {
             int group = pg;
             asm volatile("" : "+s"(group));                      // its addresses are computed there, not kept from above
-            chain3_redo<NB2, PB, LAY>(chain3_args_again(), z1s, group, lane, slice);
+            chain3_redo<NB2, PB, LAY>(tdc_args_again<TdcChain3Args>(), z1s, group, lane, slice);
         }
     }
 }

@@ -46,20 +46,22 @@ __device__ __forceinline__ int tile_logical_block(int bid, int n)
     return xcd * per + min(xcd, rem) + slot;
 }
 
-// One output by fp32 multiply-adds, for the outputs the split products cannot give.
-template <int ACT, bool CONV>
+// One output by fp32 multiply-adds over the taps inside the image.
+template <int ACT>
 __device__ __forceinline__ void tile_plain_output(const TileArgs &a, int m, int p)
 {
     const int b = tdc_div(p, a.div_P), pix = p - b * a.P;
-    const int oh = CONV ? tdc_div(pix, a.div_Wo) : 0, h0 = oh * a.stride - a.pad, w0 = (pix - oh * a.Wo) * a.stride - a.pad;
+    const int oh = tdc_div(pix, a.div_Wo), h0 = oh * a.stride - a.pad, w0 = (pix - oh * a.Wo) * a.stride - a.pad;
     const float *x = a.act + (size_t)b * a.C * a.HW;
     const unsigned short *w = reinterpret_cast<const unsigned short *>(a.w3) + (size_t)(m >> 4) * a.S * 1536;
     float sum = 0.f;
-    for (int kg = 0; kg < a.KG; ++kg) {
-        const int tap = CONV ? tdc_div(kg, a.div_NBk) : 0, c0 = 16 * (kg - tap * a.NBk);
-        const int r = tap / a.K, h = h0 + r, wx = w0 + tap - r * a.K;
-        if (CONV && (h < 0 || h >= a.H || wx < 0 || wx >= a.W)) continue;
-        const int q = CONV ? h * a.W + wx : pix;
+#pragma unroll 1
+    for (int kg = 0; kg < a.KG && sum == sum; ++kg) {
+        const int tap = tdc_div(kg, a.div_NBk), c0 = 16 * (kg - tap * a.NBk);
+        const int r = tdc_div(tap, a.div_K), h = h0 + r, wx = w0 + tap - r * a.K;
+        if (h < 0 || h >= a.H || wx < 0 || wx >= a.W) continue;
+        const int q = h * a.W + wx;
+#pragma unroll 1
         for (int k = 0; k < 16 && c0 + k < a.C; ++k) {
             const unsigned short *f = w + (size_t)(kg >> 1) * 1536 + ((m & 15) + 16 * (k >> 2)) * 8 + (kg & 1) * 4 + (k & 3);
             sum = fmaf(tdc_join(f[0], f[512], f[1024]), ACT == TDC_ACT_NHWC ? x[(size_t)q * a.C + c0 + k] : x[(size_t)(c0 + k) * a.HW + q], sum);
@@ -67,6 +69,82 @@ __device__ __forceinline__ void tile_plain_output(const TileArgs &a, int m, int 
     }
     const size_t idx = ACT == TDC_ACT_NHWC ? (size_t)p * a.M + m : ((size_t)b * a.M + m) * a.P + pix;
     a.out[idx] = tdc_apply_epilogue(a.epi, sum, m, idx);
+}
+
+// A wavefront's sums once more on the fp32 matrix cores, one load at a time (see tdc_bf3.h), unless their NaNs are x's or the
+// weights'.  Returns a bit per sum of this lane for those that an infinite weight at a tap outside the image made NaN (it is 0
+// times the weight here, and no part of the sum).  3x3, 128 -> 128 at 28x28,
+// batch 8, every value NaN: 70 us, 26 with numbers (one output after the other: 5350).
+template <int ACT, bool CONV, int MB, int PB>
+__device__ __forceinline__ unsigned tile_redo(const TileArgs &a, int lane, int p_base, int mb0, tdc_f4 (&acc)[MB][PB])
+{
+    constexpr bool SWAP = ACT == TDC_ACT_NCHW;
+    const int g = lane >> 4, l16 = lane & 15;
+    const int b0 = tdc_div(p_base, a.div_P), n_img = min((16 * PB - 1) / a.P + 2, tdc_div(a.Ptot - 1, a.div_P) + 1 - b0);
+    const size_t img_elems = (size_t)a.C * a.HW;
+    const tdc_rsrc ars = tdc_make_rsrc(a.act + (size_t)b0 * img_elems, (unsigned)(n_img * img_elems * 4));
+    const tdc_rsrc wrs = tdc_make_rsrc(a.w3, a.w_bytes);
+    const auto load_x = [&](int kg, int pb) {      // channels 4*g .. of k-group kg for pixel l16 of block pb; 0 outside
+        const int tap = CONV ? tdc_div(kg, a.div_NBk) : 0, c = 16 * (kg - tap * a.NBk) + 4 * g;
+        const int r = CONV ? tdc_div(tap, a.div_K) : 0;
+        const int p = p_base + 16 * pb + l16;
+        const bool ok = p < a.Ptot;
+        const int b = tdc_div(ok ? p : p_base, a.div_P), pix = (ok ? p : p_base) - b * a.P;
+        const int oh = CONV ? tdc_div(pix, a.div_Wo) : 0;
+        const int h = oh * a.stride - a.pad + r, w = (pix - oh * a.Wo) * a.stride - a.pad + tap - r * a.K;
+        const bool in = ok && (!CONV || (h >= 0 && h < a.H && w >= 0 && w < a.W));
+        const int q = CONV ? h * a.W + w : pix;
+        const unsigned o = (unsigned)((b - b0) * (int)img_elems + (ACT == TDC_ACT_NHWC ? q * a.C + c : c * a.HW + q)) * 4u;
+        tdc_f4 v;
+        if (ACT == TDC_ACT_NHWC) return tdc_buf_load4(ars, in && c < a.C ? o : TDC_OOB);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = tdc_buf_load(ars, in && c + j < a.C ? o + 4u * j * a.HW : TDC_OOB);
+        return v;
+    };
+    const auto load_w = [&](int kg, int mb) { return mb0 + mb < a.NBm ? tdc_join_weights(wrs, mb0 + mb, a.S, kg, lane) : tdc_f4_zero(); };
+
+    TdcFactors xs, ws;
+#pragma unroll 2
+    for (int kg = 0; kg < a.KG; ++kg) {
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) xs.see(load_x(kg, pb));
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+            if (mb0 + mb < a.NBm) ws.see(tdc_first_parts(wrs, mb0 + mb, a.S, kg, lane));
+    }
+    const bool odd_weights = tdc_any_lane(ws.nan || ws.largest == INFINITY);
+    xs.nan |= ws.nan;
+    xs.largest = fmaxf(xs.largest, ws.largest);
+    if (xs.explain_nan() && !(CONV && odd_weights)) return 0u;
+
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) acc[mb][pb] = tdc_f4_zero();
+#pragma unroll 1
+    for (int kg = 0; kg < a.KG; ++kg) {
+        tdc_f4 x[PB];
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) x[pb] = load_x(kg, pb);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            const tdc_f4 w = load_w(kg, mb);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb) acc[mb][pb] = SWAP ? tdc_mfma(x[pb][j], w[j], acc[mb][pb]) : tdc_mfma(w[j], x[pb][j], acc[mb][pb]);
+        }
+    }
+    unsigned nans = 0;
+    if (CONV && odd_weights) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) nans |= acc[mb][pb][i] != acc[mb][pb][i] ? 1u << ((mb * PB + pb) * 4 + i) : 0u;
+    }
+    return nans;
 }
 
 template <int ACT, bool CONV, int WM, int MB, int PB, int KS>
@@ -279,31 +357,25 @@ __global__ __launch_bounds__(256 * KS, 3) void tdc_tile_kernel(TileArgs a)
             for (int pb = 0; pb < PB; ++pb) acc[mb][pb] += red[((wave * MB + mb) * PB + pb) * 64 + lane];
     }
 
-    // An infinite factor has no three parts (inf - inf in the split) and turns its sums into NaN where fp32 arithmetic has an
-    // infinity.  A lane that holds a NaN computes its outputs once more, in fp32, from x and the weights put together again.
-    float all = 0.f;
+    // the lane number once more: the one above need not be kept through the loop for this
+    const int out_lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), og = out_lane >> 4, ol = out_lane & 15;
+    // factors without three parts, or a sum that overflows on the way
+    float largest = 0.f;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int pb = 0; pb < PB; ++pb) all += (acc[mb][pb][0] + acc[mb][pb][1]) + (acc[mb][pb][2] + acc[mb][pb][3]);
-    if (all != all) {
-        for (int e = 0; e < MB * PB * 4; ++e) {
-            const int i = e & 3, pb = (e >> 2) % PB, mb = (e >> 2) / PB;
-            const int p = p_base + 16 * pb + (SWAP ? 4 * g + i : l16), m = 16 * (mb0 + mb) + (SWAP ? l16 : 4 * g + i);
-            if (p >= a.Ptot || m >= a.M) continue;
-            tile_plain_output<ACT, CONV>(a, m, p);
-        }
-        return;
-    }
+        for (int pb = 0; pb < PB; ++pb) largest = tdc_largest(largest, acc[mb][pb]);
+    unsigned nans = 0;
+    if (__builtin_expect(tdc_any_lane(!(largest < INFINITY)), 0)) nans = tile_redo<ACT, CONV, MB, PB>(tdc_args_again<TileArgs>(), out_lane, p_base, mb0, acc);
 
     const auto emit = [&](int mb, int pb, tdc_f4 v) {
         if (ACT == TDC_ACT_NHWC) {
-            const int p = p_base + 16 * pb + l16, m = 16 * (mb0 + mb) + 4 * g;
+            const int p = p_base + 16 * pb + ol, m = 16 * (mb0 + mb) + 4 * og;
             if (p < a.Ptot && m < a.M) tdc_store_nhwc(a.out, a.epi, v, m, (size_t)p * a.M + m);
             return;
         }
         // four consecutive pixels of channel m
-        const int p = p_base + 16 * pb + 4 * g, m = 16 * (mb0 + mb) + l16;
+        const int p = p_base + 16 * pb + 4 * og, m = 16 * (mb0 + mb) + ol;
         if (p >= a.Ptot || m >= a.M) return;
         const int b = tdc_div(p, a.div_P), pix = p - b * a.P;
         const float bias = a.epi.bias ? a.epi.bias[m] : 0.f;
@@ -333,6 +405,16 @@ __global__ __launch_bounds__(256 * KS, 3) void tdc_tile_kernel(TileArgs a)
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) emit(mb, pb, acc[mb][pb]);
+    if (CONV && __builtin_expect(tdc_any_lane(nans != 0), 0)) {
+        __threadfence();           // behind the stores above
+        const TileArgs &args = tdc_args_again<TileArgs>();
+#pragma unroll 1
+        for (int e = 0; e < MB * PB * 4; ++e) {
+            const int i = e & 3, pb = (e >> 2) % PB, mb = (e >> 2) / PB;
+            const int p = p_base + 16 * pb + (SWAP ? 4 * og + i : ol), m = 16 * (mb0 + mb) + (SWAP ? ol : 4 * og + i);
+            if ((nans >> e & 1u) && p < args.Ptot && m < args.M) tile_plain_output<ACT>(args, m, p);
+        }
+    }
 }
 
 template <int ACT, bool CONV>

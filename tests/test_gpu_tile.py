@@ -137,3 +137,61 @@ def test_weights_without_three_parts_give_what_fp32_arithmetic_gives(orc, value,
         else:
             assert_parity(got[reached], want[reached], layer.name())
         assert_parity(got[~reached], want[~reached], layer.name())
+
+
+@pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
+def test_an_infinite_weight_at_taps_outside_the_image_is_no_part_of_the_sum(orc, nhwc):
+    layer = Layer(2, 24, 72, 13, 9, 1, 1, 3, 1, 1)
+    inputs = make_dense_inputs(layer, 81)
+    inputs["x"], inputs["W"][4, 9, 0, 2] = np.abs(inputs["x"]), -np.inf
+    inputs["x"][1, 3, 6, 6] = np.nan
+    want = _oracle(orc, layer, inputs)
+    for tm, waves in ((64, 4), (128, 8)):
+        print("[case] tiles, infinite weight", "nhwc" if nhwc else "nchw", tm, waves, flush=True)
+        got = _run(layer, inputs, tm, waves, nhwc)
+        finite = np.isfinite(want)
+        assert np.array_equal(got[~finite], want[~finite].astype(np.float32), equal_nan=True) and np.isinf(want).any() and np.isnan(want).any()
+        assert_parity(got[finite], want[finite], layer.name())
+
+
+@pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
+@pytest.mark.parametrize("layer", (Layer(8, 128, 128, 28, 28, 1, 1, 3, 1, 1), Layer(8, 512, 128, 28, 28, 1, 1, 1, 1, 0)), ids=lambda l: l.name())
+def test_nan_inputs_cost_a_second_pass_at_most(layer, nhwc):
+    """Every value NaN, or one pixel in 64: the sums they reach are NaN without being computed again, the others keep theirs.
+    Finding that out reads the factors once more, unpipelined: 2 to 3 times the usual time, 6 allowed; computing the
+    outputs one after the other would be 100 times."""
+    import torch
+    from paper_2211_03715_amd.layer import DenseConv2d
+    dev = torch.device("cuda:0")
+    inputs = make_dense_inputs(layer, 82)
+    x = torch.from_numpy(np.ascontiguousarray(inputs["x"].transpose(0, 2, 3, 1) if nhwc else inputs["x"])).to(dev)
+    some = x.clone()
+    (some[:, ::8, ::8, 5] if nhwc else some[:, 5, ::8, ::8]).fill_(float("nan"))
+    conv = DenseConv2d(layer, 0, B.make_tuning(tile_h=64, tile_w=64, waves=(4,) * 3), B.LAYOUT_NHWC if nhwc else B.LAYOUT_NCHW)
+    try:
+        W = torch.from_numpy(inputs["W"]).to(dev)
+        conv.pack(W)
+        y = torch.empty(conv.out_shape(), device=dev)
+
+        def us(inp):
+            launch, best = conv.bind(inp, y), 1e9
+            for _ in range(5):
+                a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                a.record()
+                for _ in range(10):
+                    launch()
+                b.record()
+                b.synchronize()
+                best = min(best, a.elapsed_time(b) * 100)
+            return best
+
+        us(x)
+        usual, clean = us(x), y.clone()
+        for what, bad in (("every value", torch.full_like(x, float("nan"))), ("some pixels", some)):
+            took = us(bad)
+            print("[case] tiles, NaN in", what, layer.name(), "nhwc" if nhwc else "nchw", "%.1f us, usually %.1f" % (took, usual), flush=True)
+            assert took <= 6 * usual
+            nan = torch.isnan(y)
+            assert nan.all() if bad is not some else (nan.any() and torch.equal(y[~nan], clean[~nan]))
+    finally:
+        conv.close()
