@@ -35,10 +35,10 @@
  * nothing but its kernels, so it may be captured into a HIP graph.
  *
  * Precision: fp32 in, fp32 out, sums in fp32.  Kernels bound by matrix arithmetic multiply on the bf16 matrix cores with
- * every fp32 factor split into three bf16 parts (all 24 bits); the products are at least as accurate as fp32
- * multiply-adds for normal numbers and keep an absolute accuracy of 2^-134 for factors below 2^-110.  The dense layer gives
- * infinite factors' outputs as fp32 arithmetic does; in a Tucker layer, where an infinity reaches every channel of z1 with
- * either sign, they come out as NaN.
+ * every fp32 factor split into three bf16 parts (all 24 bits).  Values that have no such parts are multiplied in fp32 as
+ * the other kernels do: infinities, NaN, magnitudes from 2^126 on, and pixels and weight tensors in which nothing reaches
+ * 2^-110.  What such values reach then takes several times as long (NaN alone: twice to three times).  A factor
+ * below 2^-110 beside larger ones, of its pixel or of its weight tensor, keeps an absolute accuracy of 2^-134.
  *
  * Errors: every function returns a tdc_status (0 = success, negative =
  * failure).  Nothing aborts, throws or prints.

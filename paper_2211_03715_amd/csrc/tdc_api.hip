@@ -362,7 +362,7 @@ int tdc_plan_create_tuned(tdc_plan **out, const tdc_shape *shape, int device, co
         p->ws_bytes += (n_w1 + n_wm + n_wmp) * sizeof(float);
     }
     if (dense) {
-        const size_t bytes = p->tuning.tile_h ? tdc_packed3_bytes(d.NB2, d.K * d.K * d.NB1) : n_w2 * sizeof(float);
+        const size_t bytes = p->tuning.tile_h ? tdc_packed3_bytes(d.NB2, d.K * d.K * d.NB1) + TDC_PACKED3_TAIL : n_w2 * sizeof(float);
         ok = ok && hipMalloc((void **)&p->core_p, bytes) == hipSuccess;
         p->ws_bytes += bytes;
     }
@@ -373,9 +373,9 @@ int tdc_plan_create_tuned(tdc_plan **out, const tdc_shape *shape, int device, co
     }
     if (!dense && !merged && p->tuning.variant != TDC_VARIANT_NAIVE) {
         const bool parts = tdc_is_chain3(p->tuning);
-        const size_t b1 = parts ? tdc_packed3_bytes(d.NB1, d.KG1) : n_w1 * sizeof(float);
-        const size_t b2 = parts ? tdc_packed3_bytes(d.NB2, d.K * d.K * d.NB1) : n_w2 * sizeof(float);
-        const size_t b3 = parts ? tdc_packed3_bytes(d.NB3, d.NB2) : n_w3 * sizeof(float);
+        const size_t b1 = parts ? tdc_packed3_bytes(d.NB1, d.KG1) + TDC_PACKED3_TAIL : n_w1 * sizeof(float);
+        const size_t b2 = parts ? tdc_packed3_bytes(d.NB2, d.K * d.K * d.NB1) + TDC_PACKED3_TAIL : n_w2 * sizeof(float);
+        const size_t b3 = parts ? tdc_packed3_bytes(d.NB3, d.NB2) + TDC_PACKED3_TAIL : n_w3 * sizeof(float);
         ok = ok && hipMalloc((void **)&p->uin_p, b1) == hipSuccess;
         ok = ok && hipMalloc((void **)&p->core_p, b2) == hipSuccess;
         ok = ok && hipMalloc((void **)&p->uout_p, b3) == hipSuccess;

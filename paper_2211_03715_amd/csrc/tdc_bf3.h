@@ -11,11 +11,15 @@
 // normal inputs (one 16 x 16 block): relative error 3.7e-8 / 2.3e-7 / 5.7e-7 / 1.1e-6 at n = 32 / 256 / 1152 / 4608, where
 // v_mfma_f32_16x16x4_f32 gives 1.1e-7 / 3.1e-7 / 7.1e-7 / 1.3e-6; all nine products give the same figures as six.
 // Time per 16 x 16 x 32 block: 6 x 16 cycles against 8 x 32.
-// Values below 2^-110 keep an absolute accuracy of 2^-134 instead of a relative one (bf16 has no smaller subnormals).
+// Values below 2^-110 keep an absolute accuracy of 2^-134 instead of a relative one (bf16 has no smaller subnormals).  Beside
+// larger ones that is below their rounding; a sum of which nothing is larger would lose bits.
 // Infinities have no three parts, nor have finite values the conversion rounds to infinity (above 3.39e38): split, they give
 // NaN (inf - inf).  Where parts are stored such a value, like every one from 2^126 on, is kept raw: its fp32 bits in the
 // second and third part, behind a first part that is a NaN (TDC_RAW).  Either way every sum it reaches is NaN; a kernel that
 // ends up with a NaN or a magnitude from 2^126 on computes those sums once more with fp32 multiply-adds on the joined parts.
+// The same where all sums of a pixel that a lane or wavefront holds are below 2^-76 and not zero, as they are if no factor
+// there reaches 2^-110: weights of a tensor whose largest is outside 2^-100 .. 2^14 are kept raw, every one, so that a tensor
+// in parts cannot lift such a factor above that (2^20 terms of 2^14 * 2^-110).
 //
 // Operand layout of v_mfma_f32_16x16x32_bf16 (D 16x16 += A 16x32 * B 32x16): lane l holds A[m = l%16][k(l/16, j)] and
 // B[k(l/16, j)][p = l%16], j = 0..7, for any assignment k(g, j) that A and B share; D as in tdc_mfma.h.  Here a step is a pair of
@@ -56,28 +60,33 @@ __device__ __forceinline__ void tdc_split2(float a, float b, unsigned &p1, unsig
 }
 
 // Largest magnitude, NaN if one is (v_maximum3_f32: two values an instruction).
-constexpr float TDC_BIG = 0x1p126f;
+constexpr float TDC_BIG = 0x1p126f, TDC_SMALL = 0x1p-76f;
 __device__ __forceinline__ float tdc_largest(float m, tdc_f4 v)
 {
     m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, fabsf(v[0])), fabsf(v[1]));
     return __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, fabsf(v[2])), fabsf(v[3]));
 }
+// The smallest of several magnitudes that is not zero, as an integer: start with ~0u.
+__device__ __forceinline__ unsigned tdc_smallest(unsigned s, float m) { return min(s, __builtin_bit_cast(unsigned, m) - 1u); }
+constexpr unsigned TDC_SMALL_BITS = (127u - 76u) << 23;
+__device__ __forceinline__ bool tdc_is_small(unsigned s) { return s < TDC_SMALL_BITS - 1u; }
 __device__ __forceinline__ bool tdc_any_lane(bool b) { return __builtin_amdgcn_ballot_w64(b) != 0; }
 
 // first part of a value whose fp32 bits are the other two
 constexpr unsigned TDC_RAW = 0x7fffu;
 
-// tdc_split2 for values that are stored: those without three parts are kept raw (a NaN is a NaN in every part)
-__device__ __forceinline__ void tdc_split2_raw(float a, float b, unsigned &p1, unsigned &p2, unsigned &p3)
+// tdc_split2 for values that are stored: those from 2^126 on or not zero and below `least` are kept raw (a NaN is a NaN in
+// every part)
+__device__ __forceinline__ void tdc_split2_raw(float a, float b, float least, unsigned &p1, unsigned &p2, unsigned &p3)
 {
     tdc_split2(a, b, p1, p2, p3);
     const unsigned ua = __builtin_bit_cast(unsigned, a), ub = __builtin_bit_cast(unsigned, b);
-    if (!(fabsf(a) < TDC_BIG)) {
+    if (!(fabsf(a) < TDC_BIG) || (a != 0.f && fabsf(a) < least)) {
         p1 = (p1 & 0xffff0000u) | (a != a ? 0x7fc0u : TDC_RAW);
         p2 = (p2 & 0xffff0000u) | ua >> 16;
         p3 = (p3 & 0xffff0000u) | (ua & 0xffffu);
     }
-    if (!(fabsf(b) < TDC_BIG)) {
+    if (!(fabsf(b) < TDC_BIG) || (b != 0.f && fabsf(b) < least)) {
         p1 = (p1 & 0xffffu) | (b != b ? 0x7fc0u : TDC_RAW) << 16;
         p2 = (p2 & 0xffffu) | (ub & 0xffff0000u);
         p3 = (p3 & 0xffffu) | ub << 16;
@@ -118,13 +127,14 @@ __device__ __forceinline__ tdc_u2 tdc_first_parts(tdc_rsrc r, int block, int ste
 // small for products or sums of three stages to overflow.
 struct TdcFactors {
     float largest = 0.f;       // magnitude of the largest that is not NaN
-    bool nan = false;
+    bool nan = false, low = false;     // low: one below 2^-38 that is not 0; without, no product of two is small (2^-76)
     __device__ __forceinline__ void see(tdc_f4 v)
     {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             nan |= v[j] != v[j];
             largest = fmaxf(largest, fabsf(v[j]));
+            low |= v[j] != 0.f && fabsf(v[j]) < 0x1p-38f;
         }
     }
     // four stored values by their first parts
@@ -163,11 +173,11 @@ __device__ __forceinline__ void tdc_split4(tdc_f4 v, tdc_u2 &p1, tdc_u2 &p2, tdc
     p3 = (tdc_u2){a3, b3};
 }
 
-__device__ __forceinline__ void tdc_split4_raw(tdc_f4 v, tdc_u2 &p1, tdc_u2 &p2, tdc_u2 &p3)
+__device__ __forceinline__ void tdc_split4_raw(tdc_f4 v, float least, tdc_u2 &p1, tdc_u2 &p2, tdc_u2 &p3)
 {
     unsigned a1, a2, a3, b1, b2, b3;
-    tdc_split2_raw(v[0], v[1], a1, a2, a3);
-    tdc_split2_raw(v[2], v[3], b1, b2, b3);
+    tdc_split2_raw(v[0], v[1], least, a1, a2, a3);
+    tdc_split2_raw(v[2], v[3], least, b1, b2, b3);
     p1 = (tdc_u2){a1, b1};
     p2 = (tdc_u2){a2, b2};
     p3 = (tdc_u2){a3, b3};

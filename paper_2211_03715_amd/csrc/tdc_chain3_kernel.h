@@ -61,6 +61,7 @@ struct Chain3Stage1 {
     int fu, fs, fmg;                                   // fetch cursor: unit, step, channel group of the unit
     unsigned xoff[RUNS ? 1 : PB];
     float largest = 0.f;                               // magnitude of this lane's largest z1 value, NaN if there is one
+    unsigned smallest = ~0u;                           // of its pixels' largest values the smallest (tdc_smallest)
 
     __device__ __forceinline__ Chain3Stage1(const TdcChain3Args &args, int lane_, int wave_, int b, int h0_, int w0_) : a(args)
     {
@@ -177,7 +178,7 @@ struct Chain3Stage1 {
             for (int mb = 0; mb < MB1; ++mb) {
                 const int blk = mg * MB1 + mb;
                 tdc_u2 p[3];
-                if (RAW) tdc_split4_raw(acc[mb][pb], p[0], p[1], p[2]);
+                if (RAW) tdc_split4_raw(acc[mb][pb], 0x1p-110f, p[0], p[1], p[2]);
                 else tdc_split4(acc[mb][pb], p[0], p[1], p[2]);
                 if (ok && blk < a.NB1) {
 #pragma unroll
@@ -203,9 +204,13 @@ struct Chain3Stage1 {
         const auto done = [&]() {
             if (++step < a.S1) return;
 #pragma unroll
-            for (int mb = 0; mb < MB1; ++mb)
+            for (int pb = 0; pb < PB; ++pb) {
+                float m = 0.f;
 #pragma unroll
-                for (int pb = 0; pb < PB; ++pb) largest = tdc_largest(largest, acc[mb][pb]);
+                for (int mb = 0; mb < MB1; ++mb) m = tdc_largest(m, acc[mb][pb]);
+                largest = __builtin_elementwise_maximum(largest, m);
+                smallest = tdc_smallest(smallest, m);
+            }
             store<false>(z1s, unit, acc);
             unit += TDC_CHAIN3_WAVES;
             step = 0;
@@ -224,7 +229,7 @@ struct Chain3Stage1 {
         }
     }
     // The wavefront's units once more in fp32, one load at a time (see tdc_bf3.h); those whose NaNs are x's or the weights' stay.
-    __device__ __forceinline__ void redo(tdc_u2 *__restrict__ z1s)
+    __device__ __forceinline__ void redo(tdc_u2 *__restrict__ z1s, bool small)
     {
         tdc_f4 x[NR];
         tdc_op3 w[MB1];
@@ -252,7 +257,7 @@ struct Chain3Stage1 {
                     seen.see((tdc_u2){u[2], u[3]});
                 }
             }
-            if (seen.explain_nan()) continue;
+            if (!small && seen.explain_nan()) continue;
             tdc_f4 acc[MB1][PB];
 #pragma unroll
             for (int mb = 0; mb < MB1; ++mb)
@@ -411,7 +416,7 @@ __device__ __forceinline__ void chain3_redo(const TdcChain3Args &a, const tdc_u2
     for (int nb = 0; nb < a.NB3; ++nb)
 #pragma unroll
         for (int kg = 0; kg < NB2; ++kg) seen.see(tdc_first_parts(ors, nb, S3, kg, lane));
-    if (seen.explain_nan()) return;
+    if (seen.explain_nan() && !tdc_any_lane(seen.low)) return;     // and z2 cannot be small
 
     tdc_f4 z2[NB2][PB];
 #pragma unroll
@@ -451,8 +456,16 @@ __device__ __forceinline__ void chain3_redo(const TdcChain3Args &a, const tdc_u2
     }
 }
 
+// Wavefronts per SIMD an instance has registers for; the rarely run code must not cost one.
+constexpr int chain3_wavefronts(int nb2, int pb, int lay, int mb1)
+{
+    if (pb > 2) return 2;
+    if (nb2 <= 2) return lay == TDC_LAY_NCHW_RUNS ? 5 - mb1 : mb1 <= 2 ? 4 : 3;
+    return nb2 == 3 && lay == TDC_LAY_NHWC ? 3 : 2;
+}
+
 template <int NB2, int PB, int LAY, int MB1>
-__global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, 2) void tdc_chain3_kernel(TdcChain3Args a)
+__global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, LAY, MB1)) void tdc_chain3_kernel(TdcChain3Args a)
 {
     constexpr bool NHWC = LAY == TDC_LAY_NHWC;
     extern __shared__ tdc_u2 z1s[];                              // [3 parts][NB1][4][pitch1], then the partial sums of ks > 1
@@ -465,8 +478,9 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, 2) void tdc_chain3_kernel(Td
     {
         Chain3Stage1<LAY, MB1> s1 = stage1(a);
         s1.run(z1s);
-        // a value without three parts among x, the weights or z1 itself
-        if (__builtin_expect(tdc_any_lane(!(s1.largest < TDC_BIG)), 0)) stage1(tdc_args_again<TdcChain3Args>()).redo(z1s);
+        // a value without three parts among x, the weights or z1 itself, or a pixel of nothing but small ones
+        if (__builtin_expect(tdc_any_lane(!(s1.largest < TDC_BIG) || tdc_is_small(s1.smallest)), 0))
+            stage1(tdc_args_again<TdcChain3Args>()).redo(z1s, tdc_any_lane(tdc_is_small(s1.smallest)));
     }
     const Chain3Tile at(a);
     __syncthreads();
@@ -564,18 +578,6 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, 2) void tdc_chain3_kernel(Td
         }
         // ---- stage 3, operands swapped in NCHW: D[pixel 4*g + i][channel l16]; NHWC: D[channel 4*g + i][pixel l16]
         constexpr int S3 = (NB2 + 1) / 2;
-        float largest = 0.f;                                     // magnitude of the largest of z2 and y, NaN if there is one
-#pragma unroll
-        for (int mb = 0; mb < NB2; ++mb)
-#pragma unroll
-            for (int pb = 0; pb < PB; ++pb) largest = tdc_largest(largest, acc2[mb][pb]);
-        asm("" : "+v"(largest));                                 // now: not behind the outputs, with all of acc2 kept until then
-        tdc_op3 zb[S3][PB];
-#pragma unroll
-        for (int st = 0; st < S3; ++st)
-#pragma unroll
-            for (int pb = 0; pb < PB; ++pb) zb[st][pb] = tdc_split_op(acc2[2 * st][pb], 2 * st + 1 < NB2 ? acc2[(2 * st + 1) % NB2][pb] : tdc_f4_zero());
-        const Chain3Out<PB, NHWC> out(a, at, pg, lane);
         const auto fetch = [&](int nb, tdc_op3(&u)[S3]) {
 #pragma unroll
             for (int st = 0; st < S3; ++st)
@@ -583,6 +585,26 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, 2) void tdc_chain3_kernel(Td
                 for (int q = 0; q < 3; ++q)
                     u[st].p[q] = __builtin_bit_cast(tdc_bf8, tdc_buf_load4(ors, (unsigned)(nb * S3 + st) * 3072u + q * 1024u + lane * 16u));
         };
+        tdc_op3 u0[S3], u1[S3];
+        fetch(slice, u0);                                        // under the splitting of z2
+        float largest = 0.f;                                     // magnitude of the largest of z2 and y, NaN if there is one
+        unsigned smallest = ~0u;                                 // of the pixels' largest z2 values the smallest
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) {
+            float m = 0.f;
+#pragma unroll
+            for (int mb = 0; mb < NB2; ++mb) m = tdc_largest(m, acc2[mb][pb]);
+            largest = __builtin_elementwise_maximum(largest, m);
+            smallest = tdc_smallest(smallest, m);
+        }
+        largest = tdc_is_small(smallest) ? INFINITY : largest;
+        asm("" : "+v"(largest));                                 // now: not behind the outputs, with all of acc2 kept until then
+        tdc_op3 zb[S3][PB];
+#pragma unroll
+        for (int st = 0; st < S3; ++st)
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb) zb[st][pb] = tdc_split_op(acc2[2 * st][pb], 2 * st + 1 < NB2 ? acc2[(2 * st + 1) % NB2][pb] : tdc_f4_zero());
+        const Chain3Out<PB, NHWC> out(a, at, pg, lane);
         // two instances of the loop, as in tdc_chain_kernel.h: without epilogue loads nothing ever waits for the stores
         const auto emit = [&](auto with_epi, int nb, const tdc_op3(&u)[S3]) {
             tdc_f4 acc3[PB];
@@ -601,8 +623,6 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, 2) void tdc_chain3_kernel(Td
             out.template put<decltype(with_epi)::value>(nb, acc3);
         };
         const auto stage3 = [&](auto with_epi) {
-            tdc_op3 u0[S3], u1[S3];
-            fetch(slice, u0);
             for (int nb = slice; nb < a.NB3; nb += 2 * ks) {
                 fetch(nb + ks, u1);
                 emit(with_epi, nb, u0);
@@ -612,7 +632,7 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, 2) void tdc_chain3_kernel(Td
         };
         if (a.epi.bias || a.epi.residual || a.epi.relu) stage3(std::true_type{});
         else stage3(std::false_type{});
-        // a NaN, or z2 too large for three parts: only then can an output be wrong
+        // a NaN, or z2 too large or too small for three parts: only then can an output be wrong
         if (__builtin_expect(tdc_any_lane(!(largest < TDC_BIG)), 0)) {
             int group = pg;
             asm volatile("" : "+s"(group));                      // its addresses are computed there, not kept from above

@@ -58,6 +58,8 @@ hipError_t tdc_launch_pack_merged(const TdcDims &d, hipStream_t s, const float *
                                   const float *U_out, float *uin_p, float *wm, float *wm_p);
 // The same re-layout with every weight split into three bf16 parts (tdc_bf3.h): [m-block][step][part][lane][8], a step being
 // two k-groups, component j = what the fp32 layout has as component j%4 of k-group 2*step + j/4 (zero past the last one).
+// An allocation holds TDC_PACKED3_TAIL bytes more, which the re-layout uses.
+constexpr size_t TDC_PACKED3_TAIL = 256;
 inline size_t tdc_packed3_bytes(int m_blocks, int k_groups) { return (size_t)m_blocks * ((k_groups + 1) / 2) * 3072; }
 hipError_t tdc_launch_pack3_core(const TdcDims &d, hipStream_t s, const float *core, void *core_p3);
 hipError_t tdc_launch_pack3(const TdcDims &d, hipStream_t s, const float *U_in, const float *core, const float *U_out,

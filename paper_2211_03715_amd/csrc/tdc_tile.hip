@@ -76,7 +76,7 @@ __device__ __forceinline__ void tile_plain_output(const TileArgs &a, int m, int 
 // times the weight here, and no part of the sum).  3x3, 128 -> 128 at 28x28,
 // batch 8, every value NaN: 70 us, 26 with numbers (one output after the other: 5350).
 template <int ACT, bool CONV, int MB, int PB>
-__device__ __forceinline__ unsigned tile_redo(const TileArgs &a, int lane, int p_base, int mb0, tdc_f4 (&acc)[MB][PB])
+__device__ __forceinline__ unsigned tile_redo(const TileArgs &a, bool small, int lane, int p_base, int mb0, tdc_f4 (&acc)[MB][PB])
 {
     constexpr bool SWAP = ACT == TDC_ACT_NCHW;
     const int g = lane >> 4, l16 = lane & 15;
@@ -115,7 +115,7 @@ __device__ __forceinline__ unsigned tile_redo(const TileArgs &a, int lane, int p
     const bool odd_weights = tdc_any_lane(ws.nan || ws.largest == INFINITY);
     xs.nan |= ws.nan;
     xs.largest = fmaxf(xs.largest, ws.largest);
-    if (xs.explain_nan() && !(CONV && odd_weights)) return 0u;
+    if (xs.explain_nan() && !small && !(CONV && odd_weights)) return 0u;
 
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
@@ -359,14 +359,43 @@ __global__ __launch_bounds__(256 * KS, 3) void tdc_tile_kernel(TileArgs a)
 
     // the lane number once more: the one above need not be kept through the loop for this
     const int out_lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), og = out_lane >> 4, ol = out_lane & 15;
-    // factors without three parts, or a sum that overflows on the way
+    // Factors without three parts, a sum that overflows on the way, or a pixel all of whose sums here are small: channels with
+    // tiny weights beside others (a filter that decayed) do not make it one.
     float largest = 0.f;
+    unsigned smallest = ~0u;
+    const auto each_pixel = [&](auto f) {           // f(largest magnitude of this lane's channels of a pixel)
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+        for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
-        for (int pb = 0; pb < PB; ++pb) largest = tdc_largest(largest, acc[mb][pb]);
+            for (int i = 0; i < (SWAP ? 4 : 1); ++i) {
+                float m = 0.f;
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) m = SWAP ? __builtin_elementwise_maximum(m, fabsf(acc[mb][pb][i])) : tdc_largest(m, acc[mb][pb]);
+                f(m);
+            }
+    };
+    each_pixel([&](float m) {
+        largest = __builtin_elementwise_maximum(largest, m);
+        smallest = tdc_smallest(smallest, m);
+    });
+    bool small = false;
+    if (__builtin_expect(tdc_any_lane(tdc_is_small(smallest)), 0)) {
+        each_pixel([&](float m) {                   // the pixel's lanes: l16, or one lane group
+            unsigned long long ok = __builtin_amdgcn_ballot_w64(!(m < TDC_SMALL));
+            if (SWAP) {
+                const unsigned long long low15 = 0x7fff7fff7fff7fffull;
+                ok = ((((ok & low15) + low15) | ok) & ~low15) >> 15;        // bit 0 of a group: any of its lanes
+                ok *= 0xffffu;
+            } else {
+                ok |= ok >> 32 | ok << 32;
+                ok |= ok >> 16 | ok << 48;
+            }
+            small |= (__builtin_amdgcn_ballot_w64(m > 0.f) & ~ok) != 0;
+        });
+    }
     unsigned nans = 0;
-    if (__builtin_expect(tdc_any_lane(!(largest < INFINITY)), 0)) nans = tile_redo<ACT, CONV, MB, PB>(tdc_args_again<TileArgs>(), out_lane, p_base, mb0, acc);
+    if (__builtin_expect(small || tdc_any_lane(!(largest < INFINITY)), 0))
+        nans = tile_redo<ACT, CONV, MB, PB>(tdc_args_again<TileArgs>(), small, out_lane, p_base, mb0, acc);
 
     const auto emit = [&](int mb, int pb, tdc_f4 v) {
         if (ACT == TDC_ACT_NHWC) {

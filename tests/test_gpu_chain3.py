@@ -172,6 +172,32 @@ def test_values_without_three_parts_give_what_fp32_arithmetic_gives(orc, extreme
             assert part.sum() == 0 or np.linalg.norm(g - w) <= 1.5e-6 * max(np.linalg.norm(w), 1e-30)
 
 
+SCALES = ((-116, 0, 0, 0), (0, -116, 0, 0), (0, 0, -116, 0), (0, 0, 0, -116), (-60, -56, 0, 0), (-50, 0, -66, 0), (-118, 60, 40, 0),
+          (0, -60, -56, 100), (-113, 13, 0, 0))
+
+
+@pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
+@pytest.mark.parametrize("layer,tile", ((Layer(2, 32, 48, 12, 12, 32, 16, 3, 1, 1), (4, 4)), (Layer(40, 20, 24, 12, 12, 40, 80, 3, 2, 1), (6, 6))),
+                         ids=lambda v: v.name() if isinstance(v, Layer) else "")
+def test_the_scale_of_the_factors_costs_no_accuracy(orc, layer, tile, nhwc):
+    """Factors, z1 or z2 below 2^-110 have no three bf16 parts with all their bits; nothing larger stands beside them here."""
+    t = B.make_tuning(variant=B.VARIANT_CHAIN, tile_h=tile[0], tile_w=tile[1], waves=(4, 4, 4), mb=(2, 3, 1), pb=(2,) * 3)
+    for scales in SCALES + ("part of the image",):
+        inputs = {k: v.copy() for k, v in make_inputs(layer, 93).items()}
+        small = np.zeros(inputs["x"].shape, bool)
+        if isinstance(scales, str):
+            small[0, :, 3:, :], small[1] = True, True
+            inputs["x"][small] *= np.float32(2.0 ** -117)
+        else:
+            for k, e in zip(("x", "U_in", "core", "U_out"), scales):
+                inputs[k] *= np.float32(2.0 ** e)
+        want, _ = orc.conv_factored(orc.Shape(**layer.asdict()), **inputs)
+        print("[case] chain3 scales", scales, layer.name(), "nhwc" if nhwc else "nchw", flush=True)
+        got = _run(layer, inputs, t, nhwc).astype(np.float64)
+        for part in (np.abs(want) < 1e-25, np.abs(want) >= 1e-25):
+            assert not part.any() or np.linalg.norm((got - want)[part] * 2.0 ** 60) <= 1.5e-6 * np.linalg.norm(want[part] * 2.0 ** 60)
+
+
 def test_the_selector_takes_it_where_pixels_fill_the_chip():
     for lay in (B.LAYOUT_NCHW, B.LAYOUT_NHWC):
         t = B.tdc_select_tuning(B.make_shape(256, 128, 128, 28, 28, 32, 32, layout=lay))

@@ -195,3 +195,25 @@ def test_nan_inputs_cost_a_second_pass_at_most(layer, nhwc):
             assert nan.all() if bad is not some else (nan.any() and torch.equal(y[~nan], clean[~nan]))
     finally:
         conv.close()
+
+
+@pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
+@pytest.mark.parametrize("layer", (Layer(2, 40, 72, 13, 9, 1, 1, 3, 1, 1), Layer(2, 40, 72, 8, 8, 1, 1, 1, 1, 0)), ids=lambda l: l.name())
+def test_the_scale_of_the_factors_costs_no_accuracy(orc, layer, nhwc):
+    """Factors below 2^-110 have no three bf16 parts with all their bits.  Whole tensors, a few pixels, and a few filters (whose
+    outputs keep the accuracy that weights of 2^-100 allow)."""
+    for what in ((-116, 0), (0, -116), (-60, -56), (-119, 60), (-113, 13), "pixels", "filters"):
+        inputs = make_dense_inputs(layer, 83)
+        if what == "pixels":
+            inputs["x"][0, :, 2:, :] *= np.float32(2.0 ** -117)
+        elif what == "filters":
+            inputs["W"][:, 8:20] *= np.float32(2.0 ** -100)
+        else:
+            inputs["x"] *= np.float32(2.0 ** what[0])
+            inputs["W"] *= np.float32(2.0 ** what[1])
+        want = _oracle(orc, layer, inputs)
+        for tm, waves in ((64, 4), (128, 8)):
+            print("[case] tiles, scales", what, layer.name(), "nhwc" if nhwc else "nchw", tm, waves, flush=True)
+            got = _run(layer, inputs, tm, waves, nhwc).astype(np.float64)
+            for part in (np.abs(want) < 1e-25, np.abs(want) >= 1e-25):
+                assert not part.any() or np.linalg.norm((got - want)[part] * 2.0 ** 60) <= 1.2e-6 * np.linalg.norm(want[part] * 2.0 ** 60)
