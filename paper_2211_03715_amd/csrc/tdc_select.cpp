@@ -699,7 +699,8 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
         // 14.8 us).  With more, the other table, fitted on batch 1, is too low by 15-45 % (it knows neither memory bandwidth nor
         // the shortcut's bytes) and they win up to 1.2 times it: 64 -> 256 at 56x56, batch 32: 59.6 -> 50.3 us in NHWC, 93.9 ->
         // 50.1 in NCHW; batch 2: 7.4 -> 6.7 and 8.7 -> 7.2 us.  16 -> 32 stays (7.4 against 10.6 us): half of every tile would be padding.
-        if (!forced.mb[1] && !forced.pb[1] && !forced.waves[1]) {
+        // Not with one or two terms to a sum, where the split products are the less exact ones.
+        if (!forced.mb[1] && !forced.pb[1] && !forced.waves[1] && d.K * d.K * d.R1 >= 3) {
             const TileChoice tc = best_tile(d, dev);
             const double tiles = (double)cdiv(d.NB2 * 16, 64) * cdiv(d.B * d.Ho * d.Wo, 64);
             const double fill = (double)d.N / (64 * cdiv(d.N, 64));     // the part of the tiles' channels that exists
@@ -791,7 +792,11 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
     const long pixels = (long)d.B * d.Ho * d.Wo;
     // With a stride that holds for two blocks too (99x146 stride 2, ranks 31 and 5: 19.4 against 21.6).
     const bool few_products = (!d.nhwc && d.Wo % 4 && (d.NB1 == 1 || (d.stride > 1 && d.NB1 * d.NB2 <= 2))) || (d.K == 1 && d.NB1 <= 2 && pixels < 64L * dev.cus);
+    // With one or two terms to a sum the split products are the less exact ones (worst case 1.67 roundings against 1, 2.05 against
+    // 1.94; from three on 2.4 against 2.5 and better): such layers stay with fp32.
+    const bool few_terms = d.C < 3 || d.K * d.K * d.R1 < 3 || d.R2 < 3;
     const auto try_chain3 = [&](Chain3Choice &c) {
+        if (few_terms) return false;
         tdc_tuning free_choice = forced;
         free_choice.mb[0] = free_choice.pb[0] = free_choice.tile_h = free_choice.tile_w = 0;
         c = best_chain3(d, dev, free_choice);
