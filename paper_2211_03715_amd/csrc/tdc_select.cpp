@@ -795,11 +795,13 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
     // With one or two terms to a sum the split products are the less exact ones (worst case 1.67 roundings against 1, 2.05 against
     // 1.94; from three on 2.4 against 2.5 and better): such layers stay with fp32.
     const bool few_terms = d.C < 3 || d.K * d.K * d.R1 < 3 || d.R2 < 3;
+    // A field that the caller has set is for the kernels below, which honour it: wavefronts and register tiles mean other things
+    // here, and the tiles that suit them are not the ones that suit this kernel (128 pixels at most).
+    bool all_open = forced.tile_h == 0 && forced.tile_w == 0;
+    for (int i = 0; i < 3; ++i) all_open = all_open && forced.waves[i] == 0 && forced.mb[i] == 0 && forced.pb[i] == 0;
     const auto try_chain3 = [&](Chain3Choice &c) {
-        if (few_terms) return false;
-        tdc_tuning free_choice = forced;
-        free_choice.mb[0] = free_choice.pb[0] = free_choice.tile_h = free_choice.tile_w = 0;
-        c = best_chain3(d, dev, free_choice);
+        if (few_terms || !all_open) return false;
+        c = best_chain3(d, dev, forced);
         return c.us < 1e299;
     };
     Chain3Choice c3;

@@ -30,3 +30,25 @@ def test_sums_of_one_or_two_terms_stay_in_fp32(layout):
     assert dense()
     if layout == B.LAYOUT_NCHW:
         assert not dense(C=1, K=1, pad=0) and not dense(C=2, K=1, pad=0)
+
+
+def test_auto_honours_the_fields_a_caller_sets():
+    """Zero in a field means the selector's choice, and only zero does: each field set alone comes back, or the tuning is
+    refused.  (wavefronts and register tiles of stage 1 and of the pixels; the other stages' are not every kernel's)"""
+    layers = (dict(), dict(batch=32, C=256, N=256, H=14, W=14, R1=64, R2=64), dict(batch=3, C=100, N=152, H=37, W=29, R1=24, R2=40, K=5, pad=2),
+              dict(batch=1, C=64, N=64, H=224, W=224, R1=64, R2=32))
+    for kw in layers:
+        for layout in (B.LAYOUT_NCHW, B.LAYOUT_NHWC):
+            for field, values in (("tile_h", (2, 7, 8)), ("tile_w", (4, 8, 14)), ("waves", (2, 4, 8)), ("mb", (1, 2)), ("pb", (1, 2))):
+                for v in values:
+                    forced = B.make_tuning(**{field: v if field.startswith("tile") else (v, 0, 0)})
+                    try:
+                        t = _auto(layout, forced, **kw)
+                    except B.TdcError as e:
+                        assert e.status == B.TDC_ERR_BAD_TUNING
+                        continue
+                    if field.startswith("tile") and t.variant in (B.VARIANT_SPLIT, B.VARIANT_MERGED):
+                        continue                                # these have no spatial tile
+                    got = getattr(t, field)
+                    assert (got if field.startswith("tile") else got[0]) == v, (kw, layout, field, v, t.as_dict())
+            assert _auto(layout, B.make_tuning(tile_h=4, tile_w=4, pb=(1, 0, 0)), **kw).pb[0] == 1
