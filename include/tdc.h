@@ -130,7 +130,8 @@ enum {
  *   waves          : wavefronts (of 64 lanes) per workgroup  (SPLIT: per stage; FUSED, CHAIN: waves[0];
  *                    MERGED: [0] for stage 1, [1] for the merged convolution, likewise mb and pb)
  *   DENSE          : either mb[1], pb[1], waves[1] (the latency kernel), or a tile: tile_h = 64 or 128 output channels
- *                    by tile_w = 64 pixels, waves[1] = 4 or 8 (two groups of 4 that split the contraction)
+ *                    by tile_w = 64 pixels, waves[1] = 4 or 8 (two groups of 4 that split the contraction).  The latency
+ *                    kernel has no tile: one below 64, half of one, or one beside mb[1] or pb[1] above 1 is ignored
  *   mb, pb         : 16-channel and 16-pixel blocks per wavefront register tile, per stage
  *                    (CHAIN uses mb[0] and pb[0]; its stage-2 tile is all of R2 by construction)
  *   CHAIN, mb[1]=3 : the same kernel on the bf16 matrix cores, factors in three parts: waves 4, mb[0] 1 to 3, pb[0] 2 or 4

@@ -123,7 +123,7 @@ int check_tuning(const tdc_plan &p, const TdcDeviceInfo &dev)
     const bool merged = t.variant == TDC_VARIANT_MERGED || t.variant == TDC_VARIANT_FUSED_MERGED ||
                         t.variant == TDC_VARIANT_MERGED_XCD;
     const int nb[3] = {dense ? p.dims.NB2 : p.dims.NB1, merged ? p.dims.NB3 : p.dims.NB2, dense ? p.dims.NB2 : p.dims.NB3};
-    if (t.variant == TDC_VARIANT_DENSE && t.tile_h) {
+    if (tdc_is_tile(t)) {
         return tdc_tile_supported(t.tile_h, t.tile_w, t.waves[1] / 4) && tdc_tile_applies(p.dims) ? TDC_OK : TDC_ERR_BAD_TUNING;
     }
     if (tdc_is_chain3(t)) {
@@ -214,7 +214,7 @@ void describe(tdc_plan &p)
     else if (t.variant == TDC_VARIANT_MERGED_XCD)
         snprintf(p.desc, sizeof(p.desc), "merged-xcd split-k(s1,s23)=(%d,%d) grid=%d model=%.1fus", t.waves[0], t.waves[1],
                  tdc_merged_xcd_grid(p.dims, t), p.model_us);
-    else if (t.variant == TDC_VARIANT_DENSE && t.tile_h)
+    else if (tdc_is_tile(t))
         snprintf(p.desc, sizeof(p.desc), "dense %dx%d conv bf3 tile=%dx%d waves=%d model=%.1fus", p.dims.K, p.dims.K, t.tile_h, t.tile_w, t.waves[1], p.model_us);
     else if (t.variant == TDC_VARIANT_DENSE)
         snprintf(p.desc, sizeof(p.desc), "dense %dx%d conv (mb,pb,waves)=(%d,%d,%d) model=%.1fus", p.dims.K, p.dims.K,
@@ -362,7 +362,7 @@ int tdc_plan_create_tuned(tdc_plan **out, const tdc_shape *shape, int device, co
         p->ws_bytes += (n_w1 + n_wm + n_wmp) * sizeof(float);
     }
     if (dense) {
-        const size_t bytes = p->tuning.tile_h ? tdc_packed3_bytes(d.NB2, d.K * d.K * d.NB1) + TDC_PACKED3_TAIL : n_w2 * sizeof(float);
+        const size_t bytes = tdc_is_tile(p->tuning) ? tdc_packed3_bytes(d.NB2, d.K * d.K * d.NB1) + TDC_PACKED3_TAIL : n_w2 * sizeof(float);
         ok = ok && hipMalloc((void **)&p->core_p, bytes) == hipSuccess;
         p->ws_bytes += bytes;
     }
@@ -560,7 +560,7 @@ int tdc_conv_tucker2_ex(tdc_plan *p, void *hip_stream, const float *x, const flo
 
 static hipError_t pack_dense(const tdc_plan &p, hipStream_t s, const float *W)
 {
-    return p.tuning.tile_h ? tdc_launch_pack3_core(p.dims, s, W, p.core_p) : tdc_launch_pack_core(p.dims, s, W, p.core_p);
+    return tdc_is_tile(p.tuning) ? tdc_launch_pack3_core(p.dims, s, W, p.core_p) : tdc_launch_pack_core(p.dims, s, W, p.core_p);
 }
 
 int tdc_plan_pack_dense(tdc_plan *p, void *hip_stream, const float *W)
@@ -595,7 +595,7 @@ int tdc_conv_dense_ex(tdc_plan *p, void *hip_stream, const float *x, const float
         p->packed_from[1] = nullptr;
         if (pack_dense(*p, s, W) != hipSuccess) return TDC_ERR_HIP;
     }
-    if (p->tuning.tile_h)
+    if (tdc_is_tile(p->tuning))
         return tdc_launch_tile_dense(p->dims, p->tuning.tile_h, p->tuning.tile_w, p->tuning.waves[1] / 4, s, x, p->core_p, y, epi) == hipSuccess ? TDC_OK : TDC_ERR_HIP;
     return tdc_launch_dense(p->dims, p->tuning, s, x, p->core_p, y, epi) == hipSuccess ? TDC_OK : TDC_ERR_HIP;
 }

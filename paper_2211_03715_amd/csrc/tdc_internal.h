@@ -84,6 +84,12 @@ hipError_t tdc_launch_dense(const TdcDims &d, const tdc_tuning &t, hipStream_t s
 
 // the same layer in tm x tp tiles of (channels x pixels) on the bf16 matrix cores (tdc_tile.hip), the contraction dealt to
 // `ks` groups of wavefronts; w3: tdc_launch_pack3_core's layout
+// A DENSE tuning asks for it with both tile fields, no smaller than 64, and no register tile; with any other tile fields it
+// means the latency kernel, which has none.
+inline bool tdc_is_tile(const tdc_tuning &t)
+{
+    return t.variant == TDC_VARIANT_DENSE && t.tile_h >= 64 && t.tile_w >= 64 && t.mb[1] <= 1 && t.pb[1] <= 1;
+}
 bool tdc_tile_supported(int tm, int tp, int ks);
 bool tdc_tile_applies(const TdcDims &d);
 hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipStream_t s, const float *x, const void *w3, float *y, const TdcEpi &epi);

@@ -626,7 +626,7 @@ int tdc_select_terms(const TdcDims &d, const TdcDeviceInfo &dev, const tdc_tunin
             stage_terms(f, dev, d.B, n_mblocks, n_pblocks, kgroups, t.mb[st], t.pb[st], t.waves[st], conv_stride);
             for (int i = 0; i < G_TERMS; ++i) sum[i] += f[i];
         };
-        if (t.variant == TDC_VARIANT_DENSE && t.tile_h) {
+        if (tdc_is_tile(t)) {
             double ft[T_TERMS];
             tile_terms(ft, d, dev, t.tile_h, t.waves[1] / 4);
             return emit(ft, kTileTermNames, T_TERMS, "dense_tile");
@@ -684,8 +684,8 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
             if (model_us) *model_us = us;
             return TDC_OK;
         };
-        if (forced.tile_h) {
-            if (forced.tile_w && forced.tile_w != 64) return TDC_ERR_BAD_TUNING;
+        if (tdc_is_tile(forced)) {
+            if (forced.tile_w != 64) return TDC_ERR_BAD_TUNING;
             const int tm = forced.tile_h, ks = forced.waves[1] ? forced.waves[1] / 4 : 1;
             if (!tdc_tile_supported(tm, 64, ks) || (forced.waves[1] && forced.waves[1] != 4 * ks)) return TDC_ERR_BAD_TUNING;
             double f[T_TERMS];

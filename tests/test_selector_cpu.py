@@ -52,3 +52,17 @@ def test_auto_honours_the_fields_a_caller_sets():
                     got = getattr(t, field)
                     assert (got if field.startswith("tile") else got[0]) == v, (kw, layout, field, v, t.as_dict())
             assert _auto(layout, B.make_tuning(tile_h=4, tile_w=4, pb=(1, 0, 0)), **kw).pb[0] == 1
+
+
+@pytest.mark.parametrize("fields", (dict(tile_h=8), dict(tile_h=96), dict(tile_h=64), dict(tile_w=64), dict(tile_h=14, tile_w=14),
+                                    dict(tile_h=64, tile_w=64, mb=(0, 2, 0)), dict(tile_h=128, tile_w=64, pb=(0, 4, 0))), ids=str)
+def test_a_dense_tuning_without_a_whole_tile_means_the_latency_kernel(fields):
+    """tile_h and tile_w are fields the latency kernel has never had: alone, small, or beside its register tile they say nothing."""
+    shape = B.make_shape(batch=2, C=64, N=128, H=28, W=28, R1=1, R2=1, K=3, stride=1, pad=1)
+    plain = {k: v for k, v in fields.items() if not k.startswith("tile")}
+    want = B.tdc_select_tuning(shape, tuning=B.make_tuning(variant=B.VARIANT_DENSE, **plain)).as_dict()
+    assert B.tdc_select_tuning(shape, tuning=B.make_tuning(variant=B.VARIANT_DENSE, **fields)).as_dict() == want
+    for k, v in plain.items():
+        assert want[k][1] == v[1] and want["tile_h"] == 0
+    full = dict(mb=(2, 2, 2), pb=(1, 1, 1), waves=(4, 4, 4), **{k: v for k, v in fields.items() if k.startswith("tile")})
+    assert B.tdc_model_terms(shape, B.make_tuning(variant=B.VARIANT_DENSE, **full))[0] == "dense"
