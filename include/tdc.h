@@ -253,8 +253,9 @@ int tdc_select_tuning(const tdc_shape *shape, int compute_units, int lds_bytes, 
  * dot product of fitted coefficients with terms computed from the shape and the tuning; this call returns the terms of
  * the fully specified tuning *tuning (every field set, as tdc_plan_get_tuning or tdc_select_tuning return it):
  * terms[0 .. *n_terms), their names (static strings) in names[] when names is not NULL, and in *model (when not NULL)
- * which coefficient table applies: "fused_latency", "fused_throughput", "chain", "fused_merged" or "stage" (the GEMM
- * launches of SPLIT, MERGED and DENSE, summed over the launches of one call).  A least-squares fit of measured
+ * which coefficient table applies: "fused_latency", "fused_throughput", "chain" (both CHAIN kernels; the other one's terms
+ * are 0), "fused_merged", "dense" and "dense_tile" (the two dense kernels) or "stage" (the GEMM launches of SPLIT and MERGED,
+ * summed over the launches of one call).  A least-squares fit of measured
  * latencies against these terms reproduces the tables the library is built with (paper section 5.5 compares its
  * model with exhaustive search the same way).  TDC_ERR_BAD_TUNING for NAIVE / AUTO, TDC_ERR_BAD_SHAPE if max_terms is
  * too small (32 is enough). */

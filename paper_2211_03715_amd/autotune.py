@@ -272,7 +272,7 @@ def analyse(path: str) -> int:
 
 COEF_HEADER = __import__("os").path.join(__import__("os").path.dirname(__import__("os").path.abspath(__file__)), "csrc", "tdc_select_coef.h")
 COEF_TABLES = {"fused_latency": "kFusedLatencyCoef", "fused_throughput": "kFusedThroughputCoef", "chain": "kChainCoef",
-               "fused_merged": "kFmCoef", "stage": "kStageCoef", "dense": "kDenseCoef"}
+               "fused_merged": "kFmCoef", "stage": "kStageCoef", "dense": "kDenseCoef", "dense_tile": "kTileCoef"}
 _VARIANT_IDS = {v: k for k, v in B.VARIANT_NAMES.items()}
 _LAYER_RE = __import__("re").compile(r"b(\d+)_c(\d+)_n(\d+)_(\d+)x(\d+)_r(\d+)-(\d+)_k(\d+)_s(\d+)_p(\d+)$")
 
@@ -319,8 +319,8 @@ def sweep_rows(paths: Iterable[str], default_layout: str = "nchw") -> Dict[str, 
                     model, names, terms = B.tdc_model_terms(shape, tuning)
                 except B.TdcError:
                     continue
-                # CHAIN is only ever chosen where every CU gets two pixel blocks or more; its table is fitted there
-                if model == "chain" and L.batch * L.Ho * L.Wo < 32 * 256:
+                # fp32 CHAIN is only ever chosen where every CU gets two pixel blocks or more; its table is fitted there
+                if model == "chain" and t["mb"][1] != 3 and L.batch * L.Ho * L.Wo < 32 * 256:
                     continue
                 by_model.setdefault(model, []).append({"layer": res["layer"], "layout": res.get("layout", default_layout),
                                                        "us": r["us"], "terms": terms, "names": names, "plan": r["plan"]})
@@ -335,6 +335,7 @@ def fit(paths: Iterable[str], default_layout: str = "nchw", models: Iterable[str
     import numpy as np
     from scipy.optimize import nnls
     out = {}
+    current = read_coefficients()
     for model, rows in sweep_rows(paths, default_layout).items():
         if models and model not in models:
             continue
@@ -346,6 +347,8 @@ def fit(paths: Iterable[str], default_layout: str = "nchw", models: Iterable[str
             best_of[key] = min(best_of.get(key, r["us"]), r["us"])
         w = np.array([(best_of[(r["layer"], r["layout"])] / r["us"]) ** near_best / r["us"] for r in rows])
         coef, _ = nnls(X * w[:, None], y * w)
+        unseen = ~X.any(axis=0)                   # a term that no row has (a layout, a kernel the sweeps lack) keeps its coefficient
+        coef[unseen] = np.array(current[model])[unseen]
         pred = X @ coef
         err = np.abs(pred - y) / y
         groups: Dict = {}
@@ -492,7 +495,7 @@ def main(argv=None) -> int:
                     help="no GPU: look the built library's own choice up in sweeps saved with --out and print how far it "
                          "lies behind the best tuning timed")
     ap.add_argument("--models", nargs="*", default=[], help="with --fit: only these coefficient tables "
-                    "(fused_latency fused_throughput chain fused_merged stage)")
+                    "(fused_latency fused_throughput chain fused_merged stage dense dense_tile)")
     ap.add_argument("--held-out", nargs="*", default=[], metavar="JSON", help="with --fit: sweeps the fit does not see, "
                     "ranked with the fitted tables as a check")
     ap.add_argument("--near-best", type=float, default=0.0, help="with --fit: exponent of (layer's best / row's latency) "

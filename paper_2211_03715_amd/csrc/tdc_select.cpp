@@ -192,11 +192,14 @@ enum {
     C_NB3_LDS, C_BLK3,                             // stage 3 per output block with weights in LDS, per MFMA quad
     C_W_KB, C_X_MB_NCHW, C_X_MB_NHWC, C_X_MB_RUNS, C_Y_MB, C_X_ROWS, C_Y_ROWS,
     C_NOVEC,                                       // per output-channel block and pixel block stored with 4-byte stores
+    // the kernel on the bf16 matrix cores has terms of its own, the launch apart: thousands of cycles of stage 1, of stages 2
+    // and 3, and chains of phases, each times what sharing a compute unit adds (see chain3_terms)
+    C_BF3_S1, C_BF3_S23, C_BF3_PHASES,
     C_TERMS
 };
 const char *const kChainTermNames[C_TERMS] = {"launch", "s1_unit", "s1_kg", "s1_mfma", "s1r_unit", "s1r_kg", "s1r_mfma",
                                               "kg2_lds", "kg2_glb", "blk2", "nb3_lds", "blk3", "w_kb", "x_mb_nchw", "x_mb_nhwc",
-                                              "x_mb_runs", "y_mb", "x_rows", "y_rows", "novec"};
+                                              "x_mb_runs", "y_mb", "x_rows", "y_rows", "novec", "bf3_s1_kcyc", "bf3_s23_kcyc", "bf3_phases"};
 
 void chain_terms(double (&f)[C_TERMS], const TdcDims &d, const TdcDeviceInfo &dev, const TdcFusedGeom &g, bool runs, int nw,
                  int mb1, int pb, int *cu_waves)
@@ -309,12 +312,8 @@ struct Chain3Choice {
     int th = 0, tw = 0, mb1 = 0, pb = 0;
 };
 
-// terms: constant; thousands of cycles of stage 1, of stages 2 and 3, and chains, each times what sharing a compute unit adds
-enum { X_LAUNCH, X_S1, X_S23, X_PHASES, X_TERMS };
-const char *const kChain3TermNames[X_TERMS] = {"launch", "s1_kcycles", "s23_kcycles", "phases"};
-const double kChain3Coef[X_TERMS] = {3.0, 0.5, 0.5, 3.0};   // (a term for the tiles' bytes and row segments made the picks worse: 28.7 -> 41.4 us at 224x224)
-
-void chain3_terms(double (&f)[X_TERMS], const TdcDims &d, const TdcDeviceInfo &dev, const TdcFusedGeom &g, bool runs, int mb1, int pb)
+// A term for the tiles' bytes and row segments made the picks worse (28.7 -> 41.4 us at 224x224).
+void chain3_terms(double (&f)[C_TERMS], const TdcDims &d, const TdcDeviceInfo &dev, const TdcFusedGeom &g, bool runs, int mb1, int pb)
 {
     const int S1 = (d.KG1 + 1) / 2, S2 = (d.K * d.K * d.NB1 + 1) / 2, S3 = (d.NB2 + 1) / 2;
     const int pb1 = runs ? 4 : 2, rpr = runs ? tdc_runs_per_row(d.W, d.Wo, g.TW, d.K, d.stride, d.pad) : 0;
@@ -326,17 +325,18 @@ void chain3_terms(double (&f)[X_TERMS], const TdcDims &d, const TdcDeviceInfo &d
     const int fit = std::max(1, std::min((int)(dev.lds_per_wg / std::max<size_t>(g.lds_bytes, 1)), 3));
     const int r = std::min(fit, (int)std::ceil(per_cu));
     const double chains = r == 1 ? std::ceil(per_cu) : (1.0 + 0.5 * (r - 1)) * std::max(1.0, per_cu / r);
-    f[X_LAUNCH] = 1.0;
-    f[X_S1] = chains * cdiv(u1, 4) * c1 * 1e-3;
-    f[X_S23] = chains * cdiv(u2, 4) * c23 / (1 << tdc_chain3_share(u2)) * 1e-3;
-    f[X_PHASES] = chains;
+    for (double &v : f) v = 0.0;
+    f[C_LAUNCH] = 1.0;
+    f[C_BF3_S1] = chains * cdiv(u1, 4) * c1 * 1e-3;
+    f[C_BF3_S23] = chains * cdiv(u2, 4) * c23 / (1 << tdc_chain3_share(u2)) * 1e-3;
+    f[C_BF3_PHASES] = chains;
 }
 
 double chain3_us(const TdcDims &d, const TdcDeviceInfo &dev, const TdcFusedGeom &g, bool runs, int mb1, int pb)
 {
-    double f[X_TERMS];
+    double f[C_TERMS];
     chain3_terms(f, d, dev, g, runs, mb1, pb);
-    return dot(kChain3Coef, f, X_TERMS);
+    return dot(kChainCoef, f, C_TERMS);
 }
 
 Chain3Choice best_chain3(const TdcDims &d, const TdcDeviceInfo &dev, const tdc_tuning &forced)
@@ -537,7 +537,6 @@ StageChoice best_stage(const TdcDeviceInfo &dev, int batch, int n_mblocks, int n
 // pair of steps in 0.77 and 1.1), a step among others 0.40 and 0.64, in NCHW a K x K layer's 4-byte loads make it 0.48 and 0.76.
 enum { T_LAUNCH, T_OWN_64, T_OWN_64X2, T_OWN_128, T_OWN_128X2, T_LOAD_64, T_LOAD_128, T_TILE_64, T_TILE_128, T_TERMS };
 const char *const kTileTermNames[T_TERMS] = {"launch", "own_64", "own_64x2", "own_128", "own_128x2", "load_64", "load_128", "tile_64", "tile_128"};
-const double kTileCoef[T_TERMS] = {3.5, 0.50, 0.77, 0.68, 1.1, 0.40, 0.64, 1.1, 3.2};
 
 void tile_terms(double (&f)[T_TERMS], const TdcDims &d, const TdcDeviceInfo &dev, int tm, int ks)
 {
@@ -600,9 +599,9 @@ int tdc_select_terms(const TdcDims &d, const TdcDeviceInfo &dev, const tdc_tunin
         return emit(f, kFusedTermNames, F_TERMS, throughput ? "fused_throughput" : "fused_latency");
     }
     if (tdc_is_chain3(t)) {
-        double f[X_TERMS];
+        double f[C_TERMS];
         chain3_terms(f, d, dev, tdc_chain3_geometry(d, t.tile_h, t.tile_w, t.pb[0]), runs, t.mb[0], t.pb[0]);
-        return emit(f, kChain3TermNames, X_TERMS, "chain");
+        return emit(f, kChainTermNames, C_TERMS, "chain");
     }
     if (t.variant == TDC_VARIANT_CHAIN) {
         const TdcFusedGeom g = tdc_chain_geometry(d, t.tile_h, t.tile_w, t.waves[0], t.pb[0], dev.lds_per_wg);

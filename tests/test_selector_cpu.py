@@ -1,6 +1,8 @@
 """What the selector may and may not choose, on the CPU."""
+import numpy as np
 import pytest
 
+from paper_2211_03715_amd import autotune as A
 from paper_2211_03715_amd import binding as B
 
 
@@ -66,3 +68,28 @@ def test_a_dense_tuning_without_a_whole_tile_means_the_latency_kernel(fields):
         assert want[k][1] == v[1] and want["tile_h"] == 0
     full = dict(mb=(2, 2, 2), pb=(1, 1, 1), waves=(4, 4, 4), **{k: v for k, v in fields.items() if k.startswith("tile")})
     assert B.tdc_model_terms(shape, B.make_tuning(variant=B.VARIANT_DENSE, **full))[0] == "dense"
+
+
+def test_every_choice_has_an_estimate_that_a_caller_can_rebuild():
+    """Terms and table of whatever the selector picks, the bf16 kernels included, have the same length, and the product is the
+    estimate: of two tunings of one kernel the pick's is the lower one."""
+    tables = A.read_coefficients()
+    for layout in (B.LAYOUT_NCHW, B.LAYOUT_NHWC):
+        shape = B.make_shape(256, 128, 128, 28, 28, 32, 32, 3, 1, 1, layout)
+        pick = B.tdc_select_tuning(shape)
+        assert _is_bf16(pick)
+        model, names, terms = B.tdc_model_terms(shape, pick)
+        assert len(tables[model]) == len(names) == len(terms) and sum(1 for t in terms if t) == 4
+        est = float(np.dot(tables[model], terms))
+        d = pick.as_dict()
+        for th, tw, mb1 in ((2, 28, 2), (4, 28, 1), (4, 16, 2), (8, 14, 2)):
+            other = B.make_tuning(variant=B.VARIANT_CHAIN, tile_h=th, tile_w=tw, waves=(4,) * 3, mb=(mb1, 3, 1), pb=tuple(d["pb"]))
+            assert est <= float(np.dot(tables[model], B.tdc_model_terms(shape, other)[2])) + 1e-9
+        dense = B.make_tuning(variant=B.VARIANT_DENSE)
+        pick = B.tdc_select_tuning(shape, tuning=dense)
+        model, names, terms = B.tdc_model_terms(shape, pick)
+        assert model == "dense_tile" and len(tables[model]) == len(names) == len(terms)
+        est = float(np.dot(tables[model], terms))
+        for tm, waves in ((64, 4), (64, 8), (128, 4), (128, 8)):
+            other = B.make_tuning(variant=B.VARIANT_DENSE, tile_h=tm, tile_w=64, waves=(waves,) * 3, mb=(1,) * 3, pb=(1,) * 3)
+            assert est <= float(np.dot(tables[model], B.tdc_model_terms(shape, other)[2])) + 1e-9
