@@ -32,6 +32,7 @@ FUSED_MENU = [(1, 1, 1, 1), (1, 1, 2, 1), (2, 2, 2, 1), (2, 2, 4, 1), (4, 4, 4, 
 TILE_H = (1, 2, 4, 7, 8, 14, 16)
 TILE_W = (4, 7, 8, 14, 16, 28, 32)
 STAGE_WAVES = (1, 2, 3, 4, 6, 8)
+DENSE_TILES = [dict(tile_h=tm, tile_w=64, waves=(0, nw, 0)) for tm in (64, 128) for nw in (4, 8)]   # the dense layer's tile kernel
 
 
 def _tiles(L: Layer):
@@ -47,6 +48,11 @@ def candidates(L: Layer, variants: Iterable[str] = ("fused", "chain", "split", "
     if "chain" in variants:
         for (th, tw), nw, mb1, pb in itertools.product(_tiles(L), (1, 2, 4, 8), (1, 2, 4), (1, 2)):
             out.append(dict(variant=B.VARIANT_CHAIN, tile_h=th, tile_w=tw, waves=(nw,) * 3, mb=(mb1, 1, 1), pb=(pb,) * 3))
+        # the bf16 matrix cores (ranks up to 80): the tiles above and, where four wavefronts have one group of pixel blocks each, all others
+        tiles = set(_tiles(L)) | {(th, tw) for th in range(1, min(L.Ho, 32) + 1) for tw in range(min(L.Wo, 4), min(L.Wo, 64) + 1)
+                                  if 16 <= th * tw <= 128 and (tw % 4 == 0 or tw == L.Wo)}
+        for (th, tw), mb1, pb in itertools.product(sorted(tiles) if L.R2 <= 80 else (), (1, 2, 3), (2, 4)):
+            out.append(dict(variant=B.VARIANT_CHAIN, tile_h=th, tile_w=tw, waves=(4,) * 3, mb=(mb1, 3, 1), pb=(pb,) * 3))
     if "fused_merged" in variants:
         small = sorted({(min(th, L.Ho), min(tw, L.Wo)) for th in (1, 2, 3, 4) for tw in (4, 7, 8, 14, 16, 28, 32)
                         if min(th, L.Ho) * min(tw, L.Wo) <= 64})
@@ -166,7 +172,7 @@ EPILOGUES = {"none": (False, False, False), "bias": (True, False, False), "bias_
 def autotune_dense(L: Layer, device: int = 0, iters: int = 200, epilogue: str = "bias_residual_relu", progress=None,
                    layout: int = B.LAYOUT_NCHW) -> Dict:
     """The dense K x K layer of L's shape (tdc_conv_dense; R1, R2 are ignored) with every register-tile / wavefront
-    combination of its one GEMM launch, timed with the given epilogue.  Same result format as autotune()."""
+    combination of its one GEMM launch and every tile of the tile kernel, timed with the given epilogue.  Same result format as autotune()."""
     import torch
     from .layer import DenseConv2d
     dev = torch.device("cuda", device)
@@ -191,6 +197,12 @@ def autotune_dense(L: Layer, device: int = 0, iters: int = 200, epilogue: str = 
     for mb, pb, nw in itertools.product((1, 2, 4), (1, 2, 4), STAGE_WAVES):
         try:
             rows.append(run(B.make_tuning(mb=(0, mb, 0), pb=(0, pb, 0), waves=(0, nw, 0))))
+        except B.TdcError as e:
+            if e.status != B.TDC_ERR_BAD_TUNING:
+                raise
+    for tile in DENSE_TILES:
+        try:
+            rows.append(run(B.make_tuning(**tile)))
         except B.TdcError as e:
             if e.status != B.TDC_ERR_BAD_TUNING:
                 raise

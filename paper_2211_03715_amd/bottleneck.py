@@ -327,11 +327,11 @@ class TuckerResNet18Body(TuckerResNetBody):
 def oracle_tunings(layout: int = B.LAYOUT_NCHW, device: int = 0, iters: int = 100, progress=None):
     """A ``tunings`` function for the blocks and networks above that replaces the selector's closed-form choice by
     exhaustive search, the paper's "oracle" setting next to its "modeling" one (section 7): the first time a convolution
-    shape is asked for, every launchable tuning of it is timed on the GPU (Tucker layers: autotune.autotune, 500-2400
-    tunings; dense layers: the 36 register-tile / wavefront combinations, with the epilogue the layer will run with),
+    shape is asked for, every launchable tuning of it is timed on the GPU (Tucker layers: autotune.autotune, 500-3000
+    tunings; dense layers: the 36 register-tile / wavefront combinations and the tiles, with the epilogue the layer will run with),
     the fastest is kept and served from then on.  Returns (function, log) -- log lists (kind, layer, model us, best us)."""
     import torch
-    from .autotune import _time, autotune
+    from .autotune import DENSE_TILES, _time, autotune
     cache, log = {}, []
 
     def dense(layer, epilogue):
@@ -339,7 +339,7 @@ def oracle_tunings(layout: int = B.LAYOUT_NCHW, device: int = 0, iters: int = 10
         x = torch.randn((layer.batch, layer.H, layer.W, layer.C) if layout == B.LAYOUT_NHWC else (layer.batch, layer.C, layer.H, layer.W), device=dev)
         W = torch.randn((layer.C, layer.N, layer.K, layer.K), device=dev) * float(layer.C * layer.K * layer.K) ** -0.5
         rows = []
-        for tun in [None] + [dict(mb=(0, mb, 0), pb=(0, pb, 0), waves=(0, nw, 0)) for mb in (1, 2, 4) for pb in (1, 2, 4) for nw in (1, 2, 4, 8)]:
+        for tun in [None] + [dict(mb=(0, mb, 0), pb=(0, pb, 0), waves=(0, nw, 0)) for mb in (1, 2, 4) for pb in (1, 2, 4) for nw in (1, 2, 4, 8)] + DENSE_TILES:
             try:
                 conv = DenseConv2d(layer, device, B.make_tuning(**tun) if tun else None, layout=layout)
             except B.TdcError:

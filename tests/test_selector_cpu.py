@@ -4,6 +4,7 @@ import pytest
 
 from paper_2211_03715_amd import autotune as A
 from paper_2211_03715_amd import binding as B
+from paper_2211_03715_amd.workloads import Layer
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -93,3 +94,14 @@ def test_every_choice_has_an_estimate_that_a_caller_can_rebuild():
         for tm, waves in ((64, 4), (64, 8), (128, 4), (128, 8)):
             other = B.make_tuning(variant=B.VARIANT_DENSE, tile_h=tm, tile_w=64, waves=(waves,) * 3, mb=(1,) * 3, pb=(1,) * 3)
             assert est <= float(np.dot(tables[model], B.tdc_model_terms(shape, other)[2])) + 1e-9
+
+
+def test_the_exhaustive_search_lists_the_kernels_the_selector_takes():
+    """The searched optimum can only be no worse than AUTO if AUTO's kernels are among the candidates."""
+    for L in (Layer(32, 128, 128, 28, 28, 32, 32, 3, 1, 1), Layer(32, 256, 256, 14, 14, 64, 64, 3, 1, 1), Layer(1, 64, 64, 224, 224, 64, 32, 3, 1, 1),
+              Layer(8, 128, 256, 56, 56, 32, 64, 3, 2, 1)):
+        pick = _auto(**L.asdict())
+        assert _is_bf16(pick)
+        listed = {(c["variant"], c.get("tile_h"), c.get("tile_w"), c["mb"][0], c["mb"][1], c.get("pb", (0,))[0]) for c in A.candidates(L)}
+        assert (pick.variant, pick.tile_h, pick.tile_w, pick.mb[0], pick.mb[1], pick.pb[0]) in listed, pick.as_dict()
+    assert not any(c["variant"] == B.VARIANT_CHAIN and c["mb"][1] == 3 for c in A.candidates(Layer(32, 512, 512, 7, 7, 128, 128, 3, 1, 1)))
