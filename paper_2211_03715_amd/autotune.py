@@ -216,6 +216,49 @@ def autotune_dense(L: Layer, device: int = 0, iters: int = 200, epilogue: str = 
             "best": rows[0], "by_variant": {"dense": rows[0]}, "rows": rows}
 
 
+def against_fp32(L: Layer, device: int = 0, iters: int = 200, layout: int = B.LAYOUT_NCHW) -> Dict:
+    """AUTO's choice and the selector's own pick of every fp32 kernel, timed in turn with three sets of buffers: {"auto_us",
+    "auto", "fp32_us", "fp32"} (microseconds and plan; the fastest of the fp32 kernels)."""
+    import torch
+    dev = torch.device("cuda", device)
+    t = {k: torch.from_numpy(v).to(dev) for k, v in make_inputs(L, 1).items()}
+    x = t["x"].permute(0, 2, 3, 1).contiguous() if layout == B.LAYOUT_NHWC else t["x"]
+    xs = [x, x.clone(), x.clone()]
+    runs = []
+    for variant, mb in ((None, 0), (B.VARIANT_FUSED, 0), (B.VARIANT_CHAIN, 1), (B.VARIANT_SPLIT, 0), (B.VARIANT_MERGED, 0), (B.VARIANT_FUSED_MERGED, 0)):
+        try:
+            conv = TuckerConv2d(L, device, None if variant is None else B.make_tuning(variant=variant, mb=(0, mb, 0)), layout=layout)
+        except B.TdcError:
+            continue
+        conv.pack(t["U_in"], t["core"], t["U_out"])
+        launches = [conv.bind(v, torch.empty(conv.out_shape(), device=dev)) for v in xs]
+        runs.append((conv, lambda launches=launches: [f() for f in launches], []))
+    for _ in range(3):
+        for conv, launch, us in runs:
+            us.append(_time(launch, max(10, iters // 3)) / 3)
+    best = min(runs[1:], key=lambda r: min(r[2]))
+    out = {"auto_us": min(runs[0][2]), "auto": runs[0][0].describe(), "fp32_us": min(best[2]), "fp32": best[0].describe()}
+    for conv, _, _ in runs:
+        conv.close()
+    return out
+
+
+def against_fp32_main(layers: List[Layer], layout: int, iters: int) -> int:
+    ratios = []
+    for L in layers:
+        r = against_fp32(L, 0, iters, layout)
+        bf3 = " bf3 " in r["auto"]
+        print("%-46s px/CU %5.0f  auto %8.2f us  fp32 %8.2f us  %5.2fx  %s | %s" % (
+            L.name(), L.batch * L.Ho * L.Wo / 256.0, r["auto_us"], r["fp32_us"], r["fp32_us"] / r["auto_us"],
+            r["auto"].split(" grid")[0], r["fp32"].split(" grid")[0].split(" model")[0]), flush=True)
+        if bf3:
+            ratios.append(r["fp32_us"] / r["auto_us"])
+    if ratios:
+        print("%d layers on the bf16 matrix cores: %.2f to %.2f times as fast as the best fp32 kernel's pick, %.2f on (geometric) average" % (
+            len(ratios), min(ratios), max(ratios), float(__import__("numpy").exp(__import__("numpy").log(ratios).mean()))))
+    return 0
+
+
 def paper_tile_rule(L: Layer, rows: List[Dict], cus: int = 256, top: float = 0.05) -> Dict:
     """The paper's tile selection (sections 5.3-5.5) applied to the FUSED kernel's tilings of one layer.
 
@@ -498,6 +541,7 @@ def main(argv=None) -> int:
     ap.add_argument("--dense", action="store_true", help="sweep the dense K x K layer of each shape (tdc_conv_dense; R1, R2 ignored) "
                     "instead of the Tucker layer: the data of the `dense` coefficient table")
     ap.add_argument("--epilogue", default="bias_residual_relu", choices=sorted(EPILOGUES), help="with --dense: what the timed calls carry")
+    ap.add_argument("--against-fp32", action="store_true", help="time the selector's choice beside its own pick of every fp32 kernel instead of sweeping")
     ap.add_argument("--out", default=None, help="JSON with every timed tuning")
     ap.add_argument("--analyse", default=None, metavar="JSON", help="no GPU: the paper's two-step tile rule on a sweep saved with --out")
     ap.add_argument("--fit", nargs="+", default=None, metavar="JSON",
@@ -526,9 +570,12 @@ def main(argv=None) -> int:
         sys.exit("autotune needs a GPU")
     B.load()
     results = []
-    print("%-46s %9s %9s %7s  %s" % ("layer", "model us", "best us", "gap", "best plan"), flush=True)
+    if not args.against_fp32:
+        print("%-46s %9s %9s %7s  %s" % ("layer", "model us", "best us", "gap", "best plan"), flush=True)
     groups = [[Layer(*[int(v) for v in spec.split(",")]) for spec in args.shapes]] if args.shapes else \
              [config_layers(cfg) for cfg in args.config]
+    if args.against_fp32:
+        return against_fp32_main([L for g in groups for L in g], B.LAYOUT_NHWC if args.layout == "nhwc" else B.LAYOUT_NCHW, args.iters)
     for layers in groups:
         seen = set()
         for L in layers:

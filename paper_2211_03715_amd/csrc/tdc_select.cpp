@@ -342,7 +342,7 @@ double chain3_us(const TdcDims &d, const TdcDeviceInfo &dev, const TdcFusedGeom 
 Chain3Choice best_chain3(const TdcDims &d, const TdcDeviceInfo &dev, const tdc_tuning &forced)
 {
     const bool runs = tdc_runs_apply(d, dev.cus);
-    Chain3Choice best;
+    Chain3Choice best, whole_blocks;
     const int th_lo = forced.tile_h ? forced.tile_h : 1, th_hi = forced.tile_h ? forced.tile_h : std::min(d.Ho, 32);
     const int tw_lo = forced.tile_w ? forced.tile_w : std::min(d.Wo, 4), tw_hi = forced.tile_w ? forced.tile_w : std::min(d.Wo, 64);
     for (int th = th_lo; th <= th_hi; ++th)
@@ -357,9 +357,15 @@ Chain3Choice best_chain3(const TdcDims &d, const TdcDeviceInfo &dev, const tdc_t
                     if (!tdc_chain3_supported(d, mb1, pb)) continue;
                     const double us = chain3_us(d, dev, g, runs, mb1, pb);
                     if (us < best.us) best = {us, th, tw, mb1, pb};
+                    if (tw % 16 == 0 && us < whole_blocks.us) whole_blocks = {us, th, tw, mb1, pb};
                 }
         }
-    return best;
+    // Large NCHW images whose rows allow no 16-byte stores: tiles whose rows are whole pixel blocks rather than of an odd width
+    // below 16, up to 1.3 times their estimate, which does not see how the stores fall (179x179, 96 -> 144, ranks 17 and 34,
+    // batch 2: 7x9 62.6 us, 4x16 51.6; 114x114, 106 -> 174, batch 5: 70.0, 60.2; six layers 1.02 to 1.26 times as fast; from
+    // even widths five layers became 1 to 12 % slower).
+    const bool narrow = !d.nhwc && d.Wo % 4 && best.tw < 16 && best.tw % 2 && best.tw < d.Wo && d.NB1 <= 2 && (long)d.B * d.Ho * d.Wo >= 128L * dev.cus;
+    return narrow && !forced.tile_w && whole_blocks.us <= 1.3 * best.us ? whole_blocks : best;
 }
 
 // FUSED_MERGED: stage 1 as in FUSED (dealt over nw wavefronts), then every wavefront runs its
@@ -789,8 +795,16 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
     // ranks 9 and 33: 6.6 against 7.3; 13x13, ranks 17 and 58: 9.5 against 10.0).
     const bool one_block = d.NB1 == 1 && d.NB2 == 1;
     const long pixels = (long)d.B * d.Ho * d.Wo;
-    // With a stride that holds for two blocks too (99x146 stride 2, ranks 31 and 5: 19.4 against 21.6).
-    const bool few_products = (!d.nhwc && d.Wo % 4 && (d.NB1 == 1 || (d.stride > 1 && d.NB1 * d.NB2 <= 2))) || (d.K == 1 && d.NB1 <= 2 && pixels < 64L * dev.cus);
+    // With a stride that holds for two blocks too (99x146 stride 2, ranks 31 and 5: 19.4 against 21.6), and in NCHW for 1x1
+    // layers of up to four blocks at stride 1 below 32 pixels (12x18, ranks 45 and 13, batch 30: 8.6 against 9.9).
+    // Below 36 pixels NCHW layers of two blocks each whose rows allow no 16-byte stores (51x47, ranks 27 and 23, batch 2: 9.5
+    // against 10.7; 7 of 8 drawn ones with up to 3x3 taps slower, 0.92 times on average).  Large strided NCHW images that only stage 1 has work
+    // for, whose tiles with halo fill the LDS (205x224 stride 2, 208 -> 16, ranks 63 and 5: 36.8 against 56.3; five drawn ones,
+    // 0.88 times on average; the same at stride 1 are faster, 71x71 and 132x132 by 1.06 and 1.27).
+    const bool few_products = (!d.nhwc && d.Wo % 4 && (d.NB1 == 1 || (d.stride > 1 && d.NB1 * d.NB2 <= 2))) || (d.K == 1 && d.NB1 <= 2 && pixels < 64L * dev.cus) ||
+                              (d.K == 1 && d.stride == 1 && !d.nhwc && d.NB1 <= 4 && pixels < 32L * dev.cus) ||
+                              (!d.nhwc && d.Wo % 4 && d.stride == 1 && d.K <= 3 && d.NB1 <= 2 && d.NB2 <= 2 && pixels < 36L * dev.cus) ||
+                              (!d.nhwc && d.stride > 1 && d.NB1 >= 4 && d.NB2 == 1 && d.N <= 64 && (long)d.Ho * d.Wo >= 6000);
     // With one or two terms to a sum the split products are the less exact ones (worst case 1.67 roundings against 1, 2.05 against
     // 1.94; from three on 2.4 against 2.5 and better): such layers stay with fp32.
     const bool few_terms = d.C < 3 || d.K * d.K * d.R1 < 3 || d.R2 < 3;
@@ -887,9 +901,13 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
         // batch 64: 50.2 against 38.3 us; 256 channels on 56x56: 17.9 against 17.4 us), 2 % ahead at best.
         variant = (f.us <= 0.92 * split_us || (pixels_fill_chip && f.us < 1e299)) ? TDC_VARIANT_FUSED : TDC_VARIANT_SPLIT;
     }
-    // From 8 pixels on what would be FUSED's runs there too (3 images of 37x29, 5x5, 100 -> 150: 15.9 -> 15.7 us; 26x19 stride 2,
-    // 476 -> 108: 77.5 -> 77.0), unless R1 is a single block (14x14, 40 -> 368, ranks 10 and 71: 14.0 against 15.3 us)
-    if (forced.variant == TDC_VARIANT_AUTO && variant == TDC_VARIANT_FUSED && !pixels_fill_chip && d.NB1 > 1 && !few_products &&
+    // From 8 pixels per compute unit on what would be FUSED's runs there too: 65 drawn layers, 1.21 times as
+    // fast on average (0.85 to 1.76).  Not at stride 1 in 1x1 layers (12x11, 372 ->
+    // 284, batch 28: 10.7 against 12.4 us), nor there with at most three blocks of R1 where NCHW rows are no multiple of 4 (26x38,
+    // 112 -> 160, ranks 20 and 32: 9.5 against 11.0; 13x13, 5x5, ranks 22 and 62: 14.6 against 16.0), nor with a single block
+    // of R1 (14x14, 40 -> 368, ranks 10 and 71: 14.0 against 15.3).
+    const bool worth_it = d.stride > 1 || (d.K > 1 && (d.nhwc || d.Wo % 4 == 0 || d.NB1 > 3));
+    if (forced.variant == TDC_VARIANT_AUTO && variant == TDC_VARIANT_FUSED && !pixels_fill_chip && d.NB1 > 1 && !few_products && worth_it &&
         pixels >= 8L * dev.cus && try_chain3(c3))
         return chain3(c3);
     if (variant == TDC_VARIANT_FUSED) {

@@ -105,3 +105,21 @@ def test_the_exhaustive_search_lists_the_kernels_the_selector_takes():
         listed = {(c["variant"], c.get("tile_h"), c.get("tile_w"), c["mb"][0], c["mb"][1], c.get("pb", (0,))[0]) for c in A.candidates(L)}
         assert (pick.variant, pick.tile_h, pick.tile_w, pick.mb[0], pick.mb[1], pick.pb[0]) in listed, pick.as_dict()
     assert not any(c["variant"] == B.VARIANT_CHAIN and c["mb"][1] == 3 for c in A.candidates(Layer(32, 512, 512, 7, 7, 128, 128, 3, 1, 1)))
+
+
+def test_where_few_pixels_leave_layers_with_the_fp32_kernels():
+    """Below 16 output pixels per compute unit: not 1x1 layers at stride 1, nor narrow NCHW ones whose rows are no multiple of 4;
+    the others are.  (26x38, 112 -> 160: 11.0 us on the bf16 matrix cores, 9.5 in fp32)"""
+    few = dict(batch=3, C=112, N=160, H=26, W=38, R1=20, R2=32)
+    assert not _is_bf16(_auto(**few))
+    assert _is_bf16(_auto(batch=6, C=137, N=100, H=29, W=18, R1=54, R2=41))                 # four blocks of R1
+    assert _is_bf16(_auto(batch=10, C=204, N=219, H=20, W=20, R1=60, R2=76))                # rows of quads
+    assert _is_bf16(_auto(B.LAYOUT_NHWC, batch=2, C=124, N=136, H=43, W=45, R1=22, R2=33))
+    one = dict(batch=28, C=372, N=284, H=12, W=11, R1=49, R2=50, K=1, pad=0)
+    assert not _is_bf16(_auto(**one)) and not _is_bf16(_auto(B.LAYOUT_NHWC, **one))
+
+
+def test_tiles_of_large_nchw_images_without_16_byte_rows():
+    """179x179: whole pixel blocks in a tile's rows (51.6 us) instead of 9 pixels (62.6)."""
+    t = _auto(batch=2, C=96, N=144, H=179, W=179, R1=17, R2=34)
+    assert _is_bf16(t) and t.tile_w % 16 == 0 and t.tile_h * t.tile_w <= 128
