@@ -70,8 +70,9 @@ def test_chain3(orc, layer, tiles, nhwc):
             # three chained sums of at most 600 terms: fp32 multiply-adds show up to 1e-6, the split products no more; two
             # parts instead of three would show 5e-6 in each
             assert np.linalg.norm(got - want) <= 1.5e-6 * max(np.linalg.norm(want), 1e-30)
-        got = _run(layer, inputs, t, nhwc, bias, residual, 0 if nhwc else 1)
-        assert_parity(got, with_epi, "%s tile %dx%d epilogue" % (layer.name(), th, tw))
+        for offset in (0,) if nhwc else (0, 1):             # 16-byte stores where rows and tile allow them, then 4-byte ones
+            got = _run(layer, inputs, t, nhwc, bias, residual, offset)
+            assert_parity(got, with_epi, "%s tile %dx%d epilogue, y + %d floats" % (layer.name(), th, tw, offset))
 
 
 FLT_MAX = float(np.finfo(np.float32).max)

@@ -12,6 +12,7 @@ from paper_2211_03715_amd import autotune as A
 from paper_2211_03715_amd import binding as B
 
 SAMPLE = os.path.join(os.path.dirname(__file__), "golden", "sweep_sample.json")
+SAMPLE_BF16 = os.path.join(os.path.dirname(__file__), "golden", "sweep_sample_bf16.json")   # the bf16 CHAIN kernel among the tunings
 
 
 @pytest.fixture(scope="module")
@@ -90,6 +91,8 @@ def test_fit_on_the_measured_sample(lib):
         assert all(c >= 0.0 for c in res["coef"])
         assert res["median_err"] < 0.15, (model, res["median_err"])
         assert max(v["regret"] for v in res["regret"].values()) < 0.15
+    fitted = A.fit([SAMPLE, SAMPLE_BF16], models=("chain",))["chain"]        # one table, both CHAIN kernels
+    assert fitted["median_err"] < 0.2 and fitted["rows"] > 150 and all(fitted["coef"][-3:])
     ev = A.evaluate([SAMPLE], A.read_coefficients())
     assert len(ev) == 4 and all(v["regret"] < 0.25 for v in ev.values())
 
@@ -99,6 +102,11 @@ def test_selector_choice_looked_up_in_the_sample(lib):
     assert len(rows) == 4
     for r in rows:
         assert r["gap"] is None or 0.0 <= r["gap"] < 0.25
+    # the first sample was taken before the kernel the selector now takes for its layers: the second one has it
+    rows = A.selector_gap([SAMPLE_BF16])
+    assert len(rows) == 4
+    for r in rows:
+        assert r["pick"]["mb"][1] == 3 and r["gap"] is not None and 0.0 <= r["gap"] < 0.15, r
 
 
 def test_coefficient_header_round_trip(lib, tmp_path):
