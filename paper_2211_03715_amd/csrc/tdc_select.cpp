@@ -716,7 +716,11 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
             // 189: 63.2 against 66.6); tiles that are half empty lose (74x50, 3x3, 288 -> 32, batch 9: 77 against 97).
             const bool quads = d.nhwc || d.Ho * d.Wo % 4 == 0;
             const double margin = tiles < 1.5 * dev.cus ? 0.95 : fill <= 0.5 ? 0.85 : tiles < 8.0 * dev.cus ? 1.2 : !quads ? 1.0 : std::max(1.2, 1.85 * fill);
-            if (tc.us < margin * c.us) return tiled(tc.tm, tc.ks, tc.us);
+            // With 4-byte stores and at most three k-groups there is little but the stores, and the latency kernel's smaller
+            // workgroups spread them better below 8 tiles per compute unit (214x214 stride 2, 32 -> 80, batch 2: 6.5 against 10.3 us;
+            // 63x63, 26 -> 104, batch 5: 6.5 against 9.2).
+            const bool only_stores = !quads && d.K * d.K * d.NB1 <= 3 && tiles < 8.0 * dev.cus;
+            if (!only_stores && tc.us < margin * c.us) return tiled(tc.tm, tc.ks, tc.us);
         }
         if (c.us >= 1e299) return TDC_ERR_BAD_TUNING;
         t->tile_h = t->tile_w = 0;

@@ -123,3 +123,9 @@ def test_tiles_of_large_nchw_images_without_16_byte_rows():
     """179x179: whole pixel blocks in a tile's rows (51.6 us) instead of 9 pixels (62.6)."""
     t = _auto(batch=2, C=96, N=144, H=179, W=179, R1=17, R2=34)
     assert _is_bf16(t) and t.tile_w % 16 == 0 and t.tile_h * t.tile_w <= 128
+
+
+def test_short_dense_contractions_with_4_byte_stores_stay_with_the_latency_kernel():
+    dense = lambda **kw: _auto(tuning=B.make_tuning(variant=B.VARIANT_DENSE), **dict(dict(K=1, pad=0, R1=1, R2=1), **kw)).tile_h
+    assert not dense(batch=2, C=32, N=80, H=214, W=214, stride=2) and not dense(batch=5, C=26, N=104, H=63, W=63)
+    assert dense(batch=5, C=26, N=104, H=64, W=64) and dense(batch=5, C=160, N=104, H=63, W=63)
