@@ -135,8 +135,8 @@ enum {
  *   mb, pb         : 16-channel and 16-pixel blocks per wavefront register tile, per stage
  *                    (CHAIN uses mb[0] and pb[0]; its stage-2 tile is all of R2 by construction)
  *   CHAIN, mb[1]=3 : the same kernel on the bf16 matrix cores, factors in three parts: waves 4, mb[0] 1 to 3, pb[0] 2 or 4
- *                    (what AUTO takes from 64 output pixels per compute unit).  R2 up to 80 (pb[0] = 4: 48); beyond that,
- *                    and for any other mb[1], the fp32 kernel */
+ *                    (what AUTO takes for most layers from 16 output pixels per compute unit, from 8 for some that would be
+ *                    FUSED's).  R2 up to 80 (pb[0] = 4: 48); beyond that, and for any other mb[1], the fp32 kernel */
 typedef struct tdc_tuning {
     int32_t variant;
     int32_t tile_h, tile_w;

@@ -209,18 +209,4 @@ __device__ __forceinline__ tdc_f4 tdc_mfma_bf(tdc_bf8 a, tdc_bf8 b, tdc_f4 c)
 // The six products, smallest first: parts of A and of B.
 constexpr int TDC_BF3_A[6] = {2, 1, 0, 1, 0, 0}, TDC_BF3_B[6] = {0, 1, 2, 0, 1, 0};
 
-// acc[mb][pb] += A(mb) * B(pb) over one 32-wide step.  SWAP: B supplies the rows of D (pixels) and A its columns.
-template <int MB, int PB, bool SWAP = false>
-__device__ __forceinline__ void tdc_mma3(tdc_f4 (&acc)[MB][PB], const tdc_op3 (&a)[MB], const tdc_op3 (&b)[PB])
-{
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int pb = 0; pb < PB; ++pb)
-                acc[mb][pb] = SWAP ? tdc_mfma_bf(b[pb].p[TDC_BF3_B[i]], a[mb].p[TDC_BF3_A[i]], acc[mb][pb])
-                                   : tdc_mfma_bf(a[mb].p[TDC_BF3_A[i]], b[pb].p[TDC_BF3_B[i]], acc[mb][pb]);
-}
-
 #endif

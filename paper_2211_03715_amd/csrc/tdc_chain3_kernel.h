@@ -13,10 +13,12 @@
 // What bounds it.  The fp32 form was bound by the fp32 matrix rate plus the phases of its one resident workgroup, which do
 // not overlap: 32 -> 32 ranks, 128 channels at 28x28, batch 256: 97 us, of which 45 us are matrix cycles and 39 us compulsory
 // bytes.  Here the products take 3/8 of the cycles, and workgroups are four wavefronts on tiles of at most 128 pixels, so that
-// two to three share a compute unit and one's loads run under another's products: 77 us (65 us where x and y of consecutive
-// calls are the same buffers); 64 -> 32 ranks, 64 channels at 224x224: 35.7 -> 28.7 us.  What is left is memory, with loads
+// two to three share a compute unit and one's loads run under another's products: 77 us (62 us where x and y of consecutive
+// calls are the same buffers); 64 -> 32 ranks, 64 channels at 224x224: 35.7 -> 27.0 us.  What is left is memory, with loads
 // one step ahead.  The weight fragments come through the L1 at 54 bytes a cycle: PB pixel blocks share one.  PB = 4 halves that
-// traffic, but needs 184 to 255 registers instead of 122 to 170 and was 2 to 10 % slower on every layer timed.
+// traffic and needs 144 to 256 registers instead of 99 to 256 (three z2 blocks in NCHW spill 19 to 22).  The selector offers
+// PB = 2 alone; with the buffers of a call in cache an exhaustive search takes PB = 4 on larger tiles in three of sixteen cases
+// (128 channels at 28x28, ranks 32, batch 128: 36.8 -> 31.4 us), with new buffers per call it was 2 to 10 % slower.
 // With few pixels (24 per compute unit) a workgroup has its compute unit to itself and the chain of its steps is the time;
 // sharing cuts it: ranks 80, 256 channels at 14x14, batch 32: 34.6 us unshared, 20.7 shared (fp32 FUSED: 33.0).
 #ifndef TDC_CHAIN3_KERNEL_H
@@ -643,7 +645,8 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
 
 }  // namespace
 
-// (z2 blocks, pixel blocks of a unit) that have an instance: what fits 256 registers beside the weights in flight
+// (z2 blocks, pixel blocks of a unit) that have an instance: what fits 256 registers beside the weights in flight, or nearly
+// so (three z2 blocks with PB = 4 in NCHW)
 #define TDC_CHAIN3_UNITS(X) X(1, 4) X(2, 4) X(3, 4) X(1, 2) X(2, 2) X(3, 2) X(4, 2) X(5, 2)
 
 template <int LAY>

@@ -305,8 +305,9 @@ FusedChoice best_chain(const TdcDims &d, const TdcDeviceInfo &dev, const tdc_tun
 // (96 per fp32 product block: six MFMAs of 16 cycles): stage 1 in rounds of four units, then one group of two pixel blocks
 // per wavefront.  Sweeps of ten layers (tiles of 32 to 800 pixels, groups of two and four blocks) were won by tiles that give
 // every wavefront exactly one group of two -- 128 pixels at most -- or lay within 4 % of such a tile, so only those are
-// compared.  Two or three workgroups that share a compute unit overlap half of their chains.  Where the pixels are few, tiles
-// of two or one groups let two or four wavefronts share each (tdc_chain3_share).
+// compared.  (With the buffers of a call in cache larger tiles win four of sixteen throughput cases, by 15 to 21 %.)  Two or
+// three workgroups that share a compute unit overlap half of their chains.  Where the pixels are few, tiles of two or one
+// groups let two or four wavefronts share each (tdc_chain3_share).
 struct Chain3Choice {
     double us = 1e300;
     int th = 0, tw = 0, mb1 = 0, pb = 0;
@@ -789,10 +790,10 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
         return TDC_OK;
     }
 
-    // Where the output pixels fill the chip (16 per compute unit) CHAIN on the bf16 matrix cores is the fastest form timed:
-    // against fp32 CHAIN or FUSED 33.0 -> 20.7, 22.3 -> 17.1 (24 pixels, ranks 80 and 64), 49.9 -> 31 (24, stride 2), 14.4 ->
-    // 11.4 (24, ranks 40), 10.1 -> 9.0 (49), 46.8 -> 33.5 (98), 37.5 -> 27.5 (196), 103.3 -> 65 us (784); 56 layers drawn over
-    // the whole range are 1.3 times faster on average.  Not with ranks of a single block below 128 pixels (36 pixels: 7.6
+    // Where the output pixels fill the chip (16 per compute unit) CHAIN on the bf16 matrix cores is the fastest form: 621 drawn
+    // layers run 1.26 times as fast on average as with the fp32 kernel chosen before (NCHW 0.86 to 2.1, NHWC 0.92 to 2.5; 21 of
+    // them 3 to 14 % slower), e.g. 34.3 -> 28.5 us (98 pixels per compute unit, stride 2), 22.2 -> 19.3 (24 pixels), 97.2 -> 77.4
+    // (784).  The estimates are not compared: they are not on one scale.  Not with ranks of a single block below 128 pixels (36 pixels: 7.6
     // against 7.9, 101: 10.4 against 11.3 us): there are few products to save there.
     // Nor, for the same reason, with one block of R1 in NCHW rows that allow no 16-byte stores (172x172 stride 2, ranks 4 and
     // 19: 15.4 against 17.0; 72x89, ranks 9 and 48: 64 against 77), nor 1x1 layers of at most two blocks on few pixels (10x12,

@@ -264,7 +264,7 @@ __global__ __launch_bounds__(256 * KS, 3) void tdc_tile_kernel(TileArgs a)
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) wlane[mb] = mb0 + mb < a.NBm ? (unsigned)((mb0 + mb) * a.S) * 3072u + lane * 16u : TDC_OOB;
     const auto fetch_w = [&](int step_, tdc_bf8(&w)[MB][3]) {
-        const int step = min(step_, a.S - 1);      // past the end: fetched, never multiplied
+        const int step = min(step_, a.S - 1);      // past the end: never multiplied, or (second group, odd S) with zero activations
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
