@@ -45,10 +45,17 @@ __global__ void pack_core_kernel(TdcDims d, const float *__restrict__ core, floa
     out[e] = (d1 < d.R1 && m < d.R2) ? core[(((size_t)d1 * d.R2 + m) * d.K + r) * d.K + s] : 0.f;
 }
 
-// The largest magnitudes below 2^126 of RANGE_BLOCKS parts of a weight tensor, behind its packed parts.
+// The largest magnitudes below 2^126 of RANGE_BLOCKS parts of each of up to three weight tensors, behind their packed parts.
 constexpr int RANGE_BLOCKS = TDC_PACKED3_TAIL / 4;
-__global__ void pack3_range_kernel(const float *__restrict__ w, size_t n, float *__restrict__ largest)
+struct RangeArgs {
+    const float *w[3];
+    size_t n[3];
+    float *largest[3];
+};
+__global__ void pack3_range_kernel(RangeArgs a)
 {
+    const float *__restrict__ w = a.w[blockIdx.y];
+    const size_t n = a.n[blockIdx.y];
     float m = 0.f;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
         const float v = fabsf(w[i]);
@@ -61,7 +68,7 @@ __global__ void pack3_range_kernel(const float *__restrict__ w, size_t n, float 
         if ((int)threadIdx.x < s) part[threadIdx.x] = fmaxf(part[threadIdx.x], part[threadIdx.x + s]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) largest[blockIdx.x] = part[0];
+    if (threadIdx.x == 0) a.largest[blockIdx.y][blockIdx.x] = part[0];
 }
 
 // One thread per pair of components of the three-part layout: e = ((mb*S + step)*64 + lane)*4 + pair.  weight(kg, k, m) is
@@ -164,20 +171,21 @@ hipError_t tdc_launch_pack_core(const TdcDims &d, hipStream_t s, const float *co
     return hipGetLastError();
 }
 
-// where the ranges of a packed tensor are, and the launch that fills them from its `n` weights
-static float *pack3_range(hipStream_t s, const float *w, size_t n, void *packed, size_t bytes)
+static float *pack3_largest(void *packed, size_t bytes) { return reinterpret_cast<float *>(static_cast<char *>(packed) + bytes); }
+
+static void launch_pack3_core(const TdcDims &d, hipStream_t s, const float *core, void *core_p3, size_t bytes)
 {
-    float *largest = reinterpret_cast<float *>(static_cast<char *>(packed) + bytes);
-    hipLaunchKernelGGL(pack3_range_kernel, dim3(RANGE_BLOCKS), dim3(256), 0, s, w, n, largest);
-    return largest;
+    const int T = 256;
+    const size_t n = bytes / 12;
+    hipLaunchKernelGGL(pack3_core_kernel, dim3((unsigned)((n + T - 1) / T)), dim3(T), 0, s, d, core, (unsigned *)core_p3, pack3_largest(core_p3, bytes), n);
 }
 
 hipError_t tdc_launch_pack3_core(const TdcDims &d, hipStream_t s, const float *core, void *core_p3)
 {
-    const int T = 256;
-    const size_t bytes = tdc_packed3_bytes(d.NB2, d.K * d.K * d.NB1), n = bytes / 12;
-    const float *largest = pack3_range(s, core, (size_t)d.R1 * d.R2 * d.K * d.K, core_p3, bytes);
-    hipLaunchKernelGGL(pack3_core_kernel, dim3((unsigned)((n + T - 1) / T)), dim3(T), 0, s, d, core, (unsigned *)core_p3, largest, n);
+    const size_t bytes = tdc_packed3_bytes(d.NB2, d.K * d.K * d.NB1);
+    const RangeArgs r = {{core}, {(size_t)d.R1 * d.R2 * d.K * d.K}, {pack3_largest(core_p3, bytes)}};
+    hipLaunchKernelGGL(pack3_range_kernel, dim3(RANGE_BLOCKS), dim3(256), 0, s, r);
+    launch_pack3_core(d, s, core, core_p3, bytes);
     return hipGetLastError();
 }
 
@@ -185,12 +193,14 @@ hipError_t tdc_launch_pack3(const TdcDims &d, hipStream_t s, const float *U_in, 
                             void *uin_p3, void *core_p3, void *uout_p3)
 {
     const int T = 256;
-    const auto matrix = [&](int rows, int cols, const float *w, void *packed, size_t bytes) {
-        const size_t n = bytes / 12;
-        const float *largest = pack3_range(s, w, (size_t)rows * cols, packed, bytes);
-        hipLaunchKernelGGL(pack3_matrix_kernel, dim3((unsigned)((n + T - 1) / T)), dim3(T), 0, s, rows, cols, w, (unsigned *)packed, largest, n);
-    };
-    matrix(d.C, d.R1, U_in, uin_p3, tdc_packed3_bytes(d.NB1, d.KG1));
-    matrix(d.R2, d.N, U_out, uout_p3, tdc_packed3_bytes(d.NB3, d.NB2));
-    return tdc_launch_pack3_core(d, s, core, core_p3);
+    const size_t b1 = tdc_packed3_bytes(d.NB1, d.KG1), b2 = tdc_packed3_bytes(d.NB2, d.K * d.K * d.NB1), b3 = tdc_packed3_bytes(d.NB3, d.NB2);
+    const RangeArgs r = {{U_in, core, U_out},
+                         {(size_t)d.C * d.R1, (size_t)d.R1 * d.R2 * d.K * d.K, (size_t)d.R2 * d.N},
+                         {pack3_largest(uin_p3, b1), pack3_largest(core_p3, b2), pack3_largest(uout_p3, b3)}};
+    hipLaunchKernelGGL(pack3_range_kernel, dim3(RANGE_BLOCKS, 3), dim3(256), 0, s, r);
+    const size_t n1 = b1 / 12, n3 = b3 / 12;
+    hipLaunchKernelGGL(pack3_matrix_kernel, dim3((unsigned)((n1 + T - 1) / T)), dim3(T), 0, s, d.C, d.R1, U_in, (unsigned *)uin_p3, r.largest[0], n1);
+    hipLaunchKernelGGL(pack3_matrix_kernel, dim3((unsigned)((n3 + T - 1) / T)), dim3(T), 0, s, d.R2, d.N, U_out, (unsigned *)uout_p3, r.largest[2], n3);
+    launch_pack3_core(d, s, core, core_p3, b2);
+    return hipGetLastError();
 }
