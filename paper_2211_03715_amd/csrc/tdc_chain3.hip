@@ -1,17 +1,19 @@
-// CHAIN on the bf16 matrix cores, host side: which shapes it covers, its tile geometry, and the launch.  The kernel is in
+// CHAIN on the fp16 matrix cores, host side: which shapes it covers, its tile geometry, and the launch.  The kernel is in
 // tdc_chain3_kernel.h; its instances are compiled in tdc_chain3_nchw.hip, tdc_chain3_runs.hip and tdc_chain3_nhwc.hip.
+#include <cmath>
+
 #include "tdc_chain3_kernel.h"
 
-hipError_t tdc_launch_chain3_nchw(const TdcChain3Args &, int, int, int, dim3, size_t, hipStream_t, bool);
-hipError_t tdc_launch_chain3_runs(const TdcChain3Args &, int, int, int, dim3, size_t, hipStream_t, bool);
-hipError_t tdc_launch_chain3_nhwc(const TdcChain3Args &, int, int, int, dim3, size_t, hipStream_t, bool);
+hipError_t tdc_launch_chain3_nchw(const TdcChain3Args &, int, int, int, int, dim3, size_t, hipStream_t, bool);
+hipError_t tdc_launch_chain3_runs(const TdcChain3Args &, int, int, int, int, dim3, size_t, hipStream_t, bool);
+hipError_t tdc_launch_chain3_nhwc(const TdcChain3Args &, int, int, int, int, dim3, size_t, hipStream_t, bool);
 
 bool tdc_chain3_supported(const TdcDims &d, int mb1, int pb)
 {
     if (mb1 < 1 || mb1 > 3 || mb1 > d.NB1) return false;
     // every weight array lies behind one buffer descriptor
     const size_t lim = 1ull << 31;
-    if (tdc_packed3_bytes(d.NB1, d.KG1) >= lim || tdc_packed3_bytes(d.NB2, d.K * d.K * d.NB1) >= lim || tdc_packed3_bytes(d.NB3, d.NB2) >= lim) return false;
+    if (tdc_split_alloc_bytes(3, d.NB1, d.KG1) >= lim || tdc_split_alloc_bytes(3, d.NB2, d.K * d.K * d.NB1) >= lim || tdc_split_alloc_bytes(3, d.NB3, d.NB2) >= lim) return false;
 #define TDC_X(N_, P_) if (d.NB2 == N_ && pb == P_) return true;
     TDC_CHAIN3_UNITS(TDC_X)
 #undef TDC_X
@@ -35,16 +37,16 @@ TdcFusedGeom tdc_chain3_geometry(const TdcDims &d, int tile_h, int tile_w, int p
     g.pitch1 = 16 * (g.QB | 1);       // an odd number of 128-byte rows: lane groups 2i and 2i + 1 use different halves of the banks
     g.pitch2 = 0;
     g.weights_in_lds = g.weights_fit = false;
-    g.lds_bytes = (size_t)96 * d.NB1 * g.pitch1;
+    g.lds_bytes = sizeof(Chain3Shared) + (size_t)32 * tdc_chain3_parts(d) * d.NB1 * g.pitch1;
     if (pb > 0 && tdc_chain3_share((g.PBk + pb - 1) / pb)) g.lds_bytes += (size_t)TDC_CHAIN3_WAVES * d.NB2 * pb * 1024;
     return g;
 }
 
 hipError_t tdc_launch_chain3(const TdcDims &d, const tdc_tuning &t, const TdcFusedGeom &g, hipStream_t s, const float *x,
-                             const void *uin_p3, const void *core_p3, const void *uout_p3, float *y, const TdcEpi &epi, bool prepare_only)
+                             const void *uin_sp, const void *core_sp, const void *uout_sp, float *y, const TdcEpi &epi, bool prepare_only)
 {
     TdcChain3Args a;
-    a.x = x; a.uin3 = uin_p3; a.core3 = core_p3; a.uout3 = uout_p3; a.y = y; a.epi = epi;
+    a.x = x; a.uin = uin_sp; a.core = core_sp; a.uout = uout_sp; a.y = y; a.epi = epi;
     a.C = d.C; a.N = d.N; a.H = d.H; a.W = d.W; a.Ho = d.Ho; a.Wo = d.Wo; a.K = d.K; a.stride = d.stride; a.pad = d.pad;
     a.NB1 = d.NB1; a.NB3 = d.NB3; a.S1 = (d.KG1 + 1) / 2; a.KG2 = d.K * d.K * d.NB1; a.S2 = (a.KG2 + 1) / 2;
     a.TH = g.TH; a.TW = g.TW; a.QH = g.QH; a.QW = g.QW; a.Q = g.Q; a.P = g.TH * g.TW; a.QB = g.QB;
@@ -59,14 +61,17 @@ hipError_t tdc_launch_chain3(const TdcDims &d, const tdc_tuning &t, const TdcFus
     a.xcd_per = (int)((long)a.tiles * d.B / 8); a.xcd_rem = (int)((long)a.tiles * d.B % 8);
     // rows of whole quads and a 16-byte aligned y; otherwise the same values go out as four 4-byte stores
     a.vec = g.TW % 4 == 0 && d.Wo % 4 == 0 && ((uintptr_t)y & 15u) == 0;
-    a.uin_bytes = (unsigned)tdc_packed3_bytes(d.NB1, d.KG1);
-    a.core_bytes = (unsigned)tdc_packed3_bytes(d.NB2, a.KG2);
-    a.uout_bytes = (unsigned)tdc_packed3_bytes(d.NB3, d.NB2);
+    const int parts = tdc_chain3_parts(d);
+    a.uin_bytes = (unsigned)tdc_split_bytes(parts, d.NB1, d.KG1);
+    a.core_bytes = (unsigned)tdc_split_bytes(parts, d.NB2, a.KG2);
+    a.uout_bytes = (unsigned)tdc_split_bytes(parts, d.NB3, d.NB2);
+    // scaled weights of 2^12 and x of 2^8: sums of sqrt(C) 2^20
+    a.z1_exp = 12 + (int)std::lround(0.5 * std::log2((double)d.C));
     a.div_tiles_x = tdc_make_div((unsigned)g.tiles_x); a.div_tiles = tdc_make_div((unsigned)a.tiles);
     a.div_QW = tdc_make_div((unsigned)g.QW); a.div_TW = tdc_make_div((unsigned)g.TW);
     a.div_NB1 = tdc_make_div((unsigned)d.NB1); a.div_K = tdc_make_div((unsigned)d.K);
     a.div_RPR = tdc_make_div((unsigned)a.RPR); a.div_mg1 = tdc_make_div((unsigned)a.n_mg1);
     const dim3 grid((unsigned)a.tiles, (unsigned)d.B);
     const auto launch = lay == TDC_LAY_NHWC ? tdc_launch_chain3_nhwc : lay == TDC_LAY_NCHW_RUNS ? tdc_launch_chain3_runs : tdc_launch_chain3_nchw;
-    return launch(a, d.NB2, t.pb[0], t.mb[0], grid, g.lds_bytes, s, prepare_only);
+    return launch(a, d.NB2, t.pb[0], t.mb[0], parts, grid, g.lds_bytes, s, prepare_only);
 }

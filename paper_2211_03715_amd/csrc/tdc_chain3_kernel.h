@@ -26,7 +26,7 @@
 
 #include <type_traits>
 
-#include "tdc_bf3.h"
+#include "tdc_split.h"
 #include "tdc_internal.h"
 #include "tdc_stage1.h"
 
@@ -34,7 +34,7 @@ constexpr int TDC_CHAIN3_WAVES = 4;
 
 struct TdcChain3Args {
     const float *x;
-    const void *uin3, *core3, *uout3;
+    const void *uin, *core, *uout;             // in parts; each with its exponents behind *_bytes
     float *y;
     TdcEpi epi;
     int C, N, H, W, Ho, Wo, K, stride, pad;
@@ -45,14 +45,20 @@ struct TdcChain3Args {
     int RPR, n_pg1, n_mg1;                     // runs per tile row; pixel groups and channel groups of stage 1
     int tiles_x, tiles, xcd_per, xcd_rem;
     int vec;                                   // NCHW: y goes out in 16-byte quads of pixels
+    int z1_exp;                                // z1 is kept 2^-z1_exp times its scaled sums
     unsigned uin_bytes, core_bytes, uout_bytes;
     TdcDiv div_tiles_x, div_tiles, div_QW, div_TW, div_RPR, div_mg1, div_NB1, div_K;
 };
 
 namespace {
 
+// LDS: the largest magnitude each wavefront has loaded first and whether it wants the tile in fp32, then z1.
+struct Chain3Shared {
+    unsigned first[TDC_CHAIN3_WAVES], bad[TDC_CHAIN3_WAVES];
+};
+
 // Stage 1 for the workgroup.  RUNS: a lane owns runs of four consecutive pixels (see TdcStage1R), a unit is 16 runs.
-template <int LAY, int MB1>
+template <int LAY, int MB1, int NP>
 struct Chain3Stage1 {
     static constexpr bool RUNS = LAY == TDC_LAY_NCHW_RUNS, NHWC = LAY == TDC_LAY_NHWC;
     static constexpr int PB = RUNS ? 4 : 2;
@@ -62,8 +68,9 @@ struct Chain3Stage1 {
     int lane, g, l16, wave, h0, w0, wa, n_units;
     int fu, fs, fmg;                                   // fetch cursor: unit, step, channel group of the unit
     unsigned xoff[RUNS ? 1 : PB];
-    float largest = 0.f;                               // magnitude of this lane's largest z1 value, NaN if there is one
-    unsigned smallest = ~0u;                           // of its pixels' largest values the smallest (tdc_smallest)
+    float x_top[PB];                                   // largest magnitude of x at this lane's pixels so far
+    unsigned smallest = ~0u, smallest_x = ~0u;         // of the pixels' largest sums and of their largest x the smallest (tdc_smallest)
+    int x_exp = 0;                                     // x is multiplied by 2^x_exp
 
     __device__ __forceinline__ Chain3Stage1(const TdcChain3Args &args, int lane_, int wave_, int b, int h0_, int w0_) : a(args)
     {
@@ -71,7 +78,7 @@ struct Chain3Stage1 {
         wa = w0 > 0 ? (w0 & ~3) : 0;
         const int HW = a.H * a.W;
         xrs = tdc_make_rsrc(a.x + (size_t)b * a.C * HW, (unsigned)a.C * HW * 4u);
-        urs = tdc_make_rsrc(a.uin3, a.uin_bytes);
+        urs = tdc_make_rsrc(a.uin, a.uin_bytes + 64u * a.NB1);      // with the exponents
         n_units = a.n_pg1 * a.n_mg1;
         fu = wave;
         place();
@@ -102,7 +109,7 @@ struct Chain3Stage1 {
         }
     }
     // channels past C read 0: in NCHW they lie beyond the image's descriptor by themselves
-    __device__ __forceinline__ void fetch(tdc_f4 (&x)[NR], tdc_op3 (&w)[MB1])
+    __device__ __forceinline__ void fetch(tdc_f4 (&x)[NR], tdc_op<NP> (&w)[MB1])
     {
         const unsigned dead = fu < n_units ? 0u : TDC_OOB;
         const unsigned HW4 = (unsigned)(a.H * a.W) * 4u;
@@ -128,9 +135,9 @@ struct Chain3Stage1 {
 #pragma unroll
         for (int mb = 0; mb < MB1; ++mb) {
             const int blk = fmg * MB1 + mb;
-            const unsigned o = ((unsigned)(blk * a.S1 + fs) * 3072u + lane * 16u) | dead | (blk < a.NB1 ? 0u : TDC_OOB);
+            const unsigned o = ((unsigned)(blk * a.S1 + fs) * (1024u * NP) + lane * 16u) | dead | (blk < a.NB1 ? 0u : TDC_OOB);
 #pragma unroll
-            for (int q = 0; q < 3; ++q) w[mb].p[q] = __builtin_bit_cast(tdc_bf8, tdc_buf_load4(urs, o + q * 1024u));
+            for (int q = 0; q < NP; ++q) w[mb].p[q] = __builtin_bit_cast(tdc_h8, tdc_buf_load4(urs, o + q * 1024u));
         }
         if (++fs == a.S1) {
             fu += TDC_CHAIN3_WAVES;
@@ -142,78 +149,93 @@ struct Chain3Stage1 {
     {
         if (!RUNS) return;
         const int left = max(-w0, 0), right = max(w0 + a.QW - a.W, 0);
-        const int per_row = left + right, total = per_row * a.QH * 12 * a.NB1;
+        const int per_row = left + right, total = per_row * a.QH * 4 * NP * a.NB1;
         for (int e = 64 * wave + lane; e < total; e += 64 * TDC_CHAIN3_WAVES) {
             const int c = e % per_row, r = (e / per_row) % a.QH, pl = e / (per_row * a.QH);
             const int qw = c < left ? c : a.QW - right + (c - left);
             z1s[pl * a.pitch1 + r * a.QW + qw] = (tdc_u2){0u, 0u};
         }
     }
-    __device__ __forceinline__ void multiply(tdc_f4 (&acc)[MB1][PB], const tdc_f4 (&x)[NR], const tdc_op3 (&w)[MB1]) const
+    __device__ __forceinline__ void multiply(tdc_f4 (&acc)[MB1][PB][NP], const tdc_f4 (&x)[NR], const tdc_op<NP> (&w)[MB1])
     {
+        const TdcScale s(x_exp);
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) {
-            tdc_op3 b;
-            if (RUNS)
-                b = tdc_split_op((tdc_f4){x[0][pb], x[1][pb], x[2][pb], x[3][pb]},
-                                 (tdc_f4){x[4 % NR][pb], x[5 % NR][pb], x[6 % NR][pb], x[7 % NR][pb]});
-            else
-                b = tdc_split_op(x[(2 * pb) % NR], x[(2 * pb + 1) % NR]);
+            const tdc_f4 lo = RUNS ? (tdc_f4){x[0][pb], x[1][pb], x[2][pb], x[3][pb]} : x[(2 * pb) % NR];
+            const tdc_f4 hi = RUNS ? (tdc_f4){x[4 % NR][pb], x[5 % NR][pb], x[6 % NR][pb], x[7 % NR][pb]} : x[(2 * pb + 1) % NR];
+            x_top[pb] = tdc_largest(tdc_largest(x_top[pb], lo), hi);
+            const tdc_op<NP> b = tdc_split_op<NP>(lo, hi, s);
 #pragma unroll
-            for (int i = 0; i < 6; ++i)
+            for (int i = 0; i < TdcProducts<NP>::N; ++i)
 #pragma unroll
-                for (int mb = 0; mb < MB1; ++mb) acc[mb][pb] = tdc_mfma_bf(w[mb].p[TDC_BF3_A[i]], b.p[TDC_BF3_B[i]], acc[mb][pb]);
+                for (int mb = 0; mb < MB1; ++mb) {
+                    tdc_f4 &c = acc[mb][pb][TdcProducts<NP>::level[i]];
+                    c = tdc_mfma_part<NP>(i, w[mb].p, b.p, c);
+                }
         }
     }
-    // RAW: for sums some of which have no three parts
-    template <bool RAW>
-    __device__ __forceinline__ void store(tdc_u2 *__restrict__ z1s, int unit, const tdc_f4 (&acc)[MB1][PB]) const
+    // the sums of a unit, from their levels, as parts of z1
+    __device__ __forceinline__ void store(tdc_u2 *__restrict__ z1s, int unit, const tdc_f4 (&acc)[MB1][PB][NP])
     {
         const int pg = tdc_div(unit, a.div_mg1), mg = unit - pg * a.n_mg1;
         const int rho = 16 * pg + l16, qh = RUNS ? tdc_div(rho, a.div_RPR) : 0;
         const int qw0 = RUNS ? wa + 4 * (rho - qh * a.RPR) - w0 : 0;
+        tdc_u4 e[MB1];                                 // exponents of the lane's channels
+#pragma unroll
+        for (int mb = 0; mb < MB1; ++mb)
+            e[mb] = __builtin_bit_cast(tdc_u4, tdc_buf_load4(urs, a.uin_bytes + (16u * (mg * MB1 + mb) + 4u * g) * 4u));
+        const TdcScale s(0);
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) {
             const bool ok = RUNS ? qh < a.QH && qw0 + pb >= 0 && qw0 + pb < a.QW : pg * PB + pb < a.QB;
             const int pix = RUNS ? qh * a.QW + qw0 + pb : 16 * (pg * PB + pb) + l16;
+            float m = 0.f;
 #pragma unroll
             for (int mb = 0; mb < MB1; ++mb) {
                 const int blk = mg * MB1 + mb;
-                tdc_u2 p[3];
-                if (RAW) tdc_split4_raw(acc[mb][pb], 0x1p-110f, p[0], p[1], p[2]);
-                else tdc_split4(acc[mb][pb], p[0], p[1], p[2]);
+                tdc_f4 v = tdc_levels<NP>(acc[mb][pb]);
+                m = tdc_largest(m, v);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = ldexpf(v[i], (int)e[mb][i] - a.z1_exp);
+                tdc_u2 p[NP];
+                tdc_split4<NP>(v, s, p);
                 if (ok && blk < a.NB1) {
 #pragma unroll
-                    for (int q = 0; q < 3; ++q) z1s[((q * a.NB1 + blk) * 4 + g) * a.pitch1 + pix] = p[q];
+                    for (int q = 0; q < NP; ++q) z1s[((q * a.NB1 + blk) * 4 + g) * a.pitch1 + pix] = p[q];
                 }
             }
+            smallest = tdc_smallest(smallest, tdc_pixel_max(m));
+            smallest_x = tdc_smallest(smallest_x, tdc_pixel_max(x_top[pb]));
         }
     }
-    __device__ __forceinline__ void run(tdc_u2 *__restrict__ z1s)
+    __device__ __forceinline__ void run(Chain3Shared &sh, tdc_u2 *__restrict__ z1s)
     {
-        tdc_f4 x0[NR], x1[NR], acc[MB1][PB];
-        tdc_op3 wa0[MB1], wa1[MB1];
+        tdc_f4 x0[NR], x1[NR], acc[MB1][PB][NP];
+        tdc_op<NP> wa0[MB1], wa1[MB1];
         fetch(x0, wa0);
         zero_outside(z1s);
+        float m = 0.f;
+#pragma unroll
+        for (int i = 0; i < NR; ++i) m = tdc_largest(m, x0[i]);
+        sh.first[wave] = tdc_wave_max(m);
+        __syncthreads();
+        const tdc_u4 first = *reinterpret_cast<const tdc_u4 *>(sh.first);
+        x_exp = tdc_scale_of((unsigned)__builtin_amdgcn_readfirstlane((int)max(max(first[0], first[1]), max(first[2], first[3]))), TDC_X_TARGET, TDC_X_OTHER);
         const int total = wave < n_units ? (n_units - wave + TDC_CHAIN3_WAVES - 1) / TDC_CHAIN3_WAVES * a.S1 : 0;
         int unit = wave, step = 0;
         const auto clear = [&]() {
 #pragma unroll
+            for (int pb = 0; pb < PB; ++pb) x_top[pb] = 0.f;
+#pragma unroll
             for (int mb = 0; mb < MB1; ++mb)
 #pragma unroll
-                for (int pb = 0; pb < PB; ++pb) acc[mb][pb] = tdc_f4_zero();
+                for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+                    for (int q = 0; q < NP; ++q) acc[mb][pb][q] = tdc_f4_zero();
         };
         const auto done = [&]() {
             if (++step < a.S1) return;
-#pragma unroll
-            for (int pb = 0; pb < PB; ++pb) {
-                float m = 0.f;
-#pragma unroll
-                for (int mb = 0; mb < MB1; ++mb) m = tdc_largest(m, acc[mb][pb]);
-                largest = __builtin_elementwise_maximum(largest, m);
-                smallest = tdc_smallest(smallest, m);
-            }
-            store<false>(z1s, unit, acc);
+            store(z1s, unit, acc);
             unit += TDC_CHAIN3_WAVES;
             step = 0;
             clear();
@@ -228,60 +250,6 @@ struct Chain3Stage1 {
                 multiply(acc, x1, wa1);
                 done();
             }
-        }
-    }
-    // The wavefront's units once more in fp32, one load at a time (see tdc_bf3.h); those whose NaNs are x's or the weights' stay.
-    __device__ __forceinline__ void redo(tdc_u2 *__restrict__ z1s, bool small)
-    {
-        tdc_f4 x[NR];
-        tdc_op3 w[MB1];
-        const auto join = [&](int mb, int h) {
-            tdc_u2 p[3];
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                const tdc_u4 u = __builtin_bit_cast(tdc_u4, w[mb].p[q]);
-                p[q] = h ? (tdc_u2){u[2], u[3]} : (tdc_u2){u[0], u[1]};
-            }
-            return tdc_join4(p);
-        };
-        for (int unit = wave; unit < n_units; unit += TDC_CHAIN3_WAVES) {
-            TdcFactors seen;
-            fu = unit;
-            place();
-            for (int i = 0; i < a.S1; ++i) {
-                fetch(x, w);
-#pragma unroll
-                for (int j = 0; j < NR; ++j) seen.see(x[j]);
-#pragma unroll
-                for (int mb = 0; mb < MB1; ++mb) {
-                    const tdc_u4 u = __builtin_bit_cast(tdc_u4, w[mb].p[0]);
-                    seen.see((tdc_u2){u[0], u[1]});
-                    seen.see((tdc_u2){u[2], u[3]});
-                }
-            }
-            if (!small && seen.explain_nan()) continue;
-            tdc_f4 acc[MB1][PB];
-#pragma unroll
-            for (int mb = 0; mb < MB1; ++mb)
-#pragma unroll
-                for (int pb = 0; pb < PB; ++pb) acc[mb][pb] = tdc_f4_zero();
-            fu = unit;
-            place();
-            for (int i = 0; i < a.S1; ++i) {
-                fetch(x, w);
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-#pragma unroll
-                    for (int mb = 0; mb < MB1; ++mb) {
-                        const tdc_f4 wh = join(mb, h);
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-#pragma unroll
-                            for (int pb = 0; pb < PB; ++pb)
-                                acc[mb][pb] = tdc_mfma(wh[j], RUNS ? x[(4 * h + j) % NR][pb] : x[(2 * pb + h) % NR][j], acc[mb][pb]);
-                    }
-            }
-            store<true>(z1s, unit, acc);
         }
     }
 };
@@ -388,108 +356,125 @@ struct Chain3Out {
     }
 };
 
-// Stages 2 and 3 of a group once more in fp32, one load at a time (see tdc_bf3.h), unless its NaNs are z1's or the weights'.
-template <int NB2, int PB, int LAY>
-__device__ __forceinline__ void chain3_redo(const TdcChain3Args &a, const tdc_u2 *__restrict__ z1s, int group, int lane, int slice)
+// The tile once more in fp32, one load at a time, z1 in fp32 where its parts were (see tdc_split.h).
+template <int NB2, int PB, int LAY, int NP>
+__device__ __forceinline__ void chain3_tile_fp32(const TdcChain3Args &a, tdc_u2 *__restrict__ z1s, int lane, int wave)
 {
     constexpr bool NHWC = LAY == TDC_LAY_NHWC;
-    constexpr int S3 = (NB2 + 1) / 2;
-    const tdc_rsrc crs = tdc_make_rsrc(a.core3, a.core_bytes), ors = tdc_make_rsrc(a.uout3, a.uout_bytes);
-    int qbase[PB];
-    chain3_z1_base<PB>(a, group, lane, qbase);
-    const auto cell_of = [&](int kg) {
-        const int tap = tdc_div(kg, a.div_NB1), r = tdc_div(tap, a.div_K);
-        return (kg - tap * a.NB1) * 4 * a.pitch1 + r * a.QW + tap - r * a.K;
-    };
-    const auto z1_at = [&](int cell, int pb) {
-        tdc_u2 u[3];
+    static_assert(NP >= 2, "16 bytes of z1 per lane, block and pixel");
+    tdc_f4 *__restrict__ z1f = reinterpret_cast<tdc_f4 *>(z1s);
+    const int g = lane >> 4, l16 = lane & 15;
+    const Chain3Tile at(a);
+    const int HW = a.H * a.W, KG1 = (a.C + 15) / 16;
+    const tdc_rsrc urs = tdc_make_rsrc(tdc_raw_base(a.uin, a.uin_bytes, a.NB1), 1024u * a.NB1 * KG1);
+    const tdc_rsrc crs = tdc_make_rsrc(tdc_raw_base(a.core, a.core_bytes, NB2), 1024u * NB2 * a.KG2);
+    const tdc_rsrc ors = tdc_make_rsrc(tdc_raw_base(a.uout, a.uout_bytes, a.NB3), 1024u * a.NB3 * NB2);
+    const tdc_rsrc xrs = tdc_make_rsrc(a.x + (size_t)at.b * a.C * HW, (unsigned)a.C * HW * 4u);
+#pragma unroll 1
+    for (int qb = wave; qb < a.QB; qb += TDC_CHAIN3_WAVES) {
+        const int q = 16 * qb + l16, qh = tdc_div(q, a.div_QW);
+        const int h = at.i0 * a.stride - a.pad + qh, w = at.j0 * a.stride - a.pad + q - qh * a.QW;
+        const bool in = q < a.Q && (unsigned)h < (unsigned)a.H && (unsigned)w < (unsigned)a.W;
+        const int pix = in ? h * a.W + w : 0;
+#pragma unroll 1
+        for (int blk = 0; blk < a.NB1; ++blk) {
+            tdc_f4 acc = tdc_f4_zero();
+#pragma unroll 1
+            for (int kg = 0; kg < KG1; ++kg) {
+                const int c = 16 * kg + 4 * g;
+                tdc_f4 x;
+                if (NHWC) {
+                    x = tdc_buf_load4(xrs, in && c < a.C ? (unsigned)(pix * a.C + c) * 4u : TDC_OOB);
+                } else {
 #pragma unroll
-        for (int q = 0; q < 3; ++q) u[q] = z1s[q * a.NB1 * 4 * a.pitch1 + cell + qbase[pb]];
-        return tdc_join4(u);
-    };
-    TdcFactors seen;
-    for (int kg = 0; kg < a.KG2; ++kg) {
-        const int cell = cell_of(kg);
+                    for (int j = 0; j < 4; ++j) x[j] = tdc_buf_load(xrs, in && c + j < a.C ? (unsigned)((c + j) * HW + pix) * 4u : TDC_OOB);
+                }
+                const tdc_f4 u = tdc_raw_weights(urs, blk, KG1, kg, lane);
 #pragma unroll
-        for (int pb = 0; pb < PB; ++pb) seen.see(z1s[cell + qbase[pb]]);
-#pragma unroll
-        for (int mb = 0; mb < NB2; ++mb) seen.see(tdc_first_parts(crs, mb, a.S2, kg, lane));
-    }
-    for (int nb = 0; nb < a.NB3; ++nb)
-#pragma unroll
-        for (int kg = 0; kg < NB2; ++kg) seen.see(tdc_first_parts(ors, nb, S3, kg, lane));
-    if (seen.explain_nan() && !tdc_any_lane(seen.low)) return;     // and z2 cannot be small
-
-    tdc_f4 z2[NB2][PB];
-#pragma unroll
-    for (int mb = 0; mb < NB2; ++mb)
-#pragma unroll
-        for (int pb = 0; pb < PB; ++pb) z2[mb][pb] = tdc_f4_zero();
-    for (int kg = 0; kg < a.KG2; ++kg) {
-        const int cell = cell_of(kg);
-        tdc_f4 z[PB];
-#pragma unroll
-        for (int pb = 0; pb < PB; ++pb) z[pb] = z1_at(cell, pb);
-#pragma unroll
-        for (int mb = 0; mb < NB2; ++mb) {
-            const tdc_f4 w = tdc_join_weights(crs, mb, a.S2, kg, lane);
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int pb = 0; pb < PB; ++pb) z2[mb][pb] = tdc_mfma(w[j], z[pb][j], z2[mb][pb]);
+                for (int j = 0; j < 4; ++j) acc = tdc_mfma(u[j], x[j], acc);
+            }
+            z1f[(blk * 4 + g) * a.pitch1 + q] = in ? acc : tdc_f4_zero();
         }
     }
     __threadfence();         // the outputs stored before are in place, these follow them
-    const Chain3Out<PB, NHWC> out(a, Chain3Tile(a), group, lane);
-    for (int nb = slice; nb < a.NB3; nb += 1 << a.lg_ks) {
-        tdc_f4 acc3[PB];
+    __syncthreads();
+    const int slice = wave & ((1 << a.lg_ks) - 1);
+#pragma unroll 1
+    for (int pg = wave >> a.lg_ks; pg < a.n_pg2; pg += TDC_CHAIN3_WAVES) {
+        int qbase[PB];
+        chain3_z1_base<PB>(a, pg, lane, qbase);
+        tdc_f4 z2[NB2][PB];
 #pragma unroll
-        for (int pb = 0; pb < PB; ++pb) acc3[pb] = tdc_f4_zero();
+        for (int mb = 0; mb < NB2; ++mb)
 #pragma unroll
-        for (int kg = 0; kg < NB2; ++kg) {
-            const tdc_f4 w = tdc_join_weights(ors, nb, S3, kg, lane);
+            for (int pb = 0; pb < PB; ++pb) z2[mb][pb] = tdc_f4_zero();
+#pragma unroll 1
+        for (int kg = 0; kg < a.KG2; ++kg) {
+            const int tap = tdc_div(kg, a.div_NB1), r = tdc_div(tap, a.div_K), dg = kg - tap * a.NB1;
+            const int cell = dg * 4 * a.pitch1 + r * a.QW + tap - r * a.K;
+            tdc_f4 z[PB];
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int pb = 0; pb < PB; ++pb) z[pb] = z1f[cell + qbase[pb]];
 #pragma unroll
-                for (int pb = 0; pb < PB; ++pb)
-                    acc3[pb] = NHWC ? tdc_mfma(w[j], z2[kg][pb][j], acc3[pb]) : tdc_mfma(z2[kg][pb][j], w[j], acc3[pb]);
+            for (int mb = 0; mb < NB2; ++mb) {
+                const tdc_f4 w = tdc_raw_weights(crs, mb, a.KG2, kg, lane);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int pb = 0; pb < PB; ++pb) z2[mb][pb] = tdc_mfma(w[j], z[pb][j], z2[mb][pb]);
+            }
         }
-        out.template put<true>(nb, acc3);
+        const Chain3Out<PB, NHWC> out(a, at, pg, lane);
+#pragma unroll 1
+        for (int nb = slice; nb < a.NB3; nb += 1 << a.lg_ks) {
+            tdc_f4 acc3[PB];
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb) acc3[pb] = tdc_f4_zero();
+#pragma unroll
+            for (int kg = 0; kg < NB2; ++kg) {
+                const tdc_f4 w = tdc_raw_weights(ors, nb, NB2, kg, lane);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int pb = 0; pb < PB; ++pb)
+                        acc3[pb] = NHWC ? tdc_mfma(w[j], z2[kg][pb][j], acc3[pb]) : tdc_mfma(z2[kg][pb][j], w[j], acc3[pb]);
+            }
+            out.template put<true>(nb, acc3);
+        }
     }
 }
 
 // Wavefronts per SIMD an instance has registers for; the rarely run code must not cost one.
-constexpr int chain3_wavefronts(int nb2, int pb, int lay, int mb1)
+constexpr int chain3_wavefronts(int nb2, int pb, int lay, int mb1, int np)
 {
+    if (np == 3 && (pb > 2 || nb2 > 3)) return 1;
     if (pb > 2) return 2;
-    if (nb2 <= 2) return lay == TDC_LAY_NCHW_RUNS ? 5 - mb1 : mb1 <= 2 ? 4 : 3;
-    return nb2 == 3 && lay == TDC_LAY_NHWC ? 3 : 2;
+    if (nb2 <= 2) return np == 3 ? 2 : lay == TDC_LAY_NCHW_RUNS ? (mb1 == 1 ? 3 : 2) : mb1 <= 2 ? 4 : 3;
+    return nb2 == 3 && lay == TDC_LAY_NHWC && np == 2 ? 3 : 2;
 }
 
-template <int NB2, int PB, int LAY, int MB1>
-__global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, LAY, MB1)) void tdc_chain3_kernel(TdcChain3Args a)
+template <int NB2, int PB, int LAY, int MB1, int NP>
+__global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, LAY, MB1, NP)) void tdc_chain3_kernel(TdcChain3Args a)
 {
-    constexpr bool NHWC = LAY == TDC_LAY_NHWC;
-    extern __shared__ tdc_u2 z1s[];                              // [3 parts][NB1][4][pitch1], then the partial sums of ks > 1
+    constexpr bool NHWC = LAY == TDC_LAY_NHWC, SWAP = !NHWC;
+    extern __shared__ tdc_u4 chain3_lds[];                       // Chain3Shared, z1 [NP parts][NB1][4][pitch1], the partial sums of ks > 1
+    Chain3Shared &sh = *reinterpret_cast<Chain3Shared *>(chain3_lds);
+    tdc_u2 *__restrict__ z1s = reinterpret_cast<tdc_u2 *>(chain3_lds + sizeof(Chain3Shared) / 16);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const auto stage1 = [&](const TdcChain3Args &args) {
-        const Chain3Tile t(args);
-        return Chain3Stage1<LAY, MB1>(args, lane, wave, t.b, t.i0 * args.stride - args.pad, t.j0 * args.stride - args.pad);
-    };
-    {
-        Chain3Stage1<LAY, MB1> s1 = stage1(a);
-        s1.run(z1s);
-        // a value without three parts among x, the weights or z1 itself, or a pixel of nothing but small ones
-        if (__builtin_expect(tdc_any_lane(!(s1.largest < TDC_BIG) || tdc_is_small(s1.smallest)), 0))
-            stage1(tdc_args_again<TdcChain3Args>()).redo(z1s, tdc_any_lane(tdc_is_small(s1.smallest)));
-    }
+    bool bad;                                                    // a pixel of too small factors, or an output that is no number
+    int x_exp;
     const Chain3Tile at(a);
+    {
+        Chain3Stage1<LAY, MB1, NP> s1(a, lane, wave, at.b, at.i0 * a.stride - a.pad, at.j0 * a.stride - a.pad);
+        s1.run(sh, z1s);
+        x_exp = s1.x_exp;
+        bad = tdc_is_small(s1.smallest, tdc_exp2i(a.z1_exp + TDC_LOWEST)) || tdc_is_small(s1.smallest_x, tdc_exp2i(max(TDC_LOWEST - x_exp, -126)));
+    }
     __syncthreads();
 
     const int plane = a.NB1 * 4 * a.pitch1;                      // cells of one part
-    const tdc_rsrc crs = tdc_make_rsrc(a.core3, a.core_bytes);
-    const tdc_rsrc ors = tdc_make_rsrc(a.uout3, a.uout_bytes);
+    const tdc_rsrc crs = tdc_make_rsrc(a.core, a.core_bytes + 64u * NB2), ors = tdc_make_rsrc(a.uout, a.uout_bytes + 64u * a.NB3);   // with the exponents
     // with fewer groups than wavefronts 2 or 4 of them share one: each takes a slice of stage 2's contraction, the sums meet in
     // LDS, and each takes every ks-th output block of stage 3 (the loop then runs once for every wavefront)
     const int ks = 1 << a.lg_ks, slice = wave & (ks - 1);
@@ -497,19 +482,22 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
         // ---- stage 2: z2 channels 16*mb + 4*g + {0..3} of pixel l16 of block pb
         int qbase[PB];
         chain3_z1_base<PB>(a, pg, lane, qbase);
-        tdc_f4 acc2[NB2][PB];
-#pragma unroll
-        for (int mb = 0; mb < NB2; ++mb)
-#pragma unroll
-            for (int pb = 0; pb < PB; ++pb) acc2[mb][pb] = tdc_f4_zero();
+        tdc_f4 z2[NB2][PB];
         {
+            tdc_f4 acc2[NB2][PB][NP];
+#pragma unroll
+            for (int mb = 0; mb < NB2; ++mb)
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+                    for (int q = 0; q < NP; ++q) acc2[mb][pb][q] = tdc_f4_zero();
             // a fetch past the last step stays inside the descriptor or reads 0, and is never multiplied
-            const auto fetch_w = [&](int step, tdc_op3(&w)[NB2]) {
+            const auto fetch_w = [&](int step, tdc_op<NP>(&w)[NB2]) {
 #pragma unroll
                 for (int mb = 0; mb < NB2; ++mb)
 #pragma unroll
-                    for (int q = 0; q < 3; ++q)
-                        w[mb].p[q] = __builtin_bit_cast(tdc_bf8, tdc_buf_load4(crs, (unsigned)(mb * a.S2 + step) * 3072u + q * 1024u + lane * 16u));
+                    for (int q = 0; q < NP; ++q)
+                        w[mb].p[q] = __builtin_bit_cast(tdc_h8, tdc_buf_load4(crs, ((unsigned)(mb * a.S2 + step) * NP + q) * 1024u + lane * 16u));
             };
             const int st0 = slice * a.S2 >> a.lg_ks, st1 = (slice + 1) * a.S2 >> a.lg_ks;
             // next k-group: tap offset toff = r*QW + s, channel block dg
@@ -527,32 +515,34 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
                 ++kg;
                 return cell;
             };
-            const auto step2 = [&](const tdc_op3(&w)[NB2]) {
+            const auto step2 = [&](const tdc_op<NP>(&w)[NB2]) {
                 const int lo = next_cell();
                 const bool whole = kg < a.KG2;                   // else the last half step, whose weights are zero: any finite cell does
                 const int nx = next_cell(), hi = whole ? nx : lo;
                 const auto read = [&](int pb) {
-                    tdc_op3 o;
+                    tdc_op<NP> o;
 #pragma unroll
-                    for (int q = 0; q < 3; ++q) {
+                    for (int q = 0; q < NP; ++q) {
                         const tdc_u2 u = z1s[q * plane + lo + qbase[pb]], v = z1s[q * plane + hi + qbase[pb]];
-                        o.p[q] = __builtin_bit_cast(tdc_bf8, (tdc_u4){u[0], u[1], v[0], v[1]});
+                        o.p[q] = __builtin_bit_cast(tdc_h8, (tdc_u4){u[0], u[1], v[0], v[1]});
                     }
                     return o;
                 };
-                tdc_op3 bb[2];
+                tdc_op<NP> bb[2];
                 bb[0] = read(0);
 #pragma unroll
                 for (int pb = 0; pb < PB; ++pb) {
                     if (pb + 1 < PB) bb[(pb + 1) & 1] = read(pb + 1);
 #pragma unroll
-                    for (int i = 0; i < 6; ++i)
+                    for (int i = 0; i < TdcProducts<NP>::N; ++i)
 #pragma unroll
-                        for (int mb = 0; mb < NB2; ++mb)
-                            acc2[mb][pb] = tdc_mfma_bf(w[mb].p[TDC_BF3_A[i]], bb[pb & 1].p[TDC_BF3_B[i]], acc2[mb][pb]);
+                        for (int mb = 0; mb < NB2; ++mb) {
+                            tdc_f4 &c = acc2[mb][pb][TdcProducts<NP>::level[i]];
+                            c = tdc_mfma_part<NP>(i, w[mb].p, bb[pb & 1].p, c);
+                        }
                 }
             };
-            tdc_op3 wv0[NB2], wv1[NB2];
+            tdc_op<NP> wv0[NB2], wv1[NB2];
             fetch_w(st0, wv0);
             for (int st = st0; st < st1; st += 2) {
                 fetch_w(st + 1, wv1);
@@ -560,13 +550,24 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
                 fetch_w(st + 2, wv0);
                 if (st + 1 < st1) step2(wv1);
             }
+            // to a common scale
+#pragma unroll
+            for (int mb = 0; mb < NB2; ++mb) {
+                const tdc_u4 e = __builtin_bit_cast(tdc_u4, tdc_buf_load4(crs, a.core_bytes + (16u * mb + 4u * (lane >> 4)) * 4u));
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb) {
+                    z2[mb][pb] = tdc_levels<NP>(acc2[mb][pb]);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) z2[mb][pb][i] = ldexpf(z2[mb][pb][i], (int)e[i]);
+                }
+            }
         }
         if (ks > 1) {      // partial sums, added in the order of the slices
-            tdc_f4 *__restrict__ red = reinterpret_cast<tdc_f4 *>(z1s + 3 * plane);
+            tdc_f4 *__restrict__ red = reinterpret_cast<tdc_f4 *>(z1s + NP * plane);
 #pragma unroll
             for (int mb = 0; mb < NB2; ++mb)
 #pragma unroll
-                for (int pb = 0; pb < PB; ++pb) red[((wave * NB2 + mb) * PB + pb) * 64 + lane] = acc2[mb][pb];
+                for (int pb = 0; pb < PB; ++pb) red[((wave * NB2 + mb) * PB + pb) * 64 + lane] = z2[mb][pb];
             __syncthreads();
             const int first = wave - slice;
 #pragma unroll
@@ -575,54 +576,80 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
                 for (int pb = 0; pb < PB; ++pb) {
                     tdc_f4 v = red[((first * NB2 + mb) * PB + pb) * 64 + lane];
                     for (int j = 1; j < ks; ++j) v += red[(((first + j) * NB2 + mb) * PB + pb) * 64 + lane];
-                    acc2[mb][pb] = v;
+                    z2[mb][pb] = v;
                 }
         }
         // ---- stage 3, operands swapped in NCHW: D[pixel 4*g + i][channel l16]; NHWC: D[channel 4*g + i][pixel l16]
         constexpr int S3 = (NB2 + 1) / 2;
-        const auto fetch = [&](int nb, tdc_op3(&u)[S3]) {
+        struct Weights {
+            tdc_op<NP> w[S3];
+            int e[NHWC ? 4 : 1];                                 // exponents of the lane's output channels
+        };
+        const auto fetch = [&](int nb, Weights &u) {
 #pragma unroll
             for (int st = 0; st < S3; ++st)
 #pragma unroll
-                for (int q = 0; q < 3; ++q)
-                    u[st].p[q] = __builtin_bit_cast(tdc_bf8, tdc_buf_load4(ors, (unsigned)(nb * S3 + st) * 3072u + q * 1024u + lane * 16u));
+                for (int q = 0; q < NP; ++q)
+                    u.w[st].p[q] = __builtin_bit_cast(tdc_h8, tdc_buf_load4(ors, ((unsigned)(nb * S3 + st) * NP + q) * 1024u + lane * 16u));
+            if constexpr (NHWC) {
+                const tdc_u4 e = __builtin_bit_cast(tdc_u4, tdc_buf_load4(ors, a.uout_bytes + (16u * nb + 4u * (lane >> 4)) * 4u));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) u.e[i] = (int)e[i];
+            } else {
+                u.e[0] = __builtin_amdgcn_raw_buffer_load_b32(ors, (int)(a.uout_bytes + (16u * nb + (lane & 15)) * 4u), 0, 0);
+            }
         };
-        tdc_op3 u0[S3], u1[S3];
+        Weights u0, u1;
         fetch(slice, u0);                                        // under the splitting of z2
-        float largest = 0.f;                                     // magnitude of the largest of z2 and y, NaN if there is one
+        float top = 0.f;                                         // largest magnitude of z2; a NaN above all
         unsigned smallest = ~0u;                                 // of the pixels' largest z2 values the smallest
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) {
             float m = 0.f;
 #pragma unroll
-            for (int mb = 0; mb < NB2; ++mb) m = tdc_largest(m, acc2[mb][pb]);
-            largest = __builtin_elementwise_maximum(largest, m);
+            for (int mb = 0; mb < NB2; ++mb) m = tdc_largest(m, z2[mb][pb]);
+            m = tdc_pixel_max(m);
+            top = __builtin_elementwise_maximum(top, m);
             smallest = tdc_smallest(smallest, m);
         }
-        largest = tdc_is_small(smallest) ? INFINITY : largest;
-        asm("" : "+v"(largest));                                 // now: not behind the outputs, with all of acc2 kept until then
-        tdc_op3 zb[S3][PB];
-#pragma unroll
-        for (int st = 0; st < S3; ++st)
-#pragma unroll
-            for (int pb = 0; pb < PB; ++pb) zb[st][pb] = tdc_split_op(acc2[2 * st][pb], 2 * st + 1 < NB2 ? acc2[(2 * st + 1) % NB2][pb] : tdc_f4_zero());
-        const Chain3Out<PB, NHWC> out(a, at, pg, lane);
-        // two instances of the loop, as in tdc_chain_kernel.h: without epilogue loads nothing ever waits for the stores
-        const auto emit = [&](auto with_epi, int nb, const tdc_op3(&u)[S3]) {
-            tdc_f4 acc3[PB];
-#pragma unroll
-            for (int pb = 0; pb < PB; ++pb) acc3[pb] = tdc_f4_zero();
+        const int z2_exp = tdc_scale_of(tdc_wave_max(top), TDC_Z2_TARGET, 0);
+        bad |= tdc_is_small(smallest, tdc_exp2i(max(TDC_LOWEST - z2_exp, -126)));
+        const int y_exp = a.z1_exp - z2_exp - x_exp;             // y is 2^(y_exp - exponent of the channel) times its sum
+        tdc_op<NP> zb[S3][PB];
+        {
+            const TdcScale s(z2_exp);
 #pragma unroll
             for (int st = 0; st < S3; ++st)
 #pragma unroll
-                for (int i = 0; i < 6; ++i)
+                for (int pb = 0; pb < PB; ++pb)
+                    zb[st][pb] = tdc_split_op<NP>(z2[2 * st][pb], 2 * st + 1 < NB2 ? z2[(2 * st + 1) % NB2][pb] : tdc_f4_zero(), s);
+        }
+        const Chain3Out<PB, NHWC> out(a, at, pg, lane);
+        float largest = 0.f;
+        // two instances of the loop, as in tdc_chain_kernel.h: without epilogue loads nothing ever waits for the stores
+        const auto emit = [&](auto with_epi, int nb, const Weights &u) {
+            tdc_f4 acc3[PB][NP], v[PB];
 #pragma unroll
-                    for (int pb = 0; pb < PB; ++pb)
-                        acc3[pb] = NHWC ? tdc_mfma_bf(u[st].p[TDC_BF3_A[i]], zb[st][pb].p[TDC_BF3_B[i]], acc3[pb])
-                                        : tdc_mfma_bf(zb[st][pb].p[TDC_BF3_B[i]], u[st].p[TDC_BF3_A[i]], acc3[pb]);
+            for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
-            for (int pb = 0; pb < PB; ++pb) largest = tdc_largest(largest, acc3[pb]);
-            out.template put<decltype(with_epi)::value>(nb, acc3);
+                for (int q = 0; q < NP; ++q) acc3[pb][q] = tdc_f4_zero();
+#pragma unroll
+            for (int st = 0; st < S3; ++st)
+#pragma unroll
+                for (int i = 0; i < TdcProducts<NP>::N; ++i)
+#pragma unroll
+                    for (int pb = 0; pb < PB; ++pb) {
+                        tdc_f4 &c = acc3[pb][TdcProducts<NP>::level[i]];
+                        c = tdc_mfma_part<NP, SWAP>(i, u.w[st].p, zb[st][pb].p, c);
+                    }
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb) {
+                v[pb] = tdc_levels<NP>(acc3[pb]);
+                largest = tdc_largest(largest, v[pb]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[pb][i] = ldexpf(v[pb][i], y_exp - u.e[NHWC ? i : 0]);
+            }
+            out.template put<decltype(with_epi)::value>(nb, v);
         };
         const auto stage3 = [&](auto with_epi) {
             for (int nb = slice; nb < a.NB3; nb += 2 * ks) {
@@ -634,13 +661,14 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
         };
         if (a.epi.bias || a.epi.residual || a.epi.relu) stage3(std::true_type{});
         else stage3(std::false_type{});
-        // a NaN, or z2 too large or too small for three parts: only then can an output be wrong
-        if (__builtin_expect(tdc_any_lane(!(largest < TDC_BIG)), 0)) {
-            int group = pg;
-            asm volatile("" : "+s"(group));                      // its addresses are computed there, not kept from above
-            chain3_redo<NB2, PB, LAY>(tdc_args_again<TdcChain3Args>(), z1s, group, lane, slice);
-        }
+        bad |= !tdc_finite(largest);
     }
+    // One wavefront's trouble is the tile's: z1 is everybody's.
+    sh.bad[wave] = tdc_any_lane(bad);
+    __syncthreads();
+    const tdc_u4 all = *reinterpret_cast<const tdc_u4 *>(sh.bad);
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)(all[0] | all[1] | all[2] | all[3])), 0))
+        chain3_tile_fp32<NB2, PB, LAY, NP>(tdc_args_again<TdcChain3Args>(), z1s, lane, wave);
 }
 
 }  // namespace
@@ -650,18 +678,19 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
 #define TDC_CHAIN3_UNITS(X) X(1, 4) X(2, 4) X(3, 4) X(1, 2) X(2, 2) X(3, 2) X(4, 2) X(5, 2)
 
 template <int LAY>
-hipError_t tdc_launch_chain3_lay(const TdcChain3Args &a, int nb2, int pb, int mb1, dim3 grid, size_t lds, hipStream_t s, bool prepare_only)
+hipError_t tdc_launch_chain3_lay(const TdcChain3Args &a, int nb2, int pb, int mb1, int parts, dim3 grid, size_t lds, hipStream_t s, bool prepare_only)
 {
-#define TDC_LAUNCH(N_, P_, M_)                                                                                    \
-    if (mb1 == M_) {                                                                                              \
-        hipError_t e = tdc_allow_lds((const void *)tdc_chain3_kernel<N_, P_, LAY, M_>, lds);                       \
-        if (e != hipSuccess || prepare_only) return e;                                                            \
-        hipLaunchKernelGGL((tdc_chain3_kernel<N_, P_, LAY, M_>), grid, dim3(64 * TDC_CHAIN3_WAVES), lds, s, a); \
-        return hipGetLastError();                                                                                 \
+#define TDC_LAUNCH(N_, P_, M_, NP_)                                                                                    \
+    if (mb1 == M_ && parts == NP_) {                                                                                   \
+        hipError_t e = tdc_allow_lds((const void *)tdc_chain3_kernel<N_, P_, LAY, M_, NP_>, lds);                       \
+        if (e != hipSuccess || prepare_only) return e;                                                                 \
+        hipLaunchKernelGGL((tdc_chain3_kernel<N_, P_, LAY, M_, NP_>), grid, dim3(64 * TDC_CHAIN3_WAVES), lds, s, a); \
+        return hipGetLastError();                                                                                      \
     }
-#define TDC_X(N_, P_)                                                                                             \
-    if (nb2 == N_ && pb == P_) {                                                                                  \
-        TDC_LAUNCH(N_, P_, 1) TDC_LAUNCH(N_, P_, 2) TDC_LAUNCH(N_, P_, 3)                                         \
+#define TDC_X(N_, P_)                                                                                                  \
+    if (nb2 == N_ && pb == P_) {                                                                                       \
+        TDC_LAUNCH(N_, P_, 1, 2) TDC_LAUNCH(N_, P_, 2, 2) TDC_LAUNCH(N_, P_, 3, 2)                                     \
+        TDC_LAUNCH(N_, P_, 1, 3) TDC_LAUNCH(N_, P_, 2, 3) TDC_LAUNCH(N_, P_, 3, 3)                                     \
     }
     TDC_CHAIN3_UNITS(TDC_X)
 #undef TDC_X

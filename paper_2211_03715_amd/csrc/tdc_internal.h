@@ -56,14 +56,24 @@ hipError_t tdc_launch_pack_core(const TdcDims &d, hipStream_t s, const float *co
 // U_in as usual; Wm[R1][N][K][K] = core x_2 U_out into `wm`, then re-laid out into `wm_p` [NB3][K*K*NB1]
 hipError_t tdc_launch_pack_merged(const TdcDims &d, hipStream_t s, const float *U_in, const float *core,
                                   const float *U_out, float *uin_p, float *wm, float *wm_p);
-// The same re-layout with every weight split into three bf16 parts (tdc_bf3.h): [m-block][step][part][lane][8], a step being
-// two k-groups, component j = what the fp32 layout has as component j%4 of k-group 2*step + j/4 (zero past the last one).
-// An allocation holds TDC_PACKED3_TAIL bytes more, which the re-layout uses.
-constexpr size_t TDC_PACKED3_TAIL = 256;
-inline size_t tdc_packed3_bytes(int m_blocks, int k_groups) { return (size_t)m_blocks * ((k_groups + 1) / 2) * 3072; }
-hipError_t tdc_launch_pack3_core(const TdcDims &d, hipStream_t s, const float *core, void *core_p3);
-hipError_t tdc_launch_pack3(const TdcDims &d, hipStream_t s, const float *U_in, const float *core, const float *U_out,
-                            void *uin_p3, void *core_p3, void *uout_p3);
+// The same re-layout with every weight split into two or three fp16 parts (tdc_split.h): [m-block][step][part][lane][8], a step
+// being two k-groups, component j = what the fp32 layout has as component j%4 of k-group 2*step + j/4 (zero past the last one).
+// Every output channel is scaled by its own power of two.  Behind the parts: an exponent per channel (how a kernel undoes the
+// scaling, see tdc_pack.hip), the same weights in fp32 in the layout above, for what the parts cannot carry, and the ranges of
+// TDC_SPLIT_CHUNKS shares of the contraction, which the scaling comes from.
+constexpr int TDC_SPLIT_CHUNKS = 16;
+inline size_t tdc_split_bytes(int parts, int m_blocks, int k_groups) { return (size_t)m_blocks * ((k_groups + 1) / 2) * 1024 * parts; }
+inline size_t tdc_split_alloc_bytes(int parts, int m_blocks, int k_groups)
+{
+    return tdc_split_bytes(parts, m_blocks, k_groups) + (size_t)m_blocks * (64 + (size_t)k_groups * 1024 + 128 * TDC_SPLIT_CHUNKS);
+}
+// Parts a weight is split into.  Two are the more accurate form from some 70 terms to a sum on (tdc_split.h); the three sums of a
+// Tucker layer add up to that from 208 on: squared errors of 78 + 0.39 n against 2.1 n - 40 (in 1e-16, n terms).
+inline int tdc_tile_parts(const TdcDims &d) { return d.K * d.K * d.R1 > 72 ? 2 : 3; }
+inline int tdc_chain3_parts(const TdcDims &d) { return d.C + d.K * d.K * d.R1 + d.R2 >= 208 ? 2 : 3; }
+hipError_t tdc_launch_split_core(const TdcDims &d, int parts, hipStream_t s, const float *core, void *core_sp);
+hipError_t tdc_launch_split_layer(const TdcDims &d, int parts, hipStream_t s, const float *U_in, const float *core, const float *U_out,
+                                  void *uin_sp, void *core_sp, void *uout_sp);
 size_t tdc_packed_floats_uin(const TdcDims &d);
 size_t tdc_packed_floats_core(const TdcDims &d);
 size_t tdc_packed_floats_uout(const TdcDims &d);
@@ -82,8 +92,8 @@ hipError_t tdc_launch_split(const TdcDims &d, const tdc_tuning &t, hipStream_t s
 hipError_t tdc_launch_dense(const TdcDims &d, const tdc_tuning &t, hipStream_t s, const float *x,
                             const float *w_p, float *y, const TdcEpi &epi);
 
-// the same layer in tm x tp tiles of (channels x pixels) on the bf16 matrix cores (tdc_tile.hip), the contraction dealt to
-// `ks` groups of wavefronts; w3: tdc_launch_pack3_core's layout
+// the same layer in tm x tp tiles of (channels x pixels) on the fp16 matrix cores (tdc_tile.hip), the contraction dealt to
+// `ks` groups of wavefronts; w: tdc_launch_split_core's layout
 // A DENSE tuning asks for it with both tile fields, no smaller than 64, and no register tile; with any other tile fields it
 // means the latency kernel, which has none.
 inline bool tdc_is_tile(const tdc_tuning &t)
@@ -92,7 +102,7 @@ inline bool tdc_is_tile(const tdc_tuning &t)
 }
 bool tdc_tile_supported(int tm, int tp, int ks);
 bool tdc_tile_applies(const TdcDims &d);
-hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipStream_t s, const float *x, const void *w3, float *y, const TdcEpi &epi);
+hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipStream_t s, const float *x, const void *w, float *y, const TdcEpi &epi);
 
 // stage 1, then stages 2 and 3 as one implicit GEMM with the merged kernel
 hipError_t tdc_launch_merged(const TdcDims &d, const tdc_tuning &t, hipStream_t s, const float *x,
@@ -134,7 +144,7 @@ hipError_t tdc_launch_chain(const TdcDims &d, const tdc_tuning &t, const TdcFuse
                             const float *x, const float *uin_p, const float *core_p,
                             const float *uout_p, float *y, const TdcEpi &epi, bool prepare_only = false);
 
-// ---- the same on the bf16 matrix cores (tdc_chain3.hip, kernel in tdc_chain3_kernel.h): weights in tdc_launch_pack3's layout,
+// ---- the same on the fp16 matrix cores (tdc_chain3.hip, kernel in tdc_chain3_kernel.h): weights in tdc_launch_split_layer's layout,
 // workgroups of four wavefronts.  A CHAIN tuning asks for it with mb[1] == TDC_CHAIN3_PARTS; pb[0] is 2 or 4.
 constexpr int TDC_CHAIN3_PARTS = 3;
 inline bool tdc_is_chain3(const tdc_tuning &t) { return t.variant == TDC_VARIANT_CHAIN && t.mb[1] == TDC_CHAIN3_PARTS; }
@@ -142,7 +152,7 @@ bool tdc_chain3_supported(const TdcDims &d, int mb1, int pb);
 int tdc_chain3_share(int pixel_groups);   // log2 of the wavefronts that work on one group of pixel blocks together
 TdcFusedGeom tdc_chain3_geometry(const TdcDims &d, int tile_h, int tile_w, int pb);
 hipError_t tdc_launch_chain3(const TdcDims &d, const tdc_tuning &t, const TdcFusedGeom &g, hipStream_t s, const float *x,
-                             const void *uin_p3, const void *core_p3, const void *uout_p3, float *y, const TdcEpi &epi,
+                             const void *uin_sp, const void *core_sp, const void *uout_sp, float *y, const TdcEpi &epi,
                              bool prepare_only = false);
 
 // ---- one-launch kernel: stage 1 into LDS, then the merged stage-2/3 convolution (tdc_fm.hip).

@@ -1,7 +1,9 @@
 // Weight re-layout kernels: caller layouts -> the frag-major packed layout of tdc_internal.h.
 // The paper (section 5.2) converts its core weights to a coalescing-friendly layout once,
 // offline; this is the same step for this library's MFMA operand order.
-#include "tdc_bf3.h"
+#include <algorithm>
+
+#include "tdc_split.h"
 #include "tdc_internal.h"
 
 size_t tdc_packed_floats_uin(const TdcDims &d) { return (size_t)d.NB1 * d.KG1 * 256; }
@@ -45,69 +47,139 @@ __global__ void pack_core_kernel(TdcDims d, const float *__restrict__ core, floa
     out[e] = (d1 < d.R1 && m < d.R2) ? core[(((size_t)d1 * d.R2 + m) * d.K + r) * d.K + s] : 0.f;
 }
 
-// The largest magnitudes below 2^126 of RANGE_BLOCKS parts of each of up to three weight tensors, behind their packed parts.
-constexpr int RANGE_BLOCKS = TDC_PACKED3_TAIL / 4;
-struct RangeArgs {
-    const float *w[3];
-    size_t n[3];
-    float *largest[3];
+// ---- parts (tdc_split.h)
+//
+// Output channel m of a weight tensor is scaled by 2^scale[m], its largest weight to 2^13 .. 2^14.  In the exponents behind the
+// parts a kernel finds
+//   U_in, core   lowest - scale[m], where lowest = the smallest scale of the tensor (that of its largest weight): what takes the
+//                scaled sums of all channels to the common scale 2^lowest;
+//   U_out, W     scale[n], for U_out plus the other two tensors' lowest: what has to be undone at the end.
+// A tensor with weights from 2^10 on beside others that the scaling takes below 2^-13 (where parts lose bits) is kept in fp32
+// alone: its parts are NaN.  Smaller weights beside ordinary ones only lose what is below the rounding of their channel's sums.
+
+// One weight tensor w[row][col][tap] -- the contraction runs over rows and taps -- and where things go.
+struct SplitTensor {
+    const float *w;
+    int rows, cols, KK, NBk, NBm, KG;      // NBk, KG: k-groups per tap and in all
+    unsigned *parts;
+    int *exponents;
+    float *raw;
+    int *top, *low;                        // largest and smallest exponent of each channel's weights, TDC_SPLIT_CHUNKS shares
+    bool last;                             // U_out, W
 };
-__global__ void pack3_range_kernel(RangeArgs a)
+constexpr int SPLIT_NONE = 100000, SPLIT_TOP = 13;
+
+__device__ __forceinline__ int split_top(const SplitTensor &t, int m)
 {
-    const float *__restrict__ w = a.w[blockIdx.y];
-    const size_t n = a.n[blockIdx.y];
-    float m = 0.f;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        const float v = fabsf(w[i]);
-        if (v < TDC_BIG) m = fmaxf(m, v);
-    }
-    __shared__ float part[256];
-    part[threadIdx.x] = m;
+    int top = -SPLIT_NONE;
+    for (int i = 0; i < TDC_SPLIT_CHUNKS; ++i) top = max(top, t.top[i * 16 * t.NBm + m]);
+    return top;
+}
+__device__ __forceinline__ int split_low(const SplitTensor &t, int m)
+{
+    int low = SPLIT_NONE;
+    for (int i = 0; i < TDC_SPLIT_CHUNKS; ++i) low = min(low, t.low[i * 16 * t.NBm + m]);
+    return low;
+}
+// channels without a finite weight that is not zero take 0
+__device__ __forceinline__ int split_scale(int top) { return top == -SPLIT_NONE ? 0 : SPLIT_TOP - top; }
+
+// over a workgroup of 256
+__device__ __forceinline__ int split_block_max(int v)
+{
+    __shared__ int part[256];
+    __syncthreads();
+    part[threadIdx.x] = v;
     __syncthreads();
     for (int s = 128; s; s >>= 1) {
-        if ((int)threadIdx.x < s) part[threadIdx.x] = fmaxf(part[threadIdx.x], part[threadIdx.x + s]);
+        if ((int)threadIdx.x < s) part[threadIdx.x] = max(part[threadIdx.x], part[threadIdx.x + s]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) a.largest[blockIdx.y][blockIdx.x] = part[0];
+    return part[0];
+}
+// the exponent of the largest weight of a tensor, and whether it is too wide for parts
+__device__ __forceinline__ void split_whole(const SplitTensor &t, int &top, bool &wide)
+{
+    int widest = -SPLIT_NONE;
+    top = -SPLIT_NONE;
+    for (int m = threadIdx.x; m < t.cols; m += 256) {
+        const int h = split_top(t, m);
+        top = max(top, h);
+        if (h != -SPLIT_NONE) widest = max(widest, h - split_low(t, m));
+    }
+    top = split_block_max(top);
+    widest = split_block_max(widest);
+    wide = top >= 10 && widest > SPLIT_TOP - TDC_LOWEST;
 }
 
-// One thread per pair of components of the three-part layout: e = ((mb*S + step)*64 + lane)*4 + pair.  weight(kg, k, m) is
-// the value of k-group kg's contraction index k (0..15) and output channel m, zero past the end of either.  A tensor whose
-// largest weight is outside 2^-100 .. 2^14 is kept raw altogether (tdc_bf3.h).
-template <class Weight>
-__device__ __forceinline__ void pack3(size_t e, int KG, unsigned *__restrict__ out, const float *__restrict__ largest, Weight weight)
+// the ranges of 64 output channels' weights among one share of the rows
+__device__ __forceinline__ void split_range(const SplitTensor &t, int block)
 {
-    float top = 0.f;
-    for (int i = 0; i < RANGE_BLOCKS; ++i) top = fmaxf(top, largest[i]);
-    const float least = top < 0x1p-100f || top > 0x1p14f ? INFINITY : 0.f;
-    const int S = (KG + 1) / 2;
-    const int pair = (int)(e & 3), lane = (int)((e >> 2) & 63);
-    const size_t blk = e >> 8;
+    __shared__ int top4[256], low4[256];
+    const int share = block % TDC_SPLIT_CHUNKS, m = block / TDC_SPLIT_CHUNKS * 64 + (threadIdx.x & 63);
+    int top = -SPLIT_NONE, low = SPLIT_NONE;
+    if (m < t.cols)
+        for (int row = share + TDC_SPLIT_CHUNKS * (threadIdx.x >> 6); row < t.rows; row += 4 * TDC_SPLIT_CHUNKS) {
+            const float *__restrict__ w = t.w + ((size_t)row * t.cols + m) * t.KK;
+            for (int i = 0; i < t.KK; ++i)
+                if (w[i] != 0.f && fabsf(w[i]) < INFINITY) {
+                    const int e = ilogbf(w[i]);
+                    top = max(top, e);
+                    low = min(low, e);
+                }
+        }
+    top4[threadIdx.x] = top;
+    low4[threadIdx.x] = low;
+    __syncthreads();
+    if (threadIdx.x < 64 && m < 16 * t.NBm) {
+        const int *p = top4 + threadIdx.x, *q = low4 + threadIdx.x;
+        t.top[share * 16 * t.NBm + m] = max(max(p[0], p[64]), max(p[128], p[192]));
+        t.low[share * 16 * t.NBm + m] = min(min(q[0], q[64]), min(q[128], q[192]));
+    }
+}
+
+struct SplitArgs {
+    SplitTensor t[3];
+    int n;                                 // 3: U_in, core, U_out; 1: W
+};
+__global__ void split_range_kernel(SplitArgs a) { if ((int)blockIdx.x < (a.t[blockIdx.y].NBm + 3) / 4 * TDC_SPLIT_CHUNKS) split_range(a.t[blockIdx.y], blockIdx.x); }
+
+// One thread per pair of components: e = ((mb*S + step)*64 + lane)*4 + pair, one workgroup per block and step.
+template <int NP>
+__global__ void split_pack_kernel(SplitArgs a)
+{
+    const SplitTensor &t = a.t[blockIdx.y];
+    const int S = (t.KG + 1) / 2;
+    if ((int)blockIdx.x >= t.NBm * S) return;
+    int top;
+    bool wide;
+    split_whole(t, top, wide);
+    const int lowest = split_scale(top);
+    int others = 0;
+    if (t.last)
+        for (int i = 0; i < a.n - 1; ++i) {
+            int o;
+            bool w;
+            split_whole(a.t[i], o, w);
+            others += split_scale(o);
+        }
+    const int pair = (int)(threadIdx.x & 3), lane = (int)(threadIdx.x >> 2);
+    const size_t blk = blockIdx.x;
     const int step = (int)(blk % S), mb = (int)(blk / S);
     const int kg = 2 * step + (pair >> 1), m = 16 * mb + (lane & 15), k = 4 * (lane >> 4) + 2 * (pair & 1);
-    unsigned p[3];
-    tdc_split2_raw(kg < KG ? weight(kg, k, m) : 0.f, kg < KG ? weight(kg, k + 1, m) : 0.f, least, p[0], p[1], p[2]);
-    for (int i = 0; i < 3; ++i) out[(blk * 3 + i) * 256 + lane * 4 + pair] = p[i];
-}
-
-__global__ void pack3_core_kernel(TdcDims d, const float *__restrict__ core, unsigned *__restrict__ out, const float *__restrict__ largest, size_t total)
-{
-    const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= total) return;
-    pack3(e, d.K * d.K * d.NB1, out, largest, [&](int kg, int k, int m) {
-        const int tap = kg / d.NB1, r = tap / d.K, s = tap % d.K, d1 = 16 * (kg % d.NB1) + k;
-        return d1 < d.R1 && m < d.R2 ? core[(((size_t)d1 * d.R2 + m) * d.K + r) * d.K + s] : 0.f;
-    });
-}
-
-// U_in [C][R1] and U_out [R2][N]: w[k][m], `rows` x `cols`
-__global__ void pack3_matrix_kernel(int rows, int cols, const float *__restrict__ w, unsigned *__restrict__ out, const float *__restrict__ largest, size_t total)
-{
-    const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= total) return;
-    pack3(e, (rows + 15) / 16, out, largest, [&](int kg, int k, int m) {
-        return 16 * kg + k < rows && m < cols ? w[(size_t)(16 * kg + k) * cols + m] : 0.f;
-    });
+    const int channel = split_top(t, m), scale = split_scale(channel);
+    const int tap = kg / t.NBk, row = 16 * (kg - tap * t.NBk) + k;
+    float v[2];
+    for (int i = 0; i < 2; ++i) v[i] = kg < t.KG && row + i < t.rows && m < t.cols ? t.w[((size_t)(row + i) * t.cols + m) * t.KK + tap] : 0.f;
+    unsigned p[NP];
+    tdc_split2<NP>(wide ? NAN : ldexpf(v[0], scale), wide ? NAN : ldexpf(v[1], scale), TdcScale(0), p);
+    for (int i = 0; i < NP; ++i) t.parts[(blk * NP + i) * 256 + lane * 4 + pair] = p[i];
+    if (kg < t.KG) {
+        float *raw = t.raw + (((size_t)mb * t.KG + kg) * 64 + lane) * 4 + 2 * (pair & 1);
+        raw[0] = v[0];
+        raw[1] = v[1];
+    }
+    if (step == 0 && pair == 0 && lane < 16) t.exponents[m] = t.last ? scale + others : channel == -SPLIT_NONE ? 0 : lowest - scale;
 }
 
 __global__ void pack_uout_kernel(TdcDims d, const float *__restrict__ U_out, float *__restrict__ out, size_t total)
@@ -171,36 +243,47 @@ hipError_t tdc_launch_pack_core(const TdcDims &d, hipStream_t s, const float *co
     return hipGetLastError();
 }
 
-static float *pack3_largest(void *packed, size_t bytes) { return reinterpret_cast<float *>(static_cast<char *>(packed) + bytes); }
-
-static void launch_pack3_core(const TdcDims &d, hipStream_t s, const float *core, void *core_p3, size_t bytes)
+static SplitTensor split_tensor(int parts, const float *w, int rows, int cols, int K, void *out, bool last)
 {
-    const int T = 256;
-    const size_t n = bytes / 12;
-    hipLaunchKernelGGL(pack3_core_kernel, dim3((unsigned)((n + T - 1) / T)), dim3(T), 0, s, d, core, (unsigned *)core_p3, pack3_largest(core_p3, bytes), n);
+    SplitTensor t;
+    t.w = w; t.rows = rows; t.cols = cols; t.KK = K * K;
+    t.NBk = (rows + 15) / 16; t.NBm = (cols + 15) / 16; t.KG = t.KK * t.NBk;
+    t.parts = (unsigned *)out;
+    t.exponents = (int *)((char *)out + tdc_split_bytes(parts, t.NBm, t.KG));
+    t.raw = (float *)(t.exponents + 16 * t.NBm);
+    t.top = (int *)(t.raw + (size_t)t.NBm * t.KG * 256);
+    t.low = t.top + 16 * t.NBm * TDC_SPLIT_CHUNKS;
+    t.last = last;
+    return t;
 }
 
-hipError_t tdc_launch_pack3_core(const TdcDims &d, hipStream_t s, const float *core, void *core_p3)
+static hipError_t launch_split(int parts, hipStream_t s, const SplitArgs &a)
 {
-    const size_t bytes = tdc_packed3_bytes(d.NB2, d.K * d.K * d.NB1);
-    const RangeArgs r = {{core}, {(size_t)d.R1 * d.R2 * d.K * d.K}, {pack3_largest(core_p3, bytes)}};
-    hipLaunchKernelGGL(pack3_range_kernel, dim3(RANGE_BLOCKS), dim3(256), 0, s, r);
-    launch_pack3_core(d, s, core, core_p3, bytes);
+    size_t ranges = 0, packs = 0;
+    for (int i = 0; i < a.n; ++i) {
+        ranges = std::max(ranges, (size_t)(a.t[i].NBm + 3) / 4 * TDC_SPLIT_CHUNKS);
+        packs = std::max(packs, (size_t)a.t[i].NBm * ((a.t[i].KG + 1) / 2));
+    }
+    hipLaunchKernelGGL(split_range_kernel, dim3((unsigned)ranges, a.n), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(parts == 2 ? split_pack_kernel<2> : split_pack_kernel<3>, dim3((unsigned)packs, a.n), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
-hipError_t tdc_launch_pack3(const TdcDims &d, hipStream_t s, const float *U_in, const float *core, const float *U_out,
-                            void *uin_p3, void *core_p3, void *uout_p3)
+hipError_t tdc_launch_split_core(const TdcDims &d, int parts, hipStream_t s, const float *core, void *core_sp)
 {
-    const int T = 256;
-    const size_t b1 = tdc_packed3_bytes(d.NB1, d.KG1), b2 = tdc_packed3_bytes(d.NB2, d.K * d.K * d.NB1), b3 = tdc_packed3_bytes(d.NB3, d.NB2);
-    const RangeArgs r = {{U_in, core, U_out},
-                         {(size_t)d.C * d.R1, (size_t)d.R1 * d.R2 * d.K * d.K, (size_t)d.R2 * d.N},
-                         {pack3_largest(uin_p3, b1), pack3_largest(core_p3, b2), pack3_largest(uout_p3, b3)}};
-    hipLaunchKernelGGL(pack3_range_kernel, dim3(RANGE_BLOCKS, 3), dim3(256), 0, s, r);
-    const size_t n1 = b1 / 12, n3 = b3 / 12;
-    hipLaunchKernelGGL(pack3_matrix_kernel, dim3((unsigned)((n1 + T - 1) / T)), dim3(T), 0, s, d.C, d.R1, U_in, (unsigned *)uin_p3, r.largest[0], n1);
-    hipLaunchKernelGGL(pack3_matrix_kernel, dim3((unsigned)((n3 + T - 1) / T)), dim3(T), 0, s, d.R2, d.N, U_out, (unsigned *)uout_p3, r.largest[2], n3);
-    launch_pack3_core(d, s, core, core_p3, b2);
-    return hipGetLastError();
+    SplitArgs a = {};
+    a.n = 1;
+    a.t[0] = split_tensor(parts, core, d.R1, d.R2, d.K, core_sp, true);
+    return launch_split(parts, s, a);
+}
+
+hipError_t tdc_launch_split_layer(const TdcDims &d, int parts, hipStream_t s, const float *U_in, const float *core, const float *U_out,
+                                  void *uin_sp, void *core_sp, void *uout_sp)
+{
+    SplitArgs a = {};
+    a.n = 3;
+    a.t[0] = split_tensor(parts, U_in, d.C, d.R1, 1, uin_sp, false);
+    a.t[1] = split_tensor(parts, core, d.R1, d.R2, d.K, core_sp, false);
+    a.t[2] = split_tensor(parts, U_out, d.R2, d.N, 1, uout_sp, true);
+    return launch_split(parts, s, a);
 }

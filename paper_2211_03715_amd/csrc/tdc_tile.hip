@@ -18,14 +18,16 @@
 // contiguous ones); this one without the interleaving 42.8 us, as it stands 39.8 us (fp32 MFMA kernel: 90.5 us).  On large
 // products it runs at 209 TFLOP/s of fp32 products, 1250 of bf16 ones -- what the vendor's bf16 GEMM of 8192^3 reaches on
 // the card (1241): power, not issue, is the limit there (all-zero operands: 273 TFLOP/s).
-#include "tdc_bf3.h"
+#include <cmath>
+
+#include "tdc_split.h"
 #include "tdc_internal.h"
 
 namespace {
 
 struct TileArgs {
     const float *act;
-    const void *w3;         // weights in three parts, [NBm][S][3][64 lanes][8 bf16] (S steps)
+    const void *w;          // weights in NP parts, [NBm][S][NP][64 lanes][8 fp16] (S steps), then their exponents
     float *out;
     TdcEpi epi;             // applied where out is the layer's y
     int C;                  // channels of act
@@ -53,7 +55,7 @@ __device__ __forceinline__ void tile_plain_output(const TileArgs &a, int m, int 
     const int b = tdc_div(p, a.div_P), pix = p - b * a.P;
     const int oh = tdc_div(pix, a.div_Wo), h0 = oh * a.stride - a.pad, w0 = (pix - oh * a.Wo) * a.stride - a.pad;
     const float *x = a.act + (size_t)b * a.C * a.HW;
-    const unsigned short *w = reinterpret_cast<const unsigned short *>(a.w3) + (size_t)(m >> 4) * a.S * 1536;
+    const float *w = reinterpret_cast<const float *>(tdc_raw_base(a.w, a.w_bytes, a.NBm)) + (size_t)(m >> 4) * a.KG * 256;
     float sum = 0.f;
 #pragma unroll 1
     for (int kg = 0; kg < a.KG && sum == sum; ++kg) {
@@ -63,8 +65,7 @@ __device__ __forceinline__ void tile_plain_output(const TileArgs &a, int m, int 
         const int q = h * a.W + wx;
 #pragma unroll 1
         for (int k = 0; k < 16 && c0 + k < a.C; ++k) {
-            const unsigned short *f = w + (size_t)(kg >> 1) * 1536 + ((m & 15) + 16 * (k >> 2)) * 8 + (kg & 1) * 4 + (k & 3);
-            sum = fmaf(tdc_join(f[0], f[512], f[1024]), ACT == TDC_ACT_NHWC ? x[(size_t)q * a.C + c0 + k] : x[(size_t)(c0 + k) * a.HW + q], sum);
+            sum = fmaf(w[(size_t)kg * 256 + ((m & 15) + 16 * (k >> 2)) * 4 + (k & 3)], ACT == TDC_ACT_NHWC ? x[(size_t)q * a.C + c0 + k] : x[(size_t)(c0 + k) * a.HW + q], sum);
         }
     }
     const size_t idx = ACT == TDC_ACT_NHWC ? (size_t)p * a.M + m : ((size_t)b * a.M + m) * a.P + pix;
@@ -76,14 +77,14 @@ __device__ __forceinline__ void tile_plain_output(const TileArgs &a, int m, int 
 // times the weight here, and no part of the sum).  3x3, 128 -> 128 at 28x28,
 // batch 8, every value NaN: 70 us, 26 with numbers (one output after the other: 5350).
 template <int ACT, bool CONV, int MB, int PB>
-__device__ __forceinline__ unsigned tile_redo(const TileArgs &a, bool small, int lane, int p_base, int mb0, tdc_f4 (&acc)[MB][PB])
+__device__ __forceinline__ unsigned tile_redo(const TileArgs &a, bool small, int lane, int p_base, int mb0, tdc_f4 (&acc)[MB][PB], bool &done)
 {
     constexpr bool SWAP = ACT == TDC_ACT_NCHW;
     const int g = lane >> 4, l16 = lane & 15;
     const int b0 = tdc_div(p_base, a.div_P), n_img = min((16 * PB - 1) / a.P + 2, tdc_div(a.Ptot - 1, a.div_P) + 1 - b0);
     const size_t img_elems = (size_t)a.C * a.HW;
     const tdc_rsrc ars = tdc_make_rsrc(a.act + (size_t)b0 * img_elems, (unsigned)(n_img * img_elems * 4));
-    const tdc_rsrc wrs = tdc_make_rsrc(a.w3, a.w_bytes);
+    const tdc_rsrc wrs = tdc_make_rsrc(tdc_raw_base(a.w, a.w_bytes, a.NBm), 1024u * a.NBm * a.KG);
     const auto load_x = [&](int kg, int pb) {      // channels 4*g .. of k-group kg for pixel l16 of block pb; 0 outside
         const int tap = CONV ? tdc_div(kg, a.div_NBk) : 0, c = 16 * (kg - tap * a.NBk) + 4 * g;
         const int r = CONV ? tdc_div(tap, a.div_K) : 0;
@@ -101,7 +102,7 @@ __device__ __forceinline__ unsigned tile_redo(const TileArgs &a, bool small, int
         for (int j = 0; j < 4; ++j) v[j] = tdc_buf_load(ars, in && c + j < a.C ? o + 4u * j * a.HW : TDC_OOB);
         return v;
     };
-    const auto load_w = [&](int kg, int mb) { return mb0 + mb < a.NBm ? tdc_join_weights(wrs, mb0 + mb, a.S, kg, lane) : tdc_f4_zero(); };
+    const auto load_w = [&](int kg, int mb) { return mb0 + mb < a.NBm ? tdc_raw_weights(wrs, mb0 + mb, a.KG, kg, lane) : tdc_f4_zero(); };
 
     TdcFactors xs, ws;
 #pragma unroll 2
@@ -110,12 +111,13 @@ __device__ __forceinline__ unsigned tile_redo(const TileArgs &a, bool small, int
         for (int pb = 0; pb < PB; ++pb) xs.see(load_x(kg, pb));
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
-            if (mb0 + mb < a.NBm) ws.see(tdc_first_parts(wrs, mb0 + mb, a.S, kg, lane));
+            ws.see(load_w(kg, mb));
     }
     const bool odd_weights = tdc_any_lane(ws.nan || ws.largest == INFINITY);
-    xs.nan |= ws.nan;
-    xs.largest = fmaxf(xs.largest, ws.largest);
-    if (xs.explain_nan() && !small && !(CONV && odd_weights)) return 0u;
+    // NaNs, and no factors large enough to overflow
+    const bool explained = tdc_any_lane(xs.nan | ws.nan) && !tdc_any_lane(xs.largest >= 0x1p30f || ws.largest >= 0x1p30f);
+    done = !(explained && !small && !(CONV && odd_weights));
+    if (!done) return 0u;
 
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
@@ -147,16 +149,22 @@ __device__ __forceinline__ unsigned tile_redo(const TileArgs &a, bool small, int
     return nans;
 }
 
-template <int ACT, bool CONV, int WM, int MB, int PB, int KS>
-__global__ __launch_bounds__(256 * KS, 3) void tdc_tile_kernel(TileArgs a)
+// Wavefronts per SIMD an instance has registers for.
+constexpr int tile_wavefronts(int mb_pb, int np) { return mb_pb > 4 ? 2 : np == 3 ? 2 : 3; }
+
+template <int ACT, bool CONV, int WM, int MB, int PB, int KS, int NP>
+__global__ __launch_bounds__(256 * KS, tile_wavefronts(MB * PB, NP)) void tdc_tile_kernel(TileArgs a)
 {
     constexpr int WP = 4 / WM, TM = 16 * MB * WM, TP = 16 * PB * WP;
     constexpr int NX = TP / 32;                    // 16-byte pieces of activations a thread brings per step
     constexpr int PITCH = TP + 4;                  // 16-byte cells
-    constexpr int VPM = (NX * (ACT == TDC_ACT_NCHW ? 40 : 34) + 20 + 6 * MB * PB - 1) / (6 * MB * PB);   // VALU instructions per MFMA
-    __shared__ tdc_u4 xs_all[KS][2][12 * PITCH];   // [part][lane group][pixel]: 4 channels of each k-group of the step
+    constexpr int NM = TdcProducts<NP>::N;
+    constexpr int VPM = (NX * (7 * NP + (ACT == TDC_ACT_NCHW ? 17 : 12)) + 20 + NM * MB * PB - 1) / (NM * MB * PB);   // VALU instructions per MFMA
+    __shared__ tdc_u4 xs_all[KS][2][4 * NP * PITCH];   // [part][lane group][pixel]: 4 channels of each k-group of the step
+    __shared__ unsigned first_all[4 * KS];             // largest magnitude among what each wavefront loads first
+    __shared__ unsigned small_all[4 * KS];             // whether a wavefront brought a pixel of too small values
     const int ks = KS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
-    tdc_u4(&xs)[2][12 * PITCH] = xs_all[ks];
+    tdc_u4(&xs)[2][4 * NP * PITCH] = xs_all[ks];
     const int t = threadIdx.x & 255, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int g = lane >> 4, l16 = lane & 15;
@@ -173,7 +181,7 @@ __global__ __launch_bounds__(256 * KS, 3) void tdc_tile_kernel(TileArgs a)
     // the tile's images; the host keeps their span below 2 GiB
     const int n_img = min((TP - 1) / a.P + 2, tdc_div(a.Ptot - 1, a.div_P) + 1 - b0);
     const tdc_rsrc ars = tdc_make_rsrc(a.act + (size_t)b0 * img_elems, (unsigned)(n_img * img_elems * 4));
-    const tdc_rsrc wrs = tdc_make_rsrc(a.w3, a.w_bytes);
+    const tdc_rsrc wrs = tdc_make_rsrc(a.w, a.w_bytes);
 
     // ---- the pixels this thread brings: byte offset of the (0, 0) tap of its first channel, tap position
     constexpr int NPIX = ACT == TDC_ACT_NCHW ? 1 : NX;
@@ -246,59 +254,75 @@ __global__ __launch_bounds__(256 * KS, 3) void tdc_tile_kernel(TileArgs a)
         }
     };
     // piece i of a step's activations: split and stored as operand halves (NCHW: two pieces, the halves of a cell, at once)
+    int x_exp = 0;                                 // x is multiplied by 2^x_exp
+    float x_top[NPIX] = {};                        // largest magnitude of what this thread has brought of a pixel
     const auto to_lds = [&](const tdc_f4(&x)[NX], tdc_u4 *__restrict__ xb, int i) {
+        const TdcScale scale(x_exp);
+        x_top[i % NPIX] = tdc_largest(x_top[i % NPIX], x[i]);
         if (ACT == TDC_ACT_NHWC) {
             tdc_u2 *__restrict__ x2 = reinterpret_cast<tdc_u2 *>(xb);
-            tdc_u2 s[3];
-            tdc_split4(x[i], s[0], s[1], s[2]);
+            tdc_u2 s[NP];
+            tdc_split4<NP>(x[i], scale, s);
 #pragma unroll
-            for (int q = 0; q < 3; ++q) x2[((q * 4 + (c4 & 3)) * PITCH + (t >> 3) + 32 * i) * 2 + (c4 >> 2)] = s[q];
+            for (int q = 0; q < NP; ++q) x2[((q * 4 + (c4 & 3)) * PITCH + (t >> 3) + 32 * i) * 2 + (c4 >> 2)] = s[q];
         } else if (i % 2) {
-            const tdc_op3 o = tdc_split_op(x[i - 1], x[i]);
+            const tdc_op<NP> o = tdc_split_op<NP>(x[i - 1], x[i], scale);
 #pragma unroll
-            for (int q = 0; q < 3; ++q) xb[(q * 4 + nq * (NX / 2) + i / 2) * PITCH + t % TP] = __builtin_bit_cast(tdc_u4, o.p[q]);
+            for (int q = 0; q < NP; ++q) xb[(q * 4 + nq * (NX / 2) + i / 2) * PITCH + t % TP] = __builtin_bit_cast(tdc_u4, o.p[q]);
         }
     };
 
     unsigned wlane[MB];
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) wlane[mb] = mb0 + mb < a.NBm ? (unsigned)((mb0 + mb) * a.S) * 3072u + lane * 16u : TDC_OOB;
-    const auto fetch_w = [&](int step_, tdc_bf8(&w)[MB][3]) {
+    for (int mb = 0; mb < MB; ++mb) wlane[mb] = mb0 + mb < a.NBm ? (unsigned)((mb0 + mb) * a.S) * (1024u * NP) + lane * 16u : TDC_OOB;
+    const auto fetch_w = [&](int step_, tdc_op<NP>(&w)[MB]) {
         const int step = min(step_, a.S - 1);      // past the end: never multiplied, or (second group, odd S) with zero activations
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int q = 0; q < 3; ++q)
-                w[mb][q] = __builtin_bit_cast(tdc_bf8, (tdc_u4)__builtin_amdgcn_raw_buffer_load_b128(wrs, (int)(wlane[mb] + q * 1024u), step * 3072, 0));
+            for (int q = 0; q < NP; ++q)
+                w[mb].p[q] = __builtin_bit_cast(tdc_h8, (tdc_u4)__builtin_amdgcn_raw_buffer_load_b128(wrs, (int)(wlane[mb] + q * 1024u), step * (1024 * NP), 0));
     };
 
     // NCHW y: operands swapped, so that a lane ends up with four consecutive pixels of one channel
     constexpr bool SWAP = ACT == TDC_ACT_NCHW;     // an NCHW activation means an NCHW y
-    tdc_f4 acc[MB][PB];
+    tdc_f4 lev[MB][PB][NP];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int pb = 0; pb < PB; ++pb) acc[mb][pb] = tdc_f4_zero();
-    const auto read_b = [&](const tdc_u4 *__restrict__ xb, int pb) {
-        tdc_op3 b;
+        for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
-        for (int q = 0; q < 3; ++q) b.p[q] = __builtin_bit_cast(tdc_bf8, xb[(q * 4 + g) * PITCH + 16 * (wp * PB + pb) + l16]);
+            for (int q = 0; q < NP; ++q) lev[mb][pb][q] = tdc_f4_zero();
+    const auto read_b = [&](const tdc_u4 *__restrict__ xb, int pb) {
+        tdc_op<NP> b;
+#pragma unroll
+        for (int q = 0; q < NP; ++q) b.p[q] = __builtin_bit_cast(tdc_h8, xb[(q * 4 + g) * PITCH + 16 * (wp * PB + pb) + l16]);
         return b;
     };
-    const auto multiply = [&](int pb, const tdc_op3 &b, const tdc_bf8(&w)[MB][3]) {
+    const auto multiply = [&](int pb, const tdc_op<NP> &b, const tdc_op<NP>(&w)[MB]) {
 #pragma unroll
-        for (int i = 0; i < 6; ++i)
+        for (int i = 0; i < NM; ++i)
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-                acc[mb][pb] = SWAP ? tdc_mfma_bf(b.p[TDC_BF3_B[i]], w[mb][TDC_BF3_A[i]], acc[mb][pb])
-                                   : tdc_mfma_bf(w[mb][TDC_BF3_A[i]], b.p[TDC_BF3_B[i]], acc[mb][pb]);
+            for (int mb = 0; mb < MB; ++mb) {
+                tdc_f4 &c = lev[mb][pb][TdcProducts<NP>::level[i]];
+                c = tdc_mfma_part<NP, SWAP>(i, w[mb].p, b.p, c);
+            }
     };
     {
         tdc_f4 x[2][NX];
-        tdc_bf8 w[2][MB][3];
+        tdc_op<NP> w[2][MB];
         fetch_w(ks, w[0]);
         fetch_x(ks, x[0]);
         fetch_x(ks + KS, x[1]);
+        float m = 0.f;
+#pragma unroll
+        for (int n = 0; n < NX; ++n) m = tdc_largest(m, x[0][n]);
+        first_all[4 * ks + wave] = tdc_wave_max(m);
+        __syncthreads();
+        unsigned first = 0;
+#pragma unroll
+        for (int i = 0; i < 4 * KS; ++i) first = max(first, first_all[i]);
+        x_exp = tdc_scale_of((unsigned)__builtin_amdgcn_readfirstlane((int)first), TDC_X_TARGET, TDC_X_OTHER);
 #pragma unroll
         for (int n = 0; n < NX; ++n) to_lds(x[0], xs[0], n);
         fetch_x(ks + 2 * KS, x[0]);
@@ -310,7 +334,7 @@ __global__ __launch_bounds__(256 * KS, 3) void tdc_tile_kernel(TileArgs a)
                 if (!more) break;
                 __syncthreads();
                 fetch_w((i + u + 1) * KS + ks, w[1 - u]);
-                tdc_op3 b[2];
+                tdc_op<NP> b[2];
                 b[0] = read_b(xs[u], 0);
 #pragma unroll
                 for (int pb = 0; pb < PB; ++pb) {
@@ -322,16 +346,16 @@ __global__ __launch_bounds__(256 * KS, 3) void tdc_tile_kernel(TileArgs a)
                 fetch_x((i + u + 3) * KS + ks, x[1 - u]);
                 // an MFMA takes 16 cycles and leaves room for two other vector instructions: the conversions of the next
                 // step's activations go in between
-                __builtin_amdgcn_sched_group_barrier(0x020, 3 * MB, 0);          // weights
-                __builtin_amdgcn_sched_group_barrier(0x100, PB > 1 ? 6 : 3, 0);
+                __builtin_amdgcn_sched_group_barrier(0x020, NP * MB, 0);          // weights
+                __builtin_amdgcn_sched_group_barrier(0x100, PB > 1 ? 2 * NP : NP, 0);
 #pragma unroll
                 for (int pb = 0; pb < PB; ++pb) {
 #pragma unroll
-                    for (int m = 0; m < 6 * MB; ++m) {
+                    for (int m = 0; m < NM * MB; ++m) {
                         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                         __builtin_amdgcn_sched_group_barrier(0x002, VPM, 0);
                         if (m % 4 == 3) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-                        if (m == 3 * MB && pb + 2 < PB) __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+                        if (m == NM / 2 * MB && pb + 2 < PB) __builtin_amdgcn_sched_group_barrier(0x100, NP, 0);
                     }
                 }
                 more = i + u + 1 < steps;
@@ -339,6 +363,26 @@ __global__ __launch_bounds__(256 * KS, 3) void tdc_tile_kernel(TileArgs a)
             if (!more) break;
         }
     }
+    {   // pixels of which this thread, in NHWC the eight that share one, brought nothing but values too small
+        unsigned smallest = ~0u;
+#pragma unroll
+        for (int i = 0; i < NPIX; ++i) {
+            unsigned u = __builtin_bit_cast(unsigned, x_top[i]);
+            if (ACT == TDC_ACT_NHWC) {
+                u = max(u, (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0xb1, 0xf, 0xf, true));      // quad_perm 1 0 3 2
+                u = max(u, (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0x4e, 0xf, 0xf, true));      // quad_perm 2 3 0 1
+                u = max(u, (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0x141, 0xf, 0xf, true));     // the other half of eight
+            }
+            smallest = tdc_smallest(smallest, __builtin_bit_cast(float, u));
+        }
+        small_all[4 * ks + wave] = tdc_any_lane(tdc_is_small(smallest, tdc_exp2i(max(TDC_LOWEST - x_exp, -126))));
+    }
+    tdc_f4 acc[MB][PB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) acc[mb][pb] = tdc_levels<NP>(lev[mb][pb]);
+    if (KS == 1) __syncthreads();
     if constexpr (KS == 2) {   // the second group's sums join the first's, always in this order
         __syncthreads();
         tdc_f4 *__restrict__ red = reinterpret_cast<tdc_f4 *>(xs_all);
@@ -359,43 +403,33 @@ __global__ __launch_bounds__(256 * KS, 3) void tdc_tile_kernel(TileArgs a)
 
     // the lane number once more: the one above need not be kept through the loop for this
     const int out_lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), og = out_lane >> 4, ol = out_lane & 15;
-    // Factors without three parts, a sum that overflows on the way, or a pixel all of whose sums here are small: channels with
-    // tiny weights beside others (a filter that decayed) do not make it one.
+    // factors too large or without a value
     float largest = 0.f;
-    unsigned smallest = ~0u;
-    const auto each_pixel = [&](auto f) {           // f(largest magnitude of this lane's channels of a pixel)
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) largest = tdc_largest(largest, acc[mb][pb]);
+    unsigned any_small = 0;
+#pragma unroll
+    for (int i = 0; i < 4 * KS; ++i) any_small |= small_all[i];
+    const bool small = __builtin_amdgcn_readfirstlane((int)any_small) != 0;
+    unsigned nans = 0;
+    bool redone = false;
+    if (__builtin_expect(small || tdc_any_lane(!tdc_finite(largest)), 0))
+        nans = tile_redo<ACT, CONV, MB, PB>(tdc_args_again<TileArgs>(), small, out_lane, p_base, mb0, acc, redone);
+    // the exponents of the lane's output channels and of x
+    const int *__restrict__ exponents = reinterpret_cast<const int *>(static_cast<const char *>(a.w) + a.w_bytes);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+        if (redone || mb0 + mb >= a.NBm) break;
+        int e[SWAP ? 1 : 4];
+#pragma unroll
+        for (int i = 0; i < (SWAP ? 1 : 4); ++i) e[i] = -x_exp - exponents[16 * (mb0 + mb) + (SWAP ? ol : 4 * og + i)];
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
-            for (int i = 0; i < (SWAP ? 4 : 1); ++i) {
-                float m = 0.f;
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb) m = SWAP ? __builtin_elementwise_maximum(m, fabsf(acc[mb][pb][i])) : tdc_largest(m, acc[mb][pb]);
-                f(m);
-            }
-    };
-    each_pixel([&](float m) {
-        largest = __builtin_elementwise_maximum(largest, m);
-        smallest = tdc_smallest(smallest, m);
-    });
-    bool small = false;
-    if (__builtin_expect(tdc_any_lane(tdc_is_small(smallest)), 0)) {
-        each_pixel([&](float m) {                   // the pixel's lanes: l16, or one lane group
-            unsigned long long ok = __builtin_amdgcn_ballot_w64(!(m < TDC_SMALL));
-            if (SWAP) {
-                const unsigned long long low15 = 0x7fff7fff7fff7fffull;
-                ok = ((((ok & low15) + low15) | ok) & ~low15) >> 15;        // bit 0 of a group: any of its lanes
-                ok *= 0xffffu;
-            } else {
-                ok |= ok >> 32 | ok << 32;
-                ok |= ok >> 16 | ok << 48;
-            }
-            small |= (__builtin_amdgcn_ballot_w64(m > 0.f) & ~ok) != 0;
-        });
+            for (int i = 0; i < 4; ++i) acc[mb][pb][i] = ldexpf(acc[mb][pb][i], e[SWAP ? 0 : i]);
     }
-    unsigned nans = 0;
-    if (__builtin_expect(small || tdc_any_lane(!(largest < INFINITY)), 0))
-        nans = tile_redo<ACT, CONV, MB, PB>(tdc_args_again<TileArgs>(), small, out_lane, p_base, mb0, acc);
 
     const auto emit = [&](int mb, int pb, tdc_f4 v) {
         if (ACT == TDC_ACT_NHWC) {
@@ -447,15 +481,16 @@ __global__ __launch_bounds__(256 * KS, 3) void tdc_tile_kernel(TileArgs a)
 }
 
 template <int ACT, bool CONV>
-hipError_t launch_act(const TileArgs &a, int tm, int tp, int ks, hipStream_t s)
+hipError_t launch_act(const TileArgs &a, int tm, int tp, int ks, int parts, hipStream_t s)
 {
     const dim3 grid((unsigned)(a.n_mt * a.n_pt));
-#define TDC_CASE(M_, P_, WM_, KS_)                                                                                  \
-    if (tm == M_ && tp == P_ && ks == KS_) {                                                                        \
-        hipLaunchKernelGGL((tdc_tile_kernel<ACT, CONV, WM_, M_ / 16 / WM_, P_ / 16 / (4 / WM_), KS_>), grid, dim3(256 * KS_), 0, s, a); \
+#define TDC_CASE(M_, P_, WM_, KS_, NP_)                                                                              \
+    if (tm == M_ && tp == P_ && ks == KS_ && parts == NP_) {                                                        \
+        hipLaunchKernelGGL((tdc_tile_kernel<ACT, CONV, WM_, M_ / 16 / WM_, P_ / 16 / (4 / WM_), KS_, NP_>), grid, dim3(256 * KS_), 0, s, a); \
         return hipGetLastError();                                                                                   \
     }
-    TDC_CASE(128, 64, 4, 1) TDC_CASE(64, 64, 2, 1) TDC_CASE(64, 64, 2, 2) TDC_CASE(128, 64, 4, 2)
+    TDC_CASE(128, 64, 4, 1, 2) TDC_CASE(64, 64, 2, 1, 2) TDC_CASE(64, 64, 2, 2, 2) TDC_CASE(128, 64, 4, 2, 2)
+    TDC_CASE(128, 64, 4, 1, 3) TDC_CASE(64, 64, 2, 1, 3) TDC_CASE(64, 64, 2, 2, 3) TDC_CASE(128, 64, 4, 2, 3)
 #undef TDC_CASE
     return hipErrorInvalidValue;
 }
@@ -469,19 +504,20 @@ bool tdc_tile_applies(const TdcDims &d)
 {
     constexpr int tp = 64;
     const size_t img = (size_t)d.C * d.H * d.W * 4, P = (size_t)d.Ho * d.Wo;
-    const size_t w = tdc_packed3_bytes(d.NB2, d.K * d.K * d.NB1);
+    const size_t w = tdc_split_alloc_bytes(3, d.NB2, d.K * d.K * d.NB1);
     return ((tp - 1) / P + 2) * img < (1ull << 31) && w < (1ull << 31) && (size_t)d.B * P < (1ull << 31) - 1024;
 }
 
-hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipStream_t s, const float *x, const void *w3, float *y, const TdcEpi &epi)
+hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipStream_t s, const float *x, const void *w, float *y, const TdcEpi &epi)
 {
     TileArgs a;
-    a.act = x; a.w3 = w3; a.out = y; a.epi = epi;
+    a.act = x; a.w = w; a.out = y; a.epi = epi;
     a.C = d.C; a.HW = d.H * d.W; a.M = d.N; a.P = d.Ho * d.Wo; a.Ptot = d.B * a.P;
     a.NBm = d.NB2; a.NBk = d.NB1; a.KG = d.K * d.K * d.NB1; a.S = (a.KG + 1) / 2;
     a.H = d.H; a.W = d.W; a.Wo = d.Wo; a.K = d.K; a.stride = d.stride; a.pad = d.pad;
     a.n_mt = (d.N + tm - 1) / tm; a.n_pt = (a.Ptot + tp - 1) / tp;
-    const size_t w_bytes = tdc_packed3_bytes(a.NBm, a.KG);
+    const int parts = tdc_tile_parts(d);
+    const size_t w_bytes = tdc_split_bytes(parts, a.NBm, a.KG);
     a.w_bytes = (unsigned)w_bytes;
     a.pt_major = w_bytes < (size_t)d.B * a.C * a.HW * 4;
     a.vec = !d.nhwc && a.P % 4 == 0 && (((uintptr_t)y | (uintptr_t)epi.residual) & 15u) == 0;
@@ -489,6 +525,6 @@ hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipSt
     a.div_NBk = tdc_make_div((unsigned)a.NBk); a.div_K = tdc_make_div((unsigned)a.K);
     a.div_inner = tdc_make_div((unsigned)(a.pt_major ? a.n_mt : a.n_pt));
     const bool conv = d.K > 1 || d.stride > 1 || d.pad > 0;
-    if (d.nhwc) return conv ? launch_act<TDC_ACT_NHWC, true>(a, tm, tp, ks, s) : launch_act<TDC_ACT_NHWC, false>(a, tm, tp, ks, s);
-    return conv ? launch_act<TDC_ACT_NCHW, true>(a, tm, tp, ks, s) : launch_act<TDC_ACT_NCHW, false>(a, tm, tp, ks, s);
+    if (d.nhwc) return conv ? launch_act<TDC_ACT_NHWC, true>(a, tm, tp, ks, parts, s) : launch_act<TDC_ACT_NHWC, false>(a, tm, tp, ks, parts, s);
+    return conv ? launch_act<TDC_ACT_NCHW, true>(a, tm, tp, ks, parts, s) : launch_act<TDC_ACT_NCHW, false>(a, tm, tp, ks, parts, s);
 }
