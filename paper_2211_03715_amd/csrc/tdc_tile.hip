@@ -18,7 +18,7 @@
 // contiguous ones); this one without the interleaving 42.8 us, as it stands 39.8 us (fp32 MFMA kernel: 90.5 us).  On large
 // products it runs at 209 TFLOP/s of fp32 products, 1250 of bf16 ones -- what the vendor's bf16 GEMM of 8192^3 reaches on
 // the card (1241): power, not issue, is the limit there (all-zero operands: 273 TFLOP/s).
-#include <cmath>
+#include <algorithm>
 
 #include "tdc_split.h"
 #include "tdc_internal.h"
@@ -37,6 +37,7 @@ struct TileArgs {
     int NBm, NBk, KG, S;    // 16-blocks of M; k-groups per tap; k-groups in all; steps
     int H, W, Wo, K, stride, pad;
     int n_mt, n_pt, pt_major;
+    int per, n_mg;          // 1x1: channel tiles of a workgroup, workgroups that share a pixel tile
     int vec;                // NCHW out: quads of pixels lie in one image and 16-byte aligned
     unsigned w_bytes;
     TdcDiv div_P, div_Wo, div_NBk, div_K, div_inner;
@@ -147,6 +148,43 @@ __device__ __forceinline__ unsigned tile_redo(const TileArgs &a, bool small, int
                 for (int i = 0; i < 4; ++i) nans |= acc[mb][pb][i] != acc[mb][pb][i] ? 1u << ((mb * PB + pb) * 4 + i) : 0u;
     }
     return nans;
+}
+
+// Whether a thread, in NHWC the eight that share a pixel, brought a pixel of nothing but values too small for all their bits.
+template <bool NHWC, int NPIX>
+__device__ __forceinline__ bool tile_too_small(const float (&x_top)[NPIX], int x_exp)
+{
+    unsigned smallest = ~0u;
+#pragma unroll
+    for (int i = 0; i < NPIX; ++i) {
+        unsigned u = __builtin_bit_cast(unsigned, x_top[i]);
+        if (NHWC) {
+            u = max(u, (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0xb1, 0xf, 0xf, true));      // quad_perm 1 0 3 2
+            u = max(u, (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0x4e, 0xf, 0xf, true));      // quad_perm 2 3 0 1
+            u = max(u, (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0x141, 0xf, 0xf, true));     // the other half of eight
+        }
+        smallest = tdc_smallest(smallest, __builtin_bit_cast(float, u));
+    }
+    return tdc_any_lane(tdc_is_small(smallest, tdc_exp2i(max(TDC_LOWEST - x_exp, -126))));
+}
+
+// Four pixels of NCHW channel m, from pixel p on, that cannot be stored at once: sums and bias in v, shortcut and ReLU here.
+__device__ __forceinline__ void tile_store_4(const TileArgs &a, tdc_f4 v, int p, int m)
+{
+    if (p >= a.Ptot) return;
+    int b = tdc_div(p, a.div_P), pix = p - b * a.P;
+#pragma unroll
+    for (int i = 0; i < 4; ++i, ++pix) {
+        if (p + i >= a.Ptot) break;
+        while (pix >= a.P) {
+            pix -= a.P;
+            ++b;
+        }
+        const size_t idx = ((size_t)b * a.M + m) * a.P + pix;
+        float u = v[i];
+        if (a.epi.residual) u += a.epi.residual[idx];
+        a.out[idx] = a.epi.relu ? fmaxf(u, 0.f) : u;
+    }
 }
 
 // Wavefronts per SIMD an instance has registers for.
@@ -363,20 +401,7 @@ __global__ __launch_bounds__(256 * KS, tile_wavefronts(MB * PB, NP)) void tdc_ti
             if (!more) break;
         }
     }
-    {   // pixels of which this thread, in NHWC the eight that share one, brought nothing but values too small
-        unsigned smallest = ~0u;
-#pragma unroll
-        for (int i = 0; i < NPIX; ++i) {
-            unsigned u = __builtin_bit_cast(unsigned, x_top[i]);
-            if (ACT == TDC_ACT_NHWC) {
-                u = max(u, (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0xb1, 0xf, 0xf, true));      // quad_perm 1 0 3 2
-                u = max(u, (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0x4e, 0xf, 0xf, true));      // quad_perm 2 3 0 1
-                u = max(u, (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0x141, 0xf, 0xf, true));     // the other half of eight
-            }
-            smallest = tdc_smallest(smallest, __builtin_bit_cast(float, u));
-        }
-        small_all[4 * ks + wave] = tdc_any_lane(tdc_is_small(smallest, tdc_exp2i(max(TDC_LOWEST - x_exp, -126))));
-    }
+    small_all[4 * ks + wave] = tile_too_small<ACT == TDC_ACT_NHWC, NPIX>(x_top, x_exp);
     tdc_f4 acc[MB][PB];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
@@ -450,19 +475,7 @@ __global__ __launch_bounds__(256 * KS, tile_wavefronts(MB * PB, NP)) void tdc_ti
             *reinterpret_cast<tdc_f4 *>(a.out + idx) = v;
             return;
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (p + i >= a.Ptot) break;
-            int bi = b, pi = pix + i;
-            while (pi >= a.P) {
-                pi -= a.P;
-                ++bi;
-            }
-            const size_t idx = ((size_t)bi * a.M + m) * a.P + pi;
-            float u = v[i] + bias;
-            if (a.epi.residual) u += a.epi.residual[idx];
-            a.out[idx] = a.epi.relu ? fmaxf(u, 0.f) : u;
-        }
+        tile_store_4(a, v + (tdc_f4){bias, bias, bias, bias}, p, m);
     };
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
@@ -480,6 +493,217 @@ __global__ __launch_bounds__(256 * KS, tile_wavefronts(MB * PB, NP)) void tdc_ti
     }
 }
 
+// ---- 1x1 layers whose whole contraction fits in LDS
+//
+// A workgroup brings its 64 pixels once, all channels, split, into LDS, and then runs over `per` tiles of 64 MB output channels: no
+// barrier between them, weights one step ahead across the tiles, bias and shortcut of a tile in flight under its products.
+template <int ACT, int MB, int NP>
+__global__ __launch_bounds__(256, MB == 2 ? 2 : 3) void tdc_tile_1x1_kernel(TileArgs a)
+{
+    constexpr bool NHWC = ACT == TDC_ACT_NHWC, SWAP = !NHWC;
+    constexpr int PB = 4, TP = 16 * PB, PITCH = TP + 4, NX = 2, NM = TdcProducts<NP>::N, CHUNK = 4;
+    constexpr int STEP = 4 * NP * PITCH;               // 16-byte cells of a step: [part][lane group][pixel]
+    extern __shared__ tdc_u4 tile_1x1_lds[];
+    tdc_u4 *__restrict__ xs = tile_1x1_lds + 2;        // behind four first magnitudes and four flags
+    unsigned *__restrict__ first_all = reinterpret_cast<unsigned *>(tile_1x1_lds), *__restrict__ small_all = first_all + 4;
+    const int t = threadIdx.x, lane = t & 63, g = lane >> 4, l16 = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int lb = tile_logical_block(blockIdx.x, gridDim.x);
+    const int pt = tdc_div(lb, a.div_inner), mt0 = (lb - pt * a.n_mg) * a.per, mt1 = min(mt0 + a.per, a.n_mt);
+    const int p_tile = pt * TP;
+    const int b0 = tdc_div(p_tile, a.div_P);
+    const size_t img_elems = (size_t)a.C * a.HW;
+    const int n_img = min((TP - 1) / a.P + 2, tdc_div(a.Ptot - 1, a.div_P) + 1 - b0);
+    const tdc_rsrc ars = tdc_make_rsrc(a.act + (size_t)b0 * img_elems, (unsigned)(n_img * img_elems * 4));
+    const tdc_rsrc wrs = tdc_make_rsrc(a.w, a.w_bytes + 64u * a.NBm);       // with the exponents
+
+    const auto fetch_w = [&](int mt, int step, tdc_op<NP>(&w)[MB]) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            const int blk = (mt * 4 + wave) * MB + mb;
+            const unsigned o = blk < a.NBm && mt < mt1 ? (unsigned)(blk * a.S + step) * (1024u * NP) + lane * 16u : TDC_OOB;
+#pragma unroll
+            for (int q = 0; q < NP; ++q) w[mb].p[q] = __builtin_bit_cast(tdc_h8, tdc_buf_load4(wrs, o + q * 1024u));
+        }
+    };
+    tdc_op<NP> w0[MB];
+    fetch_w(mt0, 0, w0);
+
+    // ---- the pixels: NHWC: a thread brings four channels of one pixel in 8 of each, NCHW: 4 NX channels of one pixel
+    int x_exp;
+    {
+        constexpr int NPIX = NHWC ? NX : 1;
+        const int c4 = t & 7, nq = t / TP;
+        unsigned poff[NPIX];
+#pragma unroll
+        for (int i = 0; i < NPIX; ++i) {
+            const int p = p_tile + (NHWC ? (t >> 3) + 32 * i : t % TP);
+            const int b = tdc_div(p < a.Ptot ? p : p_tile, a.div_P), pix = p - b * a.P;
+            poff[i] = p < a.Ptot ? (unsigned)((b - b0) * (int)img_elems + (NHWC ? pix * a.C + 4 * c4 : pix + 2 * NX * nq * a.HW)) * 4u : TDC_OOB;
+        }
+        const auto fetch_x = [&](int step, tdc_f4(&x)[NX]) {
+            const unsigned dead = (unsigned)(a.S - 1 - step) & TDC_OOB;
+            if (NHWC) {
+                const unsigned bad = dead | ((unsigned)(a.C - 1 - 32 * step - 4 * c4) & TDC_OOB);
+#pragma unroll
+                for (int i = 0; i < NX; ++i) x[i] = tdc_buf_load4(ars, (poff[i] + 128u * step) | bad | (poff[i] & TDC_OOB));
+            } else {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int c = 32 * step + 16 * h, left = a.C - 1 - c - 2 * NX * nq;   // this thread's last channel that exists
+                    const unsigned o = (poff[0] + (unsigned)(c * a.HW) * 4u) | dead | (poff[0] & TDC_OOB);
+#pragma unroll
+                    for (int n = 0; n < NX / 2; ++n)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            x[2 * n + h][j] = tdc_buf_load(ars, (o + (unsigned)((4 * n + j) * a.HW) * 4u) | ((o | (unsigned)(left - 4 * n - j)) & TDC_OOB));
+                }
+            }
+        };
+        float x_top[NPIX] = {};
+        const auto to_lds = [&](const tdc_f4(&x)[NX], const TdcScale &scale, int step) {
+            if (step >= a.S) return;
+            tdc_u4 *__restrict__ xb = xs + step * STEP;
+#pragma unroll
+            for (int i = 0; i < NX; ++i) {
+                x_top[i % NPIX] = tdc_largest(x_top[i % NPIX], x[i]);
+                if (NHWC) {
+                    tdc_u2 *__restrict__ x2 = reinterpret_cast<tdc_u2 *>(xb);
+                    tdc_u2 s[NP];
+                    tdc_split4<NP>(x[i], scale, s);
+#pragma unroll
+                    for (int q = 0; q < NP; ++q) x2[((q * 4 + (c4 & 3)) * PITCH + (t >> 3) + 32 * i) * 2 + (c4 >> 2)] = s[q];
+                } else if (i % 2) {
+                    const tdc_op<NP> o = tdc_split_op<NP>(x[i - 1], x[i], scale);
+#pragma unroll
+                    for (int q = 0; q < NP; ++q) xb[(q * 4 + nq * (NX / 2) + i / 2) * PITCH + t % TP] = __builtin_bit_cast(tdc_u4, o.p[q]);
+                }
+            }
+        };
+        tdc_f4 x[CHUNK][NX];
+#pragma unroll
+        for (int u = 0; u < CHUNK; ++u) fetch_x(u, x[u]);
+        float m = 0.f;
+#pragma unroll
+        for (int u = 0; u < CHUNK; ++u)
+#pragma unroll
+            for (int n = 0; n < NX; ++n) m = tdc_largest(m, x[u][n]);
+        first_all[wave] = tdc_wave_max(m);
+        __syncthreads();
+        const tdc_u4 first = tile_1x1_lds[0];
+        x_exp = tdc_scale_of((unsigned)__builtin_amdgcn_readfirstlane((int)max(max(first[0], first[1]), max(first[2], first[3]))), TDC_X_TARGET, TDC_X_OTHER);
+        const TdcScale scale(x_exp);
+        for (int s = 0; s < a.S; s += CHUNK) {
+#pragma unroll
+            for (int u = 0; u < CHUNK; ++u) {
+                to_lds(x[u], scale, s + u);
+                if (s + CHUNK < a.S) fetch_x(s + CHUNK + u, x[u]);
+            }
+        }
+        small_all[wave] = tile_too_small<NHWC, NPIX>(x_top, x_exp);
+    }
+    __syncthreads();
+    const tdc_u4 flags = tile_1x1_lds[1];
+    const bool small = __builtin_amdgcn_readfirstlane((int)(flags[0] | flags[1] | flags[2] | flags[3])) != 0;
+
+    // ---- where this lane's outputs are: NHWC: channels 4g.. of pixel l16 of block pb, NCHW: pixels 4g.. of channel l16
+    // (bytes from the tile's first pixel or image on; two images, or what a tile spans of smaller ones, are below 4 GiB)
+    constexpr unsigned NOWHERE = ~0u;
+    const size_t base = NHWC ? (size_t)p_tile * a.M : (size_t)b0 * a.M * a.P;
+    char *__restrict__ out = reinterpret_cast<char *>(a.out + base);
+    const char *__restrict__ shortcut = reinterpret_cast<const char *>(a.epi.residual + base);
+    unsigned out_at[PB];
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) {
+        const int p = p_tile + 16 * pb + (NHWC ? l16 : 4 * g);
+        const int b = tdc_div(p, a.div_P);
+        out_at[pb] = p >= a.Ptot ? NOWHERE : 4u * (NHWC ? (unsigned)((p - p_tile) * a.M) : (unsigned)(b - b0) * (unsigned)(a.M * a.P) + (unsigned)(p - b * a.P));
+    }
+    const bool quads = NHWC || a.vec;                  // outputs go out, and shortcuts come in, 16 bytes at a time
+    for (int mt = mt0; mt < mt1; ++mt) {
+        const int blk0 = (mt * 4 + wave) * MB;
+        // exponents, bias and shortcut of this tile, under its products
+        tdc_u4 e[MB];
+        tdc_f4 bias[MB], res[MB][PB];
+        const bool with_res = quads && a.epi.residual;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            const int m = 16 * (blk0 + mb) + (NHWC ? 4 * g : l16);
+            const bool live = m < a.M;
+            if (NHWC) {
+                e[mb] = __builtin_bit_cast(tdc_u4, tdc_buf_load4(wrs, live ? a.w_bytes + 4u * m : TDC_OOB));
+                bias[mb] = a.epi.bias && live ? (tdc_f4){a.epi.bias[m], a.epi.bias[m + 1], a.epi.bias[m + 2], a.epi.bias[m + 3]} : tdc_f4_zero();
+            } else {
+                e[mb][0] = __builtin_amdgcn_raw_buffer_load_b32(wrs, (int)(live ? a.w_bytes + 4u * m : TDC_OOB), 0, 0);
+                bias[mb][0] = a.epi.bias && live ? a.epi.bias[m] : 0.f;
+            }
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb)
+                res[mb][pb] = with_res && live && out_at[pb] != NOWHERE ? *reinterpret_cast<const tdc_f4 *>(shortcut + (out_at[pb] + 4u * (NHWC ? m : m * a.P))) : tdc_f4_zero();
+        }
+        tdc_f4 lev[MB][PB][NP];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+                for (int q = 0; q < NP; ++q) lev[mb][pb][q] = tdc_f4_zero();
+        for (int s = 0; s < a.S; ++s) {
+            tdc_op<NP> w1[MB];
+            const bool turn = s + 1 == a.S;
+            fetch_w(turn ? mt + 1 : mt, turn ? 0 : s + 1, w1);
+            const tdc_u4 *__restrict__ xb = xs + s * STEP;
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb) {
+                tdc_op<NP> b;
+#pragma unroll
+                for (int q = 0; q < NP; ++q) b.p[q] = __builtin_bit_cast(tdc_h8, xb[(q * 4 + g) * PITCH + 16 * pb + l16]);
+#pragma unroll
+                for (int i = 0; i < NM; ++i)
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb) {
+                        tdc_f4 &c = lev[mb][pb][TdcProducts<NP>::level[i]];
+                        c = tdc_mfma_part<NP, SWAP>(i, w0[mb].p, b.p, c);
+                    }
+            }
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) w0[mb] = w1[mb];
+        }
+        float largest = 0.f;
+        tdc_f4 acc[MB][PB];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb) {
+                acc[mb][pb] = tdc_levels<NP>(lev[mb][pb]);
+                largest = tdc_largest(largest, acc[mb][pb]);
+            }
+        bool redone = false;
+        if (__builtin_expect(small || tdc_any_lane(!tdc_finite(largest)), 0))
+            tile_redo<ACT, false, MB, PB>(tdc_args_again<TileArgs>(), small, lane, p_tile, blk0, acc, redone);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            const int m = 16 * (blk0 + mb) + (NHWC ? 4 * g : l16);
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb) {
+                tdc_f4 v = acc[mb][pb];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    v[i] = redone ? v[i] : ldexpf(v[i], -x_exp - (int)e[mb][NHWC ? i : 0]);
+                    v[i] += bias[mb][NHWC ? i : 0];
+                    v[i] += res[mb][pb][i];
+                }
+                if (quads) {
+                    if (a.epi.relu) v = (tdc_f4){fmaxf(v[0], 0.f), fmaxf(v[1], 0.f), fmaxf(v[2], 0.f), fmaxf(v[3], 0.f)};
+                    if (m < a.M && out_at[pb] != NOWHERE) *reinterpret_cast<tdc_f4 *>(out + (out_at[pb] + 4u * (NHWC ? m : m * a.P))) = v;
+                } else if (m < a.M) {
+                    tile_store_4(a, v, p_tile + 16 * pb + 4 * g, m);
+                }
+            }
+        }
+    }
+}
+
 template <int ACT, bool CONV>
 hipError_t launch_act(const TileArgs &a, int tm, int tp, int ks, int parts, hipStream_t s)
 {
@@ -493,6 +717,43 @@ hipError_t launch_act(const TileArgs &a, int tm, int tp, int ks, int parts, hipS
     TDC_CASE(128, 64, 4, 1, 3) TDC_CASE(64, 64, 2, 1, 3) TDC_CASE(64, 64, 2, 2, 3) TDC_CASE(128, 64, 4, 2, 3)
 #undef TDC_CASE
     return hipErrorInvalidValue;
+}
+
+// LDS of the 1x1 kernel, and the most that still leaves two workgroups on a compute unit.
+size_t tile_1x1_lds_bytes(int steps, int parts) { return 32 + (size_t)steps * parts * 4 * 68 * 16; }
+constexpr size_t TILE_1X1_LDS = 80 * 1024;
+
+// Channel tiles a workgroup takes: the share with the shortest schedule, in channel tiles of one workgroup.  Bringing the pixels
+// costs 0.3 of one; a compute unit works on `slots` workgroups at a time (registers, LDS); fewer than that at the end leave it
+// partly idle, a lone one for 1.6 times its work.  us for shares of 1 / 2 / 4 / 8: 128 -> 512 at 28x28, batch 32: 38.3 / 37.4 /
+// 42.0 / 37.3; 256 -> 1024 at 14x14: 25.0 / 21.5 / 28.2 / 48.4; 64 -> 256 at 56x56: 67.3 / 62.7 / 63.2 (four are all).
+int tile_1x1_share(int n_pt, int n_mt, int mb, size_t lds)
+{
+    constexpr int cus = 256;
+    const int slots = std::min(mb == 2 ? 2 : 3, (int)(160 * 1024 / lds));
+    int best = 1;
+    double best_time = 1e300;
+    for (int per = 1; per <= n_mt; ++per) {
+        const long wgs = (long)n_pt * ((n_mt + per - 1) / per), rounds = wgs / (cus * slots), rest = (wgs - rounds * cus * slots + cus - 1) / cus;
+        const double time = (per + 0.3) * (rounds * slots + (rest ? std::max(1.6, (double)rest) : 0.0));
+        if (time < best_time) {
+            best = per;
+            best_time = time;
+        }
+    }
+    return best;
+}
+
+template <int ACT>
+hipError_t launch_1x1(const TileArgs &a, int mb, int parts, hipStream_t s)
+{
+    const dim3 grid((unsigned)(a.n_pt * a.n_mg));
+    const size_t lds = tile_1x1_lds_bytes(a.S, parts);
+    const auto kernel = parts == 3 ? tdc_tile_1x1_kernel<ACT, 1, 3> : mb == 1 ? tdc_tile_1x1_kernel<ACT, 1, 2> : tdc_tile_1x1_kernel<ACT, 2, 2>;
+    const hipError_t e = tdc_allow_lds((const void *)kernel, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, grid, dim3(256), lds, s, a);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -525,6 +786,14 @@ hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipSt
     a.div_NBk = tdc_make_div((unsigned)a.NBk); a.div_K = tdc_make_div((unsigned)a.K);
     a.div_inner = tdc_make_div((unsigned)(a.pt_major ? a.n_mt : a.n_pt));
     const bool conv = d.K > 1 || d.stride > 1 || d.pad > 0;
+    if (!conv && ks == 1 && tile_1x1_lds_bytes(a.S, parts) <= TILE_1X1_LDS) {
+        const int mb = parts == 3 ? 1 : tm / 64;
+        a.n_mt = (d.N + 64 * mb - 1) / (64 * mb);
+        a.per = tile_1x1_share(a.n_pt, a.n_mt, mb, tile_1x1_lds_bytes(a.S, parts));
+        a.n_mg = (a.n_mt + a.per - 1) / a.per;
+        a.div_inner = tdc_make_div((unsigned)a.n_mg);
+        return d.nhwc ? launch_1x1<TDC_ACT_NHWC>(a, mb, parts, s) : launch_1x1<TDC_ACT_NCHW>(a, mb, parts, s);
+    }
     if (d.nhwc) return conv ? launch_act<TDC_ACT_NHWC, true>(a, tm, tp, ks, parts, s) : launch_act<TDC_ACT_NHWC, false>(a, tm, tp, ks, parts, s);
     return conv ? launch_act<TDC_ACT_NCHW, true>(a, tm, tp, ks, parts, s) : launch_act<TDC_ACT_NCHW, false>(a, tm, tp, ks, parts, s);
 }
