@@ -1,5 +1,6 @@
 // CHAIN on the fp16 matrix cores, host side: which shapes it covers, its tile geometry, and the launch.  The kernel is in
 // tdc_chain3_kernel.h; its instances are compiled in tdc_chain3_nchw.hip, tdc_chain3_runs.hip and tdc_chain3_nhwc.hip.
+#include <algorithm>
 #include <cmath>
 
 #include "tdc_chain3_kernel.h"
@@ -38,7 +39,7 @@ TdcFusedGeom tdc_chain3_geometry(const TdcDims &d, int tile_h, int tile_w, int p
     g.pitch2 = 0;
     g.weights_in_lds = g.weights_fit = false;
     g.lds_bytes = sizeof(Chain3Shared) + (size_t)32 * tdc_chain3_parts(d) * d.NB1 * g.pitch1;
-    if (pb > 0 && tdc_chain3_share((g.PBk + pb - 1) / pb)) g.lds_bytes += (size_t)TDC_CHAIN3_WAVES * d.NB2 * pb * 1024;
+    if (pb > 0) g.lds_bytes += tdc_chain3_share((g.PBk + pb - 1) / pb) ? (size_t)TDC_CHAIN3_WAVES * d.NB2 * pb * 1024 : (size_t)2048 * chain3_feed_pieces(d.NB2, tdc_chain3_parts(d));
     return g;
 }
 
@@ -56,12 +57,13 @@ hipError_t tdc_launch_chain3(const TdcDims &d, const tdc_tuning &t, const TdcFus
     const int lay = d.nhwc ? TDC_LAY_NHWC : d.s1_runs ? TDC_LAY_NCHW_RUNS : TDC_LAY_NCHW;
     a.RPR = tdc_runs_per_row(d.W, d.Wo, g.TW, d.K, d.stride, d.pad);
     a.n_pg1 = lay == TDC_LAY_NCHW_RUNS ? (g.QH * a.RPR + 15) / 16 : (g.QB + 1) / 2;
-    a.n_mg1 = (d.NB1 + t.mb[0] - 1) / t.mb[0];
+    // channel blocks of a stage-1 unit; three in three parts would spill
+    const int parts = tdc_chain3_parts(d), mb1 = parts == 3 ? std::min(t.mb[0], 2) : t.mb[0];
+    a.n_mg1 = (d.NB1 + mb1 - 1) / mb1;
     a.tiles_x = g.tiles_x; a.tiles = g.tiles_x * g.tiles_y;
     a.xcd_per = (int)((long)a.tiles * d.B / 8); a.xcd_rem = (int)((long)a.tiles * d.B % 8);
     // rows of whole quads and a 16-byte aligned y; otherwise the same values go out as four 4-byte stores
     a.vec = g.TW % 4 == 0 && d.Wo % 4 == 0 && ((uintptr_t)y & 15u) == 0;
-    const int parts = tdc_chain3_parts(d);
     a.uin_bytes = (unsigned)tdc_split_bytes(parts, d.NB1, d.KG1);
     a.core_bytes = (unsigned)tdc_split_bytes(parts, d.NB2, a.KG2);
     a.uout_bytes = (unsigned)tdc_split_bytes(parts, d.NB3, d.NB2);
@@ -73,5 +75,5 @@ hipError_t tdc_launch_chain3(const TdcDims &d, const tdc_tuning &t, const TdcFus
     a.div_RPR = tdc_make_div((unsigned)a.RPR); a.div_mg1 = tdc_make_div((unsigned)a.n_mg1);
     const dim3 grid((unsigned)a.tiles, (unsigned)d.B);
     const auto launch = lay == TDC_LAY_NHWC ? tdc_launch_chain3_nhwc : lay == TDC_LAY_NCHW_RUNS ? tdc_launch_chain3_runs : tdc_launch_chain3_nchw;
-    return launch(a, d.NB2, t.pb[0], t.mb[0], parts, grid, g.lds_bytes, s, prepare_only);
+    return launch(a, d.NB2, t.pb[0], mb1, parts, grid, g.lds_bytes, s, prepare_only);
 }

@@ -58,16 +58,19 @@ struct Chain3Shared {
 };
 
 // Stage 1 for the workgroup.  RUNS: a lane owns runs of four consecutive pixels (see TdcStage1R), a unit is 16 runs.
-template <int LAY, int MB1, int NP>
+template <int LAY, int MB1, int NP, bool DEEP>
 struct Chain3Stage1 {
     static constexpr bool RUNS = LAY == TDC_LAY_NCHW_RUNS, NHWC = LAY == TDC_LAY_NHWC;
     static constexpr int PB = RUNS ? 4 : 2;
     static constexpr int NR = RUNS ? 8 : 2 * PB;      // 16-byte registers of x per step
+    // Depth 1 in lean runs: three workgroups to a compute unit instead of two overlap more than a step on its way (128 channels at
+    // 28x28, ranks 32, batch 256: 72.9 -> 66.7 us)
+    static constexpr int DEPTH = NP == 2 && DEEP && !RUNS && MB1 <= 2 ? 3 : NP == 2 && RUNS && !DEEP ? 1 : 2;         // steps in registers: the one being multiplied and those on their way
     const TdcChain3Args &a;
     tdc_rsrc xrs, urs;
     int lane, g, l16, wave, h0, w0, wa, n_units;
     int fu, fs, fmg;                                   // fetch cursor: unit, step, channel group of the unit
-    unsigned xoff[RUNS ? 1 : PB];
+    unsigned xoff[PB], woff[MB1];           // byte offsets of the unit's pixels (channel 4g) and weights, or out of range
     float x_top[PB];                                   // largest magnitude of x at this lane's pixels so far
     unsigned smallest = ~0u, smallest_x = ~0u;         // of the pixels' largest sums and of their largest x the smallest (tdc_smallest)
     int x_exp = 0;                                     // x is multiplied by 2^x_exp
@@ -105,40 +108,64 @@ struct Chain3Stage1 {
                 ok = q < a.Q;
             }
             ok = ok & live & ((unsigned)h < (unsigned)a.H) & ((unsigned)w < (unsigned)a.W);   // no branches in the pipeline
-            xoff[pb] = ok ? (unsigned)(h * a.W + w) * (NHWC ? 4u * a.C : 4u) : TDC_OOB;
+            xoff[pb] = (ok ? (unsigned)(h * a.W + w) * (NHWC ? 4u * a.C : 4u) : TDC_OOB) + (NHWC ? 16u * g : 16u * g * (unsigned)(a.H * a.W));
+        }
+#pragma unroll
+        for (int mb = 0; mb < MB1; ++mb) {
+            const int blk = fmg * MB1 + mb;
+            woff[mb] = live && blk < a.NB1 ? (unsigned)(blk * a.S1) * (1024u * NP) + lane * 16u : TDC_OOB;
         }
     }
-    // channels past C read 0: in NCHW they lie beyond the image's descriptor by themselves
+    __device__ __forceinline__ static tdc_f4 load4(tdc_rsrc r, unsigned off, unsigned soff)
+    {
+        return __builtin_bit_cast(tdc_f4, (tdc_u4)__builtin_amdgcn_raw_buffer_load_b128(r, (int)off, (int)soff, 0));
+    }
+    __device__ __forceinline__ static float load1(tdc_rsrc r, unsigned off, unsigned soff)
+    {
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, (int)soff, 0));
+    }
+    // Except in runs a step moves the scalar offset alone; where a last step goes past C, its lanes' offsets are checked one by
+    // one.  (NCHW channels past C lie beyond the descriptor by themselves, but only per-lane offsets are certain to be compared with it.)
     __device__ __forceinline__ void fetch(tdc_f4 (&x)[NR], tdc_op<NP> (&w)[MB1])
     {
-        const unsigned dead = fu < n_units ? 0u : TDC_OOB;
         const unsigned HW4 = (unsigned)(a.H * a.W) * 4u;
+        if (RUNS) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int c = 32 * fs + 16 * h + 4 * g;
-            if (RUNS) {
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    x[4 * h + j] = tdc_buf_load4(xrs, ((unsigned)(c + j) * HW4 + xoff[0]) | (xoff[0] & TDC_OOB));
-            } else {
+                for (int j = 0; j < 4; ++j) x[4 * h + j] = load4(xrs, ((unsigned)(32 * fs + 16 * h + j) * HW4 + xoff[0]) | (xoff[0] & TDC_OOB), 0);
+        } else if (32 * fs + 32 <= a.C) {
+            const unsigned s = (NHWC ? 128u : 32u * HW4) * fs;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
                 for (int pb = 0; pb < PB; ++pb) {
+                    tdc_f4 &v = x[(2 * pb + h) % NR];
+                    if (NHWC) v = load4(xrs, xoff[pb] + 64u * h, s);
+                    else v = (tdc_f4){load1(xrs, xoff[pb], s + 16 * h * HW4), load1(xrs, xoff[pb], s + (16 * h + 1) * HW4),
+                                      load1(xrs, xoff[pb], s + (16 * h + 2) * HW4), load1(xrs, xoff[pb], s + (16 * h + 3) * HW4)};
+                }
+        } else {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int c = 32 * fs + 16 * h;                  // the lane's are c + 4g ..
+                const auto past = [&](int j) { return c + 4 * g + j < a.C ? 0u : TDC_OOB; };
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb) {
+                    tdc_f4 &v = x[(2 * pb + h) % NR];
                     if (NHWC) {
-                        x[2 * pb + h] = tdc_buf_load4(xrs, (xoff[pb] + 4u * c) | (c < a.C ? 0u : TDC_OOB) | (xoff[pb] & TDC_OOB));
+                        v = load4(xrs, (xoff[pb] + 4u * c) | past(0) | (xoff[pb] & TDC_OOB), 0);
                     } else {
-                        const unsigned o = ((unsigned)c * HW4 + xoff[pb]) | (xoff[pb] & TDC_OOB);
-                        x[2 * pb + h] = (tdc_f4){tdc_buf_load(xrs, o), tdc_buf_load(xrs, o + HW4), tdc_buf_load(xrs, o + 2u * HW4), tdc_buf_load(xrs, o + 3u * HW4)};
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) v[j] = load1(xrs, ((unsigned)(c + j) * HW4 + xoff[pb]) | past(j) | (xoff[pb] & TDC_OOB), 0);
                     }
                 }
             }
         }
 #pragma unroll
-        for (int mb = 0; mb < MB1; ++mb) {
-            const int blk = fmg * MB1 + mb;
-            const unsigned o = ((unsigned)(blk * a.S1 + fs) * (1024u * NP) + lane * 16u) | dead | (blk < a.NB1 ? 0u : TDC_OOB);
+        for (int mb = 0; mb < MB1; ++mb)
 #pragma unroll
-            for (int q = 0; q < NP; ++q) w[mb].p[q] = __builtin_bit_cast(tdc_h8, tdc_buf_load4(urs, o + q * 1024u));
-        }
+            for (int q = 0; q < NP; ++q) w[mb].p[q] = __builtin_bit_cast(tdc_h8, load4(urs, woff[mb] + q * 1024u, fs * (1024u * NP)));
         if (++fs == a.S1) {
             fu += TDC_CHAIN3_WAVES;
             place();
@@ -210,13 +237,14 @@ struct Chain3Stage1 {
     }
     __device__ __forceinline__ void run(Chain3Shared &sh, tdc_u2 *__restrict__ z1s)
     {
-        tdc_f4 x0[NR], x1[NR], acc[MB1][PB][NP];
-        tdc_op<NP> wa0[MB1], wa1[MB1];
-        fetch(x0, wa0);
+        tdc_f4 x[DEPTH][NR], acc[MB1][PB][NP];
+        tdc_op<NP> w[DEPTH][MB1];
+#pragma unroll
+        for (int i = 0; i == 0 || i + 1 < DEPTH; ++i) fetch(x[i], w[i]);
         zero_outside(z1s);
         float m = 0.f;
 #pragma unroll
-        for (int i = 0; i < NR; ++i) m = tdc_largest(m, x0[i]);
+        for (int i = 0; i < NR; ++i) m = tdc_largest(m, x[0][i]);
         sh.first[wave] = tdc_wave_max(m);
         __syncthreads();
         const tdc_u4 first = *reinterpret_cast<const tdc_u4 *>(sh.first);
@@ -241,13 +269,13 @@ struct Chain3Stage1 {
             clear();
         };
         clear();
-        for (int i = 0; i < total; i += 2) {
-            fetch(x1, wa1);
-            multiply(acc, x0, wa0);
-            done();
-            fetch(x0, wa0);
-            if (i + 1 < total) {
-                multiply(acc, x1, wa1);
+        for (int i = 0; i < total; i += DEPTH) {
+#pragma unroll
+            for (int u = 0; u < DEPTH; ++u) {
+                if (i + u >= total) break;
+                if (DEPTH > 1) fetch(x[(u + DEPTH - 1) % DEPTH], w[(u + DEPTH - 1) % DEPTH]);
+                multiply(acc, x[u], w[u]);
+                if (DEPTH == 1) fetch(x[0], w[0]);
                 done();
             }
         }
@@ -297,49 +325,83 @@ struct Chain3Out {
         yrs = tdc_make_rsrc(a.y + (size_t)b * a.N * P2, (unsigned)a.N * P2 * 4u);
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) {
+            const int p0 = 16 * (group * PB + pb) + (NHWC ? l16 : 4 * g);
+            const int ph = tdc_div(p0, a.div_TW);
+            int pw = p0 - ph * a.TW, oi = at.i0 + ph;
+            if (NHWC) {
+                const int oj = at.j0 + pw;
+                ypix[pb] = (p0 < a.P && oi < a.Ho && oj < a.Wo) ? oi * a.Wo + oj : -1;
+            } else {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int p = 16 * (group * PB + pb) + 4 * g + i;
-                const int ph = tdc_div(p, a.div_TW), pw = p - ph * a.TW;
-                const int oi = at.i0 + ph, oj = at.j0 + pw;
-                yq[pb][i] = (p < a.P && oi < a.Ho && oj < a.Wo) ? (unsigned)(oi * a.Wo + oj) * 4u : TDC_OOB;
+                for (int i = 0; i < 4; ++i) {
+                    if (i && ++pw == a.TW) {
+                        pw = 0;
+                        ++oi;
+                    }
+                    yq[pb][i] = (p0 + i < a.P && oi < a.Ho && at.j0 + pw < a.Wo) ? (unsigned)(oi * a.Wo + at.j0 + pw) * 4u : TDC_OOB;
+                }
             }
-            const int p = 16 * (group * PB + pb) + l16;
-            const int ph = tdc_div(p, a.div_TW), pw = p - ph * a.TW;
-            const int oi = at.i0 + ph, oj = at.j0 + pw;
-            ypix[pb] = (p < a.P && oi < a.Ho && oj < a.Wo) ? oi * a.Wo + oj : -1;
         }
     }
-    // sums of output block nb, through the epilogue
-    template <bool EPI>
-    __device__ __forceinline__ void put(int nb, tdc_f4 (&acc3)[PB]) const
+    // What the epilogue reads for a lane's outputs of one block.  NCHW rows that allow no quads read their shortcut one by one,
+    // where it is added.
+    struct Epi {
+        float bias[NHWC ? 4 : 1];
+        tdc_f4 residual[PB];
+    };
+    __device__ __forceinline__ void fetch_epi(int nb, Epi &e) const
     {
+        const int n = 16 * nb + (NHWC ? 4 * g : l16);
+        const bool live = n < a.N;
+#pragma unroll
+        for (int i = 0; i < (NHWC ? 4 : 1); ++i) e.bias[i] = a.epi.bias && live ? a.epi.bias[n + i] : 0.f;
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) {
+            const bool ok = live && (NHWC ? ypix[pb] >= 0 : a.vec && !(yq[pb][0] & TDC_OOB));
+            const size_t cell = NHWC ? ((size_t)b * P2 + ypix[pb]) * a.N + n : ((size_t)b * a.N + n) * P2 + (yq[pb][0] >> 2);
+            e.residual[pb] = a.epi.residual && ok ? *reinterpret_cast<const tdc_f4 *>(a.epi.residual + cell) : tdc_f4_zero();
+        }
+    }
+    // sums of output block nb, through the epilogue; `e`: fetched before, or null
+    template <bool EPI>
+    __device__ __forceinline__ void put(int nb, tdc_f4 (&acc3)[PB], const Epi *e) const
+    {
+        if constexpr (EPI) {
+            Epi here;
+            if (!e) {
+                fetch_epi(nb, here);
+                e = &here;
+            }
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc3[pb][i] += e->bias[NHWC ? i : 0];
+                if (a.epi.residual) acc3[pb] += e->residual[pb];
+            }
+            if (!NHWC && !a.vec && a.epi.residual) {
+                const int n = 16 * nb + l16;
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (n < a.N && !(yq[pb][i] & TDC_OOB)) acc3[pb][i] += a.epi.residual[((size_t)b * a.N + n) * P2 + (yq[pb][i] >> 2)];
+            }
+            if (a.epi.relu) {
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc3[pb][i] = fmaxf(acc3[pb][i], 0.f);
+            }
+        }
         if (NHWC) {
             const int n = 16 * nb + 4 * g;
 #pragma unroll
             for (int pb = 0; pb < PB; ++pb)
-                if (ypix[pb] >= 0 && n < a.N) {
-                    const size_t cell = ((size_t)b * P2 + ypix[pb]) * a.N + n;
-                    if constexpr (EPI) tdc_store_nhwc<true>(a.y, a.epi, acc3[pb], n, cell);
-                    else tdc_store4_stream(reinterpret_cast<tdc_f4 *>(a.y + cell), acc3[pb]);
-                }
+                if (ypix[pb] >= 0 && n < a.N) tdc_store4_stream(reinterpret_cast<tdc_f4 *>(a.y + ((size_t)b * P2 + ypix[pb]) * a.N + n), acc3[pb]);
             return;
         }
         // channels past N lie beyond the descriptor: the hardware drops those stores
         const unsigned row = (unsigned)(16 * nb + l16) * P2 * 4u;
-        if constexpr (EPI) {
-            const int n = 16 * nb + l16;
-            const float bias = (a.epi.bias && n < a.N) ? a.epi.bias[n] : 0.f;
-#pragma unroll
-            for (int pb = 0; pb < PB; ++pb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float v = acc3[pb][i] + bias;
-                    if (a.epi.residual && n < a.N && !(yq[pb][i] & TDC_OOB))
-                        v += a.epi.residual[(size_t)b * a.N * P2 + (size_t)n * P2 + (yq[pb][i] >> 2)];
-                    acc3[pb][i] = a.epi.relu ? fmaxf(v, 0.f) : v;
-                }
-        }
         typedef unsigned u4 __attribute__((ext_vector_type(4)));
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) {
@@ -439,24 +501,66 @@ __device__ __forceinline__ void chain3_tile_fp32(const TdcChain3Args &a, tdc_u2 
                     for (int pb = 0; pb < PB; ++pb)
                         acc3[pb] = NHWC ? tdc_mfma(w[j], z2[kg][pb][j], acc3[pb]) : tdc_mfma(z2[kg][pb][j], w[j], acc3[pb]);
             }
-            out.template put<true>(nb, acc3);
+            out.template put<true>(nb, acc3, nullptr);
         }
     }
 }
+
+// Weights that all four wavefronts need, through LDS: chunks of N pieces of 1 KB (a 16-row block's fragment in one part), brought by
+// all of them, two chunks ahead in registers, double-buffered.  One fragment then comes through the L1 once per workgroup and
+// not once per wavefront: at the 26 to 32 bytes a cycle it delivers, that was the time of stages 2 and 3.
+constexpr int chain3_feed_pieces(int nb2, int np)            // of the larger of the two stages' chunks
+{
+    const int s3 = (nb2 + 1) / 2, t2 = nb2 == 1 ? 4 : nb2 == 2 ? 2 : 1, u3 = s3 == 1 ? 4 : s3 == 2 ? 2 : 1;
+    return np * (nb2 * t2 > s3 * u3 ? nb2 * t2 : s3 * u3);
+}
+template <int N>
+struct Chain3Feed {
+    static constexpr int MINE = (N + TDC_CHAIN3_WAVES - 1) / TDC_CHAIN3_WAVES;
+    tdc_f4 r[2][MINE];
+    // piece(k): byte offset of piece k of the chunk
+    template <class Piece>
+    __device__ __forceinline__ void load(int u, tdc_rsrc rs, int lane, int wave, Piece piece)
+    {
+#pragma unroll
+        for (int i = 0; i < MINE; ++i) {
+            const int k = wave + TDC_CHAIN3_WAVES * i;
+            if (N % TDC_CHAIN3_WAVES == 0 || k < N) r[u][i] = tdc_buf_load4(rs, piece(k) + lane * 16u);
+        }
+    }
+    __device__ __forceinline__ void put(int u, tdc_u4 *__restrict__ buf, int lane, int wave) const
+    {
+#pragma unroll
+        for (int i = 0; i < MINE; ++i) {
+            const int k = wave + TDC_CHAIN3_WAVES * i;
+            if (N % TDC_CHAIN3_WAVES == 0 || k < N) buf[k * 64 + lane] = __builtin_bit_cast(tdc_u4, r[u][i]);
+        }
+    }
+};
+
+// Not in the deep instances that read NCHW runs: one or two workgroups to a compute unit then wait for HBM in stage 1 and for their
+// stores in stage 3, and the barriers cost more than the shared fragments save (128 -> 256 at 56x56 stride 2, batch 32: 26.1
+// against 25.4 us; 128 channels at 28x28, ranks 32, batch 256: 72.7 -> 70.5 us).
+constexpr bool chain3_shares_weights(int lay, int nb2) { return !(lay == TDC_LAY_NCHW_RUNS && nb2 >= 3); }
+
+// Three and more z2 blocks: the layers whose tiles are large and few, one or two workgroups to a compute unit.  Their instances
+// spend the registers on more steps and output blocks on their way instead of on residency.
+constexpr bool chain3_deep(int nb2, int pb, int np) { return nb2 >= 3 && pb == 2 && np == 2; }
 
 // Wavefronts per SIMD an instance has registers for; the rarely run code must not cost one.
 constexpr int chain3_wavefronts(int nb2, int pb, int lay, int mb1, int np)
 {
     if (np == 3 && (pb > 2 || nb2 > 3)) return 1;
-    if (pb > 2) return 2;
-    if (nb2 <= 2) return np == 3 ? 2 : lay == TDC_LAY_NCHW_RUNS ? (mb1 == 1 ? 3 : 2) : mb1 <= 2 ? 4 : 3;
-    return nb2 == 3 && lay == TDC_LAY_NHWC && np == 2 ? 3 : 2;
+    if (pb > 2 || nb2 > 2) return 2;
+    return np == 3 ? 2 : lay == TDC_LAY_NCHW_RUNS ? (mb1 <= 2 ? 3 : 2) : lay == TDC_LAY_NHWC && mb1 <= 2 ? 4 : 3;
 }
 
-template <int NB2, int PB, int LAY, int MB1, int NP>
+// ALL: every wavefront has a group of pixel blocks of its own (lg_ks is 0)
+template <int NB2, int PB, int LAY, int MB1, int NP, bool ALL>
 __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, LAY, MB1, NP)) void tdc_chain3_kernel(TdcChain3Args a)
 {
     constexpr bool NHWC = LAY == TDC_LAY_NHWC, SWAP = !NHWC;
+    constexpr bool DEEP = chain3_deep(NB2, PB, NP);
     extern __shared__ tdc_u4 chain3_lds[];                       // Chain3Shared, z1 [NP parts][NB1][4][pitch1], the partial sums of ks > 1
     Chain3Shared &sh = *reinterpret_cast<Chain3Shared *>(chain3_lds);
     tdc_u2 *__restrict__ z1s = reinterpret_cast<tdc_u2 *>(chain3_lds + sizeof(Chain3Shared) / 16);
@@ -466,19 +570,25 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
     int x_exp;
     const Chain3Tile at(a);
     {
-        Chain3Stage1<LAY, MB1, NP> s1(a, lane, wave, at.b, at.i0 * a.stride - a.pad, at.j0 * a.stride - a.pad);
+        Chain3Stage1<LAY, MB1, NP, DEEP> s1(a, lane, wave, at.b, at.i0 * a.stride - a.pad, at.j0 * a.stride - a.pad);
         s1.run(sh, z1s);
         x_exp = s1.x_exp;
         bad = tdc_is_small(s1.smallest, tdc_exp2i(a.z1_exp + TDC_LOWEST)) || tdc_is_small(s1.smallest_x, tdc_exp2i(max(TDC_LOWEST - x_exp, -126)));
     }
-    __syncthreads();
 
     const int plane = a.NB1 * 4 * a.pitch1;                      // cells of one part
     const tdc_rsrc crs = tdc_make_rsrc(a.core, a.core_bytes + 64u * NB2), ors = tdc_make_rsrc(a.uout, a.uout_bytes + 64u * a.NB3);   // with the exponents
     // with fewer groups than wavefronts 2 or 4 of them share one: each takes a slice of stage 2's contraction, the sums meet in
-    // LDS, and each takes every ks-th output block of stage 3 (the loop then runs once for every wavefront)
-    const int ks = 1 << a.lg_ks, slice = wave & (ks - 1);
-    for (int pg = wave >> a.lg_ks; pg < a.n_pg2; pg += TDC_CHAIN3_WAVES) {
+    // LDS, and each takes every ks-th output block of stage 3 (the loop then runs once for every wavefront).  Else every
+    // wavefront has a group, all need the same weights, and share them.
+    const int lg_ks = ALL ? 0 : a.lg_ks, ks = 1 << lg_ks, slice = wave & (ks - 1);
+    constexpr int S3 = (NB2 + 1) / 2;
+    constexpr int T2 = NB2 == 1 ? 4 : NB2 == 2 ? 2 : 1, U3 = S3 == 1 ? 4 : S3 == 2 ? 2 : 1;    // steps, output blocks of a chunk
+    constexpr int PIECES = chain3_feed_pieces(NB2, NP);
+    tdc_u4 *__restrict__ feed = reinterpret_cast<tdc_u4 *>(z1s + NP * plane);                  // two chunks
+    for (int round = 0; round < a.n_pg2; round += TDC_CHAIN3_WAVES >> lg_ks) {
+        const int pg = round + (wave >> lg_ks);
+        const bool live = pg < a.n_pg2;
         // ---- stage 2: z2 channels 16*mb + 4*g + {0..3} of pixel l16 of block pb
         int qbase[PB];
         chain3_z1_base<PB>(a, pg, lane, qbase);
@@ -499,56 +609,105 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
                     for (int q = 0; q < NP; ++q)
                         w[mb].p[q] = __builtin_bit_cast(tdc_h8, tdc_buf_load4(crs, ((unsigned)(mb * a.S2 + step) * NP + q) * 1024u + lane * 16u));
             };
-            const int st0 = slice * a.S2 >> a.lg_ks, st1 = (slice + 1) * a.S2 >> a.lg_ks;
-            // next k-group: tap offset toff = r*QW + s, channel block dg
+            const int st0 = slice * a.S2 >> lg_ks, st1 = (slice + 1) * a.S2 >> lg_ks;
+            // cell of the next k-group: channel block dg of tap (r, s)
             int kg = 2 * st0;
-            const int tap = tdc_div(kg, a.div_NB1), r = tdc_div(tap, a.div_K);
-            int dg = kg - tap * a.NB1, s = tap - r * a.K, toff = r * a.QW + s;
+            const int tap = tdc_div(kg, a.div_NB1), r = tdc_div(tap, a.div_K), step_dg = 4 * a.pitch1, step_tap = 1 - a.NB1 * step_dg, step_row = a.QW - a.K;
+            int dg = kg - tap * a.NB1, s = tap - r * a.K, cell = dg * step_dg + r * a.QW + s;
             const auto next_cell = [&]() {
-                const int cell = dg * 4 * a.pitch1 + toff;
-                const bool w1 = dg + 1 == a.NB1;
-                dg = w1 ? 0 : dg + 1;
-                const int ns = s + (w1 ? 1 : 0);
-                const bool w2 = ns == a.K;
-                s = w2 ? 0 : ns;
-                toff += (w1 ? 1 : 0) + (w2 ? a.QW - a.K : 0);
+                const int here = cell;
                 ++kg;
-                return cell;
+                cell += step_dg;
+                if (++dg == a.NB1) {
+                    dg = 0;
+                    cell += step_tap;
+                    if (++s == a.K) {
+                        s = 0;
+                        cell += step_row;
+                    }
+                }
+                return here;
             };
-            const auto step2 = [&](const tdc_op<NP>(&w)[NB2]) {
-                const int lo = next_cell();
+            // z1 of the next step, one ahead of its products; past the last one any cell does
+            const auto read_z1 = [&](tdc_op<NP>(&o)[PB]) {
+                int lo = next_cell();
+                lo = kg <= a.KG2 ? lo : 0;
                 const bool whole = kg < a.KG2;                   // else the last half step, whose weights are zero: any finite cell does
                 const int nx = next_cell(), hi = whole ? nx : lo;
-                const auto read = [&](int pb) {
-                    tdc_op<NP> o;
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
                     for (int q = 0; q < NP; ++q) {
                         const tdc_u2 u = z1s[q * plane + lo + qbase[pb]], v = z1s[q * plane + hi + qbase[pb]];
-                        o.p[q] = __builtin_bit_cast(tdc_h8, (tdc_u4){u[0], u[1], v[0], v[1]});
+                        o[pb].p[q] = __builtin_bit_cast(tdc_h8, (tdc_u4){u[0], u[1], v[0], v[1]});
                     }
-                    return o;
-                };
-                tdc_op<NP> bb[2];
-                bb[0] = read(0);
+            };
+            const auto step2 = [&](const tdc_op<NP>(&w)[NB2], const tdc_op<NP>(&z)[PB]) {
 #pragma unroll
-                for (int pb = 0; pb < PB; ++pb) {
-                    if (pb + 1 < PB) bb[(pb + 1) & 1] = read(pb + 1);
+                for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
                     for (int i = 0; i < TdcProducts<NP>::N; ++i)
 #pragma unroll
                         for (int mb = 0; mb < NB2; ++mb) {
                             tdc_f4 &c = acc2[mb][pb][TdcProducts<NP>::level[i]];
-                            c = tdc_mfma_part<NP>(i, w[mb].p, bb[pb & 1].p, c);
+                            c = tdc_mfma_part<NP>(i, w[mb].p, z[pb].p, c);
                         }
-                }
             };
-            tdc_op<NP> wv0[NB2], wv1[NB2];
-            fetch_w(st0, wv0);
-            for (int st = st0; st < st1; st += 2) {
-                fetch_w(st + 1, wv1);
-                step2(wv0);
-                fetch_w(st + 2, wv0);
-                if (st + 1 < st1) step2(wv1);
+            tdc_op<NP> z[2][PB];
+            if constexpr (ALL) {
+                Chain3Feed<NB2 * T2 * NP> f;
+                const auto load = [&](int u, int chunk) {
+                    f.load(u, crs, lane, wave, [&](int k) {
+                        const int mb = k / (T2 * NP);
+                        return (unsigned)((mb * a.S2 + chunk * T2) * NP + k - mb * T2 * NP) * 1024u;
+                    });
+                };
+                load(0, 0);
+                load(1, 1);
+                __syncthreads();                                 // z1 is there, or the chunks of the last round are read
+                f.put(0, feed, lane, wave);
+                const int chunks = (a.S2 + T2 - 1) / T2;
+                const auto read_w = [&](int u, int t, tdc_op<NP>(&w)[NB2]) {
+#pragma unroll
+                    for (int mb = 0; mb < NB2; ++mb)
+#pragma unroll
+                        for (int q = 0; q < NP; ++q) w[mb].p[q] = __builtin_bit_cast(tdc_h8, feed[(u * PIECES + (mb * T2 + t) * NP + q) * 64 + lane]);
+                };
+                read_z1(z[0]);
+                for (int c = 0; c < chunks; c += 2) {
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        if (c + u >= chunks) break;
+                        __syncthreads();
+                        load(u, c + u + 2);
+#pragma unroll
+                        for (int t = 0; t < T2; ++t) {
+                            if (!live || (c + u) * T2 + t >= a.S2) break;
+                            tdc_op<NP> w[NB2];
+                            read_w(u, t, w);
+                            const int i = T2 == 1 ? u : t & 1;
+                            read_z1(z[1 - i]);
+                            step2(w, z[i]);
+                        }
+                        f.put(1 - u, feed + (1 - u) * PIECES * 64, lane, wave);
+                    }
+                }
+            } else {
+                constexpr int DEPTH = 2;
+                tdc_op<NP> w[DEPTH][NB2];
+#pragma unroll
+                for (int i = 0; i + 1 < DEPTH; ++i) fetch_w(st0 + i, w[i]);
+                __syncthreads();                                 // z1 is there
+                read_z1(z[0]);
+                for (int st = st0; st < st1; st += DEPTH) {
+#pragma unroll
+                    for (int u = 0; u < DEPTH; ++u) {
+                        if (st + u >= st1) break;
+                        fetch_w(st + u + DEPTH - 1, w[(u + DEPTH - 1) % DEPTH]);
+                        read_z1(z[1 - u]);
+                        step2(w[u], z[u]);
+                    }
+                }
             }
             // to a common scale
 #pragma unroll
@@ -580,17 +739,10 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
                 }
         }
         // ---- stage 3, operands swapped in NCHW: D[pixel 4*g + i][channel l16]; NHWC: D[channel 4*g + i][pixel l16]
-        constexpr int S3 = (NB2 + 1) / 2;
-        struct Weights {
-            tdc_op<NP> w[S3];
-            int e[NHWC ? 4 : 1];                                 // exponents of the lane's output channels
+        struct Exponents {
+            int e[NHWC ? 4 : 1];                                 // of the lane's output channels
         };
-        const auto fetch = [&](int nb, Weights &u) {
-#pragma unroll
-            for (int st = 0; st < S3; ++st)
-#pragma unroll
-                for (int q = 0; q < NP; ++q)
-                    u.w[st].p[q] = __builtin_bit_cast(tdc_h8, tdc_buf_load4(ors, ((unsigned)(nb * S3 + st) * NP + q) * 1024u + lane * 16u));
+        const auto fetch_e = [&](int nb, Exponents &u) {
             if constexpr (NHWC) {
                 const tdc_u4 e = __builtin_bit_cast(tdc_u4, tdc_buf_load4(ors, a.uout_bytes + (16u * nb + 4u * (lane >> 4)) * 4u));
 #pragma unroll
@@ -599,8 +751,25 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
                 u.e[0] = __builtin_amdgcn_raw_buffer_load_b32(ors, (int)(a.uout_bytes + (16u * nb + (lane & 15)) * 4u), 0, 0);
             }
         };
-        Weights u0, u1;
-        fetch(slice, u0);                                        // under the splitting of z2
+        const auto fetch = [&](int nb, tdc_op<NP>(&u)[S3]) {
+#pragma unroll
+            for (int st = 0; st < S3; ++st)
+#pragma unroll
+                for (int q = 0; q < NP; ++q)
+                    u[st].p[q] = __builtin_bit_cast(tdc_h8, tdc_buf_load4(ors, ((unsigned)(nb * S3 + st) * NP + q) * 1024u + lane * 16u));
+        };
+        // the first weights, under the splitting of z2
+        Chain3Feed<U3 * S3 * NP> f3;
+        const auto load3 = [&](int u, int chunk) {
+            f3.load(u, ors, lane, wave, [&](int k) { return (unsigned)(chunk * U3 * S3 * NP + k) * 1024u; });
+        };
+        tdc_op<NP> u0[S3], u1[S3];
+        if constexpr (ALL) {
+            load3(0, 0);
+            load3(1, 1);
+        } else {
+            fetch(slice, u0);
+        }
         float top = 0.f;                                         // largest magnitude of z2; a NaN above all
         unsigned smallest = ~0u;                                 // of the pixels' largest z2 values the smallest
 #pragma unroll
@@ -613,8 +782,8 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
             smallest = tdc_smallest(smallest, m);
         }
         const int z2_exp = tdc_scale_of(tdc_wave_max(top), TDC_Z2_TARGET, 0);
-        bad |= tdc_is_small(smallest, tdc_exp2i(max(TDC_LOWEST - z2_exp, -126)));
-        const int y_exp = a.z1_exp - z2_exp - x_exp;             // y is 2^(y_exp - exponent of the channel) times its sum
+        bad |= live && tdc_is_small(smallest, tdc_exp2i(max(TDC_LOWEST - z2_exp, -126)));
+        const int y_exp = a.z1_exp - z2_exp - x_exp;            // y is 2^(y_exp - exponent of the channel) times its sum
         tdc_op<NP> zb[S3][PB];
         {
             const TdcScale s(z2_exp);
@@ -627,7 +796,8 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
         const Chain3Out<PB, NHWC> out(a, at, pg, lane);
         float largest = 0.f;
         // two instances of the loop, as in tdc_chain_kernel.h: without epilogue loads nothing ever waits for the stores
-        const auto emit = [&](auto with_epi, int nb, const Weights &u) {
+        typedef typename Chain3Out<PB, NHWC>::Epi Epi;
+        const auto emit = [&](auto with_epi, int nb, const tdc_op<NP>(&u)[S3], const Exponents &e, const Epi *epi) {
             tdc_f4 acc3[PB][NP], v[PB];
 #pragma unroll
             for (int pb = 0; pb < PB; ++pb)
@@ -640,28 +810,68 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
 #pragma unroll
                     for (int pb = 0; pb < PB; ++pb) {
                         tdc_f4 &c = acc3[pb][TdcProducts<NP>::level[i]];
-                        c = tdc_mfma_part<NP, SWAP>(i, u.w[st].p, zb[st][pb].p, c);
+                        c = tdc_mfma_part<NP, SWAP>(i, u[st].p, zb[st][pb].p, c);
                     }
 #pragma unroll
             for (int pb = 0; pb < PB; ++pb) {
                 v[pb] = tdc_levels<NP>(acc3[pb]);
                 largest = tdc_largest(largest, v[pb]);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[pb][i] = ldexpf(v[pb][i], y_exp - u.e[NHWC ? i : 0]);
+                for (int i = 0; i < 4; ++i) v[pb][i] = ldexpf(v[pb][i], y_exp - e.e[NHWC ? i : 0]);
             }
-            out.template put<decltype(with_epi)::value>(nb, v);
+            out.template put<decltype(with_epi)::value>(nb, v, epi);
         };
         const auto stage3 = [&](auto with_epi) {
-            for (int nb = slice; nb < a.NB3; nb += 2 * ks) {
-                fetch(nb + ks, u1);
-                emit(with_epi, nb, u0);
-                fetch(nb + 2 * ks, u0);
-                if (nb + ks < a.NB3) emit(with_epi, nb + ks, u1);
+            // exponents, and in the deep instances bias and shortcut, one block ahead
+            constexpr bool AHEAD = DEEP && decltype(with_epi)::value;
+            Exponents ex[2];
+            Epi epi[2];
+            const auto ahead = [&](int nb, int i) {
+                fetch_e(nb, ex[i]);
+                if constexpr (AHEAD) out.fetch_epi(nb, epi[i]);
+            };
+            ahead(slice, 0);
+            if constexpr (ALL) {
+                __syncthreads();                                 // stage 2 has read its chunks
+                f3.put(0, feed, lane, wave);
+                const int chunks = (a.NB3 + U3 - 1) / U3;
+                for (int c = 0; c < chunks; c += 2) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        if (c + h >= chunks) break;
+                        __syncthreads();
+                        load3(h, c + h + 2);
+#pragma unroll 1
+                        for (int j = 0; j < U3; ++j) {
+                            const int nb = (c + h) * U3 + j;
+                            if (!live || nb >= a.NB3) break;
+                            ahead(nb + 1, 1);
+                            tdc_op<NP> w[S3];
+#pragma unroll
+                            for (int st = 0; st < S3; ++st)
+#pragma unroll
+                                for (int q = 0; q < NP; ++q) w[st].p[q] = __builtin_bit_cast(tdc_h8, feed[(h * PIECES + (j * S3 + st) * NP + q) * 64 + lane]);
+                            emit(with_epi, nb, w, ex[0], AHEAD ? &epi[0] : nullptr);
+                            ex[0] = ex[1];
+                            if constexpr (AHEAD) epi[0] = epi[1];
+                        }
+                        f3.put(1 - h, feed + (1 - h) * PIECES * 64, lane, wave);
+                    }
+                }
+            } else {
+                for (int nb = slice; nb < a.NB3; nb += 2 * ks) {
+                    fetch(nb + ks, u1);
+                    ahead(nb + ks, 1);
+                    emit(with_epi, nb, u0, ex[0], AHEAD ? &epi[0] : nullptr);
+                    fetch(nb + 2 * ks, u0);
+                    ahead(nb + 2 * ks, 0);
+                    if (nb + ks < a.NB3) emit(with_epi, nb + ks, u1, ex[1], AHEAD ? &epi[1] : nullptr);
+                }
             }
         };
         if (a.epi.bias || a.epi.residual || a.epi.relu) stage3(std::true_type{});
         else stage3(std::false_type{});
-        bad |= !tdc_finite(largest);
+        bad |= live && !tdc_finite(largest);
     }
     // One wavefront's trouble is the tile's: z1 is everybody's.
     sh.bad[wave] = tdc_any_lane(bad);
@@ -680,17 +890,19 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
 template <int LAY>
 hipError_t tdc_launch_chain3_lay(const TdcChain3Args &a, int nb2, int pb, int mb1, int parts, dim3 grid, size_t lds, hipStream_t s, bool prepare_only)
 {
-#define TDC_LAUNCH(N_, P_, M_, NP_)                                                                                    \
-    if (mb1 == M_ && parts == NP_) {                                                                                   \
-        hipError_t e = tdc_allow_lds((const void *)tdc_chain3_kernel<N_, P_, LAY, M_, NP_>, lds);                       \
+#define TDC_LAUNCH(N_, P_, M_, NP_, ALL_)                                                                              \
+    if (mb1 == M_ && parts == NP_ && (chain3_shares_weights(LAY, N_) && a.lg_ks == 0) == ALL_) {                                                         \
+        hipError_t e = tdc_allow_lds((const void *)tdc_chain3_kernel<N_, P_, LAY, M_, NP_, ALL_>, lds);                 \
         if (e != hipSuccess || prepare_only) return e;                                                                 \
-        hipLaunchKernelGGL((tdc_chain3_kernel<N_, P_, LAY, M_, NP_>), grid, dim3(64 * TDC_CHAIN3_WAVES), lds, s, a); \
+        hipLaunchKernelGGL((tdc_chain3_kernel<N_, P_, LAY, M_, NP_, ALL_>), grid, dim3(64 * TDC_CHAIN3_WAVES), lds, s, a); \
         return hipGetLastError();                                                                                      \
     }
 #define TDC_X(N_, P_)                                                                                                  \
     if (nb2 == N_ && pb == P_) {                                                                                       \
-        TDC_LAUNCH(N_, P_, 1, 2) TDC_LAUNCH(N_, P_, 2, 2) TDC_LAUNCH(N_, P_, 3, 2)                                     \
-        TDC_LAUNCH(N_, P_, 1, 3) TDC_LAUNCH(N_, P_, 2, 3) TDC_LAUNCH(N_, P_, 3, 3)                                     \
+        TDC_LAUNCH(N_, P_, 1, 2, true) TDC_LAUNCH(N_, P_, 2, 2, true) TDC_LAUNCH(N_, P_, 3, 2, true)                   \
+        TDC_LAUNCH(N_, P_, 1, 2, false) TDC_LAUNCH(N_, P_, 2, 2, false) TDC_LAUNCH(N_, P_, 3, 2, false)                \
+        TDC_LAUNCH(N_, P_, 1, 3, true) TDC_LAUNCH(N_, P_, 2, 3, true)                                                  \
+        TDC_LAUNCH(N_, P_, 1, 3, false) TDC_LAUNCH(N_, P_, 2, 3, false)                                                \
     }
     TDC_CHAIN3_UNITS(TDC_X)
 #undef TDC_X
