@@ -323,7 +323,9 @@ void chain3_terms(double (&f)[C_TERMS], const TdcDims &d, const TdcDeviceInfo &d
     const double c1 = S1 * (mb1 * pb1 * 96.0 + pb1 * 180.0 + 250.0);
     const double c23 = S2 * (d.NB2 * pb * 96.0 + 60.0) + d.NB3 * (S3 * pb * 96.0 + 60.0);
     const double per_cu = std::max(1.0, (double)g.tiles_x * g.tiles_y * d.B / dev.cus);
-    const int fit = std::max(1, std::min((int)(dev.lds_per_wg / std::max<size_t>(g.lds_bytes, 1)), 3));
+    // workgroups that share a compute unit, as the terms were set: by the LDS of three parts and the partial sums of shared groups
+    const size_t lds = (size_t)96 * d.NB1 * g.pitch1 + (tdc_chain3_share(u2) ? (size_t)4096 * d.NB2 * pb : 0);
+    const int fit = std::max(1, std::min((int)(dev.lds_per_wg / lds), 3));
     const int r = std::min(fit, (int)std::ceil(per_cu));
     const double chains = r == 1 ? std::ceil(per_cu) : (1.0 + 0.5 * (r - 1)) * std::max(1.0, per_cu / r);
     for (double &v : f) v = 0.0;
