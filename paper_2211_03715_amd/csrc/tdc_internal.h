@@ -102,6 +102,7 @@ inline bool tdc_is_tile(const tdc_tuning &t)
 }
 bool tdc_tile_supported(int tm, int tp, int ks);
 bool tdc_tile_applies(const TdcDims &d);
+bool tdc_tile_1x1_applies(const TdcDims &d);   // one group of wavefronts runs it with all its channels in LDS
 hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipStream_t s, const float *x, const void *w, float *y, const TdcEpi &epi);
 
 // stage 1, then stages 2 and 3 as one implicit GEMM with the merged kernel

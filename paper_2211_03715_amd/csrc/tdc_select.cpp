@@ -723,6 +723,13 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
             // workgroups spread them better below 8 tiles per compute unit (214x214 stride 2, 32 -> 80, batch 2: 6.5 against 10.3 us;
             // 63x63, 26 -> 104, batch 5: 6.5 against 9.2).
             const bool only_stores = !quads && d.K * d.K * d.NB1 <= 3 && tiles < 8.0 * dev.cus;
+            // 1x1 layers whose channels stay in LDS (tdc_tile_1x1_kernel) win from three tiles per four compute units on, which
+            // neither estimate knows: NHWC, 96 -> 200 at 40x40, batch 2: 6.5 -> 4.7 us, 128 -> 512 at 28x28, batch 2: 7.0 -> 5.4, 256 -> 96,
+            // batch 8: 8.7 -> 6.6; NCHW 6.6 -> 6.1 and 7.1 -> 6.2.  Below (64 -> 256 at 56x56, batch 1: 5.2 against 5.4; 256 -> 1024
+            // at 14x14, batch 2: 6.5 against 6.7) and up to 72 channels (three parts) the choice stays, and in NCHW beyond 192
+            // channels, all brought four bytes at a time before the first product (256 -> 64 at 56x56, batch 4: 7.9 against 8.7).
+            if (tdc_tile_1x1_applies(d) && d.R1 > 72 && d.R1 <= (d.nhwc ? 256 : 192) && fill > 0.5 && tiles >= 0.75 * dev.cus)
+                return tiled(tc.ks == 1 ? tc.tm : 64, 1, tc.us);
             if (!only_stores && tc.us < margin * c.us) return tiled(tc.tm, tc.ks, tc.us);
         }
         if (c.us >= 1e299) return TDC_ERR_BAD_TUNING;
@@ -808,7 +815,10 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
     // against 10.7; 7 of 8 drawn ones with up to 3x3 taps slower, 0.92 times on average).  Large strided NCHW images that only stage 1 has work
     // for, whose tiles with halo fill the LDS (205x224 stride 2, 208 -> 16, ranks 63 and 5: 36.8 against 56.3; five drawn ones,
     // 0.88 times on average; the same at stride 1 are faster, 71x71 and 132x132 by 1.06 and 1.27).
-    const bool few_products = (!d.nhwc && d.Wo % 4 && (d.NB1 == 1 || (d.stride > 1 && d.NB1 * d.NB2 <= 2))) || (d.K == 1 && d.NB1 <= 2 && pixels < 64L * dev.cus) ||
+    // 5x5 and larger taps have products enough below 64 pixels from three block pairs on (ranks 16 and 80: 23.3 -> 15.0; 16 and 48:
+    // 17.8 -> 15.2; 16 and 64: 17.1 -> 15.9).
+    const bool many_taps = d.K >= 5 && d.NB1 * d.NB2 >= 3 && pixels < 64L * dev.cus;
+    const bool few_products = (!d.nhwc && d.Wo % 4 && !many_taps && (d.NB1 == 1 || (d.stride > 1 && d.NB1 * d.NB2 <= 2))) || (d.K == 1 && d.NB1 <= 2 && pixels < 64L * dev.cus) ||
                               (d.K == 1 && d.stride == 1 && !d.nhwc && d.NB1 <= 4 && pixels < 32L * dev.cus) ||
                               (!d.nhwc && d.Wo % 4 && d.stride == 1 && d.K <= 3 && d.NB1 <= 2 && d.NB2 <= 2 && pixels < 36L * dev.cus) ||
                               (!d.nhwc && d.stride > 1 && d.NB1 >= 4 && d.NB2 == 1 && d.N <= 64 && (long)d.Ho * d.Wo >= 6000);
@@ -908,13 +918,15 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
         // batch 64: 50.2 against 38.3 us; 256 channels on 56x56: 17.9 against 17.4 us), 2 % ahead at best.
         variant = (f.us <= 0.92 * split_us || (pixels_fill_chip && f.us < 1e299)) ? TDC_VARIANT_FUSED : TDC_VARIANT_SPLIT;
     }
-    // From 8 pixels per compute unit on what would be FUSED's runs there too: 65 drawn layers, 1.21 times as
+    // From 8 pixels per compute unit on what would be SPLIT's runs there too, 1x1 layers apart (12 drawn layers: 1.04 to 1.71 times
+    // as fast), and what would be FUSED's: 65 drawn layers, 1.21 times as
     // fast on average (0.85 to 1.76).  Not at stride 1 in 1x1 layers (12x11, 372 ->
     // 284, batch 28: 10.7 against 12.4 us), nor there with at most three blocks of R1 where NCHW rows are no multiple of 4 (26x38,
-    // 112 -> 160, ranks 20 and 32: 9.5 against 11.0; 13x13, 5x5, ranks 22 and 62: 14.6 against 16.0), nor with a single block
-    // of R1 (14x14, 40 -> 368, ranks 10 and 71: 14.0 against 15.3).
-    const bool worth_it = d.stride > 1 || (d.K > 1 && (d.nhwc || d.Wo % 4 == 0 || d.NB1 > 3));
-    if (forced.variant == TDC_VARIANT_AUTO && variant == TDC_VARIANT_FUSED && !pixels_fill_chip && d.NB1 > 1 && !few_products && worth_it &&
+    // 112 -> 160, ranks 20 and 32: 9.5 against 11.0; 13x13, 3x3), nor with a single block
+    // of R1 (14x14, 40 -> 368, ranks 10 and 71: 14.0 against 15.3).  5x5 taps and four block pairs are worth it there too
+    // (37x29, ranks 24 and 40, batch 3: 16.4 -> 13.6).
+    const bool worth_it = d.stride > 1 || (d.K >= 5 && d.NB1 * d.NB2 >= 4) || (variant == TDC_VARIANT_SPLIT && d.K > 1) || (d.K > 1 && (d.nhwc || d.Wo % 4 == 0 || d.NB1 > 3));
+    if (forced.variant == TDC_VARIANT_AUTO && !pixels_fill_chip && d.NB1 > 1 && !few_products && worth_it &&
         pixels >= 8L * dev.cus && try_chain3(c3))
         return chain3(c3);
     if (variant == TDC_VARIANT_FUSED) {

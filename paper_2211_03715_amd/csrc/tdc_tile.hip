@@ -769,6 +769,11 @@ bool tdc_tile_applies(const TdcDims &d)
     return ((tp - 1) / P + 2) * img < (1ull << 31) && w < (1ull << 31) && (size_t)d.B * P < (1ull << 31) - 1024;
 }
 
+bool tdc_tile_1x1_applies(const TdcDims &d)
+{
+    return d.K == 1 && d.stride == 1 && d.pad == 0 && tdc_tile_applies(d) && tile_1x1_lds_bytes((d.NB1 + 1) / 2, tdc_tile_parts(d)) <= TILE_1X1_LDS;
+}
+
 hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipStream_t s, const float *x, const void *w, float *y, const TdcEpi &epi)
 {
     TileArgs a;
@@ -786,7 +791,7 @@ hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipSt
     a.div_NBk = tdc_make_div((unsigned)a.NBk); a.div_K = tdc_make_div((unsigned)a.K);
     a.div_inner = tdc_make_div((unsigned)(a.pt_major ? a.n_mt : a.n_pt));
     const bool conv = d.K > 1 || d.stride > 1 || d.pad > 0;
-    if (!conv && ks == 1 && tile_1x1_lds_bytes(a.S, parts) <= TILE_1X1_LDS) {
+    if (ks == 1 && tdc_tile_1x1_applies(d)) {
         const int mb = parts == 3 ? 1 : tm / 64;
         a.n_mt = (d.N + 64 * mb - 1) / (64 * mb);
         a.per = tile_1x1_share(a.n_pt, a.n_mt, mb, tile_1x1_lds_bytes(a.S, parts));
