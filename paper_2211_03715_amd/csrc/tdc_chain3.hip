@@ -62,8 +62,8 @@ hipError_t tdc_launch_chain3(const TdcDims &d, const tdc_tuning &t, const TdcFus
     a.n_mg1 = (d.NB1 + mb1 - 1) / mb1;
     a.tiles_x = g.tiles_x; a.tiles = g.tiles_x * g.tiles_y;
     a.xcd_per = (int)((long)a.tiles * d.B / 8); a.xcd_rem = (int)((long)a.tiles * d.B % 8);
-    // rows of whole quads and a 16-byte aligned y; otherwise the same values go out as four 4-byte stores
-    a.vec = g.TW % 4 == 0 && d.Wo % 4 == 0 && ((uintptr_t)y & 15u) == 0;
+    // rows of whole quads, y and shortcut 16-byte aligned; otherwise the same values go out, and come in, four bytes at a time
+    a.vec = g.TW % 4 == 0 && d.Wo % 4 == 0 && (((uintptr_t)y | (uintptr_t)epi.residual) & 15u) == 0;
     a.uin_bytes = (unsigned)tdc_split_bytes(parts, d.NB1, d.KG1);
     a.core_bytes = (unsigned)tdc_split_bytes(parts, d.NB2, a.KG2);
     a.uout_bytes = (unsigned)tdc_split_bytes(parts, d.NB3, d.NB2);

@@ -25,7 +25,7 @@ CASES = [
 ]
 
 
-def _run(layer, inputs, tuning, nhwc, bias=None, residual=None, offset=0, bf3=True):
+def _run(layer, inputs, tuning, nhwc, bias=None, residual=None, offset=0, bf3=True, residual_offset=0):
     import torch
     from paper_2211_03715_amd.layer import TuckerConv2d
     dev = torch.device("cuda:0")
@@ -38,8 +38,11 @@ def _run(layer, inputs, tuning, nhwc, bias=None, residual=None, offset=0, bf3=Tr
         shape = conv.out_shape()
         whole = torch.full((offset + int(np.prod(shape)),), float("nan"), device=dev)
         y = whole[offset:].view(shape)                      # offset 1: only 4-byte aligned
-        conv(put(inputs["x"]), y, bias=None if bias is None else torch.from_numpy(bias).to(dev),
-             residual=None if residual is None else put(residual), relu=bias is not None)
+        if residual is not None:
+            beside = torch.zeros(residual_offset + residual.size, device=dev)
+            beside[residual_offset:] = put(residual).flatten()
+            residual = beside[residual_offset:].view(shape)
+        conv(put(inputs["x"]), y, bias=None if bias is None else torch.from_numpy(bias).to(dev), residual=residual, relu=bias is not None)
         torch.cuda.synchronize()
         got = y.cpu().numpy()
         return got.transpose(0, 3, 1, 2) if nhwc else got
@@ -70,9 +73,10 @@ def test_chain3(orc, layer, tiles, nhwc):
             # three chained sums of at most 600 terms: fp32 multiply-adds show up to 1e-6, the split products no more; two
             # parts instead of three would show 5e-6 in each
             assert np.linalg.norm(got - want) <= 1.5e-6 * max(np.linalg.norm(want), 1e-30)
-        for offset in (0,) if nhwc else (0, 1):             # 16-byte stores where rows and tile allow them, then 4-byte ones
-            got = _run(layer, inputs, t, nhwc, bias, residual, offset)
-            assert_parity(got, with_epi, "%s tile %dx%d epilogue, y + %d floats" % (layer.name(), th, tw, offset))
+        # 16 bytes at a time where rows and tile allow it, then y and then the shortcut four bytes at a time
+        for offset, r_offset in ((0, 0),) if nhwc else ((0, 0), (1, 0), (0, 1)):
+            got = _run(layer, inputs, t, nhwc, bias, residual, offset, residual_offset=r_offset)
+            assert_parity(got, with_epi, "%s tile %dx%d epilogue, y + %d floats, shortcut + %d" % (layer.name(), th, tw, offset, r_offset))
 
 
 FLT_MAX = float(np.finfo(np.float32).max)
@@ -197,6 +201,26 @@ def test_the_scale_of_the_factors_costs_no_accuracy(orc, layer, tile, nhwc):
         got = _run(layer, inputs, t, nhwc).astype(np.float64)
         for part in (np.abs(want) < 1e-25, np.abs(want) >= 1e-25):
             assert not part.any() or np.linalg.norm((got - want)[part] * 2.0 ** 60) <= 1.5e-6 * np.linalg.norm(want[part] * 2.0 ** 60)
+
+
+@pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
+@pytest.mark.parametrize("layer,tile", ((Layer(2, 72, 48, 12, 12, 32, 16, 3, 1, 1), (4, 4)), (Layer(40, 72, 24, 12, 12, 40, 80, 3, 2, 1), (6, 6))),
+                         ids=lambda v: v.name() if isinstance(v, Layer) else "")
+def test_values_far_from_those_that_set_the_scale(orc, layer, tile, nhwc):
+    """x is scaled by the first 32 channels that a workgroup loads.  Channels behind them up to 64 times larger fit in fp16 and larger
+    ones do not; pixels down to 2^-23 of them keep all their bits and smaller ones do not.  Both sides of each line."""
+    t = B.make_tuning(variant=B.VARIANT_CHAIN, tile_h=tile[0], tile_w=tile[1], waves=(4, 4, 4), mb=(2, 3, 1), pb=(2,) * 3)
+    for what, e in [("channels", e) for e in (4, 6, 7, 9, 40)] + [("pixels", -e) for e in (10, 21, 23, 25, 40)]:
+        inputs = {k: v.copy() for k, v in make_inputs(layer, 94).items()}
+        if what == "channels":
+            inputs["x"][:, -8:] *= np.float32(2.0 ** e)
+        else:
+            inputs["x"][0, :, 5:] *= np.float32(2.0 ** e)
+        want, _ = orc.conv_factored(orc.Shape(**layer.asdict()), **inputs)
+        print("[case] chain3, far from the scale", what, e, layer.name(), "nhwc" if nhwc else "nchw", flush=True)
+        err = _run(layer, inputs, t, nhwc) - want
+        # pixel by pixel, each against its own size: sums as in test_chain3
+        assert (np.linalg.norm(err, axis=1) <= 1.5e-6 * np.linalg.norm(want, axis=1)).all()
 
 
 def test_the_selector_takes_it_where_pixels_fill_the_chip():
