@@ -372,10 +372,10 @@ int tdc_plan_create_tuned(tdc_plan **out, const tdc_shape *shape, int device, co
         p->ws_bytes += (n_z1 + n_z2) * sizeof(float);
     }
     if (!dense && !merged && p->tuning.variant != TDC_VARIANT_NAIVE) {
-        const int parts = tdc_is_chain3(p->tuning) ? tdc_chain3_parts(d) : 0;
-        const size_t b1 = parts ? tdc_split_alloc_bytes(parts, d.NB1, d.KG1) : n_w1 * sizeof(float);
-        const size_t b2 = parts ? tdc_split_alloc_bytes(parts, d.NB2, d.K * d.K * d.NB1) : n_w2 * sizeof(float);
-        const size_t b3 = parts ? tdc_split_alloc_bytes(parts, d.NB3, d.NB2) : n_w3 * sizeof(float);
+        const bool parts = tdc_is_chain3(p->tuning);
+        const size_t b1 = parts ? tdc_chain3_weight_bytes(d, d.NB1, d.KG1) : n_w1 * sizeof(float);
+        const size_t b2 = parts ? tdc_chain3_weight_bytes(d, d.NB2, d.K * d.K * d.NB1) : n_w2 * sizeof(float);
+        const size_t b3 = parts ? tdc_chain3_weight_bytes(d, d.NB3, d.NB2) : n_w3 * sizeof(float);
         ok = ok && hipMalloc((void **)&p->uin_p, b1) == hipSuccess;
         ok = ok && hipMalloc((void **)&p->core_p, b2) == hipSuccess;
         ok = ok && hipMalloc((void **)&p->uout_p, b3) == hipSuccess;
@@ -491,7 +491,8 @@ static hipError_t pack_tucker(const tdc_plan &p, hipStream_t s, const float *U_i
     const int v = p.tuning.variant;
     if (v == TDC_VARIANT_MERGED || v == TDC_VARIANT_FUSED_MERGED || v == TDC_VARIANT_MERGED_XCD)
         return tdc_launch_pack_merged(p.dims, s, U_in, core, U_out, p.uin_p, p.wm, p.core_p);
-    if (tdc_is_chain3(p.tuning)) return tdc_launch_split_layer(p.dims, tdc_chain3_parts(p.dims), s, U_in, core, U_out, p.uin_p, p.core_p, p.uout_p);
+    if (tdc_is_chain3(p.tuning) && tdc_chain3_bf3(p.dims)) return tdc_launch_pack3(p.dims, s, U_in, core, U_out, p.uin_p, p.core_p, p.uout_p);
+    if (tdc_is_chain3(p.tuning)) return tdc_launch_split_layer(p.dims, s, U_in, core, U_out, p.uin_p, p.core_p, p.uout_p);
     return tdc_launch_pack(p.dims, s, U_in, core, U_out, p.uin_p, p.core_p, p.uout_p);
 }
 

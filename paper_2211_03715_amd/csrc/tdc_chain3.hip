@@ -5,9 +5,9 @@
 
 #include "tdc_chain3_kernel.h"
 
-hipError_t tdc_launch_chain3_nchw(const TdcChain3Args &, int, int, int, int, dim3, size_t, hipStream_t, bool);
-hipError_t tdc_launch_chain3_runs(const TdcChain3Args &, int, int, int, int, dim3, size_t, hipStream_t, bool);
-hipError_t tdc_launch_chain3_nhwc(const TdcChain3Args &, int, int, int, int, dim3, size_t, hipStream_t, bool);
+hipError_t tdc_launch_chain3_nchw(const TdcChain3Args &, int, int, int, dim3, size_t, hipStream_t, bool);
+hipError_t tdc_launch_chain3_runs(const TdcChain3Args &, int, int, int, dim3, size_t, hipStream_t, bool);
+hipError_t tdc_launch_chain3_nhwc(const TdcChain3Args &, int, int, int, dim3, size_t, hipStream_t, bool);
 
 bool tdc_chain3_supported(const TdcDims &d, int mb1, int pb)
 {
@@ -38,14 +38,16 @@ TdcFusedGeom tdc_chain3_geometry(const TdcDims &d, int tile_h, int tile_w, int p
     g.pitch1 = 16 * (g.QB | 1);       // an odd number of 128-byte rows: lane groups 2i and 2i + 1 use different halves of the banks
     g.pitch2 = 0;
     g.weights_in_lds = g.weights_fit = false;
-    g.lds_bytes = sizeof(Chain3Shared) + (size_t)32 * tdc_chain3_parts(d) * d.NB1 * g.pitch1;
-    if (pb > 0) g.lds_bytes += tdc_chain3_share((g.PBk + pb - 1) / pb) ? (size_t)TDC_CHAIN3_WAVES * d.NB2 * pb * 1024 : (size_t)2048 * chain3_feed_pieces(d.NB2, tdc_chain3_parts(d));
+    const bool bf3 = tdc_chain3_bf3(d);
+    g.lds_bytes = bf3 ? (size_t)96 * d.NB1 * g.pitch1 : sizeof(Chain3Shared) + (size_t)64 * d.NB1 * g.pitch1;
+    if (pb > 0) g.lds_bytes += tdc_chain3_share((g.PBk + pb - 1) / pb) ? (size_t)TDC_CHAIN3_WAVES * d.NB2 * pb * 1024 : bf3 ? 0 : (size_t)2048 * chain3_feed_pieces(d.NB2);
     return g;
 }
 
 hipError_t tdc_launch_chain3(const TdcDims &d, const tdc_tuning &t, const TdcFusedGeom &g, hipStream_t s, const float *x,
                              const void *uin_sp, const void *core_sp, const void *uout_sp, float *y, const TdcEpi &epi, bool prepare_only)
 {
+    if (tdc_chain3_bf3(d)) return tdc_launch_chain_bf3(d, t, g, s, x, uin_sp, core_sp, uout_sp, y, epi, prepare_only);
     TdcChain3Args a;
     a.x = x; a.uin = uin_sp; a.core = core_sp; a.uout = uout_sp; a.y = y; a.epi = epi;
     a.C = d.C; a.N = d.N; a.H = d.H; a.W = d.W; a.Ho = d.Ho; a.Wo = d.Wo; a.K = d.K; a.stride = d.stride; a.pad = d.pad;
@@ -57,16 +59,14 @@ hipError_t tdc_launch_chain3(const TdcDims &d, const tdc_tuning &t, const TdcFus
     const int lay = d.nhwc ? TDC_LAY_NHWC : d.s1_runs ? TDC_LAY_NCHW_RUNS : TDC_LAY_NCHW;
     a.RPR = tdc_runs_per_row(d.W, d.Wo, g.TW, d.K, d.stride, d.pad);
     a.n_pg1 = lay == TDC_LAY_NCHW_RUNS ? (g.QH * a.RPR + 15) / 16 : (g.QB + 1) / 2;
-    // channel blocks of a stage-1 unit; three in three parts would spill
-    const int parts = tdc_chain3_parts(d), mb1 = parts == 3 ? std::min(t.mb[0], 2) : t.mb[0];
-    a.n_mg1 = (d.NB1 + mb1 - 1) / mb1;
+    a.n_mg1 = (d.NB1 + t.mb[0] - 1) / t.mb[0];
     a.tiles_x = g.tiles_x; a.tiles = g.tiles_x * g.tiles_y;
     a.xcd_per = (int)((long)a.tiles * d.B / 8); a.xcd_rem = (int)((long)a.tiles * d.B % 8);
     // rows of whole quads, y and shortcut 16-byte aligned; otherwise the same values go out, and come in, four bytes at a time
     a.vec = g.TW % 4 == 0 && d.Wo % 4 == 0 && (((uintptr_t)y | (uintptr_t)epi.residual) & 15u) == 0;
-    a.uin_bytes = (unsigned)tdc_split_bytes(parts, d.NB1, d.KG1);
-    a.core_bytes = (unsigned)tdc_split_bytes(parts, d.NB2, a.KG2);
-    a.uout_bytes = (unsigned)tdc_split_bytes(parts, d.NB3, d.NB2);
+    a.uin_bytes = (unsigned)tdc_split_bytes(2, d.NB1, d.KG1);
+    a.core_bytes = (unsigned)tdc_split_bytes(2, d.NB2, a.KG2);
+    a.uout_bytes = (unsigned)tdc_split_bytes(2, d.NB3, d.NB2);
     // scaled weights of 2^12 and x of 2^8: sums of sqrt(C) 2^20
     a.z1_exp = 12 + (int)std::lround(0.5 * std::log2((double)d.C));
     a.div_tiles_x = tdc_make_div((unsigned)g.tiles_x); a.div_tiles = tdc_make_div((unsigned)a.tiles);
@@ -75,5 +75,5 @@ hipError_t tdc_launch_chain3(const TdcDims &d, const tdc_tuning &t, const TdcFus
     a.div_RPR = tdc_make_div((unsigned)a.RPR); a.div_mg1 = tdc_make_div((unsigned)a.n_mg1);
     const dim3 grid((unsigned)a.tiles, (unsigned)d.B);
     const auto launch = lay == TDC_LAY_NHWC ? tdc_launch_chain3_nhwc : lay == TDC_LAY_NCHW_RUNS ? tdc_launch_chain3_runs : tdc_launch_chain3_nchw;
-    return launch(a, d.NB2, t.pb[0], mb1, parts, grid, g.lds_bytes, s, prepare_only);
+    return launch(a, d.NB2, t.pb[0], t.mb[0], grid, g.lds_bytes, s, prepare_only);
 }

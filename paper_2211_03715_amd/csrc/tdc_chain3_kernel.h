@@ -1,26 +1,26 @@
-// CHAIN on the bf16 matrix cores: the three stages of one output tile in one launch, as in tdc_chain_kernel.h, every fp32
-// factor in three bf16 parts (tdc_bf3.h).
+// CHAIN on the fp16 matrix cores: the three stages of one output tile in one launch, as in tdc_chain_kernel.h, every fp32
+// factor in two scaled fp16 parts (tdc_split.h).  Layers of short sums run on the bf16 ones (tdc_chain_bf3_kernel.h).
 //
-//   stage 1   units of PB1 pixel blocks x MB1 channel blocks; x goes from memory into registers one step ahead, is split
-//             there, and the finished z1 values are split once more and stored as parts: 8-byte LDS cells of four channels,
+//   stage 1   units of PB1 pixel blocks x MB1 channel blocks; x goes from memory into registers one or two steps ahead, is
+//             split there, and the finished z1 values are split once more and stored as parts: 8-byte LDS cells of four channels,
 //             [part][channel block][lane group][pixel], which any pair of k-groups of stage 2 reads as operand halves;
-//   stage 2   a wavefront computes all R2 channels (NB2 blocks) of PB pixel blocks, weights streamed one step ahead;
-//   stage 3   its operand is the accumulators, split in registers; weights streamed one output block ahead.
+//   stage 2   a wavefront computes all R2 channels (NB2 blocks) of PB pixel blocks; weights come through LDS in chunks that
+//             all wavefronts share (Chain3Feed), or straight into registers one step ahead where each needs its own;
+//   stage 3   its operand is the accumulators, split in registers; weights likewise, one output block ahead.
 // A tile of one or two groups of pixel blocks has fewer groups than the workgroup has wavefronts: four or two of them then
 // share a group, each with a slice of stage 2's contraction; the partial sums meet in LDS and every wavefront goes on with all
 // of z2 and its share of the output blocks.
 //
 // What bounds it.  The fp32 form was bound by the fp32 matrix rate plus the phases of its one resident workgroup, which do
 // not overlap: 32 -> 32 ranks, 128 channels at 28x28, batch 256: 97 us, of which 45 us are matrix cycles and 39 us compulsory
-// bytes.  Here the products take 3/8 of the cycles, and workgroups are four wavefronts on tiles of at most 128 pixels, so that
-// two to three share a compute unit and one's loads run under another's products: 77 us (62 us where x and y of consecutive
-// calls are the same buffers); 64 -> 32 ranks, 64 channels at 224x224: 35.7 -> 27.0 us.  What is left is memory, with loads
-// one step ahead.  The weight fragments come through the L1 at 54 bytes a cycle: PB pixel blocks share one.  PB = 4 halves that
-// traffic and needs 144 to 256 registers instead of 99 to 256 (three z2 blocks in NCHW spill 19 to 22).  The selector offers
-// PB = 2 alone; with the buffers of a call in cache an exhaustive search takes PB = 4 on larger tiles in three of sixteen cases
-// (128 channels at 28x28, ranks 32, batch 128: 36.8 -> 31.4 us), with new buffers per call it was 2 to 10 % slower.
+// bytes.  Here the products take 3/16 of the cycles (two parts), and workgroups are four wavefronts on tiles of at most 128
+// pixels, so that two to three share a compute unit and one's loads run under another's products: 77 us with three bf16 parts and
+// every wavefront's weights through the L1, 72.6 with two fp16 parts, 67.0 with shared weights and three workgroups to a
+// compute unit; 64 -> 32 ranks, 64 channels at 224x224: 35.7 -> 27.0 -> 23.8 -> 22.5 us.  What is left is memory.  PB = 4
+// halves the reads of weight fragments and needs about 1.5 times the registers; the selector offers PB = 2 alone: PB = 4 was 2 to
+// 10 % slower with new buffers per call (three bf16 parts).
 // With few pixels (24 per compute unit) a workgroup has its compute unit to itself and the chain of its steps is the time;
-// sharing cuts it: ranks 80, 256 channels at 14x14, batch 32: 34.6 us unshared, 20.7 shared (fp32 FUSED: 33.0).
+// sharing cuts it: ranks 80, 256 channels at 14x14, batch 32, three bf16 parts: 34.6 us unshared, 20.7 shared (fp32 FUSED: 33.0).
 #ifndef TDC_CHAIN3_KERNEL_H
 #define TDC_CHAIN3_KERNEL_H
 
@@ -52,20 +52,22 @@ struct TdcChain3Args {
 
 namespace {
 
+constexpr int NP = 2;      // parts
+
 // LDS: the largest magnitude each wavefront has loaded first and whether it wants the tile in fp32, then z1.
 struct Chain3Shared {
     unsigned first[TDC_CHAIN3_WAVES], bad[TDC_CHAIN3_WAVES];
 };
 
 // Stage 1 for the workgroup.  RUNS: a lane owns runs of four consecutive pixels (see TdcStage1R), a unit is 16 runs.
-template <int LAY, int MB1, int NP, bool DEEP>
+template <int LAY, int MB1, bool DEEP>
 struct Chain3Stage1 {
     static constexpr bool RUNS = LAY == TDC_LAY_NCHW_RUNS, NHWC = LAY == TDC_LAY_NHWC;
     static constexpr int PB = RUNS ? 4 : 2;
     static constexpr int NR = RUNS ? 8 : 2 * PB;      // 16-byte registers of x per step
     // Depth 1 in lean runs: three workgroups to a compute unit instead of two overlap more than a step on its way (128 channels at
     // 28x28, ranks 32, batch 256: 72.9 -> 66.7 us)
-    static constexpr int DEPTH = NP == 2 && DEEP && !RUNS && MB1 <= 2 ? 3 : NP == 2 && RUNS && !DEEP ? 1 : 2;         // steps in registers: the one being multiplied and those on their way
+    static constexpr int DEPTH = DEEP && !RUNS && MB1 <= 2 ? 3 : RUNS && !DEEP ? 1 : 2;         // steps in registers: the one being multiplied and those on their way
     const TdcChain3Args &a;
     tdc_rsrc xrs, urs;
     int lane, g, l16, wave, h0, w0, wa, n_units;
@@ -183,7 +185,7 @@ struct Chain3Stage1 {
             z1s[pl * a.pitch1 + r * a.QW + qw] = (tdc_u2){0u, 0u};
         }
     }
-    __device__ __forceinline__ void multiply(tdc_f4 (&acc)[MB1][PB][NP], const tdc_f4 (&x)[NR], const tdc_op<NP> (&w)[MB1])
+    __device__ __forceinline__ void multiply(tdc_f4 (&acc)[MB1][PB][TDC_LEVELS], const tdc_f4 (&x)[NR], const tdc_op<NP> (&w)[MB1])
     {
         const TdcScale s(x_exp);
 #pragma unroll
@@ -202,7 +204,7 @@ struct Chain3Stage1 {
         }
     }
     // the sums of a unit, from their levels, as parts of z1
-    __device__ __forceinline__ void store(tdc_u2 *__restrict__ z1s, int unit, const tdc_f4 (&acc)[MB1][PB][NP])
+    __device__ __forceinline__ void store(tdc_u2 *__restrict__ z1s, int unit, const tdc_f4 (&acc)[MB1][PB][TDC_LEVELS])
     {
         const int pg = tdc_div(unit, a.div_mg1), mg = unit - pg * a.n_mg1;
         const int rho = 16 * pg + l16, qh = RUNS ? tdc_div(rho, a.div_RPR) : 0;
@@ -220,7 +222,7 @@ struct Chain3Stage1 {
 #pragma unroll
             for (int mb = 0; mb < MB1; ++mb) {
                 const int blk = mg * MB1 + mb;
-                tdc_f4 v = tdc_levels<NP>(acc[mb][pb]);
+                tdc_f4 v = tdc_levels(acc[mb][pb]);
                 m = tdc_largest(m, v);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) v[i] = ldexpf(v[i], (int)e[mb][i] - a.z1_exp);
@@ -237,7 +239,7 @@ struct Chain3Stage1 {
     }
     __device__ __forceinline__ void run(Chain3Shared &sh, tdc_u2 *__restrict__ z1s)
     {
-        tdc_f4 x[DEPTH][NR], acc[MB1][PB][NP];
+        tdc_f4 x[DEPTH][NR], acc[MB1][PB][TDC_LEVELS];
         tdc_op<NP> w[DEPTH][MB1];
 #pragma unroll
         for (int i = 0; i == 0 || i + 1 < DEPTH; ++i) fetch(x[i], w[i]);
@@ -259,7 +261,7 @@ struct Chain3Stage1 {
 #pragma unroll
                 for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
-                    for (int q = 0; q < NP; ++q) acc[mb][pb][q] = tdc_f4_zero();
+                    for (int q = 0; q < TDC_LEVELS; ++q) acc[mb][pb][q] = tdc_f4_zero();
         };
         const auto done = [&]() {
             if (++step < a.S1) return;
@@ -419,11 +421,10 @@ struct Chain3Out {
 };
 
 // The tile once more in fp32, one load at a time, z1 in fp32 where its parts were (see tdc_split.h).
-template <int NB2, int PB, int LAY, int NP>
+template <int NB2, int PB, int LAY>
 __device__ __forceinline__ void chain3_tile_fp32(const TdcChain3Args &a, tdc_u2 *__restrict__ z1s, int lane, int wave)
 {
     constexpr bool NHWC = LAY == TDC_LAY_NHWC;
-    static_assert(NP >= 2, "16 bytes of z1 per lane, block and pixel");
     tdc_f4 *__restrict__ z1f = reinterpret_cast<tdc_f4 *>(z1s);
     const int g = lane >> 4, l16 = lane & 15;
     const Chain3Tile at(a);
@@ -509,10 +510,10 @@ __device__ __forceinline__ void chain3_tile_fp32(const TdcChain3Args &a, tdc_u2 
 // Weights that all four wavefronts need, through LDS: chunks of N pieces of 1 KB (a 16-row block's fragment in one part), brought by
 // all of them, two chunks ahead in registers, double-buffered.  One fragment then comes through the L1 once per workgroup and
 // not once per wavefront: at the 26 to 32 bytes a cycle it delivers, that was the time of stages 2 and 3.
-constexpr int chain3_feed_pieces(int nb2, int np)            // of the larger of the two stages' chunks
+constexpr int chain3_feed_pieces(int nb2)                    // of the larger of the two stages' chunks
 {
     const int s3 = (nb2 + 1) / 2, t2 = nb2 == 1 ? 4 : nb2 == 2 ? 2 : 1, u3 = s3 == 1 ? 4 : s3 == 2 ? 2 : 1;
-    return np * (nb2 * t2 > s3 * u3 ? nb2 * t2 : s3 * u3);
+    return NP * (nb2 * t2 > s3 * u3 ? nb2 * t2 : s3 * u3);
 }
 template <int N>
 struct Chain3Feed {
@@ -545,22 +546,21 @@ constexpr bool chain3_shares_weights(int lay, int nb2) { return !(lay == TDC_LAY
 
 // Three and more z2 blocks: the layers whose tiles are large and few, one or two workgroups to a compute unit.  Their instances
 // spend the registers on more steps and output blocks on their way instead of on residency.
-constexpr bool chain3_deep(int nb2, int pb, int np) { return nb2 >= 3 && pb == 2 && np == 2; }
+constexpr bool chain3_deep(int nb2, int pb) { return nb2 >= 3 && pb == 2; }
 
 // Wavefronts per SIMD an instance has registers for; the rarely run code must not cost one.
-constexpr int chain3_wavefronts(int nb2, int pb, int lay, int mb1, int np)
+constexpr int chain3_wavefronts(int nb2, int pb, int lay, int mb1)
 {
-    if (np == 3 && (pb > 2 || nb2 > 3)) return 1;
     if (pb > 2 || nb2 > 2) return 2;
-    return np == 3 ? 2 : lay == TDC_LAY_NCHW_RUNS ? (mb1 <= 2 ? 3 : 2) : lay == TDC_LAY_NHWC && mb1 <= 2 ? 4 : 3;
+    return lay == TDC_LAY_NCHW_RUNS ? (mb1 <= 2 ? 3 : 2) : lay == TDC_LAY_NHWC && mb1 <= 2 ? 4 : 3;
 }
 
 // ALL: every wavefront has a group of pixel blocks of its own (lg_ks is 0)
-template <int NB2, int PB, int LAY, int MB1, int NP, bool ALL>
-__global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, LAY, MB1, NP)) void tdc_chain3_kernel(TdcChain3Args a)
+template <int NB2, int PB, int LAY, int MB1, bool ALL>
+__global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, LAY, MB1)) void tdc_chain3_kernel(TdcChain3Args a)
 {
     constexpr bool NHWC = LAY == TDC_LAY_NHWC, SWAP = !NHWC;
-    constexpr bool DEEP = chain3_deep(NB2, PB, NP);
+    constexpr bool DEEP = chain3_deep(NB2, PB);
     extern __shared__ tdc_u4 chain3_lds[];                       // Chain3Shared, z1 [NP parts][NB1][4][pitch1], the partial sums of ks > 1
     Chain3Shared &sh = *reinterpret_cast<Chain3Shared *>(chain3_lds);
     tdc_u2 *__restrict__ z1s = reinterpret_cast<tdc_u2 *>(chain3_lds + sizeof(Chain3Shared) / 16);
@@ -570,7 +570,7 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
     int x_exp;
     const Chain3Tile at(a);
     {
-        Chain3Stage1<LAY, MB1, NP, DEEP> s1(a, lane, wave, at.b, at.i0 * a.stride - a.pad, at.j0 * a.stride - a.pad);
+        Chain3Stage1<LAY, MB1, DEEP> s1(a, lane, wave, at.b, at.i0 * a.stride - a.pad, at.j0 * a.stride - a.pad);
         s1.run(sh, z1s);
         x_exp = s1.x_exp;
         bad = tdc_is_small(s1.smallest, tdc_exp2i(a.z1_exp + TDC_LOWEST)) || tdc_is_small(s1.smallest_x, tdc_exp2i(max(TDC_LOWEST - x_exp, -126)));
@@ -584,7 +584,7 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
     const int lg_ks = ALL ? 0 : a.lg_ks, ks = 1 << lg_ks, slice = wave & (ks - 1);
     constexpr int S3 = (NB2 + 1) / 2;
     constexpr int T2 = NB2 == 1 ? 4 : NB2 == 2 ? 2 : 1, U3 = S3 == 1 ? 4 : S3 == 2 ? 2 : 1;    // steps, output blocks of a chunk
-    constexpr int PIECES = chain3_feed_pieces(NB2, NP);
+    constexpr int PIECES = chain3_feed_pieces(NB2);
     tdc_u4 *__restrict__ feed = reinterpret_cast<tdc_u4 *>(z1s + NP * plane);                  // two chunks
     for (int round = 0; round < a.n_pg2; round += TDC_CHAIN3_WAVES >> lg_ks) {
         const int pg = round + (wave >> lg_ks);
@@ -594,13 +594,13 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
         chain3_z1_base<PB>(a, pg, lane, qbase);
         tdc_f4 z2[NB2][PB];
         {
-            tdc_f4 acc2[NB2][PB][NP];
+            tdc_f4 acc2[NB2][PB][TDC_LEVELS];
 #pragma unroll
             for (int mb = 0; mb < NB2; ++mb)
 #pragma unroll
                 for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
-                    for (int q = 0; q < NP; ++q) acc2[mb][pb][q] = tdc_f4_zero();
+                    for (int q = 0; q < TDC_LEVELS; ++q) acc2[mb][pb][q] = tdc_f4_zero();
             // a fetch past the last step stays inside the descriptor or reads 0, and is never multiplied
             const auto fetch_w = [&](int step, tdc_op<NP>(&w)[NB2]) {
 #pragma unroll
@@ -715,7 +715,7 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
                 const tdc_u4 e = __builtin_bit_cast(tdc_u4, tdc_buf_load4(crs, a.core_bytes + (16u * mb + 4u * (lane >> 4)) * 4u));
 #pragma unroll
                 for (int pb = 0; pb < PB; ++pb) {
-                    z2[mb][pb] = tdc_levels<NP>(acc2[mb][pb]);
+                    z2[mb][pb] = tdc_levels(acc2[mb][pb]);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) z2[mb][pb][i] = ldexpf(z2[mb][pb][i], (int)e[i]);
                 }
@@ -798,11 +798,11 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
         // two instances of the loop, as in tdc_chain_kernel.h: without epilogue loads nothing ever waits for the stores
         typedef typename Chain3Out<PB, NHWC>::Epi Epi;
         const auto emit = [&](auto with_epi, int nb, const tdc_op<NP>(&u)[S3], const Exponents &e, const Epi *epi) {
-            tdc_f4 acc3[PB][NP], v[PB];
+            tdc_f4 acc3[PB][TDC_LEVELS], v[PB];
 #pragma unroll
             for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
-                for (int q = 0; q < NP; ++q) acc3[pb][q] = tdc_f4_zero();
+                for (int q = 0; q < TDC_LEVELS; ++q) acc3[pb][q] = tdc_f4_zero();
 #pragma unroll
             for (int st = 0; st < S3; ++st)
 #pragma unroll
@@ -814,7 +814,7 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
                     }
 #pragma unroll
             for (int pb = 0; pb < PB; ++pb) {
-                v[pb] = tdc_levels<NP>(acc3[pb]);
+                v[pb] = tdc_levels(acc3[pb]);
                 largest = tdc_largest(largest, v[pb]);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) v[pb][i] = ldexpf(v[pb][i], y_exp - e.e[NHWC ? i : 0]);
@@ -878,7 +878,7 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
     __syncthreads();
     const tdc_u4 all = *reinterpret_cast<const tdc_u4 *>(sh.bad);
     if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)(all[0] | all[1] | all[2] | all[3])), 0))
-        chain3_tile_fp32<NB2, PB, LAY, NP>(tdc_args_again<TdcChain3Args>(), z1s, lane, wave);
+        chain3_tile_fp32<NB2, PB, LAY>(tdc_args_again<TdcChain3Args>(), z1s, lane, wave);
 }
 
 }  // namespace
@@ -888,21 +888,19 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
 #define TDC_CHAIN3_UNITS(X) X(1, 4) X(2, 4) X(3, 4) X(1, 2) X(2, 2) X(3, 2) X(4, 2) X(5, 2)
 
 template <int LAY>
-hipError_t tdc_launch_chain3_lay(const TdcChain3Args &a, int nb2, int pb, int mb1, int parts, dim3 grid, size_t lds, hipStream_t s, bool prepare_only)
+hipError_t tdc_launch_chain3_lay(const TdcChain3Args &a, int nb2, int pb, int mb1, dim3 grid, size_t lds, hipStream_t s, bool prepare_only)
 {
-#define TDC_LAUNCH(N_, P_, M_, NP_, ALL_)                                                                              \
-    if (mb1 == M_ && parts == NP_ && (chain3_shares_weights(LAY, N_) && a.lg_ks == 0) == ALL_) {                                                         \
-        hipError_t e = tdc_allow_lds((const void *)tdc_chain3_kernel<N_, P_, LAY, M_, NP_, ALL_>, lds);                 \
+#define TDC_LAUNCH(N_, P_, M_, ALL_)                                                                              \
+    if (mb1 == M_ && (chain3_shares_weights(LAY, N_) && a.lg_ks == 0) == ALL_) {                                                         \
+        hipError_t e = tdc_allow_lds((const void *)tdc_chain3_kernel<N_, P_, LAY, M_, ALL_>, lds);                 \
         if (e != hipSuccess || prepare_only) return e;                                                                 \
-        hipLaunchKernelGGL((tdc_chain3_kernel<N_, P_, LAY, M_, NP_, ALL_>), grid, dim3(64 * TDC_CHAIN3_WAVES), lds, s, a); \
+        hipLaunchKernelGGL((tdc_chain3_kernel<N_, P_, LAY, M_, ALL_>), grid, dim3(64 * TDC_CHAIN3_WAVES), lds, s, a); \
         return hipGetLastError();                                                                                      \
     }
 #define TDC_X(N_, P_)                                                                                                  \
     if (nb2 == N_ && pb == P_) {                                                                                       \
-        TDC_LAUNCH(N_, P_, 1, 2, true) TDC_LAUNCH(N_, P_, 2, 2, true) TDC_LAUNCH(N_, P_, 3, 2, true)                   \
-        TDC_LAUNCH(N_, P_, 1, 2, false) TDC_LAUNCH(N_, P_, 2, 2, false) TDC_LAUNCH(N_, P_, 3, 2, false)                \
-        TDC_LAUNCH(N_, P_, 1, 3, true) TDC_LAUNCH(N_, P_, 2, 3, true)                                                  \
-        TDC_LAUNCH(N_, P_, 1, 3, false) TDC_LAUNCH(N_, P_, 2, 3, false)                                                \
+        TDC_LAUNCH(N_, P_, 1, true) TDC_LAUNCH(N_, P_, 2, true) TDC_LAUNCH(N_, P_, 3, true)                            \
+        TDC_LAUNCH(N_, P_, 1, false) TDC_LAUNCH(N_, P_, 2, false) TDC_LAUNCH(N_, P_, 3, false)                      \
     }
     TDC_CHAIN3_UNITS(TDC_X)
 #undef TDC_X

@@ -1,7 +1,7 @@
 // Instances of the fp16-part CHAIN kernel for NCHW activations read four bytes at a time.
 #include "tdc_chain3_kernel.h"
 
-hipError_t tdc_launch_chain3_nchw(const TdcChain3Args &a, int nb2, int pb, int mb1, int parts, dim3 grid, size_t lds, hipStream_t s, bool prepare_only)
+hipError_t tdc_launch_chain3_nchw(const TdcChain3Args &a, int nb2, int pb, int mb1, dim3 grid, size_t lds, hipStream_t s, bool prepare_only)
 {
-    return tdc_launch_chain3_lay<TDC_LAY_NCHW>(a, nb2, pb, mb1, parts, grid, lds, s, prepare_only);
+    return tdc_launch_chain3_lay<TDC_LAY_NCHW>(a, nb2, pb, mb1, grid, lds, s, prepare_only);
 }

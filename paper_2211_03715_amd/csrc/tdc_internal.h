@@ -67,12 +67,25 @@ inline size_t tdc_split_alloc_bytes(int parts, int m_blocks, int k_groups)
 {
     return tdc_split_bytes(parts, m_blocks, k_groups) + (size_t)m_blocks * (64 + (size_t)k_groups * 1024 + 128 * TDC_SPLIT_CHUNKS);
 }
-// Parts a weight is split into.  Two are the more accurate form from some 70 terms to a sum on (tdc_split.h); the three sums of a
-// Tucker layer add up to that from 208 on: squared errors of 78 + 0.39 n against 2.1 n - 40 (in 1e-16, n terms).
+// Parts a weight is split into.  Two fp16 parts are the more accurate form from some 70 terms to a sum on (tdc_split.h); the three sums
+// of a Tucker layer add up to that from 208 on: squared errors of 78 + 0.39 n against 2.1 n - 40 (in 1e-16, n terms).  Below, the
+// dense tiles take three fp16 parts (1.1 times as fast as three bf16 ones) and CHAIN three bf16 ones, which need no scale and
+// so no first look at x: 90 drawn layers of such short sums run 1.05 times as fast with them on average (0.9 to 1.31, the larger where
+// memory or latency bounds them: 208x208, 48 -> 42, ranks 13 and 8, batch 3: 20.6 against 26.7 us).
 inline int tdc_tile_parts(const TdcDims &d) { return d.K * d.K * d.R1 > 72 ? 2 : 3; }
-inline int tdc_chain3_parts(const TdcDims &d) { return d.C + d.K * d.K * d.R1 + d.R2 >= 208 ? 2 : 3; }
+inline bool tdc_chain3_bf3(const TdcDims &d) { return d.C + d.K * d.K * d.R1 + d.R2 < 208; }
+// In three bf16 parts (tdc_bf3.h), unscaled and otherwise alike.  An allocation holds TDC_PACKED3_TAIL bytes more, which the
+// re-layout uses.
+constexpr size_t TDC_PACKED3_TAIL = 256;
+inline size_t tdc_packed3_bytes(int m_blocks, int k_groups) { return (size_t)m_blocks * ((k_groups + 1) / 2) * 3072; }
+inline size_t tdc_chain3_weight_bytes(const TdcDims &d, int m_blocks, int k_groups)
+{
+    return tdc_chain3_bf3(d) ? tdc_packed3_bytes(m_blocks, k_groups) + TDC_PACKED3_TAIL : tdc_split_alloc_bytes(2, m_blocks, k_groups);
+}
+hipError_t tdc_launch_pack3(const TdcDims &d, hipStream_t s, const float *U_in, const float *core, const float *U_out,
+                            void *uin_p3, void *core_p3, void *uout_p3);
 hipError_t tdc_launch_split_core(const TdcDims &d, int parts, hipStream_t s, const float *core, void *core_sp);
-hipError_t tdc_launch_split_layer(const TdcDims &d, int parts, hipStream_t s, const float *U_in, const float *core, const float *U_out,
+hipError_t tdc_launch_split_layer(const TdcDims &d, hipStream_t s, const float *U_in, const float *core, const float *U_out,
                                   void *uin_sp, void *core_sp, void *uout_sp);
 size_t tdc_packed_floats_uin(const TdcDims &d);
 size_t tdc_packed_floats_core(const TdcDims &d);
@@ -146,7 +159,7 @@ hipError_t tdc_launch_chain(const TdcDims &d, const tdc_tuning &t, const TdcFuse
                             const float *uout_p, float *y, const TdcEpi &epi, bool prepare_only = false);
 
 // ---- the same on the fp16 matrix cores (tdc_chain3.hip, kernel in tdc_chain3_kernel.h): weights in tdc_launch_split_layer's layout,
-// workgroups of four wavefronts.  A CHAIN tuning asks for it with mb[1] == TDC_CHAIN3_PARTS; pb[0] is 2 or 4.
+// workgroups of four wavefronts; layers of short sums (tdc_chain3_bf3) on the bf16 ones, weights in tdc_launch_pack3's.  A CHAIN tuning asks for it with mb[1] == TDC_CHAIN3_PARTS; pb[0] is 2 or 4.
 constexpr int TDC_CHAIN3_PARTS = 3;
 inline bool tdc_is_chain3(const tdc_tuning &t) { return t.variant == TDC_VARIANT_CHAIN && t.mb[1] == TDC_CHAIN3_PARTS; }
 bool tdc_chain3_supported(const TdcDims &d, int mb1, int pb);
@@ -155,6 +168,9 @@ TdcFusedGeom tdc_chain3_geometry(const TdcDims &d, int tile_h, int tile_w, int p
 hipError_t tdc_launch_chain3(const TdcDims &d, const tdc_tuning &t, const TdcFusedGeom &g, hipStream_t s, const float *x,
                              const void *uin_sp, const void *core_sp, const void *uout_sp, float *y, const TdcEpi &epi,
                              bool prepare_only = false);
+hipError_t tdc_launch_chain_bf3(const TdcDims &d, const tdc_tuning &t, const TdcFusedGeom &g, hipStream_t s, const float *x,
+                                const void *uin_p3, const void *core_p3, const void *uout_p3, float *y, const TdcEpi &epi,
+                                bool prepare_only = false);
 
 // ---- one-launch kernel: stage 1 into LDS, then the merged stage-2/3 convolution (tdc_fm.hip).
 // Tuning fields: tile_h, tile_w, waves[0], mb[0] = stage-1 register tile, mb[1] = output-channel

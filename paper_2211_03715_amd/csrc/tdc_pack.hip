@@ -54,7 +54,7 @@ __global__ void pack_core_kernel(TdcDims d, const float *__restrict__ core, floa
 //   U_in, core   lowest - scale[m], where lowest = the smallest scale of the tensor (that of its largest weight): what takes the
 //                scaled sums of all channels to the common scale 2^lowest;
 //   U_out, W     scale[n], for U_out plus the other two tensors' lowest: what has to be undone at the end.
-// A tensor with weights from 2^10 on beside others that the scaling takes below 2^-13 (where parts lose bits) is kept in fp32
+// A tensor with weights from 2^10 on beside others that the scaling takes below 2^-13 (three parts: 2^-1), where parts lose bits, is kept in fp32
 // alone: its parts are NaN.  Smaller weights beside ordinary ones only lose what is below the rounding of their channel's sums.
 
 // One weight tensor w[row][col][tap] -- the contraction runs over rows and taps -- and where things go.
@@ -97,8 +97,8 @@ __device__ __forceinline__ int split_block_max(int v)
     }
     return part[0];
 }
-// the exponent of the largest weight of a tensor, and whether it is too wide for parts
-__device__ __forceinline__ void split_whole(const SplitTensor &t, int &top, bool &wide)
+// the exponent of the largest weight of a tensor, and whether it is too wide for parts that keep their bits from 2^lowest on
+__device__ __forceinline__ void split_whole(const SplitTensor &t, int lowest, int &top, bool &wide)
 {
     int widest = -SPLIT_NONE;
     top = -SPLIT_NONE;
@@ -109,7 +109,7 @@ __device__ __forceinline__ void split_whole(const SplitTensor &t, int &top, bool
     }
     top = split_block_max(top);
     widest = split_block_max(widest);
-    wide = top >= 10 && widest > SPLIT_TOP - TDC_LOWEST;
+    wide = top >= 10 && widest > SPLIT_TOP - lowest;
 }
 
 // the ranges of 64 output channels' weights among one share of the rows
@@ -153,14 +153,14 @@ __global__ void split_pack_kernel(SplitArgs a)
     if ((int)blockIdx.x >= t.NBm * S) return;
     int top;
     bool wide;
-    split_whole(t, top, wide);
+    split_whole(t, tdc_lowest_weight(NP), top, wide);
     const int lowest = split_scale(top);
     int others = 0;
     if (t.last)
         for (int i = 0; i < a.n - 1; ++i) {
             int o;
             bool w;
-            split_whole(a.t[i], o, w);
+            split_whole(a.t[i], tdc_lowest_weight(NP), o, w);
             others += split_scale(o);
         }
     const int pair = (int)(threadIdx.x & 3), lane = (int)(threadIdx.x >> 2);
@@ -172,7 +172,7 @@ __global__ void split_pack_kernel(SplitArgs a)
     float v[2];
     for (int i = 0; i < 2; ++i) v[i] = kg < t.KG && row + i < t.rows && m < t.cols ? t.w[((size_t)(row + i) * t.cols + m) * t.KK + tap] : 0.f;
     unsigned p[NP];
-    tdc_split2<NP>(wide ? NAN : ldexpf(v[0], scale), wide ? NAN : ldexpf(v[1], scale), TdcScale(0), p);
+    tdc_split2<NP, tdc_lift_weights(NP)>(wide ? NAN : ldexpf(v[0], scale), wide ? NAN : ldexpf(v[1], scale), TdcScale(0), p);
     for (int i = 0; i < NP; ++i) t.parts[(blk * NP + i) * 256 + lane * 4 + pair] = p[i];
     if (kg < t.KG) {
         float *raw = t.raw + (((size_t)mb * t.KG + kg) * 64 + lane) * 4 + 2 * (pair & 1);
@@ -277,13 +277,13 @@ hipError_t tdc_launch_split_core(const TdcDims &d, int parts, hipStream_t s, con
     return launch_split(parts, s, a);
 }
 
-hipError_t tdc_launch_split_layer(const TdcDims &d, int parts, hipStream_t s, const float *U_in, const float *core, const float *U_out,
+hipError_t tdc_launch_split_layer(const TdcDims &d, hipStream_t s, const float *U_in, const float *core, const float *U_out,
                                   void *uin_sp, void *core_sp, void *uout_sp)
 {
     SplitArgs a = {};
     a.n = 3;
-    a.t[0] = split_tensor(parts, U_in, d.C, d.R1, 1, uin_sp, false);
-    a.t[1] = split_tensor(parts, core, d.R1, d.R2, d.K, core_sp, false);
-    a.t[2] = split_tensor(parts, U_out, d.R2, d.N, 1, uout_sp, true);
-    return launch_split(parts, s, a);
+    a.t[0] = split_tensor(2, U_in, d.C, d.R1, 1, uin_sp, false);
+    a.t[1] = split_tensor(2, core, d.R1, d.R2, d.K, core_sp, false);
+    a.t[2] = split_tensor(2, U_out, d.R2, d.N, 1, uout_sp, true);
+    return launch_split(2, s, a);
 }

@@ -1,20 +1,22 @@
 // fp32 products on the fp16 matrix cores, shared by the kernels that are bound by matrix arithmetic.
 //
 // gfx950 multiplies fp32 at 157 TFLOP/s and fp16 at 2500.  A value that has been scaled by a power of two into fp16's range is
-//     v = v1 + 2^-11 v2 (+ 2^-22 v3),   v1 = fp16(v), v2 = fp16(2^11 (v - v1)), v3 = fp16(2^11 (2^11 (v - v1) - v2)):
+//     v = v1 + 2^-11 (v2 + v3),   v1 = fp16(v), v2 = fp16(2^11 (v - v1)), v3 = fp16(2^11 (v - v1) - v2):
 // the parts have 11 significand bits each, so two of them are off by at most half a bit of the 24 (v3 is what is left).
-// Products of parts i and j carry 2^-11(i + j); those with i + j < parts are accumulated, in fp32 by the matrix core, one
-// accumulator per i + j ("level"), and the levels are added at the end:
-//     two parts:    a1 b1 | a1 b2 + a2 b1                                      3 MFMAs of 16 cycles per 16 x 16 x 32 block
-//     three parts:  the same | a1 b3 + a2 b2 + a3 b1                           6 (fp32 MFMA: 8 of 32)
+// The products of parts i and j with i + j < parts are accumulated, in fp32 by the matrix core, in two accumulators ("levels"), the
+// second of which is 2^11 times the sum and is added at the end.  Three parts of a weight are not lifted, w = w1 + w2 + w3, so
+// that their products need no third one: 64 x 64 tiles fit three wavefronts to a SIMD so:
+//     two parts:    w1 x1 | w1 x2 + w2 x1                                      3 MFMAs of 16 cycles per 16 x 16 x 32 block
+//     three parts:  w1 x1 + w2 x1 + w3 x1 | w1 x2 + w2 x2 + w1 x3              6 (fp32 MFMA: 8 of 32)
 // Only the accumulations of the highest level round at the scale of the result, n/32 of them.  Measured against 64 bits
 // (normal values, relative 2-norm): at n = 32 / 64 / 128 / 288 / 1152 / 4608 terms two parts 9.0e-8 / 9.7e-8 / 1.1e-7 / 1.4e-7 /
-// 2.3e-7 / 4.4e-7; three bf16 parts in one accumulator, which this replaces, 3.8e-8 / 9.3e-8 / 1.6e-7 / 2.4e-7 / 5.1e-7 / 1.08e-6;
+// 2.3e-7 / 4.4e-7; three bf16 parts in one accumulator (tdc_bf3.h) 3.8e-8 / 9.3e-8 / 1.6e-7 / 2.4e-7 / 5.1e-7 / 1.08e-6;
 // v_mfma_f32_16x16x4_f32 1.0e-7 / 1.4e-7 / 2.0e-7 / 3.1e-7 / 6.0e-7 / 1.2e-6.  Sums too short for two parts to be the most
-// accurate of these take three (tdc_tile_parts, tdc_chain3_parts).
+// accurate of these take three (tdc_tile_parts) or, in CHAIN, three bf16 ones (tdc_chain3_bf3).
 //
-// Scales.  fp16 holds 2^-24 .. 65504, so v2 keeps its 11 bits down to |v| = 2^-13 and two parts an absolute 2^-36 below that.
-//   weights      every output channel has its own exponent, the largest weight at 2^13 .. 2^14 (tdc_pack.hip);
+// Scales.  fp16 holds 2^-24 .. 65504, so v2 keeps its 11 bits down to |v| = 2^-13 and the parts an absolute 2^-36 below that.
+//   weights      every output channel has its own exponent, the largest weight at 2^13 .. 2^14 (tdc_pack.hip): three parts that
+//                are not lifted keep all 24 bits down to 2^-1 and an absolute 2^-25 below, 2^-38 of the largest weight;
 //   activations  one exponent per workgroup, which takes the largest magnitude among those it loads first to 2^10 .. 2^11
 //                (tdc_scale_of): 64 times larger values still fit, 2^23 times smaller ones keep all their bits;
 //   z1           sqrt(C) 2^12 times smaller than its sums, a constant: 2^8 or so; z2: by the largest a wavefront holds.
@@ -51,8 +53,8 @@ struct TdcScale {
     __device__ __forceinline__ explicit TdcScale(int e) : one(tdc_exp2i(e)), lift(tdc_exp2i(e + 11)) {}
 };
 
-// two scaled fp32 -> their parts, packed in pairs (two parts: 7 VALU instructions)
-template <int NP>
+// two scaled fp32 -> their parts, packed in pairs (two parts: 7 VALU instructions); LIFT: the parts behind the first times 2^11
+template <int NP, bool LIFT = true>
 __device__ __forceinline__ void tdc_split2(float a, float b, const TdcScale &s, unsigned (&p)[NP])
 {
     // Opaque after the conversion: the compiler would else convert each value a second time for its rest.  The conversion itself
@@ -64,12 +66,12 @@ __device__ __forceinline__ void tdc_split2(float a, float b, const TdcScale &s, 
         return r;
     };
     p[0] = pack(a * s.one, b * s.one);
-    float ra = a * s.lift, rb = b * s.lift;
+    float ra = a * (LIFT ? s.lift : s.one), rb = b * (LIFT ? s.lift : s.one);
 #pragma unroll
     for (int q = 1; q < NP; ++q) {
         const tdc_h2 v = __builtin_bit_cast(tdc_h2, p[q - 1]);
-        ra = fmaf((float)v[0], -2048.f, q > 1 ? ra * 2048.f : ra);
-        rb = fmaf((float)v[1], -2048.f, q > 1 ? rb * 2048.f : rb);
+        ra = fmaf((float)v[0], LIFT && q == 1 ? -2048.f : -1.f, ra);
+        rb = fmaf((float)v[1], LIFT && q == 1 ? -2048.f : -1.f, rb);
         p[q] = q + 1 < NP ? pack(ra, rb) : __builtin_bit_cast(unsigned, (tdc_h2){(_Float16)ra, (_Float16)rb});
     }
 }
@@ -104,35 +106,36 @@ __device__ __forceinline__ tdc_op<NP> tdc_split_op(tdc_f4 lo, tdc_f4 hi, const T
     return o;
 }
 
-// The products of a step, the smallest first, each with its level: A's part, B's part is level - A's.
+constexpr int TDC_LEVELS = 2;
+// whether the parts of weights are lifted
+constexpr bool tdc_lift_weights(int np) { return np == 2; }
+
+// The products of a step, the smallest first, each with its level and the weights' and the activations' part.
 template <int NP>
 struct TdcProducts;
 template <>
 struct TdcProducts<2> {
-    static constexpr int N = 3, level[3] = {1, 1, 0}, a[3] = {1, 0, 0};
+    static constexpr int N = 3, level[3] = {1, 1, 0}, w[3] = {1, 0, 0}, x[3] = {0, 1, 0};
 };
 template <>
 struct TdcProducts<3> {
-    static constexpr int N = 6, level[6] = {2, 2, 2, 1, 1, 0}, a[6] = {2, 1, 0, 1, 0, 0};
+    static constexpr int N = 6, level[6] = {0, 1, 1, 1, 0, 0}, w[6] = {2, 1, 0, 0, 1, 0}, x[6] = {0, 1, 2, 1, 0, 0};
 };
 
 // SWAP: D's rows are the pixels
 template <int NP, bool SWAP = false>
 __device__ __forceinline__ tdc_f4 tdc_mfma_part(int i, const tdc_h8 (&w)[NP], const tdc_h8 (&x)[NP], tdc_f4 c)
 {
-    const int ia = TdcProducts<NP>::a[i], ib = TdcProducts<NP>::level[i] - ia;
-    return SWAP ? __builtin_amdgcn_mfma_f32_16x16x32_f16(x[ib], w[ia], c, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x32_f16(w[ia], x[ib], c, 0, 0, 0);
+    const int iw = TdcProducts<NP>::w[i], ix = TdcProducts<NP>::x[i];
+    return SWAP ? __builtin_amdgcn_mfma_f32_16x16x32_f16(x[ix], w[iw], c, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x32_f16(w[iw], x[ix], c, 0, 0, 0);
 }
 
 // accumulators of the levels -> the sum
-template <int NP>
-__device__ __forceinline__ tdc_f4 tdc_levels(const tdc_f4 (&acc)[NP])
+__device__ __forceinline__ tdc_f4 tdc_levels(const tdc_f4 (&acc)[TDC_LEVELS])
 {
-    tdc_f4 v = acc[NP - 1];
+    tdc_f4 v;
 #pragma unroll
-    for (int q = NP - 2; q >= 0; --q)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = fmaf(v[i], 0x1p-11f, acc[q][i]);
+    for (int i = 0; i < 4; ++i) v[i] = fmaf(acc[1][i], 0x1p-11f, acc[0][i]);
     return v;
 }
 
@@ -179,6 +182,7 @@ __device__ __forceinline__ int tdc_scale_of(unsigned bits, int target, int other
 }
 constexpr int TDC_X_TARGET = 10, TDC_X_OTHER = 6, TDC_Z2_TARGET = 12;
 constexpr int TDC_LOWEST = -13;      // scaled values from 2^TDC_LOWEST on keep all their bits
+constexpr int tdc_lowest_weight(int np) { return tdc_lift_weights(np) ? TDC_LOWEST : -1; }
 
 // k-group kg's share of a lane's fp32 weights of 16-channel block `block` (layout: tdc_internal.h)
 __device__ __forceinline__ tdc_f4 tdc_raw_weights(tdc_rsrc r, int block, int k_groups, int kg, int lane)

@@ -1,6 +1,7 @@
 // The dense layer for launches that are bound by matrix arithmetic or by memory bandwidth, not by latency: an implicit GEMM
 //   D[m][p] = sum_k Wt[k][m] * Act[k][p]
-// in TM x 64 tiles (output channels x pixels), fp32 in and out, products in three bf16 parts (tdc_bf3.h).
+// in TM x 64 tiles (output channels x pixels), fp32 in and out, products in two or three scaled fp16
+// parts (tdc_split.h).
 //
 // Pixels are numbered through the whole batch, p = b*P + (pixel of image b), so small images leave no part-empty tiles.
 // A workgroup is KS groups of four wavefronts; the contraction goes in steps of two 16-wide k-groups (tap, channel block),
@@ -9,15 +10,14 @@
 // one barrier per step.  The weights were split when they were re-laid out; a wavefront loads its own fragments straight
 // into registers, one step ahead.
 //
-// What bounds it, and why this form.  The six products per fp32 product cost 768 cycles of the matrix cores for a
-// 128 x 64 step.  The other resources of a compute unit are then all about half busy: the L1 path (54 bytes a cycle
-// measured; 32 KB a step), LDS (128 bytes a cycle; 60 KB and its conflicts), and instruction issue (an MFMA leaves room for
-// two other vector instructions: the conversions are placed between them).  Measured variants of the loop, 128 x 64, on
+// What bounds it, and why this form.  Two parts cost three products per fp32 product, 384 cycles of the matrix cores for a
+// 128 x 64 step; the L1 path (24 KB a step), LDS (40 KB and its conflicts) and instruction issue (an MFMA leaves room for
+// two other vector instructions: the conversions are placed between them) are then about as busy: 3x3, 128 -> 128 at 28x28,
+// batch 8: 19.8 us with three bf16 parts, six products, 17.7 with two fp16 ones.  Variants of the loop as measured with the
+// three bf16 parts, 128 x 64, on
 // 1024 -> 512 at 14x14, batch 32 (6.6 GFLOP): both operands through LDS, two barriers a step 53 us; no LDS, every wavefront
 // loading and splitting its own pixels 64 us (NHWC loads of 16 pixels x 64 bytes run at 18 bytes a cycle, a third of
-// contiguous ones); this one without the interleaving 42.8 us, as it stands 39.8 us (fp32 MFMA kernel: 90.5 us).  On large
-// products it runs at 209 TFLOP/s of fp32 products, 1250 of bf16 ones -- what the vendor's bf16 GEMM of 8192^3 reaches on
-// the card (1241): power, not issue, is the limit there (all-zero operands: 273 TFLOP/s).
+// contiguous ones); this one without the interleaving 42.8 us, with it 39.8 us (fp32 MFMA kernel: 90.5 us).
 #include <algorithm>
 
 #include "tdc_split.h"
@@ -73,7 +73,7 @@ __device__ __forceinline__ void tile_plain_output(const TileArgs &a, int m, int 
     a.out[idx] = tdc_apply_epilogue(a.epi, sum, m, idx);
 }
 
-// A wavefront's sums once more on the fp32 matrix cores, one load at a time (see tdc_bf3.h), unless their NaNs are x's or the
+// A wavefront's sums once more on the fp32 matrix cores, one load at a time (see tdc_split.h), unless their NaNs are x's or the
 // weights'.  Returns a bit per sum of this lane for those that an infinite weight at a tap outside the image made NaN (it is 0
 // times the weight here, and no part of the sum).  3x3, 128 -> 128 at 28x28,
 // batch 8, every value NaN: 70 us, 26 with numbers (one output after the other: 5350).
@@ -188,10 +188,10 @@ __device__ __forceinline__ void tile_store_4(const TileArgs &a, tdc_f4 v, int p,
 }
 
 // Wavefronts per SIMD an instance has registers for.
-constexpr int tile_wavefronts(int mb_pb, int np) { return mb_pb > 4 ? 2 : np == 3 ? 2 : 3; }
+constexpr int tile_wavefronts(int mb_pb) { return mb_pb > 4 ? 2 : 3; }
 
 template <int ACT, bool CONV, int WM, int MB, int PB, int KS, int NP>
-__global__ __launch_bounds__(256 * KS, tile_wavefronts(MB * PB, NP)) void tdc_tile_kernel(TileArgs a)
+__global__ __launch_bounds__(256 * KS, tile_wavefronts(MB * PB)) void tdc_tile_kernel(TileArgs a)
 {
     constexpr int WP = 4 / WM, TM = 16 * MB * WM, TP = 16 * PB * WP;
     constexpr int NX = TP / 32;                    // 16-byte pieces of activations a thread brings per step
@@ -324,13 +324,13 @@ __global__ __launch_bounds__(256 * KS, tile_wavefronts(MB * PB, NP)) void tdc_ti
 
     // NCHW y: operands swapped, so that a lane ends up with four consecutive pixels of one channel
     constexpr bool SWAP = ACT == TDC_ACT_NCHW;     // an NCHW activation means an NCHW y
-    tdc_f4 lev[MB][PB][NP];
+    tdc_f4 lev[MB][PB][TDC_LEVELS];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
-            for (int q = 0; q < NP; ++q) lev[mb][pb][q] = tdc_f4_zero();
+            for (int q = 0; q < TDC_LEVELS; ++q) lev[mb][pb][q] = tdc_f4_zero();
     const auto read_b = [&](const tdc_u4 *__restrict__ xb, int pb) {
         tdc_op<NP> b;
 #pragma unroll
@@ -406,7 +406,7 @@ __global__ __launch_bounds__(256 * KS, tile_wavefronts(MB * PB, NP)) void tdc_ti
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int pb = 0; pb < PB; ++pb) acc[mb][pb] = tdc_levels<NP>(lev[mb][pb]);
+        for (int pb = 0; pb < PB; ++pb) acc[mb][pb] = tdc_levels(lev[mb][pb]);
     if (KS == 1) __syncthreads();
     if constexpr (KS == 2) {   // the second group's sums join the first's, always in this order
         __syncthreads();
@@ -641,13 +641,13 @@ __global__ __launch_bounds__(256, MB == 2 ? 2 : 3) void tdc_tile_1x1_kernel(Tile
             for (int pb = 0; pb < PB; ++pb)
                 res[mb][pb] = with_res && live && out_at[pb] != NOWHERE ? *reinterpret_cast<const tdc_f4 *>(shortcut + (out_at[pb] + 4u * (NHWC ? m : m * a.P))) : tdc_f4_zero();
         }
-        tdc_f4 lev[MB][PB][NP];
+        tdc_f4 lev[MB][PB][TDC_LEVELS];
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
-                for (int q = 0; q < NP; ++q) lev[mb][pb][q] = tdc_f4_zero();
+                for (int q = 0; q < TDC_LEVELS; ++q) lev[mb][pb][q] = tdc_f4_zero();
         for (int s = 0; s < a.S; ++s) {
             tdc_op<NP> w1[MB];
             const bool turn = s + 1 == a.S;
@@ -675,7 +675,7 @@ __global__ __launch_bounds__(256, MB == 2 ? 2 : 3) void tdc_tile_1x1_kernel(Tile
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int pb = 0; pb < PB; ++pb) {
-                acc[mb][pb] = tdc_levels<NP>(lev[mb][pb]);
+                acc[mb][pb] = tdc_levels(lev[mb][pb]);
                 largest = tdc_largest(largest, acc[mb][pb]);
             }
         bool redone = false;

@@ -217,3 +217,47 @@ def test_the_scale_of_the_factors_costs_no_accuracy(orc, layer, nhwc):
             got = _run(layer, inputs, tm, waves, nhwc).astype(np.float64)
             for part in (np.abs(want) < 1e-25, np.abs(want) >= 1e-25):
                 assert not part.any() or np.linalg.norm((got - want)[part] * 2.0 ** 60) <= 1.2e-6 * np.linalg.norm(want[part] * 2.0 ** 60)
+
+
+# 1x1 layers whose pixels, all channels, stay in LDS: 512 pixel tiles, so that a workgroup takes two or three channel tiles.
+# P odd (4-byte NCHW stores, a tile over two images) and a multiple of 4; 72 channels are the last in three parts, 73 and 76 the
+# first in two, 288 the most that fit, 292 go through the tile kernel.
+@pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
+@pytest.mark.parametrize("C", (20, 72, 73, 76, 288, 292))
+@pytest.mark.parametrize("W", (127, 128))
+def test_1x1_layers_that_run_over_several_channel_tiles(nhwc, C, W):
+    if nhwc and C % 4:
+        pytest.skip("NHWC needs channel counts that are multiples of 4")
+    layer = Layer(2, C, 136, 32768 // 2 // W, W, 1, 1, 1, 1, 0)
+    inputs = make_dense_inputs(layer, 84)
+    rng = np.random.default_rng(7)
+    bias = rng.standard_normal(layer.N, dtype=np.float32)
+    residual = rng.standard_normal((layer.batch, layer.N, layer.Ho, layer.Wo), dtype=np.float32)
+    plain = np.matmul(inputs["W"][:, :, 0, 0].astype(np.float64).T, inputs["x"].reshape(2, C, -1)).reshape(residual.shape)
+    want = np.maximum(plain + bias[None, :, None, None] + residual, 0.0)
+    for tm in (64, 128):
+        for offset in (0,) if nhwc else (0, 1):
+            print("[case] 1x1", layer.name(), "nhwc" if nhwc else "nchw", tm, offset, flush=True)
+            assert_parity(_run(layer, inputs, tm, 4, nhwc, bias, residual, offset), want, "%s tile %d" % (layer.name(), tm))
+        got = _run(layer, inputs, tm, 4, nhwc)
+        # 9e-8 (72 terms, three parts) to 1.4e-7 (288, two): three times the larger; fp32 multiply-adds show 3.1e-7 at 288
+        assert np.linalg.norm(got - plain) <= 4.2e-7 * np.linalg.norm(plain)
+
+
+@pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
+@pytest.mark.parametrize("layer", (Layer(2, 160, 72, 13, 9, 1, 1, 1, 1, 0), Layer(2, 40, 72, 13, 9, 1, 1, 3, 1, 1)), ids=lambda l: l.name())
+def test_values_far_from_those_that_set_the_scale(orc, layer, nhwc):
+    """x is scaled by what a workgroup loads first.  Channels behind that up to 64 times larger fit in fp16 and larger ones do
+    not; pixels down to 2^-23 of it keep all their bits and smaller ones do not.  Both sides of each line."""
+    for what, e in [("channels", e) for e in (4, 6, 7, 9, 40)] + [("pixels", -e) for e in (10, 21, 23, 25, 40)]:
+        inputs = make_dense_inputs(layer, 85)
+        if what == "channels":
+            inputs["x"][:, -8:] *= np.float32(2.0 ** e)
+        else:
+            inputs["x"][0, :, 5:] *= np.float32(2.0 ** e)
+        want = _oracle(orc, layer, inputs)
+        for tm, waves in ((64, 4), (128, 8)):
+            print("[case] tiles, far from the scale", what, e, layer.name(), "nhwc" if nhwc else "nchw", tm, waves, flush=True)
+            err = _run(layer, inputs, tm, waves, nhwc) - want
+            # pixel by pixel, each against its own size: 360 terms, as in test_tiles
+            assert (np.linalg.norm(err, axis=1) <= 1.2e-6 * np.linalg.norm(want, axis=1)).all()
