@@ -34,11 +34,14 @@
  * the host and never allocate, and a conv call with re-laid-out weights enqueues
  * nothing but its kernels, so it may be captured into a HIP graph.
  *
- * Precision: fp32 in, fp32 out, sums in fp32.  Kernels bound by matrix arithmetic multiply on the bf16 matrix cores with
- * every fp32 factor split into three bf16 parts (all 24 bits).  Values that have no such parts are multiplied in fp32 as
- * the other kernels do: infinities, NaN, magnitudes from 2^126 on, and pixels and weight tensors in which nothing reaches
- * 2^-110.  What such values reach then takes several times as long (NaN alone: twice to three times).  A factor
- * below 2^-110 beside larger ones, of its pixel or of its weight tensor, keeps an absolute accuracy of 2^-134.
+ * Precision: fp32 in, fp32 out, sums in fp32.  Kernels bound by matrix arithmetic multiply on the fp16 matrix cores with
+ * every fp32 factor scaled by a power of two (weights by output channel, x by workgroup) and split into two fp16 parts, 23
+ * bits, or, in sums of few terms, three; against 64 bits that is no further off than fp32 multiply-adds.  What fp16 cannot
+ * hold is multiplied in fp32 as the other kernels do: infinities, NaN, values of x more than 64 times those its workgroup
+ * loads first, and pixels of which no channel reaches 2^-23 of them.  A tile that such values reach takes several times as
+ * long (NaN alone: twice to three times).  A value of x below 2^-23 of its neighbourhood, beside larger channels of its own
+ * pixel, keeps an absolute accuracy of 2^-46 of that neighbourhood, and a weight below 2^-26 of its output channel's
+ * largest one of 2^-49 of that.
  *
  * Errors: every function returns a tdc_status (0 = success, negative =
  * failure).  Nothing aborts, throws or prints.
@@ -134,7 +137,7 @@ enum {
  *                    kernel has no tile: one below 64, half of one, or one beside mb[1] or pb[1] above 1 is ignored
  *   mb, pb         : 16-channel and 16-pixel blocks per wavefront register tile, per stage
  *                    (CHAIN uses mb[0] and pb[0]; its stage-2 tile is all of R2 by construction)
- *   CHAIN, mb[1]=3 : the same kernel on the bf16 matrix cores, factors in three parts: waves 4, mb[0] 1 to 3, pb[0] 2 or 4
+ *   CHAIN, mb[1]=3 : the same kernel on the fp16 matrix cores, factors in parts: waves 4, mb[0] 1 to 3, pb[0] 2 or 4
  *                    (what AUTO takes for most layers from 16 output pixels per compute unit, from 8 for some that would be
  *                    FUSED's).  R2 up to 80 (pb[0] = 4: 48); beyond that, and for any other mb[1], the fp32 kernel */
 typedef struct tdc_tuning {

@@ -48,7 +48,7 @@ def candidates(L: Layer, variants: Iterable[str] = ("fused", "chain", "split", "
     if "chain" in variants:
         for (th, tw), nw, mb1, pb in itertools.product(_tiles(L), (1, 2, 4, 8), (1, 2, 4), (1, 2)):
             out.append(dict(variant=B.VARIANT_CHAIN, tile_h=th, tile_w=tw, waves=(nw,) * 3, mb=(mb1, 1, 1), pb=(pb,) * 3))
-        # the bf16 matrix cores (ranks up to 80): the tiles above and, where four wavefronts have one group of pixel blocks each, all others
+        # the fp16 matrix cores (ranks up to 80): the tiles above and, where four wavefronts have one group of pixel blocks each, all others
         tiles = set(_tiles(L)) | {(th, tw) for th in range(1, min(L.Ho, 32) + 1) for tw in range(min(L.Wo, 4), min(L.Wo, 64) + 1)
                                   if 16 <= th * tw <= 128 and (tw % 4 == 0 or tw == L.Wo)}
         for (th, tw), mb1, pb in itertools.product(sorted(tiles) if L.R2 <= 80 else (), (1, 2, 3), (2, 4)):
@@ -254,7 +254,7 @@ def against_fp32_main(layers: List[Layer], layout: int, iters: int) -> int:
         if bf3:
             ratios.append(r["fp32_us"] / r["auto_us"])
     if ratios:
-        print("%d layers on the bf16 matrix cores: %.2f to %.2f times as fast as the best fp32 kernel's pick, %.2f on (geometric) average" % (
+        print("%d layers on the fp16 matrix cores: %.2f to %.2f times as fast as the best fp32 kernel's pick, %.2f on (geometric) average" % (
             len(ratios), min(ratios), max(ratios), float(__import__("numpy").exp(__import__("numpy").log(ratios).mean()))))
     return 0
 

@@ -192,7 +192,7 @@ enum {
     C_NB3_LDS, C_BLK3,                             // stage 3 per output block with weights in LDS, per MFMA quad
     C_W_KB, C_X_MB_NCHW, C_X_MB_NHWC, C_X_MB_RUNS, C_Y_MB, C_X_ROWS, C_Y_ROWS,
     C_NOVEC,                                       // per output-channel block and pixel block stored with 4-byte stores
-    // the kernel on the bf16 matrix cores has terms of its own, the launch apart: thousands of cycles of stage 1, of stages 2
+    // the kernel on the fp16 matrix cores has terms of its own, the launch apart: thousands of cycles of stage 1, of stages 2
     // and 3, and chains of phases, each times what sharing a compute unit adds (see chain3_terms)
     C_BF3_S1, C_BF3_S23, C_BF3_PHASES,
     C_TERMS
@@ -301,8 +301,8 @@ FusedChoice best_chain(const TdcDims &d, const TdcDeviceInfo &dev, const tdc_tun
     return best;
 }
 
-// CHAIN on the bf16 matrix cores (tdc_chain3.hip): a workgroup of four wavefronts is a chain of phases, in cycles of its SIMD
-// (96 per fp32 product block: six MFMAs of 16 cycles): stage 1 in rounds of four units, then one group of two pixel blocks
+// CHAIN on the fp16 matrix cores (tdc_chain3.hip): a workgroup of four wavefronts is a chain of phases, in cycles of its SIMD
+// (96 per fp32 product block, six MFMAs of 16 cycles, as the terms were set; two parts take half): stage 1 in rounds of four units, then one group of two pixel blocks
 // per wavefront.  Sweeps of ten layers (tiles of 32 to 800 pixels, groups of two and four blocks) were won by tiles that give
 // every wavefront exactly one group of two -- 128 pixels at most -- or lay within 4 % of such a tile, so only those are
 // compared.  (With the buffers of a call in cache larger tiles win four of sixteen throughput cases, by 15 to 21 %.)  Two or
@@ -538,7 +538,7 @@ StageChoice best_stage(const TdcDeviceInfo &dev, int batch, int n_mblocks, int n
     return best;
 }
 
-// The dense layer in tiles on the bf16 matrix cores (tdc_tile.hip).  Either a workgroup's own chain of steps bounds the
+// The dense layer in tiles on the fp16 matrix cores (tdc_tile.hip).  Either a workgroup's own chain of steps bounds the
 // launch -- few workgroups, each alone on its compute unit -- or the work of all of them, S steps of every tile dealt to the
 // compute units plus what a tile costs however short its contraction (first loads, epilogue).  Microseconds, from the 30
 // dense layers of the batch-32 ResNet-50-shaped network and a dozen 3x3 layers (14 % off at worst where the tile kernel
@@ -799,7 +799,7 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
         return TDC_OK;
     }
 
-    // Where the output pixels fill the chip (16 per compute unit) CHAIN on the bf16 matrix cores is the fastest form: 621 drawn
+    // Where the output pixels fill the chip (16 per compute unit) CHAIN on the fp16 matrix cores is the fastest form: 621 drawn
     // layers run 1.26 times as fast on average as with the fp32 kernel chosen before (NCHW 0.86 to 2.1, NHWC 0.92 to 2.5; 21 of
     // them 3 to 14 % slower), e.g. 34.3 -> 28.5 us (98 pixels per compute unit, stride 2), 22.2 -> 19.3 (24 pixels), 97.2 -> 77.4
     // (784).  The estimates are not compared: they are not on one scale.  Not with ranks of a single block below 128 pixels (36 pixels: 7.6

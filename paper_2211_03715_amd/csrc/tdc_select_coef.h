@@ -10,7 +10,7 @@ static const double kFusedLatencyCoef[22] = {3.0025, 0.1184, 0, 0.0828, 0, 0, 0,
 // fused, throughput regime: same terms
 static const double kFusedThroughputCoef[22] = {3.8605, 0, 0.0988, 0.0347, 0.6828, 0.1891, 0.0176, 0.0560, 0.0826, 0.0210, 0.1531, 0.0330, 0.0167, 0.1457, 0.0207, 19.2123, 11.7344, 6.1081, 48.2178, 30.6810, 0.2834, 0.4272};
 // chain: launch s1_unit s1_kg s1_mfma s1r_unit s1r_kg s1r_mfma kg2_lds kg2_glb blk2 nb3_lds blk3 w_kb x_mb_nchw x_mb_nhwc x_mb_runs y_mb x_rows y_rows novec, then
-// the bf16 kernel's own: bf3_s1_kcyc bf3_s23_kcyc bf3_phases (set from sweeps of ten layers, not by --fit)
+// the kernel in parts' own: bf3_s1_kcyc bf3_s23_kcyc bf3_phases (set from sweeps of ten layers, not by --fit)
 static const double kChainCoef[23] = {3.6918, 0.5859, 0.0211, 0.0906, 0.2783, 0.3798, 0.0096, 0.0298, 0.2335, 0.0141, 0.2690, 0.0402, 0.0235, 6.4658, 0, 15.9944, 32.4026, 0.2683, 2.9056, 0.1707, 0.5, 0.5, 3.0};
 // fused-merged: launch s1_unit s1_kg s1_mfma frag reduce x_mb_nchw x_mb_nhwc wgs
 static const double kFmCoef[9] = {2.5879, 0.2174, 0.0197, 0.0407, 0.0803, 0.4477, 38.3935, 16.4747, 0.5418};
