@@ -918,16 +918,21 @@ int tdc_select(const TdcDims &d, const TdcDeviceInfo &dev, tdc_tuning *t, double
         // batch 64: 50.2 against 38.3 us; 256 channels on 56x56: 17.9 against 17.4 us), 2 % ahead at best.
         variant = (f.us <= 0.92 * split_us || (pixels_fill_chip && f.us < 1e299)) ? TDC_VARIANT_FUSED : TDC_VARIANT_SPLIT;
     }
-    // From 8 pixels per compute unit on what would be SPLIT's runs there too, 1x1 layers apart (12 drawn layers: 1.04 to 1.71 times
-    // as fast), and what would be FUSED's: 65 drawn layers, 1.21 times as
+    // From 8 pixels per compute unit on what would be FUSED's runs there too: 65 drawn layers, 1.21 times as
     // fast on average (0.85 to 1.76).  Not at stride 1 in 1x1 layers (12x11, 372 ->
     // 284, batch 28: 10.7 against 12.4 us), nor there with at most three blocks of R1 where NCHW rows are no multiple of 4 (26x38,
     // 112 -> 160, ranks 20 and 32: 9.5 against 11.0; 13x13, 3x3), nor with a single block
     // of R1 (14x14, 40 -> 368, ranks 10 and 71: 14.0 against 15.3).  5x5 taps and four block pairs are worth it there too
     // (37x29, ranks 24 and 40, batch 3: 16.4 -> 13.6).
-    const bool worth_it = d.stride > 1 || (d.K >= 5 && d.NB1 * d.NB2 >= 4) || (variant == TDC_VARIANT_SPLIT && d.K > 1) || (d.K > 1 && (d.nhwc || d.Wo % 4 == 0 || d.NB1 > 3));
+    // What would be SPLIT's, 1x1 layers apart, where every tile has a compute unit to itself and the estimate is well below
+    // SPLIT's: 79 of 128 drawn layers, 1.33 times as fast on average (0.93 to 1.74); the others 1.06 times, 17 of them slower, where
+    // stage 1 dominates and is done again for the halo of small tiles (37x37, 432 -> 208, ranks 197 and 29, batch 2: 32.7
+    // against 59.8 us; 5x5, 304 -> 32, ranks 107 and 11: 18.4 against 29.5).
+    const bool from_split = variant == TDC_VARIANT_SPLIT && d.K > 1;
+    const bool worth_it = from_split || d.stride > 1 || (d.K >= 5 && d.NB1 * d.NB2 >= 4) || (d.K > 1 && (d.nhwc || d.Wo % 4 == 0 || d.NB1 > 3));
     if (forced.variant == TDC_VARIANT_AUTO && !pixels_fill_chip && d.NB1 > 1 && !few_products && worth_it &&
-        pixels >= 8L * dev.cus && try_chain3(c3))
+        pixels >= 8L * dev.cus && try_chain3(c3) &&
+        (variant != TDC_VARIANT_SPLIT || (from_split && c3.us <= 0.75 * split_us && (long)cdiv(d.Ho, c3.th) * cdiv(d.Wo, c3.tw) * d.B <= dev.cus)))
         return chain3(c3);
     if (variant == TDC_VARIANT_FUSED) {
         if (f.us >= 1e299) return TDC_ERR_BAD_TUNING;
