@@ -17,7 +17,7 @@ LIB = os.path.join(PKG, "libtdc.so")
 
 SOURCES = ["tdc_api.hip", "tdc_pack.hip", "tdc_naive.hip", "tdc_gemm.hip", "tdc_tile.hip", "tdc_fused.hip", "tdc_chain.hip", "tdc_chain_mb1.hip", "tdc_chain_mb2.hip", "tdc_chain_mb4.hip",
            "tdc_chain3.hip", "tdc_chain3_nchw.hip", "tdc_chain3_runs.hip", "tdc_chain3_nhwc.hip",
-           "tdc_chain_bf3.hip", "tdc_chain_bf3_nchw.hip", "tdc_chain_bf3_runs.hip", "tdc_chain_bf3_nhwc.hip", "tdc_pack_bf3.hip",
+           "tdc_chain_bf3.hip", "tdc_chain_bf3_nchw.hip", "tdc_chain_bf3_runs.hip", "tdc_chain_bf3_nhwc.hip", "tdc_pack_bf3.hip", "tdc_tile_bf3.hip",
            "tdc_fm.hip", "tdc_select.cpp", "tdc_ranks.cpp", "tdc_hosvd.cpp"]
 
 # Packed-fp32 VALU instructions are switched off for every device translation unit.

@@ -362,7 +362,9 @@ int tdc_plan_create_tuned(tdc_plan **out, const tdc_shape *shape, int device, co
         p->ws_bytes += (n_w1 + n_wm + n_wmp) * sizeof(float);
     }
     if (dense) {
-        const size_t bytes = tdc_is_tile(p->tuning) ? tdc_split_alloc_bytes(tdc_tile_parts(d), d.NB2, d.K * d.K * d.NB1) : n_w2 * sizeof(float);
+        const size_t bytes = !tdc_is_tile(p->tuning) ? n_w2 * sizeof(float)
+                             : tdc_tile_bf3(d, p->tuning.waves[1] / 4) ? tdc_packed3_bytes(d.NB2, d.K * d.K * d.NB1) + TDC_PACKED3_TAIL
+                                                                       : tdc_split_alloc_bytes(tdc_tile_parts(d), d.NB2, d.K * d.K * d.NB1);
         ok = ok && hipMalloc((void **)&p->core_p, bytes) == hipSuccess;
         p->ws_bytes += bytes;
     }
@@ -561,7 +563,9 @@ int tdc_conv_tucker2_ex(tdc_plan *p, void *hip_stream, const float *x, const flo
 
 static hipError_t pack_dense(const tdc_plan &p, hipStream_t s, const float *W)
 {
-    return tdc_is_tile(p.tuning) ? tdc_launch_split_core(p.dims, tdc_tile_parts(p.dims), s, W, p.core_p) : tdc_launch_pack_core(p.dims, s, W, p.core_p);
+    if (!tdc_is_tile(p.tuning)) return tdc_launch_pack_core(p.dims, s, W, p.core_p);
+    if (tdc_tile_bf3(p.dims, p.tuning.waves[1] / 4)) return tdc_launch_pack3_core(p.dims, s, W, p.core_p);
+    return tdc_launch_split_core(p.dims, tdc_tile_parts(p.dims), s, W, p.core_p);
 }
 
 int tdc_plan_pack_dense(tdc_plan *p, void *hip_stream, const float *W)

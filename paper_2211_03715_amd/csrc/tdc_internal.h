@@ -68,10 +68,10 @@ inline size_t tdc_split_alloc_bytes(int parts, int m_blocks, int k_groups)
     return tdc_split_bytes(parts, m_blocks, k_groups) + (size_t)m_blocks * (64 + (size_t)k_groups * 1024 + 128 * TDC_SPLIT_CHUNKS);
 }
 // Parts a weight is split into.  Two fp16 parts are the more accurate form from some 70 terms to a sum on (tdc_split.h); the three sums
-// of a Tucker layer add up to that from 208 on: squared errors of 78 + 0.39 n against 2.1 n - 40 (in 1e-16, n terms).  Below, the
-// dense tiles take three fp16 parts (1.1 times as fast as three bf16 ones) and CHAIN three bf16 ones, which need no scale and
-// so no first look at x: 90 drawn layers of such short sums run 1.05 times as fast with them on average (0.9 to 1.31, the larger where
-// memory or latency bounds them: 208x208, 48 -> 42, ranks 13 and 8, batch 3: 20.6 against 26.7 us).
+// of a Tucker layer add up to that from 208 on: squared errors of 78 + 0.39 n against 2.1 n - 40 (in 1e-16, n terms).  Below, CHAIN
+// and the dense tiles take three bf16 ones, which need no scale and so no first look at x: 90 drawn Tucker layers of such short sums run
+// 1.05 times as fast with them as with three fp16 parts on average (0.9 to 1.31, the larger where memory or latency bounds
+// them: 208x208, 48 -> 42, ranks 13 and 8, batch 3: 20.6 against 26.7 us).  1x1 layers that keep their pixels in LDS take three fp16 ones.
 inline int tdc_tile_parts(const TdcDims &d) { return d.K * d.K * d.R1 > 72 ? 2 : 3; }
 inline bool tdc_chain3_bf3(const TdcDims &d) { return d.C + d.K * d.K * d.R1 + d.R2 < 208; }
 // In three bf16 parts (tdc_bf3.h), unscaled and otherwise alike.  An allocation holds TDC_PACKED3_TAIL bytes more, which the
@@ -82,6 +82,7 @@ inline size_t tdc_chain3_weight_bytes(const TdcDims &d, int m_blocks, int k_grou
 {
     return tdc_chain3_bf3(d) ? tdc_packed3_bytes(m_blocks, k_groups) + TDC_PACKED3_TAIL : tdc_split_alloc_bytes(2, m_blocks, k_groups);
 }
+hipError_t tdc_launch_pack3_core(const TdcDims &d, hipStream_t s, const float *core, void *core_p3);
 hipError_t tdc_launch_pack3(const TdcDims &d, hipStream_t s, const float *U_in, const float *core, const float *U_out,
                             void *uin_p3, void *core_p3, void *uout_p3);
 hipError_t tdc_launch_split_core(const TdcDims &d, int parts, hipStream_t s, const float *core, void *core_sp);
@@ -116,7 +117,10 @@ inline bool tdc_is_tile(const tdc_tuning &t)
 bool tdc_tile_supported(int tm, int tp, int ks);
 bool tdc_tile_applies(const TdcDims &d);
 bool tdc_tile_1x1_applies(const TdcDims &d);   // one group of wavefronts runs it with all its channels in LDS
+inline bool tdc_tile_bf3(const TdcDims &d, int ks) { return tdc_tile_parts(d) == 3 && !(ks == 1 && tdc_tile_1x1_applies(d)); }
 hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipStream_t s, const float *x, const void *w, float *y, const TdcEpi &epi);
+// weights in tdc_launch_pack3_core's layout
+hipError_t tdc_launch_tile_bf3(const TdcDims &d, int tm, int tp, int ks, hipStream_t s, const float *x, const void *w3, float *y, const TdcEpi &epi);
 
 // stage 1, then stages 2 and 3 as one implicit GEMM with the merged kernel
 hipError_t tdc_launch_merged(const TdcDims &d, const tdc_tuning &t, hipStream_t s, const float *x,

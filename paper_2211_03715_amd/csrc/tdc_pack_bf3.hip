@@ -1,4 +1,4 @@
-// Weight re-layout in three bf16 parts (tdc_bf3.h, layout: tdc_internal.h), for the layers that run CHAIN in them.
+// Weight re-layout in three bf16 parts (tdc_bf3.h, layout: tdc_internal.h), for the layers that run CHAIN or the dense tiles in them.
 #include "tdc_bf3.h"
 #include "tdc_internal.h"
 
@@ -86,5 +86,15 @@ hipError_t tdc_launch_pack3(const TdcDims &d, hipStream_t s, const float *U_in, 
     hipLaunchKernelGGL(pack3_matrix_kernel, dim3((unsigned)((n1 + T - 1) / T)), dim3(T), 0, s, d.C, d.R1, U_in, (unsigned *)uin_p3, r.largest[0], n1);
     hipLaunchKernelGGL(pack3_matrix_kernel, dim3((unsigned)((n3 + T - 1) / T)), dim3(T), 0, s, d.R2, d.N, U_out, (unsigned *)uout_p3, r.largest[2], n3);
     hipLaunchKernelGGL(pack3_core_kernel, dim3((unsigned)((n2 + T - 1) / T)), dim3(T), 0, s, d, core, (unsigned *)core_p3, r.largest[1], n2);
+    return hipGetLastError();
+}
+
+hipError_t tdc_launch_pack3_core(const TdcDims &d, hipStream_t s, const float *core, void *core_p3)
+{
+    const int T = 256;
+    const size_t bytes = tdc_packed3_bytes(d.NB2, d.K * d.K * d.NB1), n = bytes / 12;
+    const RangeArgs r = {{core}, {(size_t)d.R1 * d.R2 * d.K * d.K}, {pack3_largest(core_p3, bytes)}};
+    hipLaunchKernelGGL(pack3_range_kernel, dim3(RANGE_BLOCKS), dim3(256), 0, s, r);
+    hipLaunchKernelGGL(pack3_core_kernel, dim3((unsigned)((n + T - 1) / T)), dim3(T), 0, s, d, core, (unsigned *)core_p3, r.largest[0], n);
     return hipGetLastError();
 }

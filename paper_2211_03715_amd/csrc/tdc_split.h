@@ -5,14 +5,14 @@
 // the parts have 11 significand bits each, so two of them are off by at most half a bit of the 24 (v3 is what is left).
 // The products of parts i and j with i + j < parts are accumulated, in fp32 by the matrix core, in two accumulators ("levels"), the
 // second of which is 2^11 times the sum and is added at the end.  Three parts of a weight are not lifted, w = w1 + w2 + w3, so
-// that their products need no third one: 64 x 64 tiles fit three wavefronts to a SIMD so:
+// that their products need no third one:
 //     two parts:    w1 x1 | w1 x2 + w2 x1                                      3 MFMAs of 16 cycles per 16 x 16 x 32 block
 //     three parts:  w1 x1 + w2 x1 + w3 x1 | w1 x2 + w2 x2 + w1 x3              6 (fp32 MFMA: 8 of 32)
 // Only the accumulations of the highest level round at the scale of the result, n/32 of them.  Measured against 64 bits
 // (normal values, relative 2-norm): at n = 32 / 64 / 128 / 288 / 1152 / 4608 terms two parts 9.0e-8 / 9.7e-8 / 1.1e-7 / 1.4e-7 /
 // 2.3e-7 / 4.4e-7; three bf16 parts in one accumulator (tdc_bf3.h) 3.8e-8 / 9.3e-8 / 1.6e-7 / 2.4e-7 / 5.1e-7 / 1.08e-6;
 // v_mfma_f32_16x16x4_f32 1.0e-7 / 1.4e-7 / 2.0e-7 / 3.1e-7 / 6.0e-7 / 1.2e-6.  Sums too short for two parts to be the most
-// accurate of these take three (tdc_tile_parts) or, in CHAIN, three bf16 ones (tdc_chain3_bf3).
+// accurate of these take three or, in most kernels, three bf16 ones (tdc_tile_parts, tdc_chain3_bf3).
 //
 // Scales.  fp16 holds 2^-24 .. 65504, so v2 keeps its 11 bits down to |v| = 2^-13 and the parts an absolute 2^-36 below that.
 //   weights      every output channel has its own exponent, the largest weight at 2^13 .. 2^14 (tdc_pack.hip): three parts that

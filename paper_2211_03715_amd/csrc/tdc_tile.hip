@@ -1,7 +1,7 @@
 // The dense layer for launches that are bound by matrix arithmetic or by memory bandwidth, not by latency: an implicit GEMM
 //   D[m][p] = sum_k Wt[k][m] * Act[k][p]
-// in TM x 64 tiles (output channels x pixels), fp32 in and out, products in two or three scaled fp16
-// parts (tdc_split.h).
+// in TM x 64 tiles (output channels x pixels), fp32 in and out, products in two scaled fp16
+// parts (tdc_split.h), three in some 1x1 layers; contractions of at most 72 terms else in three bf16 ones (tdc_tile_bf3.hip).
 //
 // Pixels are numbered through the whole batch, p = b*P + (pixel of image b), so small images leave no part-empty tiles.
 // A workgroup is KS groups of four wavefronts; the contraction goes in steps of two 16-wide k-groups (tap, channel block),
@@ -190,9 +190,10 @@ __device__ __forceinline__ void tile_store_4(const TileArgs &a, tdc_f4 v, int p,
 // Wavefronts per SIMD an instance has registers for.
 constexpr int tile_wavefronts(int mb_pb) { return mb_pb > 4 ? 2 : 3; }
 
-template <int ACT, bool CONV, int WM, int MB, int PB, int KS, int NP>
+template <int ACT, bool CONV, int WM, int MB, int PB, int KS>
 __global__ __launch_bounds__(256 * KS, tile_wavefronts(MB * PB)) void tdc_tile_kernel(TileArgs a)
 {
+    constexpr int NP = 2;                          // parts
     constexpr int WP = 4 / WM, TM = 16 * MB * WM, TP = 16 * PB * WP;
     constexpr int NX = TP / 32;                    // 16-byte pieces of activations a thread brings per step
     constexpr int PITCH = TP + 4;                  // 16-byte cells
@@ -705,16 +706,15 @@ __global__ __launch_bounds__(256, MB == 2 ? 2 : 3) void tdc_tile_1x1_kernel(Tile
 }
 
 template <int ACT, bool CONV>
-hipError_t launch_act(const TileArgs &a, int tm, int tp, int ks, int parts, hipStream_t s)
+hipError_t launch_act(const TileArgs &a, int tm, int tp, int ks, hipStream_t s)
 {
     const dim3 grid((unsigned)(a.n_mt * a.n_pt));
-#define TDC_CASE(M_, P_, WM_, KS_, NP_)                                                                              \
-    if (tm == M_ && tp == P_ && ks == KS_ && parts == NP_) {                                                        \
-        hipLaunchKernelGGL((tdc_tile_kernel<ACT, CONV, WM_, M_ / 16 / WM_, P_ / 16 / (4 / WM_), KS_, NP_>), grid, dim3(256 * KS_), 0, s, a); \
+#define TDC_CASE(M_, P_, WM_, KS_)                                                                                   \
+    if (tm == M_ && tp == P_ && ks == KS_) {                                                                        \
+        hipLaunchKernelGGL((tdc_tile_kernel<ACT, CONV, WM_, M_ / 16 / WM_, P_ / 16 / (4 / WM_), KS_>), grid, dim3(256 * KS_), 0, s, a); \
         return hipGetLastError();                                                                                   \
     }
-    TDC_CASE(128, 64, 4, 1, 2) TDC_CASE(64, 64, 2, 1, 2) TDC_CASE(64, 64, 2, 2, 2) TDC_CASE(128, 64, 4, 2, 2)
-    TDC_CASE(128, 64, 4, 1, 3) TDC_CASE(64, 64, 2, 1, 3) TDC_CASE(64, 64, 2, 2, 3) TDC_CASE(128, 64, 4, 2, 3)
+    TDC_CASE(128, 64, 4, 1) TDC_CASE(64, 64, 2, 1) TDC_CASE(64, 64, 2, 2) TDC_CASE(128, 64, 4, 2)
 #undef TDC_CASE
     return hipErrorInvalidValue;
 }
@@ -771,7 +771,16 @@ bool tdc_tile_applies(const TdcDims &d)
 
 bool tdc_tile_1x1_applies(const TdcDims &d)
 {
-    return d.K == 1 && d.stride == 1 && d.pad == 0 && tdc_tile_applies(d) && tile_1x1_lds_bytes((d.NB1 + 1) / 2, tdc_tile_parts(d)) <= TILE_1X1_LDS;
+    const int parts = tdc_tile_parts(d);
+    if (d.K != 1 || d.stride != 1 || d.pad != 0 || !tdc_tile_applies(d) || tile_1x1_lds_bytes((d.NB1 + 1) / 2, parts) > TILE_1X1_LDS) return false;
+    // Timed against the tile kernels on 121 drawn layers.  NCHW pixels that allow no 16-byte stores were slower in all of 40 (64 -> 368, 80
+    // against 110 us).  Three parts pay from 128 output channels and 3.3 tiles per compute unit on (56 -> 64, batch-bound: 14.5 against
+    // 16.1; 56 -> 140 with 3 tiles: 7.6 against 9.2; 70 -> 192 with 15: 39.6 against 33.0).  The pixels come in before the first product: with
+    // many channels that has to pay for several channel tiles (256 -> 56: 12.5 against 16.1; 260 -> 164: 30.2 against 35.9;
+    // NCHW 243 -> 44: 29.2 against 33.5; 228 -> 96: 26.8 against 22.9; 288 -> 384: 35.4 against 31.9).
+    if (!d.nhwc && (d.Ho * d.Wo) % 4) return false;
+    if (parts == 3) return d.N >= 128 && (double)((d.B * d.Ho * d.Wo + 63) / 64) * ((d.N + 63) / 64) >= 3.3 * 256;
+    return d.R1 <= (d.nhwc ? 200 : 144) || (d.N > 64 && d.R1 <= 256) || d.N > 256;
 }
 
 hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipStream_t s, const float *x, const void *w, float *y, const TdcEpi &epi)
@@ -783,6 +792,7 @@ hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipSt
     a.H = d.H; a.W = d.W; a.Wo = d.Wo; a.K = d.K; a.stride = d.stride; a.pad = d.pad;
     a.n_mt = (d.N + tm - 1) / tm; a.n_pt = (a.Ptot + tp - 1) / tp;
     const int parts = tdc_tile_parts(d);
+    if (tdc_tile_bf3(d, ks)) return tdc_launch_tile_bf3(d, tm, tp, ks, s, x, w, y, epi);
     const size_t w_bytes = tdc_split_bytes(parts, a.NBm, a.KG);
     a.w_bytes = (unsigned)w_bytes;
     a.pt_major = w_bytes < (size_t)d.B * a.C * a.HW * 4;
@@ -799,6 +809,6 @@ hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipSt
         a.div_inner = tdc_make_div((unsigned)a.n_mg);
         return d.nhwc ? launch_1x1<TDC_ACT_NHWC>(a, mb, parts, s) : launch_1x1<TDC_ACT_NCHW>(a, mb, parts, s);
     }
-    if (d.nhwc) return conv ? launch_act<TDC_ACT_NHWC, true>(a, tm, tp, ks, parts, s) : launch_act<TDC_ACT_NHWC, false>(a, tm, tp, ks, parts, s);
-    return conv ? launch_act<TDC_ACT_NCHW, true>(a, tm, tp, ks, parts, s) : launch_act<TDC_ACT_NCHW, false>(a, tm, tp, ks, parts, s);
+    if (d.nhwc) return conv ? launch_act<TDC_ACT_NHWC, true>(a, tm, tp, ks, s) : launch_act<TDC_ACT_NHWC, false>(a, tm, tp, ks, s);
+    return conv ? launch_act<TDC_ACT_NCHW, true>(a, tm, tp, ks, s) : launch_act<TDC_ACT_NCHW, false>(a, tm, tp, ks, s);
 }
