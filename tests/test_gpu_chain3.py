@@ -1,4 +1,4 @@
-"""GPU parity of CHAIN on the bf16 matrix cores (mb[1] = 3: every factor in three parts) at the sizes where it can go wrong:
+"""GPU parity of CHAIN on the 16-bit matrix cores (mb[1] = 3: every factor in two fp16 or three bf16 parts) at the sizes where it can go wrong:
 odd numbers of k-groups in each contraction, channel counts and ranks that fill no block, tiles that leave part of a pixel
 group or of the image empty, taps outside the image, the three ways x is read (NHWC, NCHW four bytes at a time, NCHW in aligned
 runs of four pixels), every unit size."""

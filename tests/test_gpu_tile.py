@@ -1,4 +1,4 @@
-"""GPU parity of the dense layer in tiles on the bf16 matrix cores (every factor in three parts), at the sizes where its
+"""GPU parity of the dense layer in tiles on the 16-bit matrix cores (every factor in two or three parts), at the sizes where its
 tiling can go wrong: contractions that are not whole steps (two 16-wide k-groups), channel counts and pixel counts that leave
 part of a tile empty, images much smaller than a tile, taps outside the image, both activation layouts, both tile heights,
 the contraction dealt to one and to two groups of wavefronts."""
