@@ -183,6 +183,9 @@ __device__ __forceinline__ int tdc_scale_of(unsigned bits, int target, int other
 constexpr int TDC_X_TARGET = 10, TDC_X_OTHER = 6, TDC_Z2_TARGET = 12;
 constexpr int TDC_LOWEST = -13;      // scaled values from 2^TDC_LOWEST on keep all their bits
 constexpr int tdc_lowest_weight(int np) { return tdc_lift_weights(np) ? TDC_LOWEST : -1; }
+constexpr float TDC_FP16_MAX = 65504.f;
+// exponent of the channels of weights that are kept out of the parts, which are NaN
+constexpr int TDC_WIDE = 1 << 20;
 
 // k-group kg's share of a lane's fp32 weights of 16-channel block `block` (layout: tdc_internal.h)
 __device__ __forceinline__ tdc_f4 tdc_raw_weights(tdc_rsrc r, int block, int k_groups, int kg, int lane)
@@ -192,8 +195,7 @@ __device__ __forceinline__ tdc_f4 tdc_raw_weights(tdc_rsrc r, int block, int k_g
 // ... which lie behind the parts and the exponents
 __device__ __forceinline__ const char *tdc_raw_base(const void *parts, unsigned parts_bytes, int m_blocks) { return static_cast<const char *>(parts) + parts_bytes + 64u * m_blocks; }
 
-// Whether the NaNs among some sums can only come from NaNs among their factors: there is one, and the other factors are too
-// small for products or sums to overflow.
+// What some factors hold: whether the NaNs among their sums can only come from NaNs among them.
 struct TdcFactors {
     float largest = 0.f;       // magnitude of the largest that is not NaN
     bool nan = false;

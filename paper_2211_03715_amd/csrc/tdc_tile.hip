@@ -74,11 +74,11 @@ __device__ __forceinline__ void tile_plain_output(const TileArgs &a, int m, int 
 }
 
 // A wavefront's sums once more on the fp32 matrix cores, one load at a time (see tdc_split.h), unless their NaNs are x's or the
-// weights'.  Returns a bit per sum of this lane for those that an infinite weight at a tap outside the image made NaN (it is 0
+// weights': there is a NaN, no infinity, and everything else fits in fp16 at the scales taken.  Returns a bit per sum of this lane for those that an infinite weight at a tap outside the image made NaN (it is 0
 // times the weight here, and no part of the sum).  3x3, 128 -> 128 at 28x28,
 // batch 8, every value NaN: 70 us, 26 with numbers (one output after the other: 5350).
 template <int ACT, bool CONV, int MB, int PB>
-__device__ __forceinline__ unsigned tile_redo(const TileArgs &a, bool small, int lane, int p_base, int mb0, tdc_f4 (&acc)[MB][PB], bool &done)
+__device__ __forceinline__ unsigned tile_redo(const TileArgs &a, bool small, int x_exp, int lane, int p_base, int mb0, tdc_f4 (&acc)[MB][PB], bool &done)
 {
     constexpr bool SWAP = ACT == TDC_ACT_NCHW;
     const int g = lane >> 4, l16 = lane & 15;
@@ -115,8 +115,8 @@ __device__ __forceinline__ unsigned tile_redo(const TileArgs &a, bool small, int
             ws.see(load_w(kg, mb));
     }
     const bool odd_weights = tdc_any_lane(ws.nan || ws.largest == INFINITY);
-    // NaNs, and no factors large enough to overflow
-    const bool explained = tdc_any_lane(xs.nan | ws.nan) && !tdc_any_lane(xs.largest >= 0x1p30f || ws.largest >= 0x1p30f);
+    const bool in_parts = reinterpret_cast<const int *>(static_cast<const char *>(a.w) + a.w_bytes)[0] != TDC_WIDE;
+    const bool explained = in_parts && tdc_any_lane(xs.nan | ws.nan) && !tdc_any_lane(ldexpf(xs.largest, x_exp) > TDC_FP16_MAX || ws.largest == INFINITY);
     done = !(explained && !small && !(CONV && odd_weights));
     if (!done) return 0u;
 
@@ -460,7 +460,7 @@ __global__ __launch_bounds__(256 * KS, tile_wavefronts(MB * PB)) void tdc_tile_k
     unsigned nans = 0;
     bool redone = false;
     if (__builtin_expect(small || tdc_any_lane(!tdc_finite(largest)), 0))
-        nans = tile_redo<ACT, CONV, MB, PB>(tdc_args_again<TileArgs>(), small, out_lane, p_base, mb0, acc, redone);
+        nans = tile_redo<ACT, CONV, MB, PB>(tdc_args_again<TileArgs>(), small, x_exp, out_lane, p_base, mb0, acc, redone);
     if (!EARLY) fetch_exponents(og, ol);
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
@@ -695,7 +695,7 @@ __global__ __launch_bounds__(256, MB == 2 ? 2 : 3) void tdc_tile_1x1_kernel(Tile
             }
         bool redone = false;
         if (__builtin_expect(small || tdc_any_lane(!tdc_finite(largest)), 0))
-            tile_redo<ACT, false, MB, PB>(tdc_args_again<TileArgs>(), small, lane, p_tile, blk0, acc, redone);
+            tile_redo<ACT, false, MB, PB>(tdc_args_again<TileArgs>(), small, x_exp, lane, p_tile, blk0, acc, redone);
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
             const int m = 16 * (blk0 + mb) + (NHWC ? 4 * g : l16);

@@ -261,3 +261,32 @@ def test_values_far_from_those_that_set_the_scale(orc, layer, nhwc):
             err = _run(layer, inputs, tm, waves, nhwc) - want
             # pixel by pixel, each against its own size: 360 terms, as in test_tiles
             assert (np.linalg.norm(err, axis=1) <= 1.2e-6 * np.linalg.norm(want, axis=1)).all()
+
+
+# 3x3: the tile kernel; 1x1: all channels in LDS, both layouts (P = 108), two and three parts
+FP16_LAYERS = (Layer(2, 40, 72, 13, 9, 1, 1, 3, 1, 1), Layer(2, 160, 72, 12, 9, 1, 1, 1, 1, 0), Layer(130, 64, 136, 14, 16, 1, 1, 1, 1, 0))
+
+
+@pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
+@pytest.mark.parametrize("layer", FP16_LAYERS, ids=lambda l: l.name())
+@pytest.mark.parametrize("what", ("beyond_fp16", "late_channels", "wide_weights", "alone"))
+def test_a_nan_explains_no_sums_but_its_own(orc, what, layer, nhwc):
+    """One NaN beside finite values that fp16 does not hold at the scale the workgroup takes: values above 1023 where the NaN
+    is among the first loads, channels 2^11 times larger behind the first loads, weights kept out of the parts."""
+    inputs = make_dense_inputs(layer, 86)
+    if what == "beyond_fp16":
+        inputs["x"][0, :, 0, 3:6] *= np.float32(2.0 ** 12)
+    elif what == "late_channels":
+        inputs["x"][:, -8:] *= np.float32(2.0 ** 11)
+    elif what == "wide_weights":
+        inputs["W"][1:3, 7, layer.K // 2, layer.K // 2] = 2.0 ** 12, 2.0 ** -20
+    inputs["x"][0, 3, 0, 0] = np.nan
+    want = _oracle(orc, layer, inputs)
+    for tm, waves in ((64, 4), (128, 8)):
+        print("[case] tiles, one NaN,", what, layer.name(), "nhwc" if nhwc else "nchw", tm, waves, flush=True)
+        got = _run(layer, inputs, tm, waves, nhwc)
+        assert np.array_equal(np.isnan(got), np.isnan(want))
+        ok = ~np.isnan(want[0, 0])
+        err, ref = (got - want)[0][:, ok], want[0][:, ok]
+        assert (np.linalg.norm(err, axis=0) <= 1.2e-6 * np.linalg.norm(ref, axis=0)).all()
+        assert (np.linalg.norm((got - want)[1:], axis=1) <= 1.2e-6 * np.linalg.norm(want[1:], axis=1)).all()
