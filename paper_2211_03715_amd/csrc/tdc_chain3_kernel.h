@@ -34,7 +34,7 @@ constexpr int TDC_CHAIN3_WAVES = 4;
 
 struct TdcChain3Args {
     const float *x;
-    const void *uin, *core, *uout;             // in parts; each with its exponents behind *_bytes
+    const void *uin, *core, *uout;             // in parts; core and uout with their exponents behind *_bytes
     float *y;
     TdcEpi epi;
     int C, N, H, W, Ho, Wo, K, stride, pad;
@@ -83,7 +83,7 @@ struct Chain3Stage1 {
         wa = w0 > 0 ? (w0 & ~3) : 0;
         const int HW = a.H * a.W;
         xrs = tdc_make_rsrc(a.x + (size_t)b * a.C * HW, (unsigned)a.C * HW * 4u);
-        urs = tdc_make_rsrc(a.uin, a.uin_bytes + 64u * a.NB1);      // with the exponents
+        urs = tdc_make_rsrc(a.uin, a.uin_bytes);
         n_units = a.n_pg1 * a.n_mg1;
         fu = wave;
         place();
@@ -209,11 +209,7 @@ struct Chain3Stage1 {
         const int pg = tdc_div(unit, a.div_mg1), mg = unit - pg * a.n_mg1;
         const int rho = 16 * pg + l16, qh = RUNS ? tdc_div(rho, a.div_RPR) : 0;
         const int qw0 = RUNS ? wa + 4 * (rho - qh * a.RPR) - w0 : 0;
-        tdc_u4 e[MB1];                                 // exponents of the lane's channels
-#pragma unroll
-        for (int mb = 0; mb < MB1; ++mb)
-            e[mb] = __builtin_bit_cast(tdc_u4, tdc_buf_load4(urs, a.uin_bytes + (16u * (mg * MB1 + mb) + 4u * g) * 4u));
-        const TdcScale s(0);
+        const TdcScale s(-a.z1_exp);
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) {
             const bool ok = RUNS ? qh < a.QH && qw0 + pb >= 0 && qw0 + pb < a.QW : pg * PB + pb < a.QB;
@@ -222,10 +218,8 @@ struct Chain3Stage1 {
 #pragma unroll
             for (int mb = 0; mb < MB1; ++mb) {
                 const int blk = mg * MB1 + mb;
-                tdc_f4 v = tdc_levels(acc[mb][pb]);
+                const tdc_f4 v = tdc_levels(acc[mb][pb]);
                 m = tdc_largest(m, v);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = ldexpf(v[i], (int)e[mb][i] - a.z1_exp);
                 tdc_u2 p[NP];
                 tdc_split4<NP>(v, s, p);
                 if (ok && blk < a.NB1) {

@@ -58,14 +58,14 @@ hipError_t tdc_launch_pack_merged(const TdcDims &d, hipStream_t s, const float *
                                   const float *U_out, float *uin_p, float *wm, float *wm_p);
 // The same re-layout with every weight split into two or three fp16 parts (tdc_split.h): [m-block][step][part][lane][8], a step
 // being two k-groups, component j = what the fp32 layout has as component j%4 of k-group 2*step + j/4 (zero past the last one).
-// Every output channel is scaled by its own power of two.  Behind the parts: an exponent per channel (how a kernel undoes the
+// Every output channel is scaled by its own power of two, which for U_in's the core's rows undo.  Behind the parts: an exponent per channel (how a kernel undoes the
 // scaling, see tdc_pack.hip), the same weights in fp32 in the layout above, for what the parts cannot carry, and the ranges of
 // TDC_SPLIT_CHUNKS shares of the contraction, which the scaling comes from.
 constexpr int TDC_SPLIT_CHUNKS = 16;
 inline size_t tdc_split_bytes(int parts, int m_blocks, int k_groups) { return (size_t)m_blocks * ((k_groups + 1) / 2) * 1024 * parts; }
 inline size_t tdc_split_alloc_bytes(int parts, int m_blocks, int k_groups)
 {
-    return tdc_split_bytes(parts, m_blocks, k_groups) + (size_t)m_blocks * (64 + (size_t)k_groups * 1024 + 128 * TDC_SPLIT_CHUNKS);
+    return tdc_split_bytes(parts, m_blocks, k_groups) + (size_t)m_blocks * (64 + (size_t)k_groups * 1024 + 192 * TDC_SPLIT_CHUNKS);
 }
 // Parts a weight is split into.  Two fp16 parts are the more accurate form from some 70 terms to a sum on (tdc_split.h); the three sums
 // of a Tucker layer add up to that from 208 on: squared errors of 78 + 0.39 n against 2.1 n - 40 (in 1e-16, n terms).  Below, CHAIN

@@ -64,8 +64,13 @@ struct SplitTensor {
     unsigned *parts;
     int *exponents;
     float *raw;
-    int *top, *low;                        // largest and smallest exponent of each channel's weights, TDC_SPLIT_CHUNKS shares
+    int *top, *low, *most;                 // of each channel's weights the largest and smallest exponent, and the largest before ranks
+                                           // are scaled, TDC_SPLIT_CHUNKS shares
     bool last;                             // U_out, W
+    // The core: U_in [rows_before][rows], whose columns are scaled each by its own power of two.  A row is scaled by the inverse,
+    // so that z1 holds all ranks at one size, and what size the ranks have between the two factors makes no difference.
+    const float *before;
+    int rows_before;
 };
 constexpr int SPLIT_NONE = 100000, SPLIT_TOP = 13;
 
@@ -83,6 +88,7 @@ __device__ __forceinline__ int split_low(const SplitTensor &t, int m)
 }
 // channels without a finite weight that is not zero take 0
 __device__ __forceinline__ int split_scale(int top) { return top == -SPLIT_NONE ? 0 : SPLIT_TOP - top; }
+__device__ __forceinline__ bool split_counts(float w) { return w != 0.f && fabsf(w) < INFINITY; }
 
 // over a workgroup of 256
 __device__ __forceinline__ int split_block_max(int v)
@@ -100,41 +106,59 @@ __device__ __forceinline__ int split_block_max(int v)
 // the exponent of the largest weight of a tensor, and whether it is too wide for parts that keep their bits from 2^lowest on
 __device__ __forceinline__ void split_whole(const SplitTensor &t, int lowest, int &top, bool &wide)
 {
-    int widest = -SPLIT_NONE;
+    int widest = -SPLIT_NONE, most = -SPLIT_NONE;
     top = -SPLIT_NONE;
     for (int m = threadIdx.x; m < t.cols; m += 256) {
         const int h = split_top(t, m);
         top = max(top, h);
+        for (int i = 0; i < TDC_SPLIT_CHUNKS; ++i) most = max(most, t.most[i * 16 * t.NBm + m]);
         if (h != -SPLIT_NONE) widest = max(widest, h - split_low(t, m));
     }
     top = split_block_max(top);
+    most = split_block_max(most);
     widest = split_block_max(widest);
-    wide = top >= 10 && widest > SPLIT_TOP - lowest;
+    wide = most >= 10 && widest > SPLIT_TOP - lowest;
+}
+
+// the scale of column m of the tensor before, by a wavefront
+__device__ __forceinline__ int split_scale_before(const SplitTensor &t, int m)
+{
+    int top = -SPLIT_NONE;
+    for (int row = threadIdx.x & 63; row < t.rows_before; row += 64) {
+        const float w = t.before[(size_t)row * t.rows + m];
+        if (split_counts(w)) top = max(top, ilogbf(w));
+    }
+    for (int s = 32; s; s >>= 1) top = max(top, __shfl_xor(top, s));
+    return split_scale(top);
 }
 
 // the ranges of 64 output channels' weights among one share of the rows
 __device__ __forceinline__ void split_range(const SplitTensor &t, int block)
 {
-    __shared__ int top4[256], low4[256];
+    __shared__ int top4[256], low4[256], most4[256];
     const int share = block % TDC_SPLIT_CHUNKS, m = block / TDC_SPLIT_CHUNKS * 64 + (threadIdx.x & 63);
-    int top = -SPLIT_NONE, low = SPLIT_NONE;
-    if (m < t.cols)
-        for (int row = share + TDC_SPLIT_CHUNKS * (threadIdx.x >> 6); row < t.rows; row += 4 * TDC_SPLIT_CHUNKS) {
-            const float *__restrict__ w = t.w + ((size_t)row * t.cols + m) * t.KK;
-            for (int i = 0; i < t.KK; ++i)
-                if (w[i] != 0.f && fabsf(w[i]) < INFINITY) {
-                    const int e = ilogbf(w[i]);
-                    top = max(top, e);
-                    low = min(low, e);
-                }
-        }
+    int top = -SPLIT_NONE, low = SPLIT_NONE, most = -SPLIT_NONE;
+    for (int row = share + TDC_SPLIT_CHUNKS * (threadIdx.x >> 6); row < t.rows; row += 4 * TDC_SPLIT_CHUNKS) {
+        const int undo = t.before ? split_scale_before(t, row) : 0;
+        const float *__restrict__ w = t.w + ((size_t)row * t.cols + m) * t.KK;
+        for (int i = 0; i < (m < t.cols ? t.KK : 0); ++i)
+            if (split_counts(w[i])) {
+                const int e = ilogbf(w[i]);
+                top = max(top, e - undo);
+                low = min(low, e - undo);
+                most = max(most, e);
+            }
+    }
     top4[threadIdx.x] = top;
     low4[threadIdx.x] = low;
+    most4[threadIdx.x] = most;
     __syncthreads();
     if (threadIdx.x < 64 && m < 16 * t.NBm) {
-        const int *p = top4 + threadIdx.x, *q = low4 + threadIdx.x;
-        t.top[share * 16 * t.NBm + m] = max(max(p[0], p[64]), max(p[128], p[192]));
-        t.low[share * 16 * t.NBm + m] = min(min(q[0], q[64]), min(q[128], q[192]));
+        const auto max4 = [](const int *p) { return max(max(p[0], p[64]), max(p[128], p[192])); };
+        const int at = share * 16 * t.NBm + m, *q = low4 + threadIdx.x;
+        t.top[at] = max4(top4 + threadIdx.x);
+        t.most[at] = max4(most4 + threadIdx.x);
+        t.low[at] = min(min(q[0], q[64]), min(q[128], q[192]));
     }
 }
 
@@ -144,7 +168,9 @@ struct SplitArgs {
 };
 __global__ void split_range_kernel(SplitArgs a) { if ((int)blockIdx.x < (a.t[blockIdx.y].NBm + 3) / 4 * TDC_SPLIT_CHUNKS) split_range(a.t[blockIdx.y], blockIdx.x); }
 
-// One thread per pair of components: e = ((mb*S + step)*64 + lane)*4 + pair, one workgroup per block and step.
+// One thread per pair of components: e = ((mb*S + step)*64 + lane)*4 + pair, one workgroup per block and step.  Exponents: W: the
+// channel's; U_in: none, its scales are the core's rows'; core: what takes a channel to the scale of the largest; U_out: the
+// channel's and that scale together.
 template <int NP>
 __global__ void split_pack_kernel(SplitArgs a)
 {
@@ -154,32 +180,34 @@ __global__ void split_pack_kernel(SplitArgs a)
     int top;
     bool wide;
     split_whole(t, tdc_lowest_weight(NP), top, wide);
-    const int lowest = split_scale(top);
-    int others = 0;
-    if (t.last)
-        for (int i = 0; i < a.n - 1; ++i) {
-            int o;
-            bool w;
-            split_whole(a.t[i], tdc_lowest_weight(NP), o, w);
-            others += split_scale(o);
-        }
+    int before = 0;
+    if (t.last && a.n == 3) {
+        int o;
+        bool w;
+        split_whole(a.t[1], tdc_lowest_weight(NP), o, w);
+        before = split_scale(o);
+    }
     const int pair = (int)(threadIdx.x & 3), lane = (int)(threadIdx.x >> 2);
     const size_t blk = blockIdx.x;
     const int step = (int)(blk % S), mb = (int)(blk / S);
     const int kg = 2 * step + (pair >> 1), m = 16 * mb + (lane & 15), k = 4 * (lane >> 4) + 2 * (pair & 1);
     const int channel = split_top(t, m), scale = split_scale(channel);
     const int tap = kg / t.NBk, row = 16 * (kg - tap * t.NBk) + k;
-    float v[2];
-    for (int i = 0; i < 2; ++i) v[i] = kg < t.KG && row + i < t.rows && m < t.cols ? t.w[((size_t)(row + i) * t.cols + m) * t.KK + tap] : 0.f;
+    float v[2], scaled[2];
+    for (int i = 0; i < 2; ++i) {
+        const bool there = kg < t.KG && row + i < t.rows;
+        v[i] = there && m < t.cols ? t.w[((size_t)(row + i) * t.cols + m) * t.KK + tap] : 0.f;
+        scaled[i] = wide ? NAN : ldexpf(v[i], scale - (t.before && there ? split_scale(split_top(a.t[0], row + i)) : 0));
+    }
     unsigned p[NP];
-    tdc_split2<NP, tdc_lift_weights(NP)>(wide ? NAN : ldexpf(v[0], scale), wide ? NAN : ldexpf(v[1], scale), TdcScale(0), p);
+    tdc_split2<NP, tdc_lift_weights(NP)>(scaled[0], scaled[1], TdcScale(0), p);
     for (int i = 0; i < NP; ++i) t.parts[(blk * NP + i) * 256 + lane * 4 + pair] = p[i];
     if (kg < t.KG) {
         float *raw = t.raw + (((size_t)mb * t.KG + kg) * 64 + lane) * 4 + 2 * (pair & 1);
         raw[0] = v[0];
         raw[1] = v[1];
     }
-    if (step == 0 && pair == 0 && lane < 16) t.exponents[m] = wide ? TDC_WIDE : t.last ? scale + others : channel == -SPLIT_NONE ? 0 : lowest - scale;
+    if (step == 0 && pair == 0 && lane < 16) t.exponents[m] = wide ? TDC_WIDE : t.last ? scale + before : channel == -SPLIT_NONE ? 0 : split_scale(top) - scale;
 }
 
 __global__ void pack_uout_kernel(TdcDims d, const float *__restrict__ U_out, float *__restrict__ out, size_t total)
@@ -253,7 +281,10 @@ static SplitTensor split_tensor(int parts, const float *w, int rows, int cols, i
     t.raw = (float *)(t.exponents + 16 * t.NBm);
     t.top = (int *)(t.raw + (size_t)t.NBm * t.KG * 256);
     t.low = t.top + 16 * t.NBm * TDC_SPLIT_CHUNKS;
+    t.most = t.low + 16 * t.NBm * TDC_SPLIT_CHUNKS;
     t.last = last;
+    t.before = nullptr;
+    t.rows_before = 0;
     return t;
 }
 
@@ -284,6 +315,8 @@ hipError_t tdc_launch_split_layer(const TdcDims &d, hipStream_t s, const float *
     a.n = 3;
     a.t[0] = split_tensor(2, U_in, d.C, d.R1, 1, uin_sp, false);
     a.t[1] = split_tensor(2, core, d.R1, d.R2, d.K, core_sp, false);
+    a.t[1].before = U_in;
+    a.t[1].rows_before = d.C;
     a.t[2] = split_tensor(2, U_out, d.R2, d.N, 1, uout_sp, true);
     return launch_split(2, s, a);
 }
