@@ -48,6 +48,7 @@ struct TdcChain3Args {
     int z1_exp;                                // z1 is kept 2^-z1_exp times its scaled sums
     unsigned uin_bytes, core_bytes, uout_bytes;
     TdcDiv div_tiles_x, div_tiles, div_QW, div_TW, div_RPR, div_mg1, div_NB1, div_K;
+    int lost2, lost3;                          // what a channel's largest output must reach, see the launch
 };
 
 namespace {
@@ -551,7 +552,7 @@ constexpr int chain3_wavefronts(int nb2, int pb, int lay, int mb1)
 
 // ALL: every wavefront has a group of pixel blocks of its own (lg_ks is 0)
 template <int NB2, int PB, int LAY, int MB1, bool ALL>
-__global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, LAY, MB1)) void tdc_chain3_kernel(TdcChain3Args a)
+__global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, LAY, MB1)) void tdc_chain3_kernel(TdcChain3Args args)
 {
     constexpr bool NHWC = LAY == TDC_LAY_NHWC, SWAP = !NHWC;
     constexpr bool DEEP = chain3_deep(NB2, PB);
@@ -560,16 +561,17 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
     tdc_u2 *__restrict__ z1s = reinterpret_cast<tdc_u2 *>(chain3_lds + sizeof(Chain3Shared) / 16);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    bool bad;                                                    // a pixel of too small factors, or an output that is no number
+    bool bad;                                                    // a pixel of too small factors, a channel of too small outputs, or one that is no number
     int x_exp;
-    const Chain3Tile at(a);
+    const Chain3Tile at(args);
     {
-        Chain3Stage1<LAY, MB1, DEEP> s1(a, lane, wave, at.b, at.i0 * a.stride - a.pad, at.j0 * a.stride - a.pad);
+        Chain3Stage1<LAY, MB1, DEEP> s1(args, lane, wave, at.b, at.i0 * args.stride - args.pad, at.j0 * args.stride - args.pad);
         s1.run(sh, z1s);
         x_exp = s1.x_exp;
-        bad = tdc_is_small(s1.smallest, tdc_exp2i(a.z1_exp + TDC_LOWEST)) || tdc_is_small(s1.smallest_x, tdc_exp2i(max(TDC_LOWEST - x_exp, -126)));
+        bad = tdc_is_small(s1.smallest, tdc_exp2i(args.z1_exp + TDC_LOWEST)) || tdc_is_small(s1.smallest_x, tdc_exp2i(max(TDC_LOWEST - x_exp, -126)));
     }
 
+    const TdcChain3Args &a = tdc_args_again<TdcChain3Args>();    // read anew, and not kept through stage 1
     const int plane = a.NB1 * 4 * a.pitch1;                      // cells of one part
     const tdc_rsrc crs = tdc_make_rsrc(a.core, a.core_bytes + 64u * NB2), ors = tdc_make_rsrc(a.uout, a.uout_bytes + 64u * a.NB3);   // with the exponents
     // with fewer groups than wavefronts 2 or 4 of them share one: each takes a slice of stage 2's contraction, the sums meet in
@@ -766,6 +768,7 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
         }
         float top = 0.f;                                         // largest magnitude of z2; a NaN above all
         unsigned smallest = ~0u;                                 // of the pixels' largest z2 values the smallest
+        unsigned lit = 0;                                        // whether z2 is not all zero at the pixels of this lane's outputs
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) {
             float m = 0.f;
@@ -774,6 +777,7 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
             m = tdc_pixel_max(m);
             top = __builtin_elementwise_maximum(top, m);
             smallest = tdc_smallest(smallest, m);
+            lit |= NHWC ? m != 0.f : (unsigned)__builtin_amdgcn_ballot_w64(m != 0.f) >> 4 * (lane >> 4) & 15u;
         }
         const int z2_exp = tdc_scale_of(tdc_wave_max(top), TDC_Z2_TARGET, 0);
         bad |= live && tdc_is_small(smallest, tdc_exp2i(max(TDC_LOWEST - z2_exp, -126)));
@@ -789,6 +793,8 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
         }
         const Chain3Out<PB, NHWC> out(a, at, pg, lane);
         float largest = 0.f;
+        const int lost = lit ? (127 + min(max(z2_exp + a.lost2, a.lost3), 126)) << 23 : 0;
+        int least = TDC_EMPTY;                                   // of the magnitudes of the channels' largest sums the least, as bits
         // two instances of the loop, as in tdc_chain_kernel.h: without epilogue loads nothing ever waits for the stores
         typedef typename Chain3Out<PB, NHWC>::Epi Epi;
         const auto emit = [&](auto with_epi, int nb, const tdc_op<NP>(&u)[S3], const Exponents &e, const Epi *epi) {
@@ -806,13 +812,27 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
                         tdc_f4 &c = acc3[pb][TdcProducts<NP>::level[i]];
                         c = tdc_mfma_part<NP, SWAP>(i, u[st].p, zb[st][pb].p, c);
                     }
+            // magnitude of a channel's largest sum among this lane's pixels
+            float m[NHWC ? 4 : 1] = {};
 #pragma unroll
             for (int pb = 0; pb < PB; ++pb) {
                 v[pb] = tdc_levels(acc3[pb]);
-                largest = tdc_largest(largest, v[pb]);
+                if constexpr (NHWC) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) m[i] = __builtin_elementwise_maximum(m[i], fabsf(v[pb][i]));
+                } else {
+                    m[0] = tdc_largest(m[0], v[pb]);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < (NHWC ? 4 : 1); ++i) {
+                largest = __builtin_elementwise_maximum(largest, m[i]);
+                least = min(least, max(__builtin_bit_cast(int, m[i]), e.e[i]));
+            }
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) v[pb][i] = ldexpf(v[pb][i], y_exp - e.e[NHWC ? i : 0]);
-            }
             out.template put<decltype(with_epi)::value>(nb, v, epi);
         };
         const auto stage3 = [&](auto with_epi) {
@@ -865,7 +885,7 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
         };
         if (a.epi.bias || a.epi.residual || a.epi.relu) stage3(std::true_type{});
         else stage3(std::false_type{});
-        bad |= live && !tdc_finite(largest);
+        bad |= live && (!tdc_finite(largest) || least < lost);
     }
     // One wavefront's trouble is the tile's: z1 is everybody's.
     sh.bad[wave] = tdc_any_lane(bad);

@@ -207,7 +207,8 @@ __global__ void split_pack_kernel(SplitArgs a)
         raw[0] = v[0];
         raw[1] = v[1];
     }
-    if (step == 0 && pair == 0 && lane < 16) t.exponents[m] = wide ? TDC_WIDE : t.last ? scale + before : channel == -SPLIT_NONE ? 0 : split_scale(top) - scale;
+    if (step == 0 && pair == 0 && lane < 16) 
+        t.exponents[m] = wide ? TDC_WIDE : channel == -SPLIT_NONE ? (t.last ? TDC_EMPTY : 0) : t.last ? scale + before : split_scale(top) - scale;
 }
 
 __global__ void pack_uout_kernel(TdcDims d, const float *__restrict__ U_out, float *__restrict__ out, size_t total)

@@ -20,6 +20,9 @@
 //   activations  one exponent per workgroup, which takes the largest magnitude among those it loads first to 2^10 .. 2^11
 //                (tdc_scale_of): 64 times larger values still fit, 2^23 times smaller ones keep all their bits;
 //   z1           sqrt(C) 2^12 times smaller than its sums, a constant: 2^8 or so; z2: by the largest a wavefront holds.
+// What is lost.  A factor below 2^TDC_LOWEST is kept to an absolute accuracy, 2^-36.  That shows where large weights meet small
+// values only, as when the weights undo what size the channels of x have: the sums are small then, a channel's over several
+// pixels (one alone may be so by chance), and each stage that writes outputs compares them with what the parts may have lost.
 // Infinities, NaN and values too large show in the results, which they make infinite or NaN; that all of a pixel's channels are
 // below 2^-13, and not zero, each stage watches as it splits them (a pixel's, not a value's: beside larger ones a lost bit is
 // below their rounding).  Either way the outputs concerned are computed once more in fp32, from weights kept beside the parts.
@@ -184,8 +187,9 @@ constexpr int TDC_X_TARGET = 10, TDC_X_OTHER = 6, TDC_Z2_TARGET = 12;
 constexpr int TDC_LOWEST = -13;      // scaled values from 2^TDC_LOWEST on keep all their bits
 constexpr int tdc_lowest_weight(int np) { return tdc_lift_weights(np) ? TDC_LOWEST : -1; }
 constexpr float TDC_FP16_MAX = 65504.f;
-// exponent of the channels of weights that are kept out of the parts, which are NaN
-constexpr int TDC_WIDE = 1 << 20;
+// exponents of the channels of weights that are kept out of the parts, which are NaN, and of channels without a finite weight that is not
+// 0: in order as integers with the bits of magnitudes, above all that are finite sums
+constexpr int TDC_WIDE = 1 << 20, TDC_EMPTY = 0x7f000000;
 
 // k-group kg's share of a lane's fp32 weights of 16-channel block `block` (layout: tdc_internal.h)
 __device__ __forceinline__ tdc_f4 tdc_raw_weights(tdc_rsrc r, int block, int k_groups, int kg, int lane)

@@ -243,22 +243,31 @@ FP16_LAYERS = ((Layer(2, 72, 48, 12, 12, 32, 16, 3, 1, 1), (4, 4)), (Layer(40, 7
 
 @pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
 @pytest.mark.parametrize("layer,tile", FP16_LAYERS, ids=lambda v: v.name() if isinstance(v, Layer) else "")
-def test_ranks_that_the_next_factor_brings_to_one_size(orc, layer, tile, nhwc):
-    """Rescaling the ranks of U_in and undoing it in the core leaves the layer what it is.  Also with pixels that use the smaller
-    half only."""
+def test_ranks_and_channels_that_the_next_factor_brings_to_one_size(orc, layer, tile, nhwc):
+    """Rescaling x's channels, the ranks of U_in or those of the core and undoing it in the next factor leaves the layer what it
+    is.  Also with pixels that use the smaller half only."""
     t = B.make_tuning(variant=B.VARIANT_CHAIN, tile_h=tile[0], tile_w=tile[1], waves=(4, 4, 4), mb=(1 if tile == (12, 12) else 2, 3, 1), pb=(2,) * 3)
     for bits in (8, 16, 20, 24, 28, 34, 40, 60):
-        for what in ("ranks 1", "half"):
+        for what in ("channels", "ranks 1", "ranks 2", "half"):
             inputs = {k: v.copy() for k, v in make_inputs(layer, 95).items()}
             grade = lambda n: (2.0 ** np.round(np.linspace(bits, 0, n))).astype(np.float32)
-            s = grade(layer.R1)
-            if what == "half":                           # the first half of the channels feeds the first, larger, half of the ranks
-                s[:layer.R1 // 2], s[layer.R1 // 2:] = 2.0 ** bits, 1
-                inputs["U_in"][:layer.C // 2, layer.R1 // 2:] = 0
-                inputs["U_in"][layer.C // 2:, :layer.R1 // 2] = 0
-                inputs["x"][0, :layer.C // 2, :, 5:] = 0
-            inputs["U_in"] *= s[None, :]
-            inputs["core"] /= s[:, None, None, None]
+            if what == "channels":
+                s = grade(layer.C)
+                inputs["x"] *= s[None, :, None, None]
+                inputs["U_in"] /= s[:, None]
+            elif what == "ranks 2":
+                s = grade(layer.R2)
+                inputs["core"] *= s[None, :, None, None]
+                inputs["U_out"] /= s[:, None]
+            else:
+                s = grade(layer.R1)
+                if what == "half":                       # the first half of the channels feeds the first, larger, half of the ranks
+                    s[:layer.R1 // 2], s[layer.R1 // 2:] = 2.0 ** bits, 1
+                    inputs["U_in"][:layer.C // 2, layer.R1 // 2:] = 0
+                    inputs["U_in"][layer.C // 2:, :layer.R1 // 2] = 0
+                    inputs["x"][0, :layer.C // 2, :, 5:] = 0
+                inputs["U_in"] *= s[None, :]
+                inputs["core"] /= s[:, None, None, None]
             want, _ = orc.conv_factored(orc.Shape(**layer.asdict()), **inputs)
             print("[case] chain3,", what, "2^%d apart" % bits, layer.name(), "nhwc" if nhwc else "nchw", flush=True)
             err = _run(layer, inputs, t, nhwc) - want
