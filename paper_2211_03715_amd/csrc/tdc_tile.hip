@@ -150,22 +150,38 @@ __device__ __forceinline__ unsigned tile_redo(const TileArgs &a, bool small, int
     return nans;
 }
 
-// Whether a thread, in NHWC the eight that share a pixel, brought a pixel of nothing but values too small for all their bits.
+// The largest magnitude of each of a tile's 64 pixels, from the threads that brought it: in NHWC eight lanes share a pixel of every 32,
+// in NCHW four wavefronts share all.  ROWS: what is kept apart until all have written.
+constexpr int tile_top_rows(int act, int ks) { return act == TDC_ACT_NHWC ? ks : 4 * ks; }
 template <bool NHWC, int NPIX>
-__device__ __forceinline__ bool tile_too_small(const float (&x_top)[NPIX], int x_exp)
+__device__ __forceinline__ void tile_put_tops(const float (&x_top)[NPIX], float (*__restrict__ tops)[64], int ks, int t)
 {
-    unsigned smallest = ~0u;
+    if (!NHWC) {
+        tops[4 * ks + (t >> 6)][t & 63] = x_top[0];
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < NPIX; ++i) {
         unsigned u = __builtin_bit_cast(unsigned, x_top[i]);
-        if (NHWC) {
-            u = max(u, (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0xb1, 0xf, 0xf, true));      // quad_perm 1 0 3 2
-            u = max(u, (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0x4e, 0xf, 0xf, true));      // quad_perm 2 3 0 1
-            u = max(u, (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0x141, 0xf, 0xf, true));     // the other half of eight
-        }
-        smallest = tdc_smallest(smallest, __builtin_bit_cast(float, u));
+        u = max(u, (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0xb1, 0xf, 0xf, true));      // quad_perm 1 0 3 2
+        u = max(u, (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0x4e, 0xf, 0xf, true));      // quad_perm 2 3 0 1
+        u = max(u, (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0x141, 0xf, 0xf, true));     // the other half of eight
+        if ((t & 7) == 0) tops[ks][(t >> 3) + 32 * i] = __builtin_bit_cast(float, u);
     }
-    return tdc_any_lane(tdc_is_small(smallest, tdc_exp2i(max(TDC_LOWEST - x_exp, -126))));
+}
+// a wavefront's, a pixel to a lane
+template <int ROWS>
+__device__ __forceinline__ unsigned tile_top(const float (*__restrict__ tops)[64], int lane)
+{
+    unsigned u = 0;
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) u = max(u, __builtin_bit_cast(unsigned, tops[i][lane]));
+    return u;
+}
+// whether there is a pixel of nothing but values too small for all their bits
+__device__ __forceinline__ bool tile_too_small(unsigned top, int x_exp)
+{
+    return tdc_any_lane(tdc_is_small(tdc_smallest(~0u, __builtin_bit_cast(float, top)), tdc_exp2i(max(TDC_LOWEST - x_exp, -126))));
 }
 
 // Four pixels of NCHW channel m, from pixel p on, that cannot be stored at once: sums and bias in v, shortcut and ReLU here.
@@ -201,7 +217,8 @@ __global__ __launch_bounds__(256 * KS, tile_wavefronts(MB * PB)) void tdc_tile_k
     constexpr int VPM = (NX * (7 * NP + (ACT == TDC_ACT_NCHW ? 17 : 12)) + 20 + NM * MB * PB - 1) / (NM * MB * PB);   // VALU instructions per MFMA
     __shared__ tdc_u4 xs_all[KS][2][4 * NP * PITCH];   // [part][lane group][pixel]: 4 channels of each k-group of the step
     __shared__ unsigned first_all[4 * KS];             // largest magnitude among what each wavefront loads first
-    __shared__ unsigned small_all[4 * KS];             // whether a wavefront brought a pixel of too small values
+    constexpr int TOP_ROWS = tile_top_rows(ACT, KS);
+    __shared__ float tops[TOP_ROWS][64];               // largest magnitudes of the pixels
     const int ks = KS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
     tdc_u4(&xs)[2][4 * NP * PITCH] = xs_all[ks];
     const int t = threadIdx.x & 255, lane = t & 63;
@@ -420,7 +437,7 @@ __global__ __launch_bounds__(256 * KS, tile_wavefronts(MB * PB)) void tdc_tile_k
             if (!more) break;
         }
     }
-    small_all[4 * ks + wave] = tile_too_small<ACT == TDC_ACT_NHWC, NPIX>(x_top, x_exp);
+    tile_put_tops<ACT == TDC_ACT_NHWC, NPIX>(x_top, tops, ks, t);
     tdc_f4 acc[MB][PB];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
@@ -453,10 +470,7 @@ __global__ __launch_bounds__(256 * KS, tile_wavefronts(MB * PB)) void tdc_tile_k
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) largest = tdc_largest(largest, acc[mb][pb]);
-    unsigned any_small = 0;
-#pragma unroll
-    for (int i = 0; i < 4 * KS; ++i) any_small |= small_all[i];
-    const bool small = __builtin_amdgcn_readfirstlane((int)any_small) != 0;
+    const bool small = tile_too_small(tile_top<TOP_ROWS>(tops, out_lane), x_exp);
     unsigned nans = 0;
     bool redone = false;
     if (__builtin_expect(small || tdc_any_lane(!tdc_finite(largest)), 0))
@@ -519,8 +533,10 @@ __global__ __launch_bounds__(256, MB == 2 ? 2 : 3) void tdc_tile_1x1_kernel(Tile
     constexpr int PB = 4, TP = 16 * PB, PITCH = TP + 4, NX = 2, NM = TdcProducts<NP>::N, CHUNK = 4;
     constexpr int STEP = 4 * NP * PITCH;               // 16-byte cells of a step: [part][lane group][pixel]
     extern __shared__ tdc_u4 tile_1x1_lds[];
-    tdc_u4 *__restrict__ xs = tile_1x1_lds + 2;        // behind four first magnitudes and four flags
-    unsigned *__restrict__ first_all = reinterpret_cast<unsigned *>(tile_1x1_lds), *__restrict__ small_all = first_all + 4;
+    constexpr int TOP_ROWS = tile_top_rows(ACT, 1);
+    unsigned *__restrict__ first_all = reinterpret_cast<unsigned *>(tile_1x1_lds);               // four first magnitudes, then
+    float(*__restrict__ tops)[64] = reinterpret_cast<float(*)[64]>(tile_1x1_lds + 1);            // largest ones of the pixels
+    tdc_u4 *__restrict__ xs = tile_1x1_lds + 1 + TOP_ROWS * 16;
     const int t = threadIdx.x, lane = t & 63, g = lane >> 4, l16 = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int lb = tile_logical_block(blockIdx.x, gridDim.x);
@@ -615,11 +631,10 @@ __global__ __launch_bounds__(256, MB == 2 ? 2 : 3) void tdc_tile_1x1_kernel(Tile
                 if (s + CHUNK < a.S) fetch_x(s + CHUNK + u, x[u]);
             }
         }
-        small_all[wave] = tile_too_small<NHWC, NPIX>(x_top, x_exp);
+        tile_put_tops<NHWC, NPIX>(x_top, tops, 0, t);
     }
     __syncthreads();
-    const tdc_u4 flags = tile_1x1_lds[1];
-    const bool small = __builtin_amdgcn_readfirstlane((int)(flags[0] | flags[1] | flags[2] | flags[3])) != 0;
+    const bool small = tile_too_small(tile_top<TOP_ROWS>(tops, lane), x_exp);
 
     // ---- where this lane's outputs are: NHWC: channels 4g.. of pixel l16 of block pb, NCHW: pixels 4g.. of channel l16
     // (bytes from the tile's first pixel or image on; two images, or what a tile spans of smaller ones, are below 4 GiB)
@@ -734,7 +749,7 @@ hipError_t launch_act(const TileArgs &a, int tm, int tp, int ks, hipStream_t s)
 }
 
 // LDS of the 1x1 kernel, and the most that still leaves two workgroups on a compute unit.
-size_t tile_1x1_lds_bytes(int steps, int parts) { return 32 + (size_t)steps * parts * 4 * 68 * 16; }
+size_t tile_1x1_lds_bytes(int steps, int parts, bool nhwc) { return 16 + 256 * (size_t)(nhwc ? 1 : 4) + (size_t)steps * parts * 4 * 68 * 16; }
 constexpr size_t TILE_1X1_LDS = 80 * 1024;
 
 // Channel tiles a workgroup takes: the share with the shortest schedule, in channel tiles of one workgroup.  Bringing the pixels
@@ -762,7 +777,7 @@ template <int ACT>
 hipError_t launch_1x1(const TileArgs &a, int mb, int parts, hipStream_t s)
 {
     const dim3 grid((unsigned)(a.n_pt * a.n_mg));
-    const size_t lds = tile_1x1_lds_bytes(a.S, parts);
+    const size_t lds = tile_1x1_lds_bytes(a.S, parts, ACT == TDC_ACT_NHWC);
     const auto kernel = parts == 3 ? tdc_tile_1x1_kernel<ACT, 1, 3> : mb == 1 ? tdc_tile_1x1_kernel<ACT, 1, 2> : tdc_tile_1x1_kernel<ACT, 2, 2>;
     const hipError_t e = tdc_allow_lds((const void *)kernel, lds);
     if (e != hipSuccess) return e;
@@ -786,7 +801,7 @@ bool tdc_tile_applies(const TdcDims &d)
 bool tdc_tile_1x1_applies(const TdcDims &d)
 {
     const int parts = tdc_tile_parts(d);
-    if (d.K != 1 || d.stride != 1 || d.pad != 0 || !tdc_tile_applies(d) || tile_1x1_lds_bytes((d.NB1 + 1) / 2, parts) > TILE_1X1_LDS) return false;
+    if (d.K != 1 || d.stride != 1 || d.pad != 0 || !tdc_tile_applies(d) || tile_1x1_lds_bytes((d.NB1 + 1) / 2, parts, d.nhwc) > TILE_1X1_LDS) return false;
     // Timed against the tile kernels on 121 drawn layers.  NCHW pixels that allow no 16-byte stores were slower in all of 40 (64 -> 368, 80
     // against 110 us).  Three parts pay from 128 output channels and 3.3 tiles per compute unit on (56 -> 64, batch-bound: 14.5 against
     // 16.1; 56 -> 140 with 3 tiles: 7.6 against 9.2; 70 -> 192 with 15: 39.6 against 33.0).  The pixels come in before the first product: with
@@ -818,7 +833,7 @@ hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipSt
     if (ks == 1 && tdc_tile_1x1_applies(d)) {
         const int mb = parts == 3 ? 1 : tm / 64;
         a.n_mt = (d.N + 64 * mb - 1) / (64 * mb);
-        a.per = tile_1x1_share(a.n_pt, a.n_mt, mb, tile_1x1_lds_bytes(a.S, parts));
+        a.per = tile_1x1_share(a.n_pt, a.n_mt, mb, tile_1x1_lds_bytes(a.S, parts, d.nhwc));
         a.n_mg = (a.n_mt + a.per - 1) / a.per;
         a.div_inner = tdc_make_div((unsigned)a.n_mg);
         return d.nhwc ? launch_1x1<TDC_ACT_NHWC>(a, mb, parts, s) : launch_1x1<TDC_ACT_NCHW>(a, mb, parts, s);

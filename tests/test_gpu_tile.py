@@ -290,3 +290,52 @@ def test_a_nan_explains_no_sums_but_its_own(orc, what, layer, nhwc):
         err, ref = (got - want)[0][:, ok], want[0][:, ok]
         assert (np.linalg.norm(err, axis=0) <= 1.2e-6 * np.linalg.norm(ref, axis=0)).all()
         assert (np.linalg.norm((got - want)[1:], axis=1) <= 1.2e-6 * np.linalg.norm(want[1:], axis=1)).all()
+
+
+def _gpu_us(launch):
+    """Least time of a call, of five blocks of ten."""
+    import torch
+    best = 1e9
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(10):
+            launch()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 100)
+    return best
+
+
+def _small_quarter(x):               # what one of the four wavefronts that share NCHW pixels brings
+    for c in range(4, x.shape[1], 16):
+        x[:, c:c + 4] *= np.float32(2.0 ** -30)
+
+
+ORDINARY = (_small_quarter,)
+
+
+@pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
+@pytest.mark.parametrize("layer", (Layer(8, 128, 128, 28, 28, 1, 1, 3, 1, 1), Layer(8, 128, 512, 28, 28, 1, 1, 1, 1, 0)), ids=lambda l: l.name())
+@pytest.mark.parametrize("values", ORDINARY, ids=lambda f: f.__name__[1:])
+def test_finite_inputs_that_fp16_holds_cost_the_usual_time(values, layer, nhwc):
+    """They are not computed again in fp32, which takes several times as long."""
+    import torch
+    from paper_2211_03715_amd.layer import DenseConv2d
+    dev = torch.device("cuda:0")
+    inputs = make_dense_inputs(layer, 88)
+    put = lambda a: torch.from_numpy(np.ascontiguousarray(a.transpose(0, 2, 3, 1) if nhwc else a)).to(dev)
+    usual = put(inputs["x"])
+    values(inputs["x"])
+    conv = DenseConv2d(layer, 0, B.make_tuning(tile_h=64, tile_w=64, waves=(4,) * 3), B.LAYOUT_NHWC if nhwc else B.LAYOUT_NCHW)
+    try:
+        W = torch.from_numpy(inputs["W"]).to(dev)
+        conv.pack(W)
+        y = torch.empty(conv.out_shape(), device=dev)
+        first, second = conv.bind(usual, y), conv.bind(put(inputs["x"]), y)
+        _gpu_us(first)
+        a, b = _gpu_us(first), _gpu_us(second)
+        print("[case] tiles,", values.__name__, layer.name(), "nhwc" if nhwc else "nchw", "%.1f us, usually %.1f" % (b, a), flush=True)
+        assert b <= 1.5 * a
+    finally:
+        conv.close()
