@@ -19,6 +19,7 @@
 // loading and splitting its own pixels 64 us (NHWC loads of 16 pixels x 64 bytes run at 18 bytes a cycle, a third of
 // contiguous ones); this one without the interleaving 42.8 us, with it 39.8 us (fp32 MFMA kernel: 90.5 us).
 #include <algorithm>
+#include <cmath>
 
 #include "tdc_split.h"
 #include "tdc_internal.h"
@@ -38,6 +39,7 @@ struct TileArgs {
     int H, W, Wo, K, stride, pad;
     int n_mt, n_pt, pt_major;
     int per, n_mg;          // 1x1: channel tiles of a workgroup, workgroups that share a pixel tile
+    int half_log_terms;     // half the logarithm (2) of a sum's terms
     int vec;                // NCHW out: quads of pixels lie in one image and 16-byte aligned
     unsigned w_bytes;
     TdcDiv div_P, div_Wo, div_NBk, div_K, div_inner;
@@ -182,6 +184,63 @@ __device__ __forceinline__ unsigned tile_top(const float (*__restrict__ tops)[64
 __device__ __forceinline__ bool tile_too_small(unsigned top, int x_exp)
 {
     return tdc_any_lane(tdc_is_small(tdc_smallest(~0u, __builtin_bit_cast(float, top)), tdc_exp2i(max(TDC_LOWEST - x_exp, -126))));
+}
+
+// What a channel's largest sum among a lane's pixels must reach, as bits: 2^22 times what the parts lose.  With scaled weights of 2^12
+// root mean square, x up to `top` times 2^x_exp and 2^(2 half_log_terms) terms two parts lose sqrt(terms) (2^-25 + 2^-39 x), of
+// three, where the weights' are not lifted, sqrt(terms) (2^-25 + 2^-28 x).  Normal values give 2^16 (2^13) times more.
+template <int NP>
+__device__ __forceinline__ int tile_lost(int half_log_terms, unsigned top, int x_exp)
+{
+    const int e = min((int)(top >> 23) - 126 + x_exp, 16);
+    return (127 + half_log_terms + max(-2, e - (NP == 2 ? 17 : 6))) << 23;
+}
+// The magnitudes of a wavefront's sums: of all the largest, NaN if there is one, and of the channels' largest the least, as bits.
+template <bool SWAP, int MB, int PB>
+__device__ __forceinline__ void tile_magnitudes(const tdc_f4 (&acc)[MB][PB], float &largest, int &least)
+{
+    largest = 0.f;
+    least = TDC_EMPTY;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int c = 0; c < (SWAP ? 1 : 4); ++c) {
+            float m = 0.f;
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+                for (int i = SWAP ? 0 : c; i < (SWAP ? 4 : c + 1); ++i) m = __builtin_elementwise_maximum(m, fabsf(acc[mb][pb][i]));
+            largest = __builtin_elementwise_maximum(largest, m);
+            least = min(least, __builtin_bit_cast(int, m));
+        }
+}
+// The least once more, of `blocks` channel blocks, of channels with weights and of sums that are no NaN, where there is one.
+template <bool SWAP, int MB, int PB>
+__device__ __forceinline__ int tile_least(const tdc_f4 (&acc)[MB][PB], const int (&w_exp)[MB][SWAP ? 1 : 4], int blocks)
+{
+    int least = TDC_EMPTY;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int c = 0; c < (SWAP ? 1 : 4); ++c) {
+            float m = -1.f;
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+                for (int i = SWAP ? 0 : c; i < (SWAP ? 4 : c + 1); ++i) m = fmaxf(m, fabsf(acc[mb][pb][i]));
+            if (m >= 0.f && mb < blocks && w_exp[mb][c] != TDC_EMPTY) least = min(least, __builtin_bit_cast(int, m));
+        }
+    return least;
+}
+// whether x is not all zero at this lane's pixels of a wavefront's blocks, the first `first`; top: tile_top
+template <bool SWAP, int PB>
+__device__ __forceinline__ bool tile_lit(unsigned top, int first, int lane)
+{
+    const unsigned long long px = __builtin_amdgcn_ballot_w64(top != 0) >> first;
+    unsigned any = 0;
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) any |= (unsigned)(px >> 16 * pb);
+    return SWAP ? any >> 4 * (lane >> 4) & 15u : any >> (lane & 15) & 1u;
 }
 
 // Four pixels of NCHW channel m, from pixel p on, that cannot be stored at once: sums and bias in v, shortcut and ReLU here.
@@ -464,18 +523,21 @@ __global__ __launch_bounds__(256 * KS, tile_wavefronts(MB * PB)) void tdc_tile_k
 
     // the lane number once more: the one above need not be kept through the loop for this
     const int out_lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), og = out_lane >> 4, ol = out_lane & 15;
-    // factors too large or without a value
-    float largest = 0.f;
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int pb = 0; pb < PB; ++pb) largest = tdc_largest(largest, acc[mb][pb]);
-    const bool small = tile_too_small(tile_top<TOP_ROWS>(tops, out_lane), x_exp);
+    // factors too small, too large or without a value
+    float largest;
+    int least;
+    tile_magnitudes<SWAP, MB, PB>(acc, largest, least);
+    const unsigned top = tile_top<TOP_ROWS>(tops, out_lane);
+    const int lost = tile_lost<NP>(a.half_log_terms, tdc_wave_max(__builtin_bit_cast(float, top)), x_exp);
+    bool small = tile_too_small(top, x_exp);
+    if (!EARLY) fetch_exponents(og, ol);
     unsigned nans = 0;
     bool redone = false;
-    if (__builtin_expect(small || tdc_any_lane(!tdc_finite(largest)), 0))
-        nans = tile_redo<ACT, CONV, MB, PB>(tdc_args_again<TileArgs>(), small, x_exp, out_lane, p_base, mb0, acc, redone);
-    if (!EARLY) fetch_exponents(og, ol);
+    if (__builtin_expect(small || tdc_any_lane(!tdc_finite(largest) || least < lost), 0)) {
+        small = small || tdc_any_lane(tile_lit<SWAP, PB>(top, 16 * PB * wp, out_lane) && tile_least<SWAP, MB, PB>(acc, w_exp, a.NBm - mb0) < lost);
+        if (small || tdc_any_lane(!tdc_finite(largest)))
+            nans = tile_redo<ACT, CONV, MB, PB>(tdc_args_again<TileArgs>(), small, x_exp, out_lane, p_base, mb0, acc, redone);
+    }
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
         if (redone || mb0 + mb >= a.NBm) break;
@@ -634,7 +696,9 @@ __global__ __launch_bounds__(256, MB == 2 ? 2 : 3) void tdc_tile_1x1_kernel(Tile
         tile_put_tops<NHWC, NPIX>(x_top, tops, 0, t);
     }
     __syncthreads();
-    const bool small = tile_too_small(tile_top<TOP_ROWS>(tops, lane), x_exp);
+    const unsigned top = tile_top<TOP_ROWS>(tops, lane);
+    const bool small = tile_too_small(top, x_exp);
+    const int lost = tile_lost<NP>(a.half_log_terms, tdc_wave_max(__builtin_bit_cast(float, top)), x_exp);
 
     // ---- where this lane's outputs are: NHWC: channels 4g.. of pixel l16 of block pb, NCHW: pixels 4g.. of channel l16
     // (bytes from the tile's first pixel or image on; two images, or what a tile spans of smaller ones, are below 4 GiB)
@@ -653,7 +717,7 @@ __global__ __launch_bounds__(256, MB == 2 ? 2 : 3) void tdc_tile_1x1_kernel(Tile
     for (int mt = mt0; mt < mt1; ++mt) {
         const int blk0 = (mt * 4 + wave) * MB;
         // exponents, bias and shortcut of this tile, under its products
-        tdc_u4 e[MB];
+        int e[MB][NHWC ? 4 : 1];
         tdc_f4 bias[MB], res[MB][PB];
         const bool with_res = quads && a.epi.residual;
 #pragma unroll
@@ -661,10 +725,12 @@ __global__ __launch_bounds__(256, MB == 2 ? 2 : 3) void tdc_tile_1x1_kernel(Tile
             const int m = 16 * (blk0 + mb) + (NHWC ? 4 * g : l16);
             const bool live = m < a.M;
             if (NHWC) {
-                e[mb] = __builtin_bit_cast(tdc_u4, tdc_buf_load4(wrs, live ? a.w_bytes + 4u * m : TDC_OOB));
+                const tdc_u4 u = __builtin_bit_cast(tdc_u4, tdc_buf_load4(wrs, a.w_bytes + 4u * m));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) e[mb][i % (NHWC ? 4 : 1)] = (int)u[i];
                 bias[mb] = a.epi.bias && live ? (tdc_f4){a.epi.bias[m], a.epi.bias[m + 1], a.epi.bias[m + 2], a.epi.bias[m + 3]} : tdc_f4_zero();
             } else {
-                e[mb][0] = __builtin_amdgcn_raw_buffer_load_b32(wrs, (int)(live ? a.w_bytes + 4u * m : TDC_OOB), 0, 0);
+                e[mb][0] = __builtin_amdgcn_raw_buffer_load_b32(wrs, (int)(a.w_bytes + 4u * m), 0, 0);
                 bias[mb][0] = a.epi.bias && live ? a.epi.bias[m] : 0.f;
             }
 #pragma unroll
@@ -699,18 +765,21 @@ __global__ __launch_bounds__(256, MB == 2 ? 2 : 3) void tdc_tile_1x1_kernel(Tile
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) w0[mb] = w1[mb];
         }
-        float largest = 0.f;
+        float largest;
+        int least;
         tdc_f4 acc[MB][PB];
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int pb = 0; pb < PB; ++pb) {
-                acc[mb][pb] = tdc_levels(lev[mb][pb]);
-                largest = tdc_largest(largest, acc[mb][pb]);
-            }
+            for (int pb = 0; pb < PB; ++pb) acc[mb][pb] = tdc_levels(lev[mb][pb]);
+        tile_magnitudes<SWAP, MB, PB>(acc, largest, least);
         bool redone = false;
-        if (__builtin_expect(small || tdc_any_lane(!tdc_finite(largest)), 0))
-            tile_redo<ACT, false, MB, PB>(tdc_args_again<TileArgs>(), small, x_exp, lane, p_tile, blk0, acc, redone);
+        if (__builtin_expect(small || tdc_any_lane(!tdc_finite(largest) || least < lost), 0)) {
+            const bool lit = tile_lit<SWAP, PB>(tile_top<TOP_ROWS>(tops, lane), 0, lane);
+            const bool too_small = small || tdc_any_lane(lit && tile_least<SWAP, MB, PB>(acc, e, a.NBm - blk0) < lost);
+            if (too_small || tdc_any_lane(!tdc_finite(largest)))
+                tile_redo<ACT, false, MB, PB>(tdc_args_again<TileArgs>(), too_small, x_exp, lane, p_tile, blk0, acc, redone);
+        }
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
             const int m = 16 * (blk0 + mb) + (NHWC ? 4 * g : l16);
@@ -719,7 +788,7 @@ __global__ __launch_bounds__(256, MB == 2 ? 2 : 3) void tdc_tile_1x1_kernel(Tile
                 tdc_f4 v = acc[mb][pb];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    v[i] = redone ? v[i] : ldexpf(v[i], -x_exp - (int)e[mb][NHWC ? i : 0]);
+                    v[i] = redone ? v[i] : ldexpf(v[i], -x_exp - e[mb][NHWC ? i : 0]);
                     v[i] += bias[mb][NHWC ? i : 0];
                     v[i] += res[mb][pb][i];
                 }
@@ -825,6 +894,7 @@ hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipSt
     const size_t w_bytes = tdc_split_bytes(parts, a.NBm, a.KG);
     a.w_bytes = (unsigned)w_bytes;
     a.pt_major = w_bytes < (size_t)d.B * a.C * a.HW * 4;
+    a.half_log_terms = (int)std::lround(0.5 * std::log2((double)d.K * d.K * d.C));
     a.vec = !d.nhwc && a.P % 4 == 0 && (((uintptr_t)y | (uintptr_t)epi.residual) & 15u) == 0;
     a.div_P = tdc_make_div((unsigned)a.P); a.div_Wo = tdc_make_div((unsigned)a.Wo);
     a.div_NBk = tdc_make_div((unsigned)a.NBk); a.div_K = tdc_make_div((unsigned)a.K);

@@ -292,6 +292,26 @@ def test_a_nan_explains_no_sums_but_its_own(orc, what, layer, nhwc):
         assert (np.linalg.norm((got - want)[1:], axis=1) <= 1.2e-6 * np.linalg.norm(want[1:], axis=1)).all()
 
 
+@pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
+@pytest.mark.parametrize("layer", FP16_LAYERS, ids=lambda l: l.name())
+def test_channels_that_the_weights_bring_to_one_size(orc, layer, nhwc):
+    """x in channels of very different size, which the weights undo: the result is that of the same layer without.  Parts of
+    fp16 keep x and the weights to an absolute accuracy only, which shows from some 2^20 between the channels on."""
+    for bits in (8, 16, 20, 24, 28, 34, 40, 60):
+        inputs = make_dense_inputs(layer, 87)
+        for of in ("even", "late"):
+            s = np.ones(layer.C, np.float32)
+            s[slice(None, None, 2) if of == "even" else slice(None, layer.C // 2)] = 2.0 ** bits
+            there = dict(x=inputs["x"] * s[None, :, None, None], W=inputs["W"] / s[:, None, None, None])
+            if of == "even":
+                there["x"][0, ::2, :, 4:] = 0            # pixels of nothing but the smaller channels
+            want = _oracle(orc, layer, there)
+            for tm, waves in ((64, 4), (128, 8)):
+                print("[case] tiles, channels 2^%d apart" % bits, of, layer.name(), "nhwc" if nhwc else "nchw", tm, waves, flush=True)
+                err = _run(layer, there, tm, waves, nhwc) - want
+                assert (np.linalg.norm(err, axis=1) <= 1.2e-6 * np.linalg.norm(want, axis=1)).all()
+
+
 def _gpu_us(launch):
     """Least time of a call, of five blocks of ten."""
     import torch
