@@ -37,8 +37,8 @@
  * Precision: fp32 in, fp32 out, sums in fp32.  Kernels bound by matrix arithmetic multiply on the fp16 matrix cores with
  * every fp32 factor scaled by a power of two (weights by output channel, x by workgroup) and split into two fp16 parts, 23
  * bits, or, in sums of few terms, into three fp16 or three unscaled bf16 ones; against 64 bits that is no further off than
- * fp32 multiply-adds.  What fp16 cannot hold is multiplied in fp32 as the other kernels do: infinities, NaN, values of x more than 64 times those its workgroup
- * loads first, and pixels of which no channel reaches 2^-23 of them (bf16: values
+ * fp32 multiply-adds.  What fp16 cannot hold is multiplied in fp32 as the other kernels do: infinities, NaN, values of x more than 512 times those its workgroup
+ * loads first, and pixels of which no channel reaches 2^-19 of them (bf16: values
  * from 2^126 on, pixels below 2^-110).  A tile that such values reach takes several times as
  * long (NaN alone: twice to three times).  A value of x below 2^-23 of its neighbourhood, beside larger channels of its own
  * pixel, keeps an absolute accuracy of 2^-46 of that neighbourhood, and a weight below 2^-26 of its output channel's

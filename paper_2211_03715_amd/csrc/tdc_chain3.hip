@@ -67,12 +67,13 @@ hipError_t tdc_launch_chain3(const TdcDims &d, const tdc_tuning &t, const TdcFus
     a.uin_bytes = (unsigned)tdc_split_bytes(2, d.NB1, d.KG1);
     a.core_bytes = (unsigned)tdc_split_bytes(2, d.NB2, a.KG2);
     a.uout_bytes = (unsigned)tdc_split_bytes(2, d.NB3, d.NB2);
-    // scaled weights of 2^12 and x of 2^8: sums of sqrt(C) 2^20
-    a.z1_exp = 12 + (int)std::lround(0.5 * std::log2((double)d.C));
+    // Scaled weights of 2^12 and x of 2^4.5 give sums of sqrt(C) 2^16.5; where neither changes sign they reach C 2^20, still below 2^16
+    // at 4096 channels.
+    a.z1_exp = 11 + (int)std::lround(0.5 * std::log2((double)d.C));
     // A channel's largest output among a lane's pixels must be 2^22 times what the parts lose.  With scaled weights of 2^12 and values of
     // 2^12 at most, root mean square, z1 is off by 2^-36 (x, U_in and its own parts), the scaled z2 by sqrt(K K R1) 2^-23.5 before its
     // scale 2^z2_exp and by its parts' 2^-37 behind it, and the sums of the outputs by sqrt(R2) (2^12 of that + 2^-25).  Normal values
-    // give 2^16 times more.  As exponents: of what comes from in front of z2's scale, with that 0, and of the rest.
+    // give 2^17 times more.  As exponents: of what comes from in front of z2's scale, with that 0, and of the rest.
     const double r2 = 0.5 * std::log2((double)d.R2);
     a.lost2 = (int)std::lround(11 + r2 + 0.5 * std::log2((double)d.K * d.K * d.R1));
     a.lost3 = (int)std::lround(r2 - 2);

@@ -241,7 +241,7 @@ struct Chain3Stage1 {
         zero_outside(z1s);
         float m = 0.f;
 #pragma unroll
-        for (int i = 0; i < NR; ++i) m = tdc_largest(m, x[0][i]);
+        for (int i = 0; i < NR; ++i) m = tdc_largest_number(m, x[0][i]);
         sh.first[wave] = tdc_wave_max(m);
         __syncthreads();
         const tdc_u4 first = *reinterpret_cast<const tdc_u4 *>(sh.first);

@@ -17,9 +17,11 @@
 // Scales.  fp16 holds 2^-24 .. 65504, so v2 keeps its 11 bits down to |v| = 2^-13 and the parts an absolute 2^-36 below that.
 //   weights      every output channel has its own exponent, the largest weight at 2^13 .. 2^14 (tdc_pack.hip): three parts that
 //                are not lifted keep all 24 bits down to 2^-1 and an absolute 2^-25 below, 2^-38 of the largest weight;
-//   activations  one exponent per workgroup, which takes the largest magnitude among those it loads first to 2^10 .. 2^11
-//                (tdc_scale_of): 64 times larger values still fit, 2^23 times smaller ones keep all their bits;
-//   z1           sqrt(C) 2^12 times smaller than its sums, a constant: 2^8 or so; z2: by the largest a wavefront holds.
+//   activations  one exponent per workgroup, which takes the largest magnitude among those it loads first to 2^6 .. 2^7
+//                (tdc_scale_of): 512 times larger values still fit, 2^19 times smaller ones keep all their bits (from 2^10 on
+//                it would be 64 times and 2^23: channels of larger values behind the first ones are the commoner thing);
+//   z1           sqrt(C) 2^11 times smaller than its sums, a constant: 2^5 or so, and below 2^14 where all signs agree;
+//   z2           by the largest a wavefront holds.
 // What is lost.  A factor below 2^TDC_LOWEST is kept to an absolute accuracy, 2^-36.  That shows where large weights meet small
 // values only, as when the weights undo what size the channels of x have: the sums are small then, a channel's over several
 // pixels (one alone may be so by chance), and each stage that writes outputs compares them with what the parts may have lost.
@@ -150,6 +152,8 @@ __device__ __forceinline__ float tdc_largest(float m, tdc_f4 v)
     m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, fabsf(v[0])), fabsf(v[1]));
     return __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, fabsf(v[2])), fabsf(v[3]));
 }
+// Largest magnitude of those that are numbers.
+__device__ __forceinline__ float tdc_largest_number(float m, tdc_f4 v) { return fmaxf(fmaxf(fmaxf(m, fabsf(v[0])), fmaxf(fabsf(v[1]), fabsf(v[2]))), fabsf(v[3])); }
 // The smallest of several magnitudes that is not zero, as an integer: start with ~0u.
 __device__ __forceinline__ unsigned tdc_smallest(unsigned s, float m) { return min(s, __builtin_bit_cast(unsigned, m) - 1u); }
 __device__ __forceinline__ bool tdc_is_small(unsigned s, float limit) { return s < __builtin_bit_cast(unsigned, limit) - 1u; }
@@ -183,7 +187,7 @@ __device__ __forceinline__ int tdc_scale_of(unsigned bits, int target, int other
     const int e = (int)(bits >> 23);
     return e == 0 || e >= 255 ? other : min(target + 127 - e, 100);
 }
-constexpr int TDC_X_TARGET = 10, TDC_X_OTHER = 6, TDC_Z2_TARGET = 12;
+constexpr int TDC_X_TARGET = 6, TDC_X_OTHER = 6, TDC_Z2_TARGET = 12;
 constexpr int TDC_LOWEST = -13;      // scaled values from 2^TDC_LOWEST on keep all their bits
 constexpr int tdc_lowest_weight(int np) { return tdc_lift_weights(np) ? TDC_LOWEST : -1; }
 constexpr float TDC_FP16_MAX = 65504.f;

@@ -188,7 +188,7 @@ __device__ __forceinline__ bool tile_too_small(unsigned top, int x_exp)
 
 // What a channel's largest sum among a lane's pixels must reach, as bits: 2^22 times what the parts lose.  With scaled weights of 2^12
 // root mean square, x up to `top` times 2^x_exp and 2^(2 half_log_terms) terms two parts lose sqrt(terms) (2^-25 + 2^-39 x), of
-// three, where the weights' are not lifted, sqrt(terms) (2^-25 + 2^-28 x).  Normal values give 2^16 (2^13) times more.
+// three, where the weights' are not lifted, sqrt(terms) (2^-25 + 2^-28 x).  Normal values give 2^18 (2^15) times more.
 template <int NP>
 __device__ __forceinline__ int tile_lost(int half_log_terms, unsigned top, int x_exp)
 {
@@ -443,7 +443,7 @@ __global__ __launch_bounds__(256 * KS, tile_wavefronts(MB * PB)) void tdc_tile_k
         fetch_x(ks + KS, x[1]);
         float m = 0.f;
 #pragma unroll
-        for (int n = 0; n < NX; ++n) m = tdc_largest(m, x[0][n]);
+        for (int n = 0; n < NX; ++n) m = tdc_largest_number(m, x[0][n]);
         first_all[4 * ks + wave] = tdc_wave_max(m);
         __syncthreads();
         unsigned first = 0;
@@ -680,7 +680,7 @@ __global__ __launch_bounds__(256, MB == 2 ? 2 : 3) void tdc_tile_1x1_kernel(Tile
 #pragma unroll
         for (int u = 0; u < CHUNK; ++u)
 #pragma unroll
-            for (int n = 0; n < NX; ++n) m = tdc_largest(m, x[u][n]);
+            for (int n = 0; n < NX; ++n) m = tdc_largest_number(m, x[u][n]);
         first_all[wave] = tdc_wave_max(m);
         __syncthreads();
         const tdc_u4 first = tile_1x1_lds[0];

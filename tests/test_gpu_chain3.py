@@ -5,7 +5,7 @@ runs of four pixels), every unit size."""
 import numpy as np
 import pytest
 
-from parity_util import assert_parity
+from parity_util import assert_parity, gpu_us
 from paper_2211_03715_amd import binding as B
 from paper_2211_03715_amd.workloads import Layer, make_inputs
 
@@ -207,10 +207,10 @@ def test_the_scale_of_the_factors_costs_no_accuracy(orc, layer, tile, nhwc):
 @pytest.mark.parametrize("layer,tile", ((Layer(2, 72, 48, 12, 12, 32, 16, 3, 1, 1), (4, 4)), (Layer(40, 72, 24, 12, 12, 40, 80, 3, 2, 1), (6, 6))),
                          ids=lambda v: v.name() if isinstance(v, Layer) else "")
 def test_values_far_from_those_that_set_the_scale(orc, layer, tile, nhwc):
-    """x is scaled by the first 32 channels that a workgroup loads.  Channels behind them up to 64 times larger fit in fp16 and larger
-    ones do not; pixels down to 2^-23 of them keep all their bits and smaller ones do not.  Both sides of each line."""
+    """x is scaled by the first 32 channels that a workgroup loads.  Channels behind them up to 512 times larger fit in fp16 and larger
+    ones do not; pixels down to 2^-19 of them keep all their bits and smaller ones do not.  Both sides of each line."""
     t = B.make_tuning(variant=B.VARIANT_CHAIN, tile_h=tile[0], tile_w=tile[1], waves=(4, 4, 4), mb=(2, 3, 1), pb=(2,) * 3)
-    for what, e in [("channels", e) for e in (4, 6, 7, 9, 40)] + [("pixels", -e) for e in (10, 21, 23, 25, 40)]:
+    for what, e in [("channels", e) for e in (4, 6, 7, 9, 11, 40)] + [("pixels", -e) for e in (10, 17, 19, 21, 23, 25, 40)]:
         inputs = {k: v.copy() for k, v in make_inputs(layer, 94).items()}
         if what == "channels":
             inputs["x"][:, -8:] *= np.float32(2.0 ** e)
@@ -272,3 +272,41 @@ def test_ranks_and_channels_that_the_next_factor_brings_to_one_size(orc, layer, 
             print("[case] chain3,", what, "2^%d apart" % bits, layer.name(), "nhwc" if nhwc else "nchw", flush=True)
             err = _run(layer, inputs, t, nhwc) - want
             assert (np.linalg.norm(err, axis=1) <= 1.5e-6 * np.linalg.norm(want, axis=1)).all(), (what, bits)
+
+
+def _larger_late(i):                 # behind what sets the scale
+    i["x"][:, -8:] *= np.float32(200.0)
+
+
+def _flat(i):                        # sums without a change of sign, C times a product and not sqrt(C)
+    i["x"][...] = 1.9
+    i["U_in"][...] = 0.05
+
+
+@pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
+@pytest.mark.parametrize("layer,tile", ((Layer(32, 512, 64, 14, 14, 32, 32, 3, 1, 1), (4, 14)), (Layer(32, 256, 128, 14, 14, 64, 64, 3, 1, 1), (2, 14))),
+                         ids=lambda v: v.name() if isinstance(v, Layer) else "")
+@pytest.mark.parametrize("values", (_larger_late, _flat), ids=lambda f: f.__name__[1:])
+def test_finite_inputs_that_fp16_holds_cost_the_usual_time(values, layer, tile, nhwc):
+    """They are not computed again in fp32, which takes several times as long."""
+    import torch
+    from paper_2211_03715_amd.layer import TuckerConv2d
+    dev = torch.device("cuda:0")
+    usual = make_inputs(layer, 96)
+    other = {k: v.copy() for k, v in usual.items()}
+    values(other)
+    t = B.make_tuning(variant=B.VARIANT_CHAIN, tile_h=tile[0], tile_w=tile[1], waves=(4, 4, 4), mb=(2, 3, 1), pb=(2,) * 3)
+    us = []
+    for inputs in (usual, other):
+        conv = TuckerConv2d(layer, 0, t, B.LAYOUT_NHWC if nhwc else B.LAYOUT_NCHW)
+        try:
+            w = [torch.from_numpy(inputs[k]).to(dev) for k in ("U_in", "core", "U_out")]
+            conv.pack(*w)
+            x = torch.from_numpy(np.ascontiguousarray(inputs["x"].transpose(0, 2, 3, 1) if nhwc else inputs["x"])).to(dev)
+            launch = conv.bind(x, torch.empty(conv.out_shape(), device=dev))
+            gpu_us(launch)
+            us.append(gpu_us(launch))
+        finally:
+            conv.close()
+    print("[case] chain3,", values.__name__, layer.name(), "nhwc" if nhwc else "nchw", "%.1f us, usually %.1f" % (us[1], us[0]), flush=True)
+    assert us[1] <= 1.5 * us[0]
