@@ -571,7 +571,7 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
         bad = tdc_is_small(s1.smallest, tdc_exp2i(args.z1_exp + TDC_LOWEST)) || tdc_is_small(s1.smallest_x, tdc_exp2i(max(TDC_LOWEST - x_exp, -126)));
     }
 
-    const TdcChain3Args &a = tdc_args_again<TdcChain3Args>();    // read anew, and not kept through stage 1
+    const TdcChain3Args a = tdc_args_again<TdcChain3Args>();    // read anew, and not kept through stage 1
     const int plane = a.NB1 * 4 * a.pitch1;                      // cells of one part
     const tdc_rsrc crs = tdc_make_rsrc(a.core, a.core_bytes + 64u * NB2), ors = tdc_make_rsrc(a.uout, a.uout_bytes + 64u * a.NB3);   // with the exponents
     // with fewer groups than wavefronts 2 or 4 of them share one: each takes a slice of stage 2's contraction, the sums meet in
@@ -794,7 +794,7 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
         const Chain3Out<PB, NHWC> out(a, at, pg, lane);
         float largest = 0.f;
         const int lost = lit ? (127 + min(max(z2_exp + a.lost2, a.lost3), 126)) << 23 : 0;
-        int least = TDC_EMPTY;                                   // of the magnitudes of the channels' largest sums the least, as bits
+        int least = 0x7f800000;                                  // of the magnitudes of the channels' largest sums the least, as bits
         // two instances of the loop, as in tdc_chain_kernel.h: without epilogue loads nothing ever waits for the stores
         typedef typename Chain3Out<PB, NHWC>::Epi Epi;
         const auto emit = [&](auto with_epi, int nb, const tdc_op<NP>(&u)[S3], const Exponents &e, const Epi *epi) {
@@ -812,22 +812,25 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
                         tdc_f4 &c = acc3[pb][TdcProducts<NP>::level[i]];
                         c = tdc_mfma_part<NP, SWAP>(i, u[st].p, zb[st][pb].p, c);
                     }
-            // magnitude of a channel's largest sum among this lane's pixels
-            float m[NHWC ? 4 : 1] = {};
 #pragma unroll
             for (int pb = 0; pb < PB; ++pb) {
                 v[pb] = tdc_levels(acc3[pb]);
-                if constexpr (NHWC) {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) m[i] = __builtin_elementwise_maximum(m[i], fabsf(v[pb][i]));
-                } else {
-                    m[0] = tdc_largest(m[0], v[pb]);
-                }
+                largest = tdc_largest(largest, v[pb]);
             }
+            // a channel's largest among this lane's pixels, of those that are no NaN
 #pragma unroll
             for (int i = 0; i < (NHWC ? 4 : 1); ++i) {
-                largest = __builtin_elementwise_maximum(largest, m[i]);
-                least = min(least, max(__builtin_bit_cast(int, m[i]), e.e[i]));
+                float m = fabsf(v[0][i]);
+#pragma unroll
+                for (int pb = 0; pb < PB; pb += NHWC ? 2 : 1) {
+                    if (NHWC) {
+                        m = tdc_max3_abs(m, v[pb][i], v[pb + 1][i]);
+                    } else {
+                        m = tdc_max3_abs(m, v[pb][0], v[pb][1]);
+                        m = tdc_max3_abs(m, v[pb][2], v[pb][3]);
+                    }
+                }
+                least = min(least, __builtin_bit_cast(int, m));
             }
 #pragma unroll
             for (int pb = 0; pb < PB; ++pb)

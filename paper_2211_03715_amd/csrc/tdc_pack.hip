@@ -197,7 +197,7 @@ __global__ void split_pack_kernel(SplitArgs a)
     for (int i = 0; i < 2; ++i) {
         const bool there = kg < t.KG && row + i < t.rows;
         v[i] = there && m < t.cols ? t.w[((size_t)(row + i) * t.cols + m) * t.KK + tap] : 0.f;
-        scaled[i] = wide ? NAN : ldexpf(v[i], scale - (t.before && there ? split_scale(split_top(a.t[0], row + i)) : 0));
+        scaled[i] = wide ? NAN : t.last && channel == -SPLIT_NONE && v[i] == 0.f ? (there ? ((row + i) % 2 ? 0x1p12f : 0x1p13f) : 0.f) : ldexpf(v[i], scale - (t.before && there ? split_scale(split_top(a.t[0], row + i)) : 0));
     }
     unsigned p[NP];
     tdc_split2<NP, tdc_lift_weights(NP)>(scaled[0], scaled[1], TdcScale(0), p);

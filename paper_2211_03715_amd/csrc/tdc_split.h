@@ -152,6 +152,14 @@ __device__ __forceinline__ float tdc_largest(float m, tdc_f4 v)
     m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, fabsf(v[0])), fabsf(v[1]));
     return __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, fabsf(v[2])), fabsf(v[3]));
 }
+// max(a, |b|, |c|) of those that are no NaN.  Asm: fmaxf would take an instruction more for each that might be a signalling NaN.  b and
+// c must not come from the matrix cores directly (see tdc_split2).
+__device__ __forceinline__ float tdc_max3_abs(float a, float b, float c)
+{
+    float m;
+    asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(m) : "v"(a), "v"(b), "v"(c));
+    return m;
+}
 // Largest magnitude of those that are numbers.
 __device__ __forceinline__ float tdc_largest_number(float m, tdc_f4 v) { return fmaxf(fmaxf(fmaxf(m, fabsf(v[0])), fmaxf(fabsf(v[1]), fabsf(v[2]))), fabsf(v[3])); }
 // The smallest of several magnitudes that is not zero, as an integer: start with ~0u.
@@ -191,9 +199,10 @@ constexpr int TDC_X_TARGET = 6, TDC_X_OTHER = 6, TDC_Z2_TARGET = 12;
 constexpr int TDC_LOWEST = -13;      // scaled values from 2^TDC_LOWEST on keep all their bits
 constexpr int tdc_lowest_weight(int np) { return tdc_lift_weights(np) ? TDC_LOWEST : -1; }
 constexpr float TDC_FP16_MAX = 65504.f;
-// exponents of the channels of weights that are kept out of the parts, which are NaN, and of channels without a finite weight that is not
-// 0: in order as integers with the bits of magnitudes, above all that are finite sums
-constexpr int TDC_WIDE = 1 << 20, TDC_EMPTY = 0x7f000000;
+// Exponents of the channels of weights that are kept out of the parts, which are NaN, and of output channels without a weight that is
+// not 0.  The latter have weights of 2^12 and 2^13 in parts, so that their sums are of the usual size and no stage need know
+// them; the exponent then makes them 0.
+constexpr int TDC_WIDE = 1 << 20, TDC_EMPTY = 1 << 21;
 
 // k-group kg's share of a lane's fp32 weights of 16-channel block `block` (layout: tdc_internal.h)
 __device__ __forceinline__ tdc_f4 tdc_raw_weights(tdc_rsrc r, int block, int k_groups, int kg, int lane)

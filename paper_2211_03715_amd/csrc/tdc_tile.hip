@@ -200,7 +200,7 @@ template <bool SWAP, int MB, int PB>
 __device__ __forceinline__ void tile_magnitudes(const tdc_f4 (&acc)[MB][PB], float &largest, int &least)
 {
     largest = 0.f;
-    least = TDC_EMPTY;
+    least = 0x7f800000;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -214,11 +214,11 @@ __device__ __forceinline__ void tile_magnitudes(const tdc_f4 (&acc)[MB][PB], flo
             least = min(least, __builtin_bit_cast(int, m));
         }
 }
-// The least once more, of `blocks` channel blocks, of channels with weights and of sums that are no NaN, where there is one.
+// The least once more, of `blocks` channel blocks and of sums that are no NaN, where there is one.
 template <bool SWAP, int MB, int PB>
-__device__ __forceinline__ int tile_least(const tdc_f4 (&acc)[MB][PB], const int (&w_exp)[MB][SWAP ? 1 : 4], int blocks)
+__device__ __forceinline__ int tile_least(const tdc_f4 (&acc)[MB][PB], int blocks)
 {
-    int least = TDC_EMPTY;
+    int least = 0x7f800000;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -228,7 +228,7 @@ __device__ __forceinline__ int tile_least(const tdc_f4 (&acc)[MB][PB], const int
             for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
                 for (int i = SWAP ? 0 : c; i < (SWAP ? 4 : c + 1); ++i) m = fmaxf(m, fabsf(acc[mb][pb][i]));
-            if (m >= 0.f && mb < blocks && w_exp[mb][c] != TDC_EMPTY) least = min(least, __builtin_bit_cast(int, m));
+            if (m >= 0.f && mb < blocks) least = min(least, __builtin_bit_cast(int, m));
         }
     return least;
 }
@@ -534,7 +534,7 @@ __global__ __launch_bounds__(256 * KS, tile_wavefronts(MB * PB)) void tdc_tile_k
     unsigned nans = 0;
     bool redone = false;
     if (__builtin_expect(small || tdc_any_lane(!tdc_finite(largest) || least < lost), 0)) {
-        small = small || tdc_any_lane(tile_lit<SWAP, PB>(top, 16 * PB * wp, out_lane) && tile_least<SWAP, MB, PB>(acc, w_exp, a.NBm - mb0) < lost);
+        small = small || tdc_any_lane(tile_lit<SWAP, PB>(top, 16 * PB * wp, out_lane) && tile_least<SWAP, MB, PB>(acc, a.NBm - mb0) < lost);
         if (small || tdc_any_lane(!tdc_finite(largest)))
             nans = tile_redo<ACT, CONV, MB, PB>(tdc_args_again<TileArgs>(), small, x_exp, out_lane, p_base, mb0, acc, redone);
     }
@@ -776,7 +776,7 @@ __global__ __launch_bounds__(256, MB == 2 ? 2 : 3) void tdc_tile_1x1_kernel(Tile
         bool redone = false;
         if (__builtin_expect(small || tdc_any_lane(!tdc_finite(largest) || least < lost), 0)) {
             const bool lit = tile_lit<SWAP, PB>(tile_top<TOP_ROWS>(tops, lane), 0, lane);
-            const bool too_small = small || tdc_any_lane(lit && tile_least<SWAP, MB, PB>(acc, e, a.NBm - blk0) < lost);
+            const bool too_small = small || tdc_any_lane(lit && tile_least<SWAP, MB, PB>(acc, a.NBm - blk0) < lost);
             if (too_small || tdc_any_lane(!tdc_finite(largest)))
                 tile_redo<ACT, false, MB, PB>(tdc_args_again<TileArgs>(), too_small, x_exp, lane, p_tile, blk0, acc, redone);
         }

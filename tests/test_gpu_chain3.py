@@ -283,10 +283,16 @@ def _flat(i):                        # sums without a change of sign, C times a 
     i["U_in"][...] = 0.05
 
 
+def _dead(i):                        # filters without a weight, images without a value
+    i["U_out"][:, ::2] = 0
+    i["U_out"][:, :17] = 0
+    i["x"][1::2] = 0
+
+
 @pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
 @pytest.mark.parametrize("layer,tile", ((Layer(32, 512, 64, 14, 14, 32, 32, 3, 1, 1), (4, 14)), (Layer(32, 256, 128, 14, 14, 64, 64, 3, 1, 1), (2, 14))),
                          ids=lambda v: v.name() if isinstance(v, Layer) else "")
-@pytest.mark.parametrize("values", (_larger_late, _flat), ids=lambda f: f.__name__[1:])
+@pytest.mark.parametrize("values", (_larger_late, _flat, _dead), ids=lambda f: f.__name__[1:])
 def test_finite_inputs_that_fp16_holds_cost_the_usual_time(values, layer, tile, nhwc):
     """They are not computed again in fp32, which takes several times as long."""
     import torch
@@ -303,9 +309,13 @@ def test_finite_inputs_that_fp16_holds_cost_the_usual_time(values, layer, tile, 
             w = [torch.from_numpy(inputs[k]).to(dev) for k in ("U_in", "core", "U_out")]
             conv.pack(*w)
             x = torch.from_numpy(np.ascontiguousarray(inputs["x"].transpose(0, 2, 3, 1) if nhwc else inputs["x"])).to(dev)
-            launch = conv.bind(x, torch.empty(conv.out_shape(), device=dev))
+            y = torch.empty(conv.out_shape(), device=dev)
+            launch = conv.bind(x, y)
             gpu_us(launch)
             us.append(gpu_us(launch))
+            if values is _dead and inputs is other:
+                got = y.permute(0, 3, 1, 2) if nhwc else y
+                assert not got[:, ::2].any() and not got[:, :17].any() and not got[1::2].any() and got[0, 17].any()
         finally:
             conv.close()
     print("[case] chain3,", values.__name__, layer.name(), "nhwc" if nhwc else "nchw", "%.1f us, usually %.1f" % (us[1], us[0]), flush=True)

@@ -312,16 +312,22 @@ def test_channels_that_the_weights_bring_to_one_size(orc, layer, nhwc):
                 assert (np.linalg.norm(err, axis=1) <= 1.2e-6 * np.linalg.norm(want, axis=1)).all()
 
 
-def _small_quarter(x):               # what one of the four wavefronts that share NCHW pixels brings
-    for c in range(4, x.shape[1], 16):
-        x[:, c:c + 4] *= np.float32(2.0 ** -30)
+def _small_quarter(i):               # what one of the four wavefronts that share NCHW pixels brings
+    for c in range(4, i["x"].shape[1], 16):
+        i["x"][:, c:c + 4] *= np.float32(2.0 ** -30)
 
 
-def _larger_late(x):                 # behind what sets the scale
-    x[:, -8:] *= np.float32(200.0)
+def _larger_late(i):                 # behind what sets the scale
+    i["x"][:, -8:] *= np.float32(200.0)
 
 
-ORDINARY = (_small_quarter, _larger_late)
+def _dead(i):                        # filters without a weight, images without a value
+    i["W"][:, ::2] = 0
+    i["W"][:, :17] = 0
+    i["x"][1::2] = 0
+
+
+ORDINARY = (_small_quarter, _larger_late, _dead)
 
 
 @pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
@@ -332,19 +338,24 @@ def test_finite_inputs_that_fp16_holds_cost_the_usual_time(values, layer, nhwc):
     import torch
     from paper_2211_03715_amd.layer import DenseConv2d
     dev = torch.device("cuda:0")
-    inputs = make_dense_inputs(layer, 88)
     put = lambda a: torch.from_numpy(np.ascontiguousarray(a.transpose(0, 2, 3, 1) if nhwc else a)).to(dev)
-    usual = put(inputs["x"])
-    values(inputs["x"])
+    usual = make_dense_inputs(layer, 88)
+    other = {k: v.copy() for k, v in usual.items()}
+    values(other)
     conv = DenseConv2d(layer, 0, B.make_tuning(tile_h=64, tile_w=64, waves=(4,) * 3), B.LAYOUT_NHWC if nhwc else B.LAYOUT_NCHW)
     try:
-        W = torch.from_numpy(inputs["W"]).to(dev)
-        conv.pack(W)
+        us = []
         y = torch.empty(conv.out_shape(), device=dev)
-        first, second = conv.bind(usual, y), conv.bind(put(inputs["x"]), y)
-        gpu_us(first)
-        a, b = gpu_us(first), gpu_us(second)
-        print("[case] tiles,", values.__name__, layer.name(), "nhwc" if nhwc else "nchw", "%.1f us, usually %.1f" % (b, a), flush=True)
-        assert b <= 1.5 * a
+        for inputs in (usual, other):
+            W = torch.from_numpy(inputs["W"]).to(dev)
+            conv.pack(W)
+            launch = conv.bind(put(inputs["x"]), y)
+            gpu_us(launch)
+            us.append(gpu_us(launch))
+        print("[case] tiles,", values.__name__, layer.name(), "nhwc" if nhwc else "nchw", "%.1f us, usually %.1f" % (us[1], us[0]), flush=True)
+        assert us[1] <= 1.5 * us[0]
+        if values is _dead:
+            y = y.permute(0, 3, 1, 2) if nhwc else y
+            assert not y[:, ::2].any() and not y[:, :17].any() and not y[1::2].any() and y[0, 17].any()
     finally:
         conv.close()
