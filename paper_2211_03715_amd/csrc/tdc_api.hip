@@ -106,10 +106,11 @@ TdcDims make_dims(const tdc_shape &s)
     return d;
 }
 
-TdcFusedGeom chain_geometry(const TdcDims &d, const tdc_tuning &t, int lds_limit)
+TdcFusedGeom chain_geometry(TdcDims d, const tdc_tuning &t, const TdcDeviceInfo &dev)
 {
+    d.s1_runs = tdc_runs_apply(d, dev.cus);
     return tdc_is_chain3(t) ? tdc_chain3_geometry(d, t.tile_h, t.tile_w, t.pb[0])
-                            : tdc_chain_geometry(d, t.tile_h, t.tile_w, t.waves[0], t.pb[0], lds_limit);
+                            : tdc_chain_geometry(d, t.tile_h, t.tile_w, t.waves[0], t.pb[0], dev.lds_per_wg);
 }
 
 int check_tuning(const tdc_plan &p, const TdcDeviceInfo &dev)
@@ -320,7 +321,7 @@ int tdc_plan_create_tuned(tdc_plan **out, const tdc_shape *shape, int device, co
     if (rc == TDC_OK && p->tuning.variant == TDC_VARIANT_FUSED)
         p->geom = tdc_fused_geometry(p->dims, p->tuning.tile_h, p->tuning.tile_w, dev.lds_per_wg);
     if (rc == TDC_OK && p->tuning.variant == TDC_VARIANT_CHAIN)
-        p->geom = chain_geometry(p->dims, p->tuning, dev.lds_per_wg);
+        p->geom = chain_geometry(p->dims, p->tuning, dev);
     if (rc == TDC_OK && p->tuning.variant == TDC_VARIANT_FUSED_MERGED)
         p->geom = tdc_fm_geometry(p->dims, p->tuning.tile_h, p->tuning.tile_w, p->tuning.waves[0], p->tuning.mb[1]);
     if (rc == TDC_OK) rc = check_tuning(*p, dev);
@@ -432,7 +433,7 @@ int tdc_select_tuning(const tdc_shape *shape, int compute_units, int lds_bytes, 
     if (rc == TDC_OK && tmp.tuning.variant == TDC_VARIANT_FUSED)
         tmp.geom = tdc_fused_geometry(tmp.dims, tmp.tuning.tile_h, tmp.tuning.tile_w, dev.lds_per_wg);
     if (rc == TDC_OK && tmp.tuning.variant == TDC_VARIANT_CHAIN)
-        tmp.geom = chain_geometry(tmp.dims, tmp.tuning, dev.lds_per_wg);
+        tmp.geom = chain_geometry(tmp.dims, tmp.tuning, dev);
     if (rc == TDC_OK && tmp.tuning.variant == TDC_VARIANT_FUSED_MERGED)
         tmp.geom = tdc_fm_geometry(tmp.dims, tmp.tuning.tile_h, tmp.tuning.tile_w, tmp.tuning.waves[0], tmp.tuning.mb[1]);
     if (rc == TDC_OK) rc = check_tuning(tmp, dev);
@@ -461,7 +462,7 @@ int tdc_model_terms(const tdc_shape *shape, const tdc_tuning *tuning, int comput
     if (tuning->variant == TDC_VARIANT_FUSED)
         tmp.geom = tdc_fused_geometry(tmp.dims, tuning->tile_h, tuning->tile_w, lds_bytes);
     if (tuning->variant == TDC_VARIANT_CHAIN)
-        tmp.geom = chain_geometry(tmp.dims, *tuning, lds_bytes);
+        tmp.geom = chain_geometry(tmp.dims, *tuning, dev);
     if (tuning->variant == TDC_VARIANT_FUSED_MERGED)
         tmp.geom = tdc_fm_geometry(tmp.dims, tuning->tile_h, tuning->tile_w, tuning->waves[0], tuning->mb[1]);
     rc = check_tuning(tmp, dev);

@@ -40,7 +40,10 @@ TdcFusedGeom tdc_chain3_geometry(const TdcDims &d, int tile_h, int tile_w, int p
     g.weights_in_lds = g.weights_fit = false;
     const bool bf3 = tdc_chain3_bf3(d);
     g.lds_bytes = bf3 ? (size_t)96 * d.NB1 * g.pitch1 : sizeof(Chain3Shared) + (size_t)64 * d.NB1 * g.pitch1;
-    if (pb > 0) g.lds_bytes += tdc_chain3_share((g.PBk + pb - 1) / pb) ? (size_t)TDC_CHAIN3_WAVES * d.NB2 * pb * 1024 : bf3 ? 0 : (size_t)2048 * chain3_feed_pieces(d.NB2);
+    if (pb <= 0) return g;
+    const int lay = d.nhwc ? TDC_LAY_NHWC : d.s1_runs ? TDC_LAY_NCHW_RUNS : TDC_LAY_NCHW;
+    if (tdc_chain3_share((g.PBk + pb - 1) / pb)) g.lds_bytes += (size_t)TDC_CHAIN3_WAVES * d.NB2 * pb * 1024;
+    else if (!bf3 && chain3_shares_weights(lay, d.NB2)) g.lds_bytes += (size_t)2048 * chain3_feed_pieces(d.NB2);
     return g;
 }
 

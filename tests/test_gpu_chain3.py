@@ -320,3 +320,16 @@ def test_finite_inputs_that_fp16_holds_cost_the_usual_time(values, layer, tile, 
             conv.close()
     print("[case] chain3,", values.__name__, layer.name(), "nhwc" if nhwc else "nchw", "%.1f us, usually %.1f" % (us[1], us[0]), flush=True)
     assert us[1] <= 1.5 * us[0]
+
+
+def test_a_plan_takes_no_lds_for_weights_that_its_kernel_does_not_share():
+    """Instances that read runs and hold three or more z2 blocks keep z1 only: 9 x 57 pixels in 33 blocks, two channel blocks of
+    64 bytes a pixel, and 32 bytes.  The others keep two chunks of weights beside it."""
+    layer = Layer(32, 128, 256, 56, 56, 32, 64, 3, 2, 1)
+    for lay, extra in ((B.LAYOUT_NCHW, 0), (B.LAYOUT_NHWC, 2 * 8 * 1024)):
+        t = B.make_tuning(variant=B.VARIANT_CHAIN, tile_h=4, tile_w=28, waves=(4, 4, 4), mb=(2, 3, 1), pb=(2,) * 3)
+        plan = B.tdc_plan_create(B.make_shape(*[getattr(layer, k) for k in ("batch", "C", "N", "H", "W", "R1", "R2", "K", "stride", "pad")], layout=lay), 0, t)
+        try:
+            assert "lds=%dB" % (32 + 64 * 2 * 16 * 33 + extra) in B.tdc_plan_describe(plan)
+        finally:
+            B.tdc_plan_destroy(plan)
