@@ -401,6 +401,8 @@ int tdc_plan_create_tuned(tdc_plan **out, const tdc_shape *shape, int device, co
             e = tdc_launch_chain(d, p->tuning, p->geom, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, none, true);
         else if (p->tuning.variant == TDC_VARIANT_FUSED_MERGED)
             e = tdc_launch_fm(d, p->tuning, p->geom, nullptr, nullptr, nullptr, nullptr, nullptr, none, true);
+        else if (dense && tdc_is_tile(p->tuning))
+            e = tdc_launch_tile_dense(d, p->tuning.tile_h, p->tuning.tile_w, p->tuning.waves[1] / 4, nullptr, nullptr, nullptr, nullptr, none, true);
         if (e != hipSuccess) {
             (void)hipGetLastError();
             tdc_plan_destroy(p);

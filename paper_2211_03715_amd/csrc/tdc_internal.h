@@ -118,7 +118,8 @@ bool tdc_tile_supported(int tm, int tp, int ks);
 bool tdc_tile_applies(const TdcDims &d);
 bool tdc_tile_1x1_applies(const TdcDims &d);   // one group of wavefronts runs it with all its channels in LDS
 inline bool tdc_tile_bf3(const TdcDims &d, int ks) { return tdc_tile_parts(d) == 3 && !(ks == 1 && tdc_tile_1x1_applies(d)); }
-hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipStream_t s, const float *x, const void *w, float *y, const TdcEpi &epi);
+hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipStream_t s, const float *x, const void *w, float *y, const TdcEpi &epi,
+                                 bool prepare_only = false);
 // weights in tdc_launch_pack3_core's layout
 hipError_t tdc_launch_tile_bf3(const TdcDims &d, int tm, int tp, int ks, hipStream_t s, const float *x, const void *w3, float *y, const TdcEpi &epi);
 

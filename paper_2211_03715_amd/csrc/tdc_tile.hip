@@ -843,13 +843,13 @@ int tile_1x1_share(int n_pt, int n_mt, int mb, size_t lds)
 }
 
 template <int ACT>
-hipError_t launch_1x1(const TileArgs &a, int mb, int parts, hipStream_t s)
+hipError_t launch_1x1(const TileArgs &a, int mb, int parts, hipStream_t s, bool prepare_only)
 {
     const dim3 grid((unsigned)(a.n_pt * a.n_mg));
     const size_t lds = tile_1x1_lds_bytes(a.S, parts, ACT == TDC_ACT_NHWC);
     const auto kernel = parts == 3 ? tdc_tile_1x1_kernel<ACT, 1, 3> : mb == 1 ? tdc_tile_1x1_kernel<ACT, 1, 2> : tdc_tile_1x1_kernel<ACT, 2, 2>;
     const hipError_t e = tdc_allow_lds((const void *)kernel, lds);
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || prepare_only) return e;
     hipLaunchKernelGGL(kernel, grid, dim3(256), lds, s, a);
     return hipGetLastError();
 }
@@ -881,8 +881,9 @@ bool tdc_tile_1x1_applies(const TdcDims &d)
     return d.R1 <= (d.nhwc ? 200 : 144) || (d.N > 64 && d.R1 <= 256) || d.N > 256;
 }
 
-hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipStream_t s, const float *x, const void *w, float *y, const TdcEpi &epi)
+hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipStream_t s, const float *x, const void *w, float *y, const TdcEpi &epi, bool prepare_only)
 {
+    if (prepare_only && !(ks == 1 && tdc_tile_1x1_applies(d))) return hipSuccess;      // nothing to set up
     TileArgs a;
     a.act = x; a.w = w; a.out = y; a.epi = epi;
     a.C = d.C; a.HW = d.H * d.W; a.M = d.N; a.P = d.Ho * d.Wo; a.Ptot = d.B * a.P;
@@ -906,7 +907,7 @@ hipError_t tdc_launch_tile_dense(const TdcDims &d, int tm, int tp, int ks, hipSt
         a.per = tile_1x1_share(a.n_pt, a.n_mt, mb, tile_1x1_lds_bytes(a.S, parts, d.nhwc));
         a.n_mg = (a.n_mt + a.per - 1) / a.per;
         a.div_inner = tdc_make_div((unsigned)a.n_mg);
-        return d.nhwc ? launch_1x1<TDC_ACT_NHWC>(a, mb, parts, s) : launch_1x1<TDC_ACT_NCHW>(a, mb, parts, s);
+        return d.nhwc ? launch_1x1<TDC_ACT_NHWC>(a, mb, parts, s, prepare_only) : launch_1x1<TDC_ACT_NCHW>(a, mb, parts, s, prepare_only);
     }
     if (d.nhwc) return conv ? launch_act<TDC_ACT_NHWC, true>(a, tm, tp, ks, s) : launch_act<TDC_ACT_NHWC, false>(a, tm, tp, ks, s);
     return conv ? launch_act<TDC_ACT_NCHW, true>(a, tm, tp, ks, s) : launch_act<TDC_ACT_NCHW, false>(a, tm, tp, ks, s);

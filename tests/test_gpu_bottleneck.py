@@ -113,6 +113,42 @@ def test_large_lds_kernels_under_graph_capture(orc, variant):
         conv.close()
 
 
+@pytest.mark.parametrize("nhwc", [False, True], ids=["nchw", "nhwc"])
+def test_a_1x1_layer_in_lds_is_captured_as_its_plan_s_first_launch(orc, nhwc):
+    """256 channels of 64 pixels in two parts are 70 KB of dynamic LDS, which the plan asks for and not its first call."""
+    import torch
+    from paper_2211_03715_amd.layer import DenseConv2d
+    from paper_2211_03715_amd.workloads import Layer, make_dense_inputs
+    layer = Layer(16, 256, 264, 14, 14, 1, 1, 1, 1, 0)
+    dev = torch.device("cuda:0")
+    inputs = [make_dense_inputs(layer, seed) for seed in (33, 34)]
+    wants = [orc.conv_dense_with(orc.Shape(**layer.asdict()), i["x"], inputs[0]["W"].astype(np.float64))[0] for i in inputs]
+    put = lambda a: torch.from_numpy(np.ascontiguousarray(a.transpose(0, 2, 3, 1) if nhwc else a)).to(dev)
+    print("[case] graph capture, 1x1 in LDS", layer.name(), "nhwc" if nhwc else "nchw", flush=True)
+    conv = DenseConv2d(layer, 0, B.make_tuning(tile_h=128, tile_w=64, waves=(4,) * 3), B.LAYOUT_NHWC if nhwc else B.LAYOUT_NCHW)
+    try:
+        W = torch.from_numpy(inputs[0]["W"]).to(dev)
+        conv.pack(W)
+        x, y = torch.empty_like(put(inputs[0]["x"])), torch.full(conv.out_shape(), float("nan"), device=dev)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            conv.bind(x, y)()
+        for rep in range(3):
+            for i, want in zip(inputs, wants):
+                x.copy_(put(i["x"]))
+                y.fill_(float("nan"))
+                torch.cuda.synchronize()
+                graph.replay()
+                torch.cuda.synchronize()
+                got = y.cpu().numpy()
+                assert_parity(got.transpose(0, 3, 1, 2) if nhwc else got, want, "replay %d [%s]" % (rep, conv.describe()))
+                eager = conv(x)
+                torch.cuda.synchronize()
+                assert torch.equal(eager, y)
+    finally:
+        conv.close()
+
+
 @pytest.mark.parametrize("layout", [B.LAYOUT_NCHW, B.LAYOUT_NHWC], ids=["nchw", "nhwc"])
 @pytest.mark.parametrize("shape", [(1, 32, 16, 14, 14, 8, 8, 2, 64), (2, 24, 12, 9, 11, 8, 12, 2, 48), (1, 16, 16, 10, 7, 8, 8, 1, 64),
                                    (1, 256, 128, 56, 56, 32, 32, 2, 512)],
