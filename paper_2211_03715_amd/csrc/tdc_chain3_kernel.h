@@ -55,10 +55,18 @@ namespace {
 
 constexpr int NP = 2;      // parts
 
-// LDS: the largest magnitude each wavefront has loaded first and whether it wants the tile in fp32, then z1.
+// LDS: the largest magnitude each wavefront has loaded first (later what it has seen) and whether it wants the tile in fp32, then z1.
+enum { CHAIN3_SMALL = 1, CHAIN3_NO_NUMBER = 2, CHAIN3_NAN = 1, CHAIN3_TOO_LARGE = 2 };
 struct Chain3Shared {
     unsigned first[TDC_CHAIN3_WAVES], bad[TDC_CHAIN3_WAVES];
 };
+
+// x is multiplied by 2 to this
+__device__ __forceinline__ int chain3_x_exp(const Chain3Shared &sh)
+{
+    const tdc_u4 first = *reinterpret_cast<const tdc_u4 *>(sh.first);
+    return tdc_scale_of((unsigned)__builtin_amdgcn_readfirstlane((int)max(max(first[0], first[1]), max(first[2], first[3]))), TDC_X_TARGET, TDC_X_OTHER);
+}
 
 // Stage 1 for the workgroup.  RUNS: a lane owns runs of four consecutive pixels (see TdcStage1R), a unit is 16 runs.
 template <int LAY, int MB1, bool DEEP>
@@ -244,8 +252,7 @@ struct Chain3Stage1 {
         for (int i = 0; i < NR; ++i) m = tdc_largest_number(m, x[0][i]);
         sh.first[wave] = tdc_wave_max(m);
         __syncthreads();
-        const tdc_u4 first = *reinterpret_cast<const tdc_u4 *>(sh.first);
-        x_exp = tdc_scale_of((unsigned)__builtin_amdgcn_readfirstlane((int)max(max(first[0], first[1]), max(first[2], first[3]))), TDC_X_TARGET, TDC_X_OTHER);
+        x_exp = chain3_x_exp(sh);
         const int total = wave < n_units ? (n_units - wave + TDC_CHAIN3_WAVES - 1) / TDC_CHAIN3_WAVES * a.S1 : 0;
         int unit = wave, step = 0;
         const auto clear = [&]() {
@@ -415,6 +422,53 @@ struct Chain3Out {
     }
 };
 
+// Whether the NaNs among a tile's outputs are x's: there is one, all weights are numbers and in parts, and nothing that is no NaN overflowed
+// in x or z1.  The outputs then are what fp32 gives.  For the workgroup.
+template <int LAY>
+__device__ __forceinline__ bool chain3_nan_explained(const TdcChain3Args &a, Chain3Shared &sh, const tdc_u2 *__restrict__ z1s, int lane, int wave)
+{
+    constexpr bool NHWC = LAY == TDC_LAY_NHWC;
+    if (*reinterpret_cast<const int *>(static_cast<const char *>(a.uin) + a.uin_bytes)) return false;
+    const int g = lane >> 4, l16 = lane & 15;
+    const Chain3Tile at(a);
+    const int HW = a.H * a.W;
+    const tdc_rsrc xrs = tdc_make_rsrc(a.x + (size_t)at.b * a.C * HW, (unsigned)a.C * HW * 4u);
+    TdcFactors xs;
+#pragma unroll 1
+    for (int qb = wave; qb < a.QB; qb += TDC_CHAIN3_WAVES) {
+        const int q = 16 * qb + l16, qh = tdc_div(q, a.div_QW);
+        const int h = at.i0 * a.stride - a.pad + qh, w = at.j0 * a.stride - a.pad + q - qh * a.QW;
+        const bool in = q < a.Q && (unsigned)h < (unsigned)a.H && (unsigned)w < (unsigned)a.W;
+        const int pix = in ? h * a.W + w : 0;
+#pragma unroll 4
+        for (int kc = 0; kc < a.C; kc += 16) {
+            const int c = kc + 4 * g;
+            tdc_f4 x;
+            if (NHWC) {
+                x = tdc_buf_load4(xrs, in && c < a.C ? (unsigned)(pix * a.C + c) * 4u : TDC_OOB);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) x[j] = tdc_buf_load(xrs, in && c + j < a.C ? (unsigned)((c + j) * HW + pix) * 4u : TDC_OOB);
+            }
+            xs.see(x);
+        }
+    }
+    bool large = ldexpf(xs.largest, chain3_x_exp(sh)) > TDC_FP16_MAX;
+#pragma unroll 1
+    for (int plane = wave; plane < 4 * a.NB1; plane += TDC_CHAIN3_WAVES)
+#pragma unroll 1
+        for (int q = lane; q < a.Q; q += 64) {
+            const tdc_u2 u = z1s[plane * a.pitch1 + q];          // four first parts: an infinity is a value too large
+#pragma unroll
+            for (int j = 0; j < 4; ++j) large |= (u[j >> 1] >> 16 * (j & 1) & 0x7fffu) == 0x7c00u;
+        }
+    __syncthreads();                                             // the scale is read
+    sh.first[wave] = (tdc_any_lane(xs.nan) ? CHAIN3_NAN : 0) | (tdc_any_lane(large) ? CHAIN3_TOO_LARGE : 0);
+    __syncthreads();
+    const tdc_u4 all = *reinterpret_cast<const tdc_u4 *>(sh.first);
+    return __builtin_amdgcn_readfirstlane((int)(all[0] | all[1] | all[2] | all[3])) == CHAIN3_NAN;
+}
+
 // The tile once more in fp32, one load at a time, z1 in fp32 where its parts were (see tdc_split.h).
 template <int NB2, int PB, int LAY>
 __device__ __forceinline__ void chain3_tile_fp32(const TdcChain3Args &a, tdc_u2 *__restrict__ z1s, int lane, int wave)
@@ -561,7 +615,8 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
     tdc_u2 *__restrict__ z1s = reinterpret_cast<tdc_u2 *>(chain3_lds + sizeof(Chain3Shared) / 16);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    bool bad;                                                    // a pixel of too small factors, a channel of too small outputs, or one that is no number
+    bool bad;                                                    // a pixel of too small factors, or a channel of too small outputs
+    bool no_number = false;                                      // an output
     int x_exp;
     const Chain3Tile at(args);
     {
@@ -766,21 +821,21 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
         } else {
             fetch(slice, u0);
         }
-        float top = 0.f;                                         // largest magnitude of z2; a NaN above all
+        float top = 0.f;                                         // largest magnitude of z2 that is no NaN
         unsigned smallest = ~0u;                                 // of the pixels' largest z2 values the smallest
         unsigned lit = 0;                                        // whether z2 is not all zero at the pixels of this lane's outputs
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) {
             float m = 0.f;
 #pragma unroll
-            for (int mb = 0; mb < NB2; ++mb) m = tdc_largest(m, z2[mb][pb]);
+            for (int mb = 0; mb < NB2; ++mb) m = tdc_max3_abs(tdc_max3_abs(m, z2[mb][pb][0], z2[mb][pb][1]), z2[mb][pb][2], z2[mb][pb][3]);
             m = tdc_pixel_max(m);
             top = __builtin_elementwise_maximum(top, m);
             smallest = tdc_smallest(smallest, m);
             lit |= NHWC ? m != 0.f : (unsigned)__builtin_amdgcn_ballot_w64(m != 0.f) >> 4 * (lane >> 4) & 15u;
         }
         const int z2_exp = tdc_scale_of(tdc_wave_max(top), TDC_Z2_TARGET, 0);
-        bad |= live && tdc_is_small(smallest, tdc_exp2i(max(TDC_LOWEST - z2_exp, -126)));
+        bad |= tdc_is_small(smallest, tdc_exp2i(max(TDC_LOWEST - z2_exp, -126)));
         const int y_exp = a.z1_exp - z2_exp - x_exp;            // y is 2^(y_exp - exponent of the channel) times its sum
         tdc_op<NP> zb[S3][PB];
         {
@@ -888,14 +943,19 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
         };
         if (a.epi.bias || a.epi.residual || a.epi.relu) stage3(std::true_type{});
         else stage3(std::false_type{});
-        bad |= live && (!tdc_finite(largest) || least < lost);
+        bad |= least < lost;
+        no_number |= !tdc_finite(largest);
     }
     // One wavefront's trouble is the tile's: z1 is everybody's.
-    sh.bad[wave] = tdc_any_lane(bad);
+    sh.bad[wave] = (tdc_any_lane(bad) ? CHAIN3_SMALL : 0) | (tdc_any_lane(no_number) ? CHAIN3_NO_NUMBER : 0);
     __syncthreads();
     const tdc_u4 all = *reinterpret_cast<const tdc_u4 *>(sh.bad);
-    if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)(all[0] | all[1] | all[2] | all[3])), 0))
-        chain3_tile_fp32<NB2, PB, LAY>(tdc_args_again<TdcChain3Args>(), z1s, lane, wave);
+    const unsigned any = (unsigned)__builtin_amdgcn_readfirstlane((int)(all[0] | all[1] | all[2] | all[3]));
+    if (__builtin_expect(any, 0)) {
+        const TdcChain3Args &cold = tdc_args_again<TdcChain3Args>();
+        if (any == CHAIN3_NO_NUMBER && chain3_nan_explained<LAY>(cold, sh, z1s, lane, wave)) return;
+        chain3_tile_fp32<NB2, PB, LAY>(cold, z1s, lane, wave);
+    }
 }
 
 }  // namespace

@@ -65,7 +65,7 @@ constexpr int TDC_SPLIT_CHUNKS = 16;
 inline size_t tdc_split_bytes(int parts, int m_blocks, int k_groups) { return (size_t)m_blocks * ((k_groups + 1) / 2) * 1024 * parts; }
 inline size_t tdc_split_alloc_bytes(int parts, int m_blocks, int k_groups)
 {
-    return tdc_split_bytes(parts, m_blocks, k_groups) + (size_t)m_blocks * (64 + (size_t)k_groups * 1024 + 192 * TDC_SPLIT_CHUNKS);
+    return tdc_split_bytes(parts, m_blocks, k_groups) + (size_t)m_blocks * (64 + (size_t)k_groups * 1024 + 256 * TDC_SPLIT_CHUNKS);
 }
 // Parts a weight is split into.  Two fp16 parts are the more accurate form from some 70 terms to a sum on (tdc_split.h); the three sums
 // of a Tucker layer add up to that from 208 on: squared errors of 78 + 0.39 n against 2.1 n - 40 (in 1e-16, n terms).  Below, CHAIN

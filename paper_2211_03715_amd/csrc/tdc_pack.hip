@@ -64,8 +64,8 @@ struct SplitTensor {
     unsigned *parts;
     int *exponents;
     float *raw;
-    int *top, *low, *most;                 // of each channel's weights the largest and smallest exponent, and the largest before ranks
-                                           // are scaled, TDC_SPLIT_CHUNKS shares
+    int *top, *low, *most, *odd;           // of each channel's weights the largest and smallest exponent, the largest before ranks
+                                           // are scaled, and whether one is no number, TDC_SPLIT_CHUNKS shares
     bool last;                             // U_out, W
     // The core: U_in [rows_before][rows], whose columns are scaled each by its own power of two.  A row is scaled by the inverse,
     // so that z1 holds all ranks at one size, and what size the ranks have between the two factors makes no difference.
@@ -135,29 +135,33 @@ __device__ __forceinline__ int split_scale_before(const SplitTensor &t, int m)
 // the ranges of 64 output channels' weights among one share of the rows
 __device__ __forceinline__ void split_range(const SplitTensor &t, int block)
 {
-    __shared__ int top4[256], low4[256], most4[256];
+    __shared__ int top4[256], low4[256], most4[256], odd4[256];
     const int share = block % TDC_SPLIT_CHUNKS, m = block / TDC_SPLIT_CHUNKS * 64 + (threadIdx.x & 63);
-    int top = -SPLIT_NONE, low = SPLIT_NONE, most = -SPLIT_NONE;
+    int top = -SPLIT_NONE, low = SPLIT_NONE, most = -SPLIT_NONE, odd = 0;
     for (int row = share + TDC_SPLIT_CHUNKS * (threadIdx.x >> 6); row < t.rows; row += 4 * TDC_SPLIT_CHUNKS) {
         const int undo = t.before ? split_scale_before(t, row) : 0;
         const float *__restrict__ w = t.w + ((size_t)row * t.cols + m) * t.KK;
-        for (int i = 0; i < (m < t.cols ? t.KK : 0); ++i)
+        for (int i = 0; i < (m < t.cols ? t.KK : 0); ++i) {
+            odd |= !(fabsf(w[i]) < INFINITY);
             if (split_counts(w[i])) {
                 const int e = ilogbf(w[i]);
                 top = max(top, e - undo);
                 low = min(low, e - undo);
                 most = max(most, e);
             }
+        }
     }
     top4[threadIdx.x] = top;
     low4[threadIdx.x] = low;
     most4[threadIdx.x] = most;
+    odd4[threadIdx.x] = odd;
     __syncthreads();
     if (threadIdx.x < 64 && m < 16 * t.NBm) {
         const auto max4 = [](const int *p) { return max(max(p[0], p[64]), max(p[128], p[192])); };
         const int at = share * 16 * t.NBm + m, *q = low4 + threadIdx.x;
         t.top[at] = max4(top4 + threadIdx.x);
         t.most[at] = max4(most4 + threadIdx.x);
+        t.odd[at] = max4(odd4 + threadIdx.x);
         t.low[at] = min(min(q[0], q[64]), min(q[128], q[192]));
     }
 }
@@ -169,7 +173,7 @@ struct SplitArgs {
 __global__ void split_range_kernel(SplitArgs a) { if ((int)blockIdx.x < (a.t[blockIdx.y].NBm + 3) / 4 * TDC_SPLIT_CHUNKS) split_range(a.t[blockIdx.y], blockIdx.x); }
 
 // One thread per pair of components: e = ((mb*S + step)*64 + lane)*4 + pair, one workgroup per block and step.  Exponents: W: the
-// channel's; U_in: none, its scales are the core's rows'; core: what takes a channel to the scale of the largest; U_out: the
+// channel's; U_in: none, its scales are the core's rows', but in the first place whether all weights of the layer are numbers and in parts; core: what takes a channel to the scale of the largest; U_out: the
 // channel's and that scale together.
 template <int NP>
 __global__ void split_pack_kernel(SplitArgs a)
@@ -207,8 +211,21 @@ __global__ void split_pack_kernel(SplitArgs a)
         raw[0] = v[0];
         raw[1] = v[1];
     }
-    if (step == 0 && pair == 0 && lane < 16) 
+    if (a.n == 3 && blockIdx.y == 0) {
+        if (blk) return;
+        int odd = 0;
+        for (int i = 0; i < 3; ++i) {
+            int o;
+            bool w;
+            split_whole(a.t[i], tdc_lowest_weight(NP), o, w);
+            odd |= w;
+            for (int j = threadIdx.x; j < 16 * a.t[i].NBm * TDC_SPLIT_CHUNKS; j += 256) odd |= a.t[i].odd[j];
+        }
+        odd = split_block_max(odd);
+        if (threadIdx.x == 0) t.exponents[0] = odd;
+    } else if (step == 0 && pair == 0 && lane < 16) {
         t.exponents[m] = wide ? TDC_WIDE : channel == -SPLIT_NONE ? (t.last ? TDC_EMPTY : 0) : t.last ? scale + before : split_scale(top) - scale;
+    }
 }
 
 __global__ void pack_uout_kernel(TdcDims d, const float *__restrict__ U_out, float *__restrict__ out, size_t total)
@@ -283,6 +300,7 @@ static SplitTensor split_tensor(int parts, const float *w, int rows, int cols, i
     t.top = (int *)(t.raw + (size_t)t.NBm * t.KG * 256);
     t.low = t.top + 16 * t.NBm * TDC_SPLIT_CHUNKS;
     t.most = t.low + 16 * t.NBm * TDC_SPLIT_CHUNKS;
+    t.odd = t.most + 16 * t.NBm * TDC_SPLIT_CHUNKS;
     t.last = last;
     t.before = nullptr;
     t.rows_before = 0;

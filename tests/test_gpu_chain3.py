@@ -333,3 +333,69 @@ def test_a_plan_takes_no_lds_for_weights_that_its_kernel_does_not_share():
             assert "lds=%dB" % (32 + 64 * 2 * 16 * 33 + extra) in B.tdc_plan_describe(plan)
         finally:
             B.tdc_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
+@pytest.mark.parametrize("layer,tile", ((Layer(64, 128, 128, 28, 28, 32, 32, 3, 1, 1), (4, 28)), (Layer(32, 256, 256, 14, 14, 64, 64, 3, 1, 1), (2, 14))),
+                         ids=lambda v: v.name() if isinstance(v, Layer) else "")
+def test_nan_inputs_cost_a_second_pass_at_most(layer, tile, nhwc):
+    """Every value NaN, or one pixel in 64: the outputs they reach are NaN without being computed again, the others keep theirs.
+    Finding that out reads x once more, unpipelined: 1.5 to 2.5 times the usual time, 4 allowed; the tiles in fp32 would be 4 to 5."""
+    import torch
+    from paper_2211_03715_amd.layer import TuckerConv2d
+    dev = torch.device("cuda:0")
+    inputs = make_inputs(layer, 97)
+    x = torch.from_numpy(np.ascontiguousarray(inputs["x"].transpose(0, 2, 3, 1) if nhwc else inputs["x"])).to(dev)
+    some = x.clone()
+    (some[:, ::8, ::8, 5] if nhwc else some[:, 5, ::8, ::8]).fill_(float("nan"))
+    t = B.make_tuning(variant=B.VARIANT_CHAIN, tile_h=tile[0], tile_w=tile[1], waves=(4, 4, 4), mb=(2, 3, 1), pb=(2,) * 3)
+    conv = TuckerConv2d(layer, 0, t, B.LAYOUT_NHWC if nhwc else B.LAYOUT_NCHW)
+    try:
+        w = [torch.from_numpy(inputs[k]).to(dev) for k in ("U_in", "core", "U_out")]
+        conv.pack(*w)
+        y = torch.empty(conv.out_shape(), device=dev)
+        gpu_us(conv.bind(x, y))
+        usual, clean = gpu_us(conv.bind(x, y)), y.clone()
+        for what, bad in (("every value", torch.full_like(x, float("nan"))), ("some pixels", some)):
+            took = gpu_us(conv.bind(bad, y))
+            print("[case] chain3, NaN in", what, layer.name(), "nhwc" if nhwc else "nchw", "%.1f us, usually %.1f" % (took, usual), flush=True)
+            assert took <= 4 * usual
+            nan = torch.isnan(y)
+            assert nan.all() if bad is not some else nan.any()
+            assert bad is not some or (y[~nan] - clean[~nan]).norm() <= 1e-6 * clean[~nan].norm()
+    finally:
+        conv.close()
+
+
+@pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
+@pytest.mark.parametrize("layer,tile", FP16_LAYERS, ids=lambda v: v.name() if isinstance(v, Layer) else "")
+@pytest.mark.parametrize("what", ("beyond_fp16", "late_channels", "overflowing_z1", "wide_weights", "infinite_weight", "nan_weight", "alone"))
+def test_a_nan_explains_no_outputs_but_its_own(orc, what, layer, tile, nhwc):
+    """One NaN beside finite values that fp16 does not hold at the scale the workgroup takes, beside z1 that it does not hold, and with weights
+    that are kept out of the parts or are no numbers."""
+    inputs = {k: v.copy() for k, v in make_inputs(layer, 98).items()}
+    if what == "beyond_fp16":
+        inputs["x"][0, :, 0, 3:6] *= np.float32(2.0 ** 14)
+    elif what == "late_channels":
+        inputs["x"][:, -8:] *= np.float32(2.0 ** 14)
+    elif what == "overflowing_z1":
+        inputs["x"][0, :, 2:4, 3:5] = 300.0
+        inputs["U_in"][...] = 1.0
+        for k in ("core", "U_out"):                      # z1's channels are all alike: no differences of theirs
+            inputs[k] = np.abs(inputs[k])
+    elif what == "wide_weights":
+        inputs["U_out"][:2, 7] = 2.0 ** 12, 2.0 ** -20
+    elif what == "infinite_weight":
+        inputs["U_out"][1, 2] = np.inf
+    elif what == "nan_weight":
+        inputs["U_out"][1, 2] = np.nan
+    inputs["x"][0, 3, 0, 0] = np.nan
+    t = B.make_tuning(variant=B.VARIANT_CHAIN, tile_h=tile[0], tile_w=tile[1], waves=(4, 4, 4), mb=(1 if tile == (12, 12) else 2, 3, 1), pb=(2,) * 3)
+    with np.errstate(invalid="ignore", over="ignore"):
+        want, _ = orc.conv_factored(orc.Shape(**layer.asdict()), **inputs)
+    print("[case] chain3, one NaN,", what, layer.name(), "nhwc" if nhwc else "nchw", flush=True)
+    got = _run(layer, inputs, t, nhwc)
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
+    with np.errstate(invalid="ignore"):
+        err, ref = np.where(np.isfinite(want), got - want, 0), np.where(np.isfinite(want), want, 0)
+    assert (np.linalg.norm(err, axis=(2, 3)) <= 1.5e-6 * np.linalg.norm(ref, axis=(2, 3))).all()      # an image's channel
