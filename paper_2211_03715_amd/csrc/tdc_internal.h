@@ -60,7 +60,7 @@ hipError_t tdc_launch_pack_merged(const TdcDims &d, hipStream_t s, const float *
 // being two k-groups, component j = what the fp32 layout has as component j%4 of k-group 2*step + j/4 (zero past the last one).
 // Every output channel is scaled by its own power of two, which for U_in's the core's rows undo.  Behind the parts: an exponent per channel (how a kernel undoes the
 // scaling, see tdc_pack.hip), the same weights in fp32 in the layout above, for what the parts cannot carry, and the ranges of
-// TDC_SPLIT_CHUNKS shares of the contraction, which the scaling comes from.
+// TDC_SPLIT_CHUNKS shares of the contraction, from which the scaling comes.
 constexpr int TDC_SPLIT_CHUNKS = 16;
 inline size_t tdc_split_bytes(int parts, int m_blocks, int k_groups) { return (size_t)m_blocks * ((k_groups + 1) / 2) * 1024 * parts; }
 inline size_t tdc_split_alloc_bytes(int parts, int m_blocks, int k_groups)

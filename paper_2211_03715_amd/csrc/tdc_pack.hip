@@ -49,13 +49,10 @@ __global__ void pack_core_kernel(TdcDims d, const float *__restrict__ core, floa
 
 // ---- parts (tdc_split.h)
 //
-// Output channel m of a weight tensor is scaled by 2^scale[m], its largest weight to 2^13 .. 2^14.  In the exponents behind the
-// parts a kernel finds
-//   U_in, core   lowest - scale[m], where lowest = the smallest scale of the tensor (that of its largest weight): what takes the
-//                scaled sums of all channels to the common scale 2^lowest;
-//   U_out, W     scale[n], for U_out plus the other two tensors' lowest: what has to be undone at the end.
-// A tensor with weights from 2^10 on beside others that the scaling takes below 2^-13 (three parts: 2^-1), where parts lose bits, is kept in fp32
-// alone: its parts are NaN.  Smaller weights beside ordinary ones only lose what is below the rounding of their channel's sums.
+// Output channel m of a weight tensor is scaled by 2^scale[m], its largest weight to 2^13 .. 2^14; rows of the core by the inverse of U_in's
+// scales before that.  A channel that has weights from 2^10 on beside others that the scaling takes below 2^-13 (three parts: 2^-1), where
+// parts lose bits, is kept in fp32 alone: its parts are NaN.  Smaller weights beside ordinary ones only lose what is below the
+// rounding of their channel's sums, or else those are watched (tdc_split.h).
 
 // One weight tensor w[row][col][tap] -- the contraction runs over rows and taps -- and where things go.
 struct SplitTensor {
@@ -74,18 +71,6 @@ struct SplitTensor {
 };
 constexpr int SPLIT_NONE = 100000, SPLIT_TOP = 13;
 
-__device__ __forceinline__ int split_top(const SplitTensor &t, int m)
-{
-    int top = -SPLIT_NONE;
-    for (int i = 0; i < TDC_SPLIT_CHUNKS; ++i) top = max(top, t.top[i * 16 * t.NBm + m]);
-    return top;
-}
-__device__ __forceinline__ int split_low(const SplitTensor &t, int m)
-{
-    int low = SPLIT_NONE;
-    for (int i = 0; i < TDC_SPLIT_CHUNKS; ++i) low = min(low, t.low[i * 16 * t.NBm + m]);
-    return low;
-}
 // channels without a finite weight that is not zero take 0
 __device__ __forceinline__ int split_scale(int top) { return top == -SPLIT_NONE ? 0 : SPLIT_TOP - top; }
 __device__ __forceinline__ bool split_counts(float w) { return w != 0.f && fabsf(w) < INFINITY; }
@@ -103,21 +88,11 @@ __device__ __forceinline__ int split_block_max(int v)
     }
     return part[0];
 }
-// the exponent of the largest weight of a tensor, and whether it is too wide for parts that keep their bits from 2^lowest on
-__device__ __forceinline__ void split_whole(const SplitTensor &t, int lowest, int &top, bool &wide)
+// the largest of a channel's shares, by the 16 lanes that have one each
+__device__ __forceinline__ int split_share_max(int v)
 {
-    int widest = -SPLIT_NONE, most = -SPLIT_NONE;
-    top = -SPLIT_NONE;
-    for (int m = threadIdx.x; m < t.cols; m += 256) {
-        const int h = split_top(t, m);
-        top = max(top, h);
-        for (int i = 0; i < TDC_SPLIT_CHUNKS; ++i) most = max(most, t.most[i * 16 * t.NBm + m]);
-        if (h != -SPLIT_NONE) widest = max(widest, h - split_low(t, m));
-    }
-    top = split_block_max(top);
-    most = split_block_max(most);
-    widest = split_block_max(widest);
-    wide = most >= 10 && widest > SPLIT_TOP - lowest;
+    for (int s = 8; s; s >>= 1) v = max(v, __shfl_xor(v, s));
+    return v;
 }
 
 // the scale of column m of the tensor before, by a wavefront
@@ -170,38 +145,54 @@ struct SplitArgs {
     SplitTensor t[3];
     int n;                                 // 3: U_in, core, U_out; 1: W
 };
-__global__ void split_range_kernel(SplitArgs a) { if ((int)blockIdx.x < (a.t[blockIdx.y].NBm + 3) / 4 * TDC_SPLIT_CHUNKS) split_range(a.t[blockIdx.y], blockIdx.x); }
+__global__ void split_range_kernel(SplitArgs a)
+{
+    if (a.n == 3 && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) a.t[0].exponents[0] = 0;
+    if ((int)blockIdx.x < (a.t[blockIdx.y].NBm + 3) / 4 * TDC_SPLIT_CHUNKS) split_range(a.t[blockIdx.y], blockIdx.x);
+}
 
 // One thread per pair of components: e = ((mb*S + step)*64 + lane)*4 + pair, one workgroup per block and step.  Exponents: W: the
-// channel's; U_in: none, its scales are the core's rows', but in the first place whether all weights of the layer are numbers and in parts; core: what takes a channel to the scale of the largest; U_out: the
-// channel's and that scale together.
+// channel's; U_in: none, its scales are the core's rows', but in the first place whether a weight of the layer is no number or not in
+// parts; core: what takes a channel to the scale of the largest; U_out: the channel's and that scale together.
 template <int NP>
 __global__ void split_pack_kernel(SplitArgs a)
 {
+    static_assert(TDC_SPLIT_CHUNKS == 16, "a share to each of 16 lanes");
     const SplitTensor &t = a.t[blockIdx.y];
     const int S = (t.KG + 1) / 2;
     if ((int)blockIdx.x >= t.NBm * S) return;
-    int top;
-    bool wide;
-    split_whole(t, tdc_lowest_weight(NP), top, wide);
-    int before = 0;
-    if (t.last && a.n == 3) {
-        int o;
-        bool w;
-        split_whole(a.t[1], tdc_lowest_weight(NP), o, w);
-        before = split_scale(o);
-    }
     const int pair = (int)(threadIdx.x & 3), lane = (int)(threadIdx.x >> 2);
     const size_t blk = blockIdx.x;
     const int step = (int)(blk % S), mb = (int)(blk / S);
+    __shared__ int scales[16], wides[16], undo[2][16];
+    {   // 16 channels, 16 shares of each
+        const int share = threadIdx.x & 15, c = threadIdx.x >> 4, at = share * 16 * t.NBm + 16 * mb + c;
+        const int top = split_share_max(t.top[at]), low = -split_share_max(-t.low[at]), most = split_share_max(t.most[at]), odd = split_share_max(t.odd[at]);
+        const bool empty = top == -SPLIT_NONE, wide = !empty && most >= 10 && top - low > SPLIT_TOP - tdc_lowest_weight(NP);
+        if (share == 0) {
+            scales[c] = empty ? SPLIT_NONE : split_scale(top);
+            wides[c] = wide;
+            if (a.n == 3 && step == 0 && (wide || odd)) atomicOr(a.t[0].exponents, 1);
+        }
+        if (t.before)
+            for (int h = 0; h < 2; ++h) {
+                const int kg = 2 * step + h, row = 16 * (kg % t.NBk) + c;
+                const int v = split_share_max(kg < t.KG && row < t.rows ? a.t[0].top[share * 16 * a.t[0].NBm + row] : -SPLIT_NONE);
+                if (share == 0) undo[h][c] = split_scale(v);
+            }
+    }
+    __syncthreads();
     const int kg = 2 * step + (pair >> 1), m = 16 * mb + (lane & 15), k = 4 * (lane >> 4) + 2 * (pair & 1);
-    const int channel = split_top(t, m), scale = split_scale(channel);
+    const int scale = scales[lane & 15];
+    const bool wide = wides[lane & 15], empty = scale == SPLIT_NONE;
     const int tap = kg / t.NBk, row = 16 * (kg - tap * t.NBk) + k;
     float v[2], scaled[2];
     for (int i = 0; i < 2; ++i) {
         const bool there = kg < t.KG && row + i < t.rows;
         v[i] = there && m < t.cols ? t.w[((size_t)(row + i) * t.cols + m) * t.KK + tap] : 0.f;
-        scaled[i] = wide ? NAN : t.last && channel == -SPLIT_NONE && v[i] == 0.f ? (there ? ((row + i) % 2 ? 0x1p12f : 0x1p13f) : 0.f) : ldexpf(v[i], scale - (t.before && there ? split_scale(split_top(a.t[0], row + i)) : 0));
+        scaled[i] = ldexpf(v[i], (empty ? 0 : scale) - (t.before ? undo[pair >> 1][k + i] : 0));
+        if (wide) scaled[i] = NAN;
+        if (t.last && empty && v[i] == 0.f) scaled[i] = there ? ((row + i) % 2 ? 0x1p12f : 0x1p13f) : 0.f;       // see TDC_EMPTY
     }
     unsigned p[NP];
     tdc_split2<NP, tdc_lift_weights(NP)>(scaled[0], scaled[1], TdcScale(0), p);
@@ -211,20 +202,17 @@ __global__ void split_pack_kernel(SplitArgs a)
         raw[0] = v[0];
         raw[1] = v[1];
     }
-    if (a.n == 3 && blockIdx.y == 0) {
-        if (blk) return;
-        int odd = 0;
-        for (int i = 0; i < 3; ++i) {
-            int o;
-            bool w;
-            split_whole(a.t[i], tdc_lowest_weight(NP), o, w);
-            odd |= w;
-            for (int j = threadIdx.x; j < 16 * a.t[i].NBm * TDC_SPLIT_CHUNKS; j += 256) odd |= a.t[i].odd[j];
-        }
-        odd = split_block_max(odd);
-        if (threadIdx.x == 0) t.exponents[0] = odd;
-    } else if (step == 0 && pair == 0 && lane < 16) {
-        t.exponents[m] = wide ? TDC_WIDE : channel == -SPLIT_NONE ? (t.last ? TDC_EMPTY : 0) : t.last ? scale + before : split_scale(top) - scale;
+    if (step || (a.n == 3 && blockIdx.y == 0)) return;
+    int lowest = 0;                                    // the scale of the core's largest channel
+    if (a.n == 3) {
+        const SplitTensor &c = a.t[1];
+        int top = -SPLIT_NONE;
+        for (int i = threadIdx.x; i < 16 * c.NBm * TDC_SPLIT_CHUNKS; i += 256) top = max(top, c.top[i]);
+        lowest = split_scale(split_block_max(top));
+    }
+    if (threadIdx.x < 16) {
+        const int sc = scales[threadIdx.x];
+        t.exponents[16 * mb + threadIdx.x] = wides[threadIdx.x] ? TDC_WIDE : sc == SPLIT_NONE ? (t.last ? TDC_EMPTY : 0) : t.last ? sc + lowest : lowest - sc;
     }
 }
 

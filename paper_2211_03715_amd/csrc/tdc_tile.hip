@@ -117,7 +117,9 @@ __device__ __forceinline__ unsigned tile_redo(const TileArgs &a, bool small, int
             ws.see(load_w(kg, mb));
     }
     const bool odd_weights = tdc_any_lane(ws.nan || ws.largest == INFINITY);
-    const bool in_parts = reinterpret_cast<const int *>(static_cast<const char *>(a.w) + a.w_bytes)[0] != TDC_WIDE;
+    bool in_parts = true;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) in_parts &= !tdc_any_lane(mb0 + mb < a.NBm && reinterpret_cast<const int *>(static_cast<const char *>(a.w) + a.w_bytes)[16 * min(mb0 + mb, a.NBm - 1) + l16] == TDC_WIDE);
     const bool explained = in_parts && tdc_any_lane(xs.nan | ws.nan) && !tdc_any_lane(ldexpf(xs.largest, x_exp) > TDC_FP16_MAX || ws.largest == INFINITY);
     done = !(explained && !small && !(CONV && odd_weights));
     if (!done) return 0u;
