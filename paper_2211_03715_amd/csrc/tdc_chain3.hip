@@ -14,7 +14,7 @@ bool tdc_chain3_supported(const TdcDims &d, int mb1, int pb)
     if (mb1 < 1 || mb1 > 3 || mb1 > d.NB1) return false;
     // every weight array lies behind one buffer descriptor
     const size_t lim = 1ull << 31;
-    if (tdc_split_alloc_bytes(3, d.NB1, d.KG1) >= lim || tdc_split_alloc_bytes(3, d.NB2, d.K * d.K * d.NB1) >= lim || tdc_split_alloc_bytes(3, d.NB3, d.NB2) >= lim) return false;
+    if (tdc_packed3_bytes(d.NB1, d.KG1) >= lim || tdc_packed3_bytes(d.NB2, d.K * d.K * d.NB1) >= lim || tdc_packed3_bytes(d.NB3, d.NB2) >= lim) return false;
 #define TDC_X(N_, P_) if (d.NB2 == N_ && pb == P_) return true;
     TDC_CHAIN3_UNITS(TDC_X)
 #undef TDC_X

@@ -865,13 +865,14 @@ bool tdc_tile_applies(const TdcDims &d)
 {
     constexpr int tp = 64;
     const size_t img = (size_t)d.C * d.H * d.W * 4, P = (size_t)d.Ho * d.Wo;
-    const size_t w = tdc_split_alloc_bytes(3, d.NB2, d.K * d.K * d.NB1);
+    const size_t w = tdc_packed3_bytes(d.NB2, d.K * d.K * d.NB1);      // the largest of the forms, and than what lies behind any parts
     return ((tp - 1) / P + 2) * img < (1ull << 31) && w < (1ull << 31) && (size_t)d.B * P < (1ull << 31) - 1024;
 }
 
 bool tdc_tile_1x1_applies(const TdcDims &d)
 {
     const int parts = tdc_tile_parts(d);
+    if (tdc_split_bytes(parts, d.NB2, d.NB1) + (size_t)64 * d.NB2 >= 1ull << 31) return false;      // with the exponents
     if (d.K != 1 || d.stride != 1 || d.pad != 0 || !tdc_tile_applies(d) || tile_1x1_lds_bytes((d.NB1 + 1) / 2, parts, d.nhwc) > TILE_1X1_LDS) return false;
     // Timed against the tile kernels on 121 drawn layers.  NCHW pixels that allow no 16-byte stores were slower in all of 40 (64 -> 368, 80
     // against 110 us).  Three parts pay from 128 output channels and 3.3 tiles per compute unit on (56 -> 64, batch-bound: 14.5 against

@@ -129,3 +129,19 @@ def test_short_dense_contractions_with_4_byte_stores_stay_with_the_latency_kerne
     dense = lambda **kw: _auto(tuning=B.make_tuning(variant=B.VARIANT_DENSE), **dict(dict(K=1, pad=0, R1=1, R2=1), **kw)).tile_h
     assert not dense(batch=2, C=32, N=80, H=214, W=214, stride=2) and not dense(batch=5, C=26, N=104, H=63, W=63)
     assert dense(batch=5, C=26, N=104, H=64, W=64) and dense(batch=5, C=160, N=104, H=63, W=63)
+
+
+def test_dense_tiles_take_weights_up_to_2_GiB_in_three_parts():
+    """What a kernel addresses behind one descriptor is its weights in parts, six bytes each at most: up to 357 million of them.  The copy in
+    fp32 beside them has a descriptor of its own."""
+    for C, N, K, fits in ((5120, 5120, 3, True), (16384, 16384, 1, True), (20480, 18432, 1, False), (6400, 6400, 3, False)):
+        shape = B.make_shape(1, C, N, 64, 64, 1, 1, K, 1, K // 2)
+        assert (C * N * K * K * 6 < 2 ** 31) == fits
+        forced = B.make_tuning(variant=B.VARIANT_DENSE, tile_h=64, tile_w=64, waves=(4, 4, 4))
+        if fits:
+            assert B.tdc_select_tuning(shape, tuning=forced).tile_h == 64
+            assert B.tdc_select_tuning(shape, tuning=B.make_tuning(variant=B.VARIANT_DENSE)).tile_h >= 64
+        else:
+            with pytest.raises(B.TdcError):
+                B.tdc_select_tuning(shape, tuning=forced)
+            assert B.tdc_select_tuning(shape, tuning=B.make_tuning(variant=B.VARIANT_DENSE)).tile_h == 0
