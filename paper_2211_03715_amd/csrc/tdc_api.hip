@@ -191,9 +191,10 @@ void describe(tdc_plan &p)
     const tdc_tuning &t = p.tuning;
     const char *names[] = {"auto", "naive", "split", "fused"};
     if (tdc_is_chain3(t))
-        snprintf(p.desc, sizeof(p.desc), "chain bf3 tile=%dx%d in=%dx%d waves=%d units(mb1,pb)=(%d,%d) grid=%dx%d lds=%zuB model=%.1fus",
+        // "bf3" is what the whole family is called in tables and tunings; `parts` says which of its kernels runs
+        snprintf(p.desc, sizeof(p.desc), "chain bf3 tile=%dx%d in=%dx%d waves=%d units(mb1,pb)=(%d,%d) grid=%dx%d lds=%zuB parts=%s model=%.1fus",
                  t.tile_h, t.tile_w, p.geom.QH, p.geom.QW, t.waves[0], t.mb[0], t.pb[0], p.geom.tiles_x * p.geom.tiles_y, p.dims.B,
-                 p.geom.lds_bytes, p.model_us);
+                 p.geom.lds_bytes, tdc_chain3_bf3(p.dims) ? "bf16x3" : "fp16x2", p.model_us);
     else if (t.variant == TDC_VARIANT_CHAIN)
         snprintf(p.desc, sizeof(p.desc),
                  "chain tile=%dx%d in=%dx%d waves=%d units(mb1,pb)=(%d,%d) grid=%dx%d lds=%zuB%s model=%.1fus",
@@ -216,7 +217,9 @@ void describe(tdc_plan &p)
         snprintf(p.desc, sizeof(p.desc), "merged-xcd split-k(s1,s23)=(%d,%d) grid=%d model=%.1fus", t.waves[0], t.waves[1],
                  tdc_merged_xcd_grid(p.dims, t), p.model_us);
     else if (tdc_is_tile(t))
-        snprintf(p.desc, sizeof(p.desc), "dense %dx%d conv bf3 tile=%dx%d waves=%d model=%.1fus", p.dims.K, p.dims.K, t.tile_h, t.tile_w, t.waves[1], p.model_us);
+        snprintf(p.desc, sizeof(p.desc), "dense %dx%d conv bf3 tile=%dx%d waves=%d parts=%s%s model=%.1fus", p.dims.K, p.dims.K, t.tile_h, t.tile_w, t.waves[1],
+                 tdc_tile_bf3(p.dims, t.waves[1] / 4) ? "bf16x3" : tdc_tile_parts(p.dims) == 3 ? "fp16x3" : "fp16x2",
+                 t.waves[1] == 4 && tdc_tile_1x1_applies(p.dims) ? " pixels-in-lds" : "", p.model_us);
     else if (t.variant == TDC_VARIANT_DENSE)
         snprintf(p.desc, sizeof(p.desc), "dense %dx%d conv (mb,pb,waves)=(%d,%d,%d) model=%.1fus", p.dims.K, p.dims.K,
                  t.mb[1], t.pb[1], t.waves[1], p.model_us);

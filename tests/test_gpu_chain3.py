@@ -22,6 +22,12 @@ CASES = [
     (Layer(40, 64, 96, 28, 28, 20, 33, 3, 2, 1), ((7, 14), (14, 12))),   # runs, stride 2
     (Layer(40, 20, 24, 12, 12, 16, 16, 3, 1, 1), ((12, 12), (5, 8))),    # runs, tiles past the last row and column
     (Layer(5, 8, 36, 32, 36, 50, 60, 1, 1, 0), ((4, 32), (8, 8))),       # runs, 1x1, C below one group
+    # sums long enough for two fp16 parts, in runs: one and two z2 blocks (weights shared through LDS), five (not shared), C no
+    # multiple of 32, tiles of five and more pixel blocks that end past the last row and column
+    (Layer(40, 72, 24, 12, 12, 40, 16, 3, 1, 1), ((12, 12), (10, 8))),
+    (Layer(40, 100, 36, 12, 12, 20, 32, 3, 1, 1), ((10, 8), (5, 12))),
+    (Layer(40, 44, 24, 12, 12, 40, 80, 3, 1, 1), ((10, 8),)),
+    (Layer(20, 104, 20, 32, 36, 24, 28, 3, 2, 1), ((10, 12),)),
 ]
 
 
@@ -33,6 +39,8 @@ def _run(layer, inputs, tuning, nhwc, bias=None, residual=None, offset=0, bf3=Tr
     conv = TuckerConv2d(layer, 0, tuning, layout=B.LAYOUT_NHWC if nhwc else B.LAYOUT_NCHW)
     try:
         assert ("bf3" in conv.describe()) == bf3, conv.describe()
+        fp16 = layer.C + layer.K ** 2 * layer.R1 + layer.R2 >= 208
+        assert not bf3 or ("parts=fp16x2" if fp16 else "parts=bf16x3") in conv.describe(), conv.describe()
         w = [torch.from_numpy(inputs[k]).to(dev) for k in ("U_in", "core", "U_out")]
         conv.pack(*w)
         shape = conv.out_shape()
@@ -71,7 +79,7 @@ def test_chain3(orc, layer, tiles, nhwc):
             got = _run(layer, inputs, t, nhwc)
             assert_parity(got, want, "%s tile %dx%d units %d,%d" % (layer.name(), th, tw, mb1, pb))
             # three chained sums of at most 600 terms: fp32 multiply-adds show up to 1e-6, the split products no more; two
-            # parts instead of three would show 5e-6 in each
+            # bf16 parts would show 5e-6 in each
             assert np.linalg.norm(got - want) <= 1.5e-6 * max(np.linalg.norm(want), 1e-30)
         # 16 bytes at a time where rows and tile allow it, then y and then the shortcut four bytes at a time
         for offset, r_offset in ((0, 0),) if nhwc else ((0, 0), (1, 0), (0, 1)):
@@ -153,7 +161,10 @@ EXTREMES = (_masked_x, _infinite_x, _large_U_in, _large_core, _large_U_out, _inf
 @pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
 @pytest.mark.parametrize("layer,tiles", ((Layer(2, 32, 48, 12, 12, 32, 16, 3, 1, 1), ((12, 12), (4, 4))),
                                          (Layer(40, 20, 24, 12, 12, 16, 33, 3, 2, 1), ((6, 6), (5, 4))),
-                                         (Layer(40, 20, 24, 12, 12, 40, 80, 1, 1, 0), ((12, 12), (5, 8)))),
+                                         (Layer(40, 20, 24, 12, 12, 40, 80, 1, 1, 0), ((12, 12), (5, 8))),
+                                         # two fp16 parts, in runs: two z2 blocks, and four
+                                         (Layer(40, 72, 24, 12, 12, 40, 20, 3, 1, 1), ((12, 12), (10, 8))),
+                                         (Layer(80, 160, 24, 12, 12, 40, 60, 1, 1, 0), ((8, 12),))),
                          ids=lambda v: v.name() if isinstance(v, Layer) else "")
 @pytest.mark.parametrize("extreme", EXTREMES, ids=lambda f: f.__name__[1:])
 def test_values_without_three_parts_give_what_fp32_arithmetic_gives(orc, extreme, layer, tiles, nhwc):
@@ -182,7 +193,8 @@ SCALES = ((-116, 0, 0, 0), (0, -116, 0, 0), (0, 0, -116, 0), (0, 0, 0, -116), (-
 
 
 @pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
-@pytest.mark.parametrize("layer,tile", ((Layer(2, 32, 48, 12, 12, 32, 16, 3, 1, 1), (4, 4)), (Layer(40, 20, 24, 12, 12, 40, 80, 3, 2, 1), (6, 6))),
+@pytest.mark.parametrize("layer,tile", ((Layer(2, 32, 48, 12, 12, 32, 16, 3, 1, 1), (4, 4)), (Layer(40, 20, 24, 12, 12, 40, 80, 3, 2, 1), (6, 6)),
+                                        (Layer(40, 72, 24, 12, 12, 40, 20, 3, 1, 1), (10, 8))),
                          ids=lambda v: v.name() if isinstance(v, Layer) else "")
 def test_the_scale_of_the_factors_costs_no_accuracy(orc, layer, tile, nhwc):
     """Factors, z1 or z2 below 2^-110 have no three bf16 parts with all their bits; nothing larger stands beside them here."""

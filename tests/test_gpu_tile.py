@@ -31,13 +31,15 @@ def _oracle(orc, layer, inputs, bias=None, residual=None):
     return want
 
 
-def _run(layer, inputs, tm, waves, nhwc, bias=None, residual=None, offset=0):
+def _run(layer, inputs, tm, waves, nhwc, bias=None, residual=None, offset=0, in_lds=None, parts=""):
     import torch
     from paper_2211_03715_amd.layer import DenseConv2d
     dev = torch.device("cuda:0")
     put = lambda a: torch.from_numpy(np.ascontiguousarray(a.transpose(0, 2, 3, 1) if nhwc else a)).to(dev)
     conv = DenseConv2d(layer, 0, B.make_tuning(tile_h=tm, tile_w=64, waves=(waves,) * 3), B.LAYOUT_NHWC if nhwc else B.LAYOUT_NCHW)
     try:
+        assert in_lds is None or ("pixels-in-lds" in conv.describe()) == in_lds, conv.describe()
+        assert not parts or "parts=" + parts in conv.describe(), conv.describe()
         W = torch.from_numpy(inputs["W"]).to(dev)
         conv.pack(W)
         shape = conv.out_shape()
@@ -65,7 +67,7 @@ def test_tiles(orc, layer, nhwc):
             got = _run(layer, inputs, tm, waves, nhwc)
             assert_parity(got, want, "%s tile %d waves %d" % (layer.name(), tm, waves))
             # fp32 sums of at most 800 terms here: an fp32 chain shows about 6e-7 (sqrt(800) roundings of 2^-25 relative to the
-            # root of the sum), the split products about the same; two parts instead of three would show 5e-6
+            # root of the sum), the split products about the same; two bf16 parts would show 5e-6
             rel = np.linalg.norm(got - want) / np.linalg.norm(want)
             assert rel <= 1.2e-6, rel
 
@@ -290,6 +292,52 @@ def test_a_nan_explains_no_sums_but_its_own(orc, what, layer, nhwc):
         err, ref = (got - want)[0][:, ok], want[0][:, ok]
         assert (np.linalg.norm(err, axis=0) <= 1.2e-6 * np.linalg.norm(ref, axis=0)).all()
         assert (np.linalg.norm((got - want)[1:], axis=1) <= 1.2e-6 * np.linalg.norm(want[1:], axis=1)).all()
+
+
+# What x or a weight may hold that no parts do, in 1x1 layers whose pixels stay in LDS
+def _infinite_x(i):
+    i["x"][0, 3, 4, 5] = np.inf
+
+
+def _largest_x(i):
+    i["x"][0, 3, 4, 5], i["x"][0, 9, 7, 2] = np.finfo(np.float32).max, -np.finfo(np.float32).max
+    i["W"] = np.clip(i["W"], -0.5, 0.5)
+
+
+def _nan_and_infinite_x(i):
+    i["x"][0, 3, 4, 5], i["x"][0, 5, 1, 1] = np.inf, np.nan
+
+
+def _largest_weight(i):
+    i["W"][5, 7] = np.finfo(np.float32).max
+    i["x"] *= np.float32(1e-12)
+
+
+def _infinite_weight(i):
+    i["W"][5, 7] = -np.inf
+
+
+def _nan_weight(i):
+    i["W"][5, 7] = np.nan
+
+
+@pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
+@pytest.mark.parametrize("layer", FP16_LAYERS[1:], ids=lambda l: l.name())
+@pytest.mark.parametrize("extreme", (_infinite_x, _largest_x, _nan_and_infinite_x, _largest_weight, _infinite_weight, _nan_weight), ids=lambda f: f.__name__[1:])
+def test_1x1_layers_in_lds_with_values_that_no_parts_hold(orc, extreme, layer, nhwc):
+    inputs = make_dense_inputs(layer, 89)
+    extreme(inputs)
+    with np.errstate(invalid="ignore"):
+        want = _oracle(orc, layer, inputs)
+    for tm in (64, 128):                                 # one and two channel blocks to a wavefront where there are two parts
+        print("[case] 1x1 in LDS,", extreme.__name__, layer.name(), "nhwc" if nhwc else "nchw", tm, flush=True)
+        got = _run(layer, inputs, tm, 4, nhwc, in_lds=True, parts="fp16x3" if layer.C <= 72 else "fp16x2")
+        finite = np.isfinite(want)
+        assert (extreme in (_largest_x, _largest_weight)) == finite.all()
+        assert np.array_equal(got[~finite], want[~finite].astype(np.float32), equal_nan=True)
+        reached = finite & (np.abs(want) > 1e25 if extreme is not _largest_weight else np.abs(want) > 1e10)
+        for part in (reached, finite & ~reached):        # sums of at most 160 terms, as in test_tiles
+            assert np.linalg.norm(got[part] - want[part]) <= 1.2e-6 * np.linalg.norm(want[part])
 
 
 @pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
