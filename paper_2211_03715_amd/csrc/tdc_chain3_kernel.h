@@ -823,7 +823,8 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
         }
         float top = 0.f;                                         // largest magnitude of z2 that is no NaN
         unsigned smallest = ~0u;                                 // of the pixels' largest z2 values the smallest
-        unsigned lit = 0;                                        // whether z2 is not all zero at the pixels of this lane's outputs
+        int lit = 0;                                             // pixels at which z2 is not all zero, of those this lane judges (see emit)
+        bool first_lit = false;
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) {
             float m = 0.f;
@@ -832,8 +833,18 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
             m = tdc_pixel_max(m);
             top = __builtin_elementwise_maximum(top, m);
             smallest = tdc_smallest(smallest, m);
-            lit |= NHWC ? m != 0.f : (unsigned)__builtin_amdgcn_ballot_w64(m != 0.f) >> 4 * (lane >> 4) & 15u;
+            const int p = 16 * (pg * PB + pb) + (lane & 15);
+            lit += NHWC ? m != 0.f && p < a.P : __builtin_popcount((unsigned)__builtin_amdgcn_ballot_w64(m != 0.f && p < a.P) >> 4 * (lane >> 4) & 15u);
+            first_lit |= m != 0.f && p >= a.P;                   // past the last pixel the first stands in
         }
+        if (NHWC) {
+            lit += tdc_row_ror8(lit);
+            lit += (int)((first_lit | tdc_row_ror8(first_lit)) != 0) & (int)(pg * PB * 16 + (lane & 7) != 0);
+        }
+        // Few sums may be small by chance, four hardly ever: lanes of fewer are judged only where a wavefront has no others.  (128 -> 128 at
+        // 28x28, batch 10, NHWC, tiles of 5 x 7, whose last blocks hold three pixels: judged by lanes of one or two pixels each, three
+        // of four layers of a network ran a tile twice, 30 us instead of 12.)
+        const bool judged = lit > (tdc_any_lane(lit > 3) ? 3 : tdc_any_lane(lit > 1) ? 1 : 0);
         const int z2_exp = tdc_scale_of(tdc_wave_max(top), TDC_Z2_TARGET, 0);
         bad |= tdc_is_small(smallest, tdc_exp2i(max(TDC_LOWEST - z2_exp, -126)));
         const int y_exp = a.z1_exp - z2_exp - x_exp;            // y is 2^(y_exp - exponent of the channel) times its sum
@@ -848,7 +859,7 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
         }
         const Chain3Out<PB, NHWC> out(a, at, pg, lane);
         float largest = 0.f;
-        const int lost = lit ? (127 + min(max(z2_exp + a.lost2, a.lost3), 126)) << 23 : 0;
+        const int lost = judged ? (127 + min(max(z2_exp + a.lost2, a.lost3), 126)) << 23 : 0;
         int least = 0x7f800000;                                  // of the magnitudes of the channels' largest sums the least, as bits
         // two instances of the loop, as in tdc_chain_kernel.h: without epilogue loads nothing ever waits for the stores
         typedef typename Chain3Out<PB, NHWC>::Epi Epi;
@@ -872,7 +883,7 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
                 v[pb] = tdc_levels(acc3[pb]);
                 largest = tdc_largest(largest, v[pb]);
             }
-            // a channel's largest among this lane's pixels, of those that are no NaN
+            // a channel's largest among this lane's pixels, of those that are no NaN, in NHWC with those of the lane eight further
 #pragma unroll
             for (int i = 0; i < (NHWC ? 4 : 1); ++i) {
                 float m = fabsf(v[0][i]);
@@ -885,7 +896,8 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
                         m = tdc_max3_abs(m, v[pb][2], v[pb][3]);
                     }
                 }
-                least = min(least, __builtin_bit_cast(int, m));
+                const int bits = __builtin_bit_cast(int, m);
+                least = min(least, NHWC ? max(bits, tdc_row_ror8(bits)) : bits);
             }
 #pragma unroll
             for (int pb = 0; pb < PB; ++pb)

@@ -24,7 +24,7 @@
 //   z2           by the largest a wavefront holds.
 // What is lost.  A factor below 2^TDC_LOWEST is kept to an absolute accuracy, 2^-36.  That shows where large weights meet small
 // values only, as when the weights undo what size the channels of x have: the sums are small then, a channel's over several
-// pixels (one alone may be so by chance), and each stage that writes outputs compares them with what the parts may have lost.
+// pixels (one or two may be so by chance), and each stage that writes outputs compares them with what the parts may have lost.
 // Infinities, NaN and values too large show in the results, which they make infinite or NaN; that all of a pixel's channels are
 // below 2^-13, and not zero, each stage watches as it splits them (a pixel's, not a value's: beside larger ones a lost bit is
 // below their rounding).  Either way the outputs concerned are computed once more in fp32, from weights kept beside the parts.
@@ -177,6 +177,9 @@ __device__ __forceinline__ float tdc_pixel_max(float m)
     const auto b = __builtin_amdgcn_permlane16_swap(v, v, false, false);
     return __builtin_bit_cast(float, max(b[0], b[1]));
 }
+
+// what the lane eight further in a row of 16 holds
+__device__ __forceinline__ int tdc_row_ror8(int v) { return __builtin_amdgcn_mov_dpp(v, 0x128, 0xf, 0xf, true); }
 
 // the largest of a wavefront, as bits, in a scalar register
 __device__ __forceinline__ unsigned tdc_wave_max(float m)

@@ -216,10 +216,23 @@ __device__ __forceinline__ void tile_magnitudes(const tdc_f4 (&acc)[MB][PB], flo
             least = min(least, __builtin_bit_cast(int, m));
         }
 }
-// The least once more, of `blocks` channel blocks and of sums that are no NaN, where there is one.
+// Whether a wavefront lost a channel: the least once more, of `blocks` channel blocks and of sums that are no NaN, over the pixels of
+// lanes that are put together until some have four at which x is not all zero: fewer sums may be small by chance.  top: tile_top;
+// first: the wavefront's first pixel.
 template <bool SWAP, int MB, int PB>
-__device__ __forceinline__ int tile_least(const tdc_f4 (&acc)[MB][PB], int blocks)
+__device__ __forceinline__ bool tile_lost_any(const tdc_f4 (&acc)[MB][PB], int blocks, unsigned top, int first, int lane, int lost)
 {
+    constexpr int NEXT = SWAP ? 16 : 8, END = SWAP ? 64 : 0;       // a lane holds four pixels of each block, or one
+    const auto further = [](int step) { return SWAP ? 2 * step : step / 2; };
+    const unsigned long long px = __builtin_amdgcn_ballot_w64(top != 0) >> first;
+    int lit = 0;
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) lit += SWAP ? __builtin_popcount((unsigned)(px >> 16 * pb) >> 4 * (lane >> 4) & 15u) : (int)(px >> (16 * pb + (lane & 15)) & 1u);
+    int end = NEXT;                                                 // all steps in front of it are taken
+    do {
+        lit += __shfl_xor(lit, end);
+        end = further(end);
+    } while (end != END && !tdc_any_lane(lit > 3));
     int least = 0x7f800000;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
@@ -230,19 +243,11 @@ __device__ __forceinline__ int tile_least(const tdc_f4 (&acc)[MB][PB], int block
             for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
                 for (int i = SWAP ? 0 : c; i < (SWAP ? 4 : c + 1); ++i) m = fmaxf(m, fabsf(acc[mb][pb][i]));
+#pragma unroll 1
+            for (int step = NEXT; step != end; step = further(step)) m = fmaxf(m, __shfl_xor(m, step));
             if (m >= 0.f && mb < blocks) least = min(least, __builtin_bit_cast(int, m));
         }
-    return least;
-}
-// whether x is not all zero at this lane's pixels of a wavefront's blocks, the first `first`; top: tile_top
-template <bool SWAP, int PB>
-__device__ __forceinline__ bool tile_lit(unsigned top, int first, int lane)
-{
-    const unsigned long long px = __builtin_amdgcn_ballot_w64(top != 0) >> first;
-    unsigned any = 0;
-#pragma unroll
-    for (int pb = 0; pb < PB; ++pb) any |= (unsigned)(px >> 16 * pb);
-    return SWAP ? any >> 4 * (lane >> 4) & 15u : any >> (lane & 15) & 1u;
+    return tdc_any_lane(lit > (tdc_any_lane(lit > 3) ? 3 : 0) && least < lost);
 }
 
 // Four pixels of NCHW channel m, from pixel p on, that cannot be stored at once: sums and bias in v, shortcut and ReLU here.
@@ -536,7 +541,7 @@ __global__ __launch_bounds__(256 * KS, tile_wavefronts(MB * PB)) void tdc_tile_k
     unsigned nans = 0;
     bool redone = false;
     if (__builtin_expect(small || tdc_any_lane(!tdc_finite(largest) || least < lost), 0)) {
-        small = small || tdc_any_lane(tile_lit<SWAP, PB>(top, 16 * PB * wp, out_lane) && tile_least<SWAP, MB, PB>(acc, a.NBm - mb0) < lost);
+        small = small || tile_lost_any<SWAP, MB, PB>(acc, a.NBm - mb0, top, 16 * PB * wp, out_lane, lost);
         if (small || tdc_any_lane(!tdc_finite(largest)))
             nans = tile_redo<ACT, CONV, MB, PB>(tdc_args_again<TileArgs>(), small, x_exp, out_lane, p_base, mb0, acc, redone);
     }
@@ -777,8 +782,7 @@ __global__ __launch_bounds__(256, MB == 2 ? 2 : 3) void tdc_tile_1x1_kernel(Tile
         tile_magnitudes<SWAP, MB, PB>(acc, largest, least);
         bool redone = false;
         if (__builtin_expect(small || tdc_any_lane(!tdc_finite(largest) || least < lost), 0)) {
-            const bool lit = tile_lit<SWAP, PB>(tile_top<TOP_ROWS>(tops, lane), 0, lane);
-            const bool too_small = small || tdc_any_lane(lit && tile_least<SWAP, MB, PB>(acc, a.NBm - blk0) < lost);
+            const bool too_small = small || tile_lost_any<SWAP, MB, PB>(acc, a.NBm - blk0, tile_top<TOP_ROWS>(tops, lane), 0, lane, lost);
             if (too_small || tdc_any_lane(!tdc_finite(largest)))
                 tile_redo<ACT, false, MB, PB>(tdc_args_again<TileArgs>(), too_small, x_exp, lane, p_tile, blk0, acc, redone);
         }

@@ -407,3 +407,26 @@ def test_finite_inputs_that_fp16_holds_cost_the_usual_time(values, layer, nhwc):
             assert not y[:, ::2].any() and not y[:, :17].any() and not y[1::2].any() and y[0, 17].any()
     finally:
         conv.close()
+
+
+@pytest.mark.parametrize("nhwc", (False, True), ids=("nchw", "nhwc"))
+@pytest.mark.parametrize("layer,pixel", ((Layer(1, 128, 64, 10, 10, 1, 1, 3, 1, 1), 97), (Layer(1, 256, 136, 2, 36, 1, 1, 1, 1, 0), 70),
+                                         (Layer(1, 64, 64, 1, 1, 1, 1, 3, 1, 1), None)), ids=lambda v: v.name() if isinstance(v, Layer) else "")
+def test_one_sum_that_is_small_by_chance_has_no_tile_computed_again(orc, layer, pixel, nhwc):
+    """A channel that one of the last pixels, alone in its lane, happens to give nothing.  The other channels would not keep their bits if
+    the tile were computed again.  A single pixel in all is judged by itself: only its values are checked."""
+    inputs = make_dense_inputs(layer, 90)
+    p = pixel or 0
+    x = np.pad(inputs["x"][0].astype(np.float64), ((0, 0), (layer.pad,) * 2, (layer.pad,) * 2))
+    h, w = p // layer.W, p % layer.W
+    v = x[:, h:h + layer.K, w:w + layer.K].ravel()
+    there = dict(inputs, W=inputs["W"].copy())
+    u = inputs["W"][:, 7].astype(np.float64).ravel()
+    there["W"][:, 7] = (u - v * (v @ u) / (v @ v)).reshape(there["W"][:, 7].shape)
+    others = np.arange(layer.N) != 7
+    for tm, waves in ((64, 4), (64, 8), (128, 4)):
+        print("[case] tiles, small by chance", layer.name(), "nhwc" if nhwc else "nchw", tm, waves, flush=True)
+        got, clean = _run(layer, there, tm, waves, nhwc), _run(layer, inputs, tm, waves, nhwc)
+        assert abs(got[0, 7, h, w]) < 1e-5
+        assert pixel is None or np.array_equal(got[:, others], clean[:, others])
+        assert_parity(got, _oracle(orc, layer, there), layer.name())
