@@ -839,7 +839,7 @@ __global__ __launch_bounds__(64 * TDC_CHAIN3_WAVES, chain3_wavefronts(NB2, PB, L
         }
         if (NHWC) {
             lit += tdc_row_ror8(lit);
-            lit += (int)((first_lit | tdc_row_ror8(first_lit)) != 0) & (int)(pg * PB * 16 + (lane & 7) != 0);
+            lit += (int)(lit > 0) & (int)((first_lit | tdc_row_ror8(first_lit)) != 0) & (int)(pg * PB * 16 + (lane & 7) != 0);
         }
         // Few sums may be small by chance, four hardly ever: lanes of fewer are judged only where a wavefront has no others.  (128 -> 128 at
         // 28x28, batch 10, NHWC, tiles of 5 x 7, whose last blocks hold three pixels: judged by lanes of one or two pixels each, three
