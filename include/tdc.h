@@ -40,9 +40,10 @@
  * fp32 multiply-adds.  What fp16 cannot hold is multiplied in fp32 as the other kernels do: infinities, NaN, values of x more than 512 times those its workgroup
  * loads first, and pixels of which no channel reaches 2^-19 of them (bf16: values
  * from 2^126 on, pixels below 2^-110).  A tile that such values reach takes several times as
- * long (NaN alone: twice to three times).  A value of x below 2^-23 of its neighbourhood, beside larger channels of its own
- * pixel, keeps an absolute accuracy of 2^-46 of that neighbourhood, and a weight below 2^-26 of its output channel's
- * largest one of 2^-49 of that.
+ * long (NaN alone: up to three times).  A value of x below 2^-19 of its neighbourhood, beside larger channels of its own
+ * pixel, keeps an absolute accuracy of 2^-42 of that neighbourhood, and a weight below 2^-26 of its output channel's
+ * largest one of 2^-49 of that.  Where sums are so small that this would show in a channel's outputs, as when weights undo
+ * such differences, their tile is multiplied in fp32 as well.
  *
  * Errors: every function returns a tdc_status (0 = success, negative =
  * failure).  Nothing aborts, throws or prints.

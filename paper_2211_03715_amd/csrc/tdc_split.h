@@ -27,7 +27,7 @@
 // pixels (one or two may be so by chance), and each stage that writes outputs compares them with what the parts may have lost.
 // Infinities, NaN and values too large show in the results, which they make infinite or NaN; that all of a pixel's channels are
 // below 2^-13, and not zero, each stage watches as it splits them (a pixel's, not a value's: beside larger ones a lost bit is
-// below their rounding).  Either way the outputs concerned are computed once more in fp32, from weights kept beside the parts.
+// below their rounding, unless weights undo the difference, which is what the outputs are compared for).  Either way the outputs concerned are computed once more in fp32, from weights kept beside the parts.
 //
 // Operand layout of v_mfma_f32_16x16x32_f16 (D 16x16 += A 16x32 * B 32x16): lane l holds A[m = l%16][k(l/16, j)] and
 // B[k(l/16, j)][p = l%16], j = 0..7, for any assignment k(g, j) that A and B share; D as in tdc_mfma.h.  Here a step is a pair of
